@@ -242,7 +242,7 @@ int kvb_compact(const kvb_shape *shape, const kvb_store *store, const int32_t *s
  * len[b] outside 0..Lmax is clamped to Lmax with KVB_STATUS_OVERFLOW.
  * With a 16-bit rec_dtype the outputs read the records as stored (rounded), like everywhere
  * else; the delta values themselves are solved for in fp32 before they are rounded -- all
- * rows at once up to 64 tokens, 16 rows at a time above that -- so a row's delta value does
+ * rows at once up to 64 tokens, 64 rows at a time above that -- so a row's delta value does
  * not see the rounding of the rows solved with it.
  */
 int kvb_direct(const kvb_shape *shape, const kvb_store *store, const int32_t *slot,

@@ -1,5 +1,5 @@
-// kvb_direct: kvb_direct_mfma_kernel, kvb_direct_mfma_long_kernel (16-bit inputs, d = 128) and kvb_direct_kernel
-// (fp32 inputs and the other head sizes).
+// kvb_direct: kvb_direct_mfma_kernel (16-bit inputs, d = 128) and kvb_direct_kernel (fp32 inputs and the other
+// head sizes).
 #include "kvb_device.h"
 
 namespace kvb_impl {
@@ -114,16 +114,13 @@ __global__ __launch_bounds__(NT) void kvb_direct_kernel(const DirectArgs a)
 
 // ---------------------------------------------------------------------------
 // kvb_direct for 16-bit inputs (bf16 or fp16) and d = 128, on the matrix cores throughout.
-// What the two kernels below share.
 //
 // The context is cut into blocks of 16 rows.  With N_il = beta_i Gamma_il (k_i.k_l) (l < i)
 // and M_il = Gamma_il (q_i.k_l) (l <= i) the parallel form (Eq. 13) is
 //     (I + N) U = Diag(beta) V,      O = M U.
-// The kernel for up to 128 tokens solves it block row by block row,
-//     U_d = T_d ( beta V_d - sum_{e<d} N_de U_e ),      O_d = sum_{e<=d} M_de U_e,
-// T_d = (I + N_dd)^-1 by blocked inversion (unit_lower_inverse16 below; N_dd is strictly lower),
-// with fp32 operands on v_mfma_f32_16x16x4_f32 (exact products) after the Gram tiles; the
-// kernel for up to 64 tokens forms the whole inverse and multiplies (see its own header).
+// The diagonal blocks T_d = (I + N_dd)^-1 come from a blocked inversion (unit_lower_inverse16 below; N_dd is
+// strictly lower) with fp32 operands on v_mfma_f32_16x16x4_f32 (exact products); the kernel then forms the
+// whole inverse and multiplies (see its own header).
 //   * Gram tiles (k.k, q.k over dk = 128, 16-bit operands): v_mfma_f32_16x16x32_{bf16,f16}.
 //
 // Register chaining.  Call "A-form" of a 16x16 matrix X the register layout in which lane l
@@ -207,6 +204,25 @@ __device__ __forceinline__ f32x4_t gram16(const TIn *arow, const TIn *brow, int 
     return c;
 }
 
+// Waits until the matrix instructions that produce these values have written them (8 wait states cover
+// the 16-bit 16x16x32 instruction).  The compiler inserts such waits itself, but where a block of matrix
+// instructions is skipped by a branch it looked back along the path through that block only, and the
+// other path read a register before its sum had arrived; sums that end in such blocks are therefore
+// settled by hand before anything else reads them.
+template <int N>
+__device__ __forceinline__ void settle(f32x4_t (&x)[N][2])
+{
+    asm volatile("s_nop 7" : "+v"(x[0][0]));   // (volatile: the ones below stay behind it)
+#pragma unroll
+    for (int i = 0; i < 2 * N; ++i)
+        if (i > 0)
+            asm volatile("" : "+v"(x[i / 2][i % 2]));
+}
+__device__ __forceinline__ void settle(f32x4_t &x, f32x4_t &y)
+{
+    asm volatile("s_nop 7" : "+v"(x), "+v"(y));
+}
+
 // ---------------------------------------------------------------------------
 // Pieces.  A fp32 value x is cut into NP values of the 16-bit input type, x = x_1 + ... + x_NP
 // (+ a remainder below 2^-24 |x| for three bf16 pieces, 2^-22 |x| for two fp16 pieces), each
@@ -267,6 +283,10 @@ __device__ __forceinline__ f32x4_t mm16_pieces(const uint2 (&x)[NPX], const uint
     } else if constexpr (NPX == 3 && NPY == 1) {
         ins(x[2], zero, y[0], y[0]);        // X3 Y
         ins(x[0], x[1], y[0], y[0]);        // X1 Y + X2 Y
+    } else if constexpr (NPX == 3 && NPY == 2) {
+        ins(x[2], x[2], y[0], y[1]);        // X3 Y1 + X3 Y2
+        ins(x[1], x[1], y[0], y[1]);        // X2 Y1 + X2 Y2
+        ins(x[0], x[0], y[0], y[1]);        // X1 Y1 + X1 Y2
     } else if constexpr (NPX == 2 && NPY == 2) {
         ins(x[1], x[1], y[0], y[1]);        // X2 Y1 + X2 Y2
         ins(x[0], x[0], y[0], y[1]);        // X1 Y1 + X1 Y2
@@ -303,13 +323,27 @@ __device__ __forceinline__ f32x4_t mm16_pieces(const uint2 (&x)[NPX], const uint
 // A_32, W_20, W_21; then the pieces of A^ -- and the pieces of M next to it: 36 KB for bf16,
 // four workgroups per CU (28 KB and five for fp16).  A wave owns 32 dv columns: column tile c of wave w holds columns
 // 32 w + 2 n + c (n = 0..15), so a lane's two tiles are adjacent columns.
+//
+// LONG: contexts of up to 128 tokens, in two panels of 64 rows.  The first is the method above; its
+// U_0 stays in registers, in pieces.  The second sees the first through N' = Gamma K_1 K_0^T (no beta)
+// and M' = Gamma Q_1 K_0^T, 4 x 4 tiles each:
+//     X = V_1 - N' U_0        U_1 = A^_1 X        O_1 = M' U_0 + M_1 U_1
+// with A^_1 formed like A^_0.  X is fp32, so it goes through the 16-bit instruction in pieces as U
+// does.  A context of up to 64 tokens in a LONG launch leaves after the first panel.  The line to LONG
+// lies at Lmax = 64 because the 64-row kernel is the faster one there (four or five workgroups per CU
+// instead of three).  Bound by the issue of vector and matrix instructions at three long-lived waves per
+// SIMD.  96 contexts of ~U(1,128), 32 heads, bf16 with fp32 records: 192 -> 130 us against the kernel
+// before it (8 block rows solved one after the other with fp32 matrix instructions); 128 of ~U(1,100),
+// fp16 throughout: 193 -> 127 us.  Two workgroups per CU without any spill were 5 % slower than three that
+// spill 32 words of the weighted query tiles; pieces of U_0 kept in registers instead of cut again: two fit.
 // ---------------------------------------------------------------------------
 // Workgroups per CU: the two fp16 pieces need 28 KB of LDS and 92 registers, which leaves room for
 // five (6 % faster than four on ragged lengths); the three bf16 pieces need 36 KB and 124.
-template <typename T>
-constexpr int DIRECT_WG_PER_CU = __is_same(T, f16_t) ? 5 : 4;
-template <typename TIn, typename TRec, bool PAGED>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PER_CU<TIn>, DIRECT_WG_PER_CU<TIn>))) void kvb_direct_mfma_kernel(
+// LONG: 46 KB and 168 registers, three.
+template <typename T, bool LONG>
+constexpr int DIRECT_WG_PER_CU = LONG ? 3 : __is_same(T, f16_t) ? 5 : 4;
+template <typename TIn, typename TRec, bool LONG, bool PAGED>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PER_CU<TIn, LONG>, DIRECT_WG_PER_CU<TIn, LONG>))) void kvb_direct_mfma_kernel(
     const int32_t *len_arg, int32_t Hv_arg, int32_t nblocks_arg, const DirectArgs a)
 {
     // The three leading arguments repeat a.len, a.Hv and the grid size: as plain leading kernel arguments
@@ -317,13 +351,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     // len[b] -- the head of the dependent chain to the first key byte -- goes out at once instead of after
     // the round trip that fetches the argument block.
     constexpr int D = 128;
-    constexpr int LM = 64;   // longest context of this kernel
+    constexpr int LM = 64;   // rows of a panel
     constexpr int NB = LM / 16;                 // blocks of 16 rows (4)
     constexpr int NLOW = NB * (NB + 1) / 2;     // lower-triangular block pairs (10)
     constexpr int GS = D + 8;                   // LDS row stride of the staged keys (272 B:
                                                 // consecutive rows start 4 banks apart)
-    constexpr int NP = pieces_of_f32<TIn>();    // pieces of a fp32 tile
-    constexpr int NPU = sizeof(TRec) == 2 ? 1 : NP;   // a 16-bit record is one piece as it stands
+    // Type of the pieces: the input type, whose values are then exact operands, but bf16 in every LONG kernel.
+    // fp16 has not the range there: products beyond 65504 (queries and keys need not be normalised) have no
+    // piece, and the second piece of a value below 0.25 is subnormal, in steps of 6e-8, which over two panels
+    // adds up to twice the error of fp32 products (8.9e-7 of the outputs at 128 tokens).  A fp16 value of V or
+    // of a record is then two bf16 pieces, exactly.
+    using TP = std::conditional_t<LONG, bf16_t, TIn>;
+    constexpr bool SAME = __is_same(TP, TIn);   // an input value is its own single piece
+    constexpr int NP = pieces_of_f32<TP>();     // pieces of a fp32 tile
+    constexpr int NPU = sizeof(TRec) == 4 ? NP : SAME ? 1 : 2;   // a 16-bit record is one piece as it stands
     static_assert(NB == NW, "one diagonal block per wave");
     constexpr int STAGE_BYTES = LM * GS * 2;
     constexpr int PIECE_BYTES = NLOW * NP * 512;        // pieces of A^ (and as much again for M)
@@ -333,9 +374,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     constexpr int OFF_LATE = PIECE_BYTES;               // T_2, T_3, A_32, W_20, W_21 (read while they are)
     constexpr int X_BYTES = STAGE_BYTES > OFF_LATE + 5 * F32_TILE ? STAGE_BYTES : OFF_LATE + 5 * F32_TILE;
     static_assert(OFF_T01 + 2 * F32_TILE <= OFF_LATE, "the early tiles lie under the pieces only");
-    __shared__ __attribute__((aligned(16))) unsigned char region[X_BYTES + PIECE_BYTES];
-    __shared__ __attribute__((aligned(16))) float sG[LM];
-    __shared__ __attribute__((aligned(16))) float sB[LM];
+    // second panel (LONG): the keys of both panels staged, then the pieces of the 4 x 4 tiles N' (later M')
+    // in the place of the pieces of M
+    constexpr int CROSS_BYTES = NB * NB * NP * 512;
+    constexpr int REGION_BYTES = !LONG                                     ? X_BYTES + PIECE_BYTES
+                                 : X_BYTES + CROSS_BYTES > 2 * STAGE_BYTES ? X_BYTES + CROSS_BYTES
+                                                                           : 2 * STAGE_BYTES;
+    static_assert(CROSS_BYTES >= PIECE_BYTES, "the pieces of M fit where those of N' were");
+    __shared__ __attribute__((aligned(16))) unsigned char region[REGION_BYTES];
+    __shared__ __attribute__((aligned(16))) float sG[LONG ? 2 * LM : LM];
+    __shared__ __attribute__((aligned(16))) float sB[LONG ? 2 * LM : LM];
     __shared__ int sBlk[NW][MAX_BLOCKS];
     TIn *sK = reinterpret_cast<TIn *>(region);
     auto pieceA = [&](int tile, int p) { return reinterpret_cast<uint2 *>(region + (tile * NP + p) * 512); };
@@ -402,12 +450,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     }
     const size_t gb_o = ((size_t)b * Lmax + min(lane, L - 1)) * a.Hv + h;
     float g_raw = a.g[gb_o], beta_raw = a.beta[gb_o];   // (every wave: a branch around a load costs more)
+    float g_raw1 = 0.0f, beta_raw1 = 0.0f;
+    if constexpr (LONG) {
+        const size_t gb_o1 = ((size_t)b * Lmax + min(LM + lane, L - 1)) * a.Hv + h;
+        g_raw1 = a.g[gb_o1];
+        beta_raw1 = a.beta[gb_o1];
+    }
 
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, a.cap, sBlk[wave], lane, load_block_id<PAGED>(a.st, s, lane));
     auto ru = [&](int l) { return pg.row(l, a.Hv, h); };
     auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };
     const Out<TIn> out{a.out, a.out_wide != 0};
-    const int nb = (L + 15) / 16;
+    const int nb = ((LONG ? min(L, LM) : L) + 15) / 16;
     auto tri = [](int d, int e) { return d * (d + 1) / 2 + e; };    // slot of pair d >= e
     auto trn = [](int d, int e) { return d * (d - 1) / 2 + e; };    // slot of pair d > e
     // fp32 tiles in LDS are row-major 16 x 16: A-form is one 16-byte access, B-form four 4-byte ones
@@ -435,20 +489,30 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     auto off_n = [&](int d, int e) { return OFF_N + trn(d, e) * F32_TILE; };
     auto off_t = [&](int d) { return d < 2 ? OFF_T01 + d * F32_TILE : OFF_LATE + (d - 2) * F32_TILE; };
 
-    // cumulative log decay (inclusive scan over the wave) and beta
-    if (wave == 0) {
-        float gv = lane < L ? g_raw : 0.0f;
-        const float bv = lane < L ? beta_raw : 0.0f;
+    // cumulative log decay (inclusive scan over the wave) and beta; wave 1 takes the second panel's and
+    // scans the first one's again for the sum it starts from
+    auto wave_scan = [&](float gv) {
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const float t = __shfl_up(gv, off);
             if (lane >= off)
                 gv += t;
         }
-        sG[lane] = gv;
-        sB[lane] = bv;
-        if (lane < L)
-            a.st.buf_G[ru(lane)] = gv;
+        return gv;
+    };
+    if (wave == 0 || (LONG && wave == 1)) {
+        float gv = wave_scan(lane < L ? g_raw : 0.0f);
+        float bv = lane < L ? beta_raw : 0.0f;
+        int row = lane;
+        if (LONG && wave == 1) {
+            row = LM + lane;
+            gv = __shfl(gv, 63) + wave_scan(row < L ? g_raw1 : 0.0f);
+            bv = row < L ? beta_raw1 : 0.0f;
+        }
+        sG[row] = gv;
+        sB[row] = bv;
+        if (row < L)
+            a.st.buf_G[ru(row)] = gv;
     }
     // stage K; the thread that loaded a piece of K also appends it to the buffer
     TIn *kb = static_cast<TIn *>(a.st.buf_k);
@@ -521,7 +585,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
             }
             if (isq) {
                 uint2 pc[NP];
-                split_tile<TIn, NP>(o, pc);
+                split_tile<TP, NP>(o, pc);
 #pragma unroll
                 for (int p = 0; p < NP; ++p)
                     pieceM(tri(d, e), p)[lane] = pc[p];
@@ -530,132 +594,184 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
             }
         }
     }
-    // T_d = (I + N_dd)^-1 for d = wave.  The raw diagonal tile is symmetric, so the same registers
-    // give the A-form (row 16 d + c16, column 16 d + 4 lq + v) and the B-form (row and column swapped).
-    f32x4_t t_own = {0.f, 0.f, 0.f, 0.f};   // T_wave, A-form
-    if (wave < nb) {
-        const int d = wave;
+    // T_d = (I + N_dd)^-1 of the 16 rows from row0 on.  The raw diagonal tile is symmetric, so the same
+    // registers give the A-form (row row0 + c16, column row0 + 4 lq + v) and the B-form (row and column swapped).
+    const f32x4_t z4 = {0.f, 0.f, 0.f, 0.f};
+    auto diagonal_inverse = [&](int row0, const f32x4_t &gdiag) {
         f32x4_t na, nbm, ia;   // N in both forms; identity mask (the same in both forms)
-        const float gc = sG[16 * d + c16], bc = sB[16 * d + c16];
-        const float4 gq4 = *reinterpret_cast<const float4 *>(&sG[16 * d + 4 * lq]);
-        const float4 bq4 = *reinterpret_cast<const float4 *>(&sB[16 * d + 4 * lq]);
+        const float gc = sG[row0 + c16], bc = sB[row0 + c16];
+        const float4 gq4 = *reinterpret_cast<const float4 *>(&sG[row0 + 4 * lq]);
+        const float4 bq4 = *reinterpret_cast<const float4 *>(&sB[row0 + 4 * lq]);
         const float gq[4] = {gq4.x, gq4.y, gq4.z, gq4.w}, bq[4] = {bq4.x, bq4.y, bq4.z, bq4.w};
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int ia_i = 16 * d + c16, ia_l = 16 * d + 4 * lq + v;    // A-form indices
-            const int ib_i = ia_l, ib_l = ia_i;                            // B-form indices
+            const int ia_i = row0 + c16, ia_l = row0 + 4 * lq + v;    // A-form indices
+            const int ib_i = ia_l, ib_l = ia_i;                        // B-form indices
             na[v] = (ia_i < L && ia_l < ia_i) ? bc * fast_exp(gc - gq[v]) * gdiag[v] : 0.0f;
             nbm[v] = (ib_i < L && ib_l < ib_i) ? bq[v] * fast_exp(gq[v] - gc) * gdiag[v] : 0.0f;
             ia[v] = ia_i == ia_l ? 1.0f : 0.0f;
         }
-        t_own = unit_lower_inverse16(na, nbm, ia, c16, lq);
-        if (nb > 1)
-            put_a(off_t(d), t_own);
-    }
-    __syncthreads();
-
-    // ---- the off-diagonal tiles of A = (I + N)^-1, first half: A_10, A_32 and W = C P^-1 -------
-    const f32x4_t z4 = {0.f, 0.f, 0.f, 0.f};
+        return unit_lower_inverse16(na, nbm, ia, c16, lq);
+    };
     f32x4_t w_own = z4;    // W_2w (waves 0, 1) or W_3,w-2 (waves 2, 3), B-form
     f32x4_t a_lvl2 = z4;   // A_10 (wave 1) or A_32 (wave 3), A-form
-    if (nb > 1) {          // (uniform; mm16(x_a, y_b) = B-form of X Y, mm16(y_b, x_a) = its A-form)
-        if (wave == 0 || wave == 2) {
-            const int dr = wave == 0 ? 2 : 3;        // block row of C
-            if (dr < nb) {
-                const f32x4_t y1a = mm16(lds_b(off_t(1)), lds_a(off_n(dr, 1)), z4);   // N_d1 T_1
-                const f32x4_t y2a = mm16(lds_b(off_n(1, 0)), y1a, z4);                // N_d1 T_1 N_10
-                w_own = mm16(lds_a(off_n(dr, 0)) - y2a, lds_b(off_t(0)), z4);         // (N_d0 - ...) T_0
-                if (wave == 0)
-                    put_lane(OFF_W20, w_own);
+    // ---- the off-diagonal tiles of A = (I + N)^-1, first half: A_10, A_32 and W = C P^-1, for the nb
+    // row blocks of a panel (uniform; mm16(x_a, y_b) = B-form of X Y, mm16(y_b, x_a) = its A-form)
+    auto inverse_first_half = [&](int nb, const f32x4_t &t_own) {
+        if (nb > 1) {
+            if (wave == 0 || wave == 2) {
+                const int dr = wave == 0 ? 2 : 3;        // block row of C
+                if (dr < nb) {
+                    const f32x4_t y1a = mm16(lds_b(off_t(1)), lds_a(off_n(dr, 1)), z4);   // N_d1 T_1
+                    const f32x4_t y2a = mm16(lds_b(off_n(1, 0)), y1a, z4);                // N_d1 T_1 N_10
+                    w_own = mm16(lds_a(off_n(dr, 0)) - y2a, lds_b(off_t(0)), z4);         // (N_d0 - ...) T_0
+                    if (wave == 0)
+                        put_lane(OFF_W20, w_own);
+                }
+            } else if (wave == 1) {
+                const f32x4_t pb = mm16(lds_a(off_n(1, 0)), lds_b(off_t(0)), z4);          // N_10 T_0
+                a_lvl2 = -mm16(pb, t_own, z4);                                             // -T_1 (N_10 T_0)
+                if (nb > 2) {
+                    w_own = mm16(lds_a(off_n(2, 1)), lds_b(off_t(1)), z4);                 // N_21 T_1
+                    put_lane(OFF_W21, w_own);
+                }
+            } else if (nb == 4) {   // wave 3
+                w_own = mm16(lds_a(off_n(3, 1)), lds_b(off_t(1)), z4);                     // N_31 T_1
+                const f32x4_t pb = mm16(lds_a(off_n(3, 2)), lds_b(off_t(2)), z4);          // N_32 T_2
+                a_lvl2 = -mm16(pb, t_own, z4);                                             // -T_3 (N_32 T_2)
+                put_a(OFF_A32, a_lvl2);
             }
-        } else if (wave == 1) {
-            const f32x4_t pb = mm16(lds_a(off_n(1, 0)), lds_b(off_t(0)), z4);          // N_10 T_0
-            a_lvl2 = -mm16(pb, t_own, z4);                                             // -T_1 (N_10 T_0)
-            if (nb > 2) {
-                w_own = mm16(lds_a(off_n(2, 1)), lds_b(off_t(1)), z4);                 // N_21 T_1
-                put_lane(OFF_W21, w_own);
-            }
-        } else if (nb == 4) {   // wave 3
-            w_own = mm16(lds_a(off_n(3, 1)), lds_b(off_t(1)), z4);                     // N_31 T_1
-            const f32x4_t pb = mm16(lds_a(off_n(3, 2)), lds_b(off_t(2)), z4);          // N_32 T_2
-            a_lvl2 = -mm16(pb, t_own, z4);                                             // -T_3 (N_32 T_2)
-            put_a(OFF_A32, a_lvl2);
         }
-    }
-    __syncthreads();
-
+    };
     // ---- second half: A_2e = -T_2 W_2e, A_3e = -(A_32 W_2e + T_3 W_3e); then every tile of A,
     // its columns scaled by beta (A^ = A Diag(beta)), goes to LDS in pieces.  The pieces take the
     // place of the N tiles, T_0 and T_1, which nobody reads any more.
-    auto put_pieces = [&](int d, int e, const f32x4_t &xa) {
-        const float4 b4 = *reinterpret_cast<const float4 *>(&sB[16 * e + 4 * lq]);
-        uint2 pc[NP];
-        split_tile<TIn, NP>(f32x4_t{xa[0] * b4.x, xa[1] * b4.y, xa[2] * b4.z, xa[3] * b4.w}, pc);
+    auto inverse_second_half = [&](int row0, int nb, const f32x4_t &t_own) {
+        auto put_pieces = [&](int d, int e, const f32x4_t &xa) {
+            const float4 b4 = *reinterpret_cast<const float4 *>(&sB[row0 + 16 * e + 4 * lq]);
+            uint2 pc[NP];
+            split_tile<TP, NP>(f32x4_t{xa[0] * b4.x, xa[1] * b4.y, xa[2] * b4.z, xa[3] * b4.w}, pc);
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
-            pieceA(tri(d, e), p)[lane] = pc[p];
+            for (int p = 0; p < NP; ++p)
+                pieceA(tri(d, e), p)[lane] = pc[p];
+        };
+        if (wave < nb)
+            put_pieces(wave, wave, t_own);
+        if (wave == 1 && nb > 1)
+            put_pieces(1, 0, a_lvl2);
+        if (wave == 3 && nb == 4)
+            put_pieces(3, 2, a_lvl2);
+        if (wave < 2) {
+            if (nb > 2)
+                put_pieces(2, wave, -mm16(w_own, lds_a(OFF_T2), z4));
+        } else if (nb == 4) {
+            const f32x4_t w2b = lds_lane(wave == 2 ? OFF_W20 : OFF_W21);
+            f32x4_t x = mm16(w2b, lds_a(OFF_A32), z4);
+            x = mm16(w_own, lds_a(OFF_T3), x);
+            put_pieces(3, wave - 2, -x);
+        }
     };
-    if (wave < nb)
-        put_pieces(wave, wave, t_own);
-    if (wave == 1 && nb > 1)
-        put_pieces(1, 0, a_lvl2);
-    if (wave == 3 && nb == 4)
-        put_pieces(3, 2, a_lvl2);
-    if (wave < 2) {
-        if (nb > 2)
-            put_pieces(2, wave, -mm16(w_own, lds_a(OFF_T2), z4));
-    } else if (nb == 4) {
-        const f32x4_t w2b = lds_lane(wave == 2 ? OFF_W20 : OFF_W21);
-        f32x4_t x = mm16(w2b, lds_a(OFF_A32), z4);
-        x = mm16(w_own, lds_a(OFF_T3), x);
-        put_pieces(3, wave - 2, -x);
+    f32x4_t t_own = z4;   // T_wave, A-form
+    if (wave < nb) {
+        t_own = diagonal_inverse(16 * wave, gdiag);
+        if (nb > 1)
+            put_a(off_t(wave), t_own);
     }
+    __syncthreads();
+    inverse_first_half(nb, t_own);
+    __syncthreads();
+    inverse_second_half(0, nb, t_own);
     __syncthreads();
 
     // ---- U = A^ V and O = M U on the 16-bit matrix instruction, this wave's 32 columns ----------
     // Operand of the values for two row blocks (e, e + 1) and column tile c: the lane's 8 slots are
     // rows 16 e + 4 lq + 0..3 and 16 (e + 1) + 4 lq + 0..3; a word of v_raw holds both column tiles.
-    uint4 vop[NB / 2][2];
+    // (LONG takes the blocks one by one: a pair of tiles of which one lies above the diagonal multiplies its
+    // values by zero, which a NaN among them would pass on to earlier rows.)
+    constexpr int NPV = SAME ? 1 : 2;
+    uint4 vop[LONG ? 1 : NB / 2][2];
+    uint2 vpc[LONG ? NB : 1][2][NPV];   // pieces of V_e, column tile c
+    if constexpr (!LONG) {
 #pragma unroll
-    for (int e2 = 0; e2 < NB / 2; ++e2) {
-        const uint32_t *w0 = v_raw[2 * e2], *w1 = v_raw[2 * e2 + 1];
-        vop[e2][0] = uint4{__builtin_amdgcn_perm(w0[1], w0[0], 0x05040100u), __builtin_amdgcn_perm(w0[3], w0[2], 0x05040100u),
-                           __builtin_amdgcn_perm(w1[1], w1[0], 0x05040100u), __builtin_amdgcn_perm(w1[3], w1[2], 0x05040100u)};
-        vop[e2][1] = uint4{__builtin_amdgcn_perm(w0[1], w0[0], 0x07060302u), __builtin_amdgcn_perm(w0[3], w0[2], 0x07060302u),
-                           __builtin_amdgcn_perm(w1[1], w1[0], 0x07060302u), __builtin_amdgcn_perm(w1[3], w1[2], 0x07060302u)};
+        for (int e2 = 0; e2 < NB / 2; ++e2) {
+            const uint32_t *w0 = v_raw[2 * e2], *w1 = v_raw[2 * e2 + 1];
+            vop[e2][0] = uint4{__builtin_amdgcn_perm(w0[1], w0[0], 0x05040100u), __builtin_amdgcn_perm(w0[3], w0[2], 0x05040100u),
+                               __builtin_amdgcn_perm(w1[1], w1[0], 0x05040100u), __builtin_amdgcn_perm(w1[3], w1[2], 0x05040100u)};
+            vop[e2][1] = uint4{__builtin_amdgcn_perm(w0[1], w0[0], 0x07060302u), __builtin_amdgcn_perm(w0[3], w0[2], 0x07060302u),
+                               __builtin_amdgcn_perm(w1[1], w1[0], 0x07060302u), __builtin_amdgcn_perm(w1[3], w1[2], 0x07060302u)};
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < NB; ++e) {
+            const uint32_t *w = v_raw[e];
+            if constexpr (SAME) {
+                vpc[e][0][0] = uint2{__builtin_amdgcn_perm(w[1], w[0], 0x05040100u), __builtin_amdgcn_perm(w[3], w[2], 0x05040100u)};
+                vpc[e][1][0] = uint2{__builtin_amdgcn_perm(w[1], w[0], 0x07060302u), __builtin_amdgcn_perm(w[3], w[2], 0x07060302u)};
+            } else {
+                float2 vv[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    vv[v] = unpack_pair<TIn>(w[v]);
+                split_tile<TP, NPV>(f32x4_t{vv[0].x, vv[1].x, vv[2].x, vv[3].x}, vpc[e][0]);
+                split_tile<TP, NPV>(f32x4_t{vv[0].y, vv[1].y, vv[2].y, vv[3].y}, vpc[e][1]);
+            }
+        }
     }
     uint2 upc[NB][2][NPU];   // the pieces of U_e, column tile c (B-form)
+    auto cut_u = [](const f32x4_t &u, uint2(&p)[NPU]) {   // (16-bit records: already rounded)
+        if constexpr (NPU == 1)
+            p[0] = uint2{pack_pair<TRec>(u[0], u[1]), pack_pair<TRec>(u[2], u[3])};
+        else
+            split_tile<TP, NPU>(u, p);
+    };
+    // what the second panel keeps of U_0: one or two pieces as they are, but the fp32 values instead of
+    // three (16 registers less; they are cut again where they are used)
+    constexpr bool RECUT = NPU > 2;
+    f32x4_t ukeep[LONG && RECUT ? NB : 1][2];
     const size_t outp = (((size_t)b * Lmax) * a.Hv + h) * D;
     TRec *up = static_cast<TRec *>(a.st.buf_u);
 #pragma unroll
     for (int d = 0; d < NB; ++d) {
         if (d < nb) {   // uniform
             f32x4_t U[2] = {z4, z4}, o[2] = {z4, z4};
+            if constexpr (!LONG) {
 #pragma unroll
-            for (int p = NP - 1; p >= 0; --p) {   // smallest pieces first
+                for (int p = NP - 1; p >= 0; --p) {   // smallest pieces first
 #pragma unroll
-                for (int e2 = 0; e2 <= d / 2; ++e2) {
-                    const uint2 lo = pieceA(tri(d, 2 * e2), p)[lane];
-                    uint2 hi = {0u, 0u};
-                    if (2 * e2 + 1 <= d)
-                        hi = pieceA(tri(d, 2 * e2 + 1), p)[lane];
-                    const uint4 aop = {lo.x, lo.y, hi.x, hi.y};
+                    for (int e2 = 0; e2 <= d / 2; ++e2) {
+                        const uint2 lo = pieceA(tri(d, 2 * e2), p)[lane];
+                        uint2 hi = {0u, 0u};
+                        if (2 * e2 + 1 <= d)
+                            hi = pieceA(tri(d, 2 * e2 + 1), p)[lane];
+                        const uint4 aop = {lo.x, lo.y, hi.x, hi.y};
+#pragma unroll
+                        for (int c = 0; c < 2; ++c)
+                            U[c] = mfma16x32<TP>(aop, vop[e2][c], U[c]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e <= d; ++e) {
+                    uint2 ap[NP];
+#pragma unroll
+                    for (int p = 0; p < NP; ++p)
+                        ap[p] = pieceA(tri(d, e), p)[lane];
 #pragma unroll
                     for (int c = 0; c < 2; ++c)
-                        U[c] = mfma16x32<TIn>(aop, vop[e2][c], U[c]);
+                        U[c] = mm16_pieces<TP, NP, NPV>(ap, vpc[e][c], U[c]);
                 }
             }
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 if constexpr (sizeof(TRec) == 2) {
-                    // the outputs read the records as stored; a rounded value is one piece as it stands
+                    // the outputs read the records as stored
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                         U[c][v] = rounded_to<TRec>(U[c][v]);
-                    upc[d][c][0] = uint2{pack_pair<TRec>(U[c][0], U[c][1]), pack_pair<TRec>(U[c][2], U[c][3])};
-                } else {
-                    split_tile<TIn, NPU>(U[c], upc[d][c]);
                 }
+                cut_u(U[c], upc[d][c]);
+                if constexpr (LONG && RECUT)
+                    ukeep[d][c] = U[c];
             }
 #pragma unroll
             for (int e = 0; e <= d; ++e) {
@@ -665,7 +781,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                     mp[p] = pieceM(tri(d, e), p)[lane];
 #pragma unroll
                 for (int c = 0; c < 2; ++c)
-                    o[c] = mm16_pieces<TIn, NP, NPU>(mp, upc[e][c], o[c]);
+                    o[c] = mm16_pieces<TP, NP, NPU>(mp, upc[e][c], o[c]);
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -679,309 +795,266 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
             }
         }
     }
-    if (h == 0 && tid == 0)
-        a.st.fill[s] = L;
-}
-
-// ---------------------------------------------------------------------------
-// kvb_direct for contexts of 65 .. 128 tokens (16-bit inputs, d = 128): the block-row method with 8
-// blocks of 16 rows.  Kept apart from the kernel above, which is tuned around "4 blocks, one per wave" (its raw
-// Gram tiles and query operands all fit in registers at once).  Here a wave owns two diagonal
-// blocks and 16 of the 64 off-diagonal k.k and q.k tiles; the query rows of a tile are fetched
-// one tile ahead; the tile region (80 tiles, 80 KB) again takes the place of the staged keys.
-// ---------------------------------------------------------------------------
-template <typename TIn, typename TRec, bool PAGED>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void kvb_direct_mfma_long_kernel(
-    const DirectArgs a)
-{
-    constexpr int D = 128;
-    constexpr int NB = 8;                       // blocks of 16 rows
-    constexpr int LM = 16 * NB;                 // 128
-    constexpr int NLOW = NB * (NB + 1) / 2;     // block pairs d >= e (36)
-    constexpr int NKK = NB * (NB - 1) / 2;      // off-diagonal k.k pairs (28)
-    constexpr int NTPW = NB * NB / NW;          // off-diagonal k.k + all q.k tiles per wave (16)
-    constexpr int DPW = NB / NW;                // diagonal blocks per wave (2)
-    constexpr int GS = D + 8;
-    constexpr int STAGE_BYTES = LM * GS * 2;
-    constexpr int TILE_BYTES = (NKK + NLOW + NB) * 64 * 16;   // 72 KB: two workgroups per CU
-    __shared__ __attribute__((aligned(16))) unsigned char region[STAGE_BYTES > TILE_BYTES ? STAGE_BYTES : TILE_BYTES];
-    __shared__ __attribute__((aligned(16))) float sG[LM];
-    __shared__ __attribute__((aligned(16))) float sB[LM];
-    __shared__ int sBlk[NW][MAX_BLOCKS];
-    TIn *sK = reinterpret_cast<TIn *>(region);
-    float4(*tN)[64] = reinterpret_cast<float4(*)[64]>(region);
-    float4(*tM)[64] = tN + NKK;
-    float4(*tT)[64] = tM + NLOW;
-
-    // (the wave index as a scalar: conditions and tile numbers derived from it are then uniform for
-    // the compiler, scalar branches instead of masked ones)
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
-    const int c16 = lane % 16, lq = lane / 16;
-    const int lb = logical_block();
-    const int b = lb / a.Hv;
-    const int h = lb % a.Hv;
-    const int r = a.Hv / a.Hk;
-    const int hk = h / r;
-    const int Lmax = a.Lmax;
-
-    const int s = a.slot[b];
-    if (s < 0 || s >= a.st.n_slots)
-        return;
-    int L = a.len[b];
-    if (L < 0 || L > Lmax) {
-        L = Lmax;
-        if (tid == 0 && a.st.status)
-            atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
-    }
-    if (L == 0) {
-        if (h == 0 && tid == 0)
-            a.st.fill[s] = 0;
-        return;
-    }
-    const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, a.cap, sBlk[wave], lane, load_block_id<PAGED>(a.st, s, lane));
-    auto ru = [&](int l) { return pg.row(l, a.Hv, h); };
-    auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };
-    const TIn *qin = static_cast<const TIn *>(a.q);
-    const TIn *kin = static_cast<const TIn *>(a.k);
-    const TIn *vin = static_cast<const TIn *>(a.v);
-    const Out<TIn> out{a.out, a.out_wide != 0};
-    const int nb = (L + 15) / 16;
-    auto tri = [](int d, int e) { return d * (d + 1) / 2 + e; };    // slot of pair d >= e
-    auto trn = [](int d, int e) { return d * (d - 1) / 2 + e; };    // slot of pair d > e
-    // tile t of the dealing order -> block pair: t < NKK are the k.k pairs (d > e), row by row,
-    // then the q.k pairs (d >= e), row by row.  Uniform, a handful of scalar steps.
-    auto pair_of = [&](int t, int &d, int &e, bool &isq) {
-        isq = t >= NKK;
-        if (!isq) {
-            d = 1;
-            while (t >= d) {
-                t -= d;
-                ++d;
+    if constexpr (LONG) {
+        if (L > LM) {   // uniform
+            const int nb1 = (L - LM + 15) / 16;
+            // keys of both panels for staging (the first panel's again: their place in LDS was needed), and
+            // this wave's 16 query rows in operand layout
+            u32x4_t ks[2 * NB], qo[4];
+#pragma unroll
+            for (int p = 0; p < 2 * NB; ++p)
+                ks[p] = *reinterpret_cast<const u32x4_t *>(kbase + (uint32_t)min(16 * p + srow, L - 1) * qk_stride + 8 * sc8);
+            {
+                const uint32_t o = (uint32_t)min(LM + 16 * wave + c16, L - 1) * qk_stride + 8 * lq;
+#pragma unroll
+                for (int st = 0; st < 4; ++st)
+                    qo[st] = *reinterpret_cast<const u32x4_t *>(qbase + o + 32 * st);
             }
-        } else {
-            t -= NKK;
-            d = 0;
-            while (t > d) {
-                t -= d + 1;
-                ++d;
+            __syncthreads();   // the first panel's pieces are no longer read
+            TIn *sK1 = reinterpret_cast<TIn *>(region + STAGE_BYTES);
+#pragma unroll
+            for (int p = 0; p < NB; ++p) {
+                *reinterpret_cast<u32x4_t *>(sK + (16 * p + srow) * GS + 8 * sc8) = ks[p];
+                *reinterpret_cast<u32x4_t *>(sK1 + (16 * p + srow) * GS + 8 * sc8) = ks[NB + p];
+                if (h % r == 0 && LM + 16 * p + srow < L)
+                    *reinterpret_cast<u32x4_t *>(kb + rk(LM + 16 * p + srow) * D + 8 * sc8) = ks[NB + p];
             }
-        }
-        e = t;
-    };
+            __syncthreads();
 
-    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-    const int srow = tid / 16, sc8 = tid % 16;
-    const TIn *kbase = kin + ((size_t)b * Lmax * a.Hk + hk) * D;
-    const TIn *qbase = qin + ((size_t)b * Lmax * a.Hk + hk) * D;
-    const TIn *vbase = vin + ((size_t)b * Lmax * a.Hv + h) * D;
-    const uint32_t qk_stride = (uint32_t)a.Hk * D, v_stride = (uint32_t)a.Hv * D;
-    const int col2 = 32 * wave + 2 * c16;
-
-    // ---- keys: load, stage, append to the buffer --------------------------------
-    u32x4_t kst[NB];
+            // ---- Gram tiles of block row `wave` of this panel, keys and queries against the keys of the first
+            // panel (4 tiles) and of this one (up to the diagonal), weighted as they are (A-form: row LM + 16 wave +
+            // c16, columns 4 lq + v of the block)
+            f32x4_t n0[NB], m0[NB], n1[NB], m1[NB], gd1 = z4;
+            const int i1 = LM + 16 * wave + c16;
+            {
+                u32x4_t ko[4];
 #pragma unroll
-    for (int p = 0; p < NB; ++p) {   // rows past the context re-read its last row (never used)
-        const uint32_t o = (uint32_t)min(16 * p + srow, L - 1) * qk_stride + 8 * sc8;
-        kst[p] = *reinterpret_cast<const u32x4_t *>(kbase + o);   // (no branch around a load, as above)
-    }
-    // cumulative log decay and beta: wave 0 takes tokens 0..63, wave 1 tokens 64..127 (it adds
-    // the sum of the first 64 decays, which it forms itself)
-    if (wave < 2) {
-        const int t0 = 64 * wave + lane;
-        float gv = t0 < L ? a.g[((size_t)b * Lmax + t0) * a.Hv + h] : 0.0f;
-        const float bv = t0 < L ? a.beta[((size_t)b * Lmax + t0) * a.Hv + h] : 0.0f;
-        float base = 0.0f;
-        if (wave == 1) {
-            base = lane < L ? a.g[((size_t)b * Lmax + lane) * a.Hv + h] : 0.0f;
+                for (int st = 0; st < 4; ++st)
+                    ko[st] = *reinterpret_cast<const u32x4_t *>(sK1 + (16 * wave + c16) * GS + 8 * lq + 32 * st);
+                auto pair = [&](const TIn *arow, f32x4_t &n, f32x4_t &m) {
+                    n = m = z4;
 #pragma unroll
-            for (int off = 1; off < 64; off <<= 1)
-                base += __shfl_xor(base, off);
-        }
+                    for (int st = 0; st < 4; ++st) {
+                        const uint4 av = *reinterpret_cast<const uint4 *>(arow + 8 * lq + 32 * st);
+                        n = mfma16x32<TIn>(av, __builtin_bit_cast(uint4, ko[st]), n);
+                        m = mfma16x32<TIn>(av, __builtin_bit_cast(uint4, qo[st]), m);
+                    }
+                    settle(n, m);
+                };
+                const float gi = sG[i1], bi = sB[i1];
+                auto weigh = [&](int l0, const f32x4_t &x, float si, bool strict) {
+                    const float4 gl4 = *reinterpret_cast<const float4 *>(&sG[l0]);
+                    const float gl[4] = {gl4.x, gl4.y, gl4.z, gl4.w};
+                    f32x4_t o;
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const float t = __shfl_up(gv, off);
-            if (lane >= off)
-                gv += t;
-        }
-        gv += base;
-        sG[t0] = gv;
-        sB[t0] = bv;
-        if (t0 < L)
-            a.st.buf_G[ru(t0)] = gv;
-    }
-    TIn *kb = static_cast<TIn *>(a.st.buf_k);
+                    for (int v = 0; v < 4; ++v) {
+                        const int l = l0 + v;
+                        const bool ok = i1 < L && (strict ? l < i1 : l <= i1);
+                        o[v] = ok ? si * fast_exp(gi - gl[v]) * x[v] : 0.0f;
+                    }
+                    return o;
+                };
 #pragma unroll
-    for (int p = 0; p < NB; ++p) {
-        if (p < nb) {   // uniform
-            *reinterpret_cast<u32x4_t *>(sK + (16 * p + srow) * GS + 8 * sc8) = kst[p];
-            if (h % r == 0 && 16 * p + srow < L)
-                *reinterpret_cast<u32x4_t *>(kb + rk(16 * p + srow) * D + 8 * sc8) = kst[p];
-        }
-    }
-    __syncthreads();
-
-    // ---- raw Gram tiles ----------------------------------------------------------
-    f32x4_t gdiag[DPW];
-#pragma unroll
-    for (int x = 0; x < DPW; ++x) {
-        const int d = wave + NW * x;
-        gdiag[x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        if (d < nb)
-            gdiag[x] = gram16<TIn, GS>(sK + (16 * d + c16) * GS, sK + (16 * d + c16) * GS, lq);
-    }
-    // query rows of a q.k tile, in the operand layout (row 16 d + c16, k = 8 lq + 32 step),
-    // requested one tile ahead of their use
-    auto load_q = [&](int t, u32x4_t(&qq)[4]) {
-        int d, e;
-        bool isq;
-        pair_of(t, d, e, isq);
-        const uint32_t o = (uint32_t)min(16 * d + c16, L - 1) * qk_stride + 8 * lq;
-#pragma unroll
-        for (int st = 0; st < 4; ++st)   // (also for k.k tiles and empty blocks: no branch around a load)
-            qq[st] = *reinterpret_cast<const u32x4_t *>(qbase + o + 32 * st);
-    };
-    f32x4_t gsh[NTPW];
-    u32x4_t qa[4], qb[4];
-    load_q(wave, qa);
-#pragma unroll
-    for (int n = 0; n < NTPW; ++n) {
-        const int t = wave + NW * n;
-        if (n + 1 < NTPW) {
-            if (n % 2 == 0)
-                load_q(t + NW, qb);
-            else
-                load_q(t + NW, qa);
-        }
-        int d, e;
-        bool isq;
-        pair_of(t, d, e, isq);
-        gsh[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        if (d < nb) {   // uniform
-            if (!isq) {
-                gsh[n] = gram16<TIn, GS>(sK + (16 * e + c16) * GS, sK + (16 * d + c16) * GS, lq);
-            } else {
-                const TIn *arow = sK + (16 * e + c16) * GS;
-#pragma unroll
-                for (int st = 0; st < 4; ++st) {
-                    const uint4 av = *reinterpret_cast<const uint4 *>(arow + 8 * lq + 32 * st);
-                    gsh[n] = mfma16x32<TIn>(av, __builtin_bit_cast(uint4, n % 2 == 0 ? qa[st] : qb[st]), gsh[n]);
+                for (int e = 0; e < NB; ++e) {
+                    n0[e] = m0[e] = n1[e] = m1[e] = z4;
+                    if (wave < nb1) {
+                        pair(sK + (16 * e + c16) * GS, n0[e], m0[e]);
+                        n0[e] = weigh(16 * e + 4 * lq, n0[e], 1.0f, true);
+                        m0[e] = weigh(16 * e + 4 * lq, m0[e], 1.0f, true);
+                        if (e <= wave) {
+                            pair(sK1 + (16 * e + c16) * GS, n1[e], m1[e]);
+                            if (e < wave)
+                                n1[e] = weigh(LM + 16 * e + 4 * lq, n1[e], bi, true);
+                            else   // (the diagonal tile stays raw: diagonal_inverse weighs it in both forms)
+                                gd1 = n1[e];
+                            m1[e] = weigh(LM + 16 * e + 4 * lq, m1[e], 1.0f, false);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
-        }
-    }
-    __syncthreads();   // every wave is done with the staged rows: the region now takes the tiles
-
-    // v in B-form: rows 16 d + 4 lq + v, this lane's two adjacent columns
-    uint32_t v_raw[NB][4];
+            __syncthreads();   // the staged keys are no longer read
+            auto pieceX = [&](int d, int e, int p) {   // of the 4 x 4 tiles N', later M'
+                return reinterpret_cast<uint2 *>(region + X_BYTES + ((NB * d + e) * NP + p) * 512);
+            };
+            auto put_cross = [&](int e, const f32x4_t &x) {
+                uint2 pc[NP];
+                split_tile<TP, NP>(x, pc);
 #pragma unroll
-    for (int d = 0; d < NB; ++d)
+                for (int p = 0; p < NP; ++p)
+                    pieceX(wave, e, p)[lane] = pc[p];
+            };
+            t_own = z4;
+            if (wave < nb1) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            v_raw[d][v] = *reinterpret_cast<const uint32_t *>(
-                vbase + (uint32_t)min(16 * d + 4 * lq + v, L - 1) * v_stride + col2);
-        }
-
-    // weights and masks.  A-form element of tile (d, e): row i = 16 d + c16, column l = 16 e + 4 lq + v.
-#pragma unroll
-    for (int n = 0; n < NTPW; ++n) {
-        int d, e;
-        bool isq;
-        pair_of(wave + NW * n, d, e, isq);
-        if (d < nb) {
-            const int i = 16 * d + c16;
-            // (LDS reads without a condition, then selects: a read under a condition becomes a
-            // branch with a wait of its own, one round trip per element)
-            const float gi = sG[i];
-            const float si = isq ? 1.0f : -sB[i];
-            const float4 gl4 = *reinterpret_cast<const float4 *>(&sG[16 * e + 4 * lq]);
-            const float gl[4] = {gl4.x, gl4.y, gl4.z, gl4.w};
-            float o[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int l = 16 * e + 4 * lq + v;
-                const bool ok = i < L && (isq ? l <= i : l < i);
-                o[v] = ok ? si * fast_exp(gi - gl[v]) * gsh[n][v] : 0.0f;
+                for (int e = 0; e < NB; ++e) {
+                    put_cross(e, -n0[e]);
+                    if (e < wave)
+                        put_a(off_n(wave, e), n1[e]);
+                }
+                t_own = diagonal_inverse(LM + 16 * wave, gd1);
+                if (nb1 > 1)
+                    put_a(off_t(wave), t_own);
             }
-            const float4 o4 = make_float4(o[0], o[1], o[2], o[3]);
-            if (isq)
-                tM[tri(d, e)][lane] = o4;
-            else
-                tN[trn(d, e)][lane] = o4;
-        }
-    }
-    // T_d = (I + N_dd)^-1 for this wave's diagonal blocks (see the kernel above)
-#pragma unroll
-    for (int x = 0; x < DPW; ++x) {
-        const int d = wave + NW * x;
-        if (d < nb) {
-            f32x4_t na, nbm, ia;
-            const float gc = sG[16 * d + c16], bc = sB[16 * d + c16];
-            const float4 gq4 = *reinterpret_cast<const float4 *>(&sG[16 * d + 4 * lq]);
-            const float4 bq4 = *reinterpret_cast<const float4 *>(&sB[16 * d + 4 * lq]);
-            const float gq[4] = {gq4.x, gq4.y, gq4.z, gq4.w}, bq[4] = {bq4.x, bq4.y, bq4.z, bq4.w};
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int ia_i = 16 * d + c16, ia_l = 16 * d + 4 * lq + v;
-                const int ib_i = ia_l, ib_l = ia_i;
-                na[v] = (ia_i < L && ia_l < ia_i) ? bc * fast_exp(gc - gq[v]) * gdiag[x][v] : 0.0f;
-                nbm[v] = (ib_i < L && ib_l < ib_i) ? bq[v] * fast_exp(gq[v] - gc) * gdiag[x][v] : 0.0f;
-                ia[v] = ia_i == ia_l ? 1.0f : 0.0f;
-            }
-            const f32x4_t p = unit_lower_inverse16(na, nbm, ia, c16, lq);
-            tT[d][lane] = make_float4(p[0], p[1], p[2], p[3]);
-        }
-    }
-    __syncthreads();
+            __syncthreads();
 
-    // ---- block forward substitution and outputs, this wave's 32 columns ----------
-    f32x4_t U[NB][2];
-    const size_t outp = (((size_t)b * Lmax) * a.Hv + h) * D;
-    TRec *up = static_cast<TRec *>(a.st.buf_u);
-#pragma unroll
-    for (int d = 0; d < NB; ++d) {
-        if (d < nb) {   // uniform
-            f32x4_t acc[2], o[2];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = 16 * d + 4 * lq + v;
-                const float bi = sB[i];   // zero beyond the context
-                const float2 vv = unpack_pair<TIn>(v_raw[d][v]);
-                acc[0][v] = bi * vv.x;
-                acc[1][v] = bi * vv.y;
-            }
-            o[0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            o[1] = o[0];
-#pragma unroll
-            for (int e = 0; e < d; ++e) {
-                const float4 n4 = tN[trn(d, e)][lane];
-                const float4 m4 = tM[tri(d, e)][lane];
-                const f32x4_t nn = {n4.x, n4.y, n4.z, n4.w}, mm = {m4.x, m4.y, m4.z, m4.w};
+            // The products below go through the right factor block by block: its pieces are cut once and meet
+            // every row block, whose eight sums are independent chains.
+            auto first_panel_pieces = [&](int e, uint2(&up0)[2][NPU]) {
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    acc[c] = mm16(nn, U[e][c], acc[c]);
-                    o[c] = mm16(mm, U[e][c], o[c]);
+                    if constexpr (RECUT) {
+                        // (opaque, or the compiler keeps the pieces of an earlier cut in registers instead)
+                        asm volatile("" : "+v"(ukeep[e][c]));
+                        split_tile<TP, NPU>(ukeep[e][c], up0[c]);
+                    } else {
+#pragma unroll
+                        for (int p = 0; p < NPU; ++p)
+                            up0[c][p] = upc[e][c][p];
+                    }
+                }
+            };
+            auto cross_product = [&](f32x4_t(&acc)[NB][2]) {   // acc_d += sum_e (tile d, e in LDS) U_0e
+#pragma unroll
+                for (int e = 0; e < NB; ++e) {
+                    uint2 up0[2][NPU];
+                    first_panel_pieces(e, up0);
+#pragma unroll
+                    for (int d = 0; d < NB; ++d) {
+                        if (d < nb1) {   // uniform
+                            uint2 tp[NP];
+#pragma unroll
+                            for (int p = 0; p < NP; ++p)
+                                tp[p] = pieceX(d, e, p)[lane];
+#pragma unroll
+                            for (int c = 0; c < 2; ++c)
+                                acc[d][c] = mm16_pieces<TP, NP, NPU>(tp, up0[c], acc[d][c]);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // (one step's operands in registers at a time)
+                }
+            };
+            // ---- X = V_1 - N' U_0 beside the first half of the inverse
+            // (v in B-form: rows LM + 16 d + 4 lq + v, this lane's two columns; needed at the end only)
+            uint32_t v1_raw[NB][4];
+#pragma unroll
+            for (int d = 0; d < NB; ++d)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    v1_raw[d][v] = *reinterpret_cast<const uint32_t *>(
+                        vbase + (uint32_t)min(LM + 16 * d + 4 * lq + v, L - 1) * v_stride + col2);
+            inverse_first_half(nb1, t_own);
+            f32x4_t x[NB][2];
+#pragma unroll
+            for (int d = 0; d < NB; ++d)
+                x[d][0] = x[d][1] = z4;
+            cross_product(x);   // (N' is stored negated)
+            settle(x);
+#pragma unroll
+            for (int d = 0; d < NB; ++d)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float2 vv = unpack_pair<TIn>(v1_raw[d][v]);
+                    x[d][0][v] += vv.x;
+                    x[d][1][v] += vv.y;
+                }
+            __syncthreads();
+            inverse_second_half(LM, nb1, t_own);
+            if (wave < nb1) {
+#pragma unroll
+                for (int e = 0; e < NB; ++e)
+                    put_cross(e, m0[e]);   // M' in the place of N'
+            }
+            __syncthreads();
+
+            // ---- M' U_0, then U_1 = A^_1 X: row block e is complete with step e
+            f32x4_t o1[NB][2], u1[NB][2];
+#pragma unroll
+            for (int d = 0; d < NB; ++d)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    o1[d][c] = u1[d][c] = z4;
+            cross_product(o1);
+            settle(o1);
+#pragma unroll
+            for (int e = 0; e < NB; ++e) {
+                if (e < nb1) {   // uniform
+                    uint2 xp[2][NP];
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+                        split_tile<TP, NP>(x[e][c], xp[c]);
+#pragma unroll
+                    for (int d = e; d < NB; ++d) {
+                        if (d < nb1) {   // uniform
+                            uint2 ap[NP];
+#pragma unroll
+                            for (int p = 0; p < NP; ++p)
+                                ap[p] = pieceA(tri(d, e), p)[lane];
+#pragma unroll
+                            for (int c = 0; c < 2; ++c)
+                                u1[d][c] = mm16_pieces<TP, NP, NP>(ap, xp[c], u1[d][c]);
+                        }
+                    }
+                    settle(u1[e][0], u1[e][1]);
+                    if constexpr (sizeof(TRec) == 2) {
+#pragma unroll
+                        for (int c = 0; c < 2; ++c)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                u1[e][c][v] = rounded_to<TRec>(u1[e][c][v]);
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int i = LM + 16 * e + 4 * lq + v;
+                        if (i < L)
+                            store2_nt(up + (ru(i) * D + col2), u1[e][0][v], u1[e][1][v]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            __syncthreads();   // M' is no longer read: the pieces of M_1 take its place
+            if (wave < nb1) {
+#pragma unroll
+                for (int e = 0; e < NB; ++e) {
+                    if (e <= wave) {
+                        uint2 pc[NP];
+                        split_tile<TP, NP>(m1[e], pc);
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+                            pieceM(tri(wave, e), p)[lane] = pc[p];
+                    }
                 }
             }
-            const float4 t4 = tT[d][lane];
-            const float4 m4 = tM[tri(d, d)][lane];
-            const f32x4_t tt = {t4.x, t4.y, t4.z, t4.w}, mm = {m4.x, m4.y, m4.z, m4.w};
+            __syncthreads();
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                U[d][c] = mm16(tt, acc[c], f32x4_t{0.f, 0.f, 0.f, 0.f});
-                if constexpr (sizeof(TRec) == 2) {   // later blocks and this block's outputs read the records as stored
+            for (int e = 0; e < NB; ++e) {
+                if (e < nb1) {   // uniform
+                    uint2 up1[2][NPU];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        U[d][c][v] = rounded_to<TRec>(U[d][c][v]);
+                    for (int c = 0; c < 2; ++c) {
+                        cut_u(u1[e][c], up1[c]);
+                    }
+#pragma unroll
+                    for (int d = e; d < NB; ++d) {
+                        if (d < nb1) {   // uniform
+                            uint2 mp[NP];
+#pragma unroll
+                            for (int p = 0; p < NP; ++p)
+                                mp[p] = pieceM(tri(d, e), p)[lane];
+#pragma unroll
+                            for (int c = 0; c < 2; ++c)
+                                o1[d][c] = mm16_pieces<TP, NP, NPU>(mp, up1[c], o1[d][c]);
+                        }
+                    }
+                    settle(o1[e][0], o1[e][1]);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int i = LM + 16 * e + 4 * lq + v;
+                        if (i < L)
+                            out.put2_nt(outp + ((uint32_t)i * v_stride + col2), a.scale * o1[e][0][v], a.scale * o1[e][1][v]);
+                    }
                 }
-                o[c] = mm16(mm, U[d][c], o[c]);
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = 16 * d + 4 * lq + v;
-                if (i < L) {
-                    out.put2(outp + ((uint32_t)i * v_stride + col2), a.scale * o[0][v], a.scale * o[1][v]);
-                    store2(up + (ru(i) * D + col2), U[d][0][v], U[d][1][v]);
-                }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
@@ -996,12 +1069,14 @@ int launch_direct(int dk, int in_dtype, int rec_dtype, const DirectArgs &a, int 
 {
     if (dk == 128 && in_dtype != KVB_F32)
         return dispatch_types16(in_dtype, rec_dtype, [&]<typename TIn, typename TRec>() {
-            if (a.Lmax > 64)   // 5 .. 8 blocks of 16 rows
-                LAUNCH_PAGED(blocks, stream, a, kvb_direct_mfma_long_kernel<TIn, TRec);
+            if (a.Lmax > 64 && a.st.block_table)   // two panels of 64 rows
+                launch(kvb_direct_mfma_kernel<TIn, TRec, true, true>, blocks, stream, a.len, a.Hv, blocks, a);
+            else if (a.Lmax > 64)
+                launch(kvb_direct_mfma_kernel<TIn, TRec, true, false>, blocks, stream, a.len, a.Hv, blocks, a);
             else if (a.st.block_table)
-                launch(kvb_direct_mfma_kernel<TIn, TRec, true>, blocks, stream, a.len, a.Hv, blocks, a);
+                launch(kvb_direct_mfma_kernel<TIn, TRec, false, true>, blocks, stream, a.len, a.Hv, blocks, a);
             else
-                launch(kvb_direct_mfma_kernel<TIn, TRec, false>, blocks, stream, a.len, a.Hv, blocks, a);
+                launch(kvb_direct_mfma_kernel<TIn, TRec, false, false>, blocks, stream, a.len, a.Hv, blocks, a);
         });
     if (a.Lmax > 64)   // the plain kernel holds a 64-token context in LDS
         return KVB_EUNSUPPORTED;
