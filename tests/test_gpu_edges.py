@@ -22,3 +22,12 @@ def test_direct_second_panel(in_dtype, rec_dtype, block_size):
                      then_decode=False, rec_dtype=rec_dtype, out_dtype=rec_dtype, block_size=block_size)
     say("direct, second panel, %s/%s: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((in_dtype, rec_dtype) + e))
     H.check(e, in_dtype, rec_dtype, "second panel")
+
+
+@pytest.mark.parametrize("B, Hk, Hv", [(3, 8, 24), (5, 3, 9), (1, 1, 4), (2, 4, 4), (7, 16, 32)])
+@pytest.mark.parametrize("Lmax", [33, 90])
+def test_direct_every_unit_is_taken_once(B, Hk, Hv, Lmax):
+    """Head counts that deal over the 8 XCDs and ones that do not; an untaken unit leaves NaN in its outputs."""
+    e = _direct_case(B=B, Hk=Hk, Hv=Hv, d=128, Lmax=Lmax, cap=Lmax, in_dtype="bf16", seed=810 + B + Lmax)
+    say("direct, B=%d heads %d/%d Lmax=%d: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((B, Hk, Hv, Lmax) + e))
+    H.check(e, "bf16", what="dealt units")
