@@ -56,9 +56,8 @@ extern "C" {
  * allowed rec_dtype / out_dtype) is the pair the kernels are built and measured for: matrix-
  * instruction kernels for kvb_verify, kvb_verify_tree, kvb_flush and kvb_direct, the streaming
  * decode kernel for kvb_decode / kvb_decode_flush.  KVB_F32 inputs at any head size, and
- * d = 32 or 64 with any input type, run plain vector-ALU kernels that exist for correctness
- * (the fp32 parity workload, small test shapes): same results, no performance claim, and
- * kvb_direct is limited to 64 tokens there. */
+ * d = 32 or 64 with any input type, run vector-ALU kernels (kvb_direct: the fp32 matrix
+ * instruction): same results, and kvb_direct is limited to 64 tokens there. */
 
 #define KVB_MAX_CAP        128 /* largest `cap` (the paper buffers at most d records, Sec. 3.4) */
 #define KVB_MAX_DRAFTS       8 /* largest T of kvb_verify (Sec. 4.2 sweeps up to 8)             */
@@ -242,8 +241,8 @@ int kvb_compact(const kvb_shape *shape, const kvb_store *store, const int32_t *s
  * len[b] outside 0..Lmax is clamped to Lmax with KVB_STATUS_OVERFLOW.
  * With a 16-bit rec_dtype the outputs read the records as stored (rounded), like everywhere
  * else; the delta values themselves are solved for in fp32 before they are rounded -- all
- * rows at once up to 64 tokens, 64 rows at a time above that -- so a row's delta value does
- * not see the rounding of the rows solved with it.
+ * rows at once up to 64 tokens, 64 rows at a time above that (d = 128) -- so a row's delta
+ * value does not see the rounding of the rows solved with it.
  */
 int kvb_direct(const kvb_shape *shape, const kvb_store *store, const int32_t *slot,
                const int32_t *len, int32_t Lmax,

@@ -6,7 +6,7 @@
 //                        kvb_step_bf16_r16.hip, kvb_step_f16.hip, kvb_step_f16_r16.hip
 //   kvb_verify_kernel.h  kvb_verify_mfma_kernel; instantiated by kvb_verify_bf16.hip, kvb_verify_f16.hip
 //   kvb_flush.hip        kvb_flush_mfma_kernel, kvb_flush_kernel, kvb_compact_kernel
-//   kvb_direct.hip       kvb_direct_mfma_kernel, kvb_direct_kernel
+//   kvb_direct.hip       kvb_direct_mfma_kernel, kvb_direct_rows_kernel
 //   kvb_api.hip          argument checks, the extern "C" entry points, the kernel timer
 //
 // Element types (Sec. 4.1: 16-bit vectors and records beside a fp32 state): TIn is the type of
@@ -26,7 +26,7 @@
 //                           16-bit pieces of the fp32 factor
 //   kvb_flush_kernel        the same for the other types and head sizes: vector ALUs
 //   kvb_direct_mfma_kernel  short contexts, 16-bit inputs / d = 128: matrix cores throughout
-//   kvb_direct_kernel       short contexts, other types and head sizes
+//   kvb_direct_rows_kernel  short contexts, other types and head sizes: fp32 matrix instruction, block row by block row
 //
 // Notation follows App. A.1: gamma_i = exp(G_i), Gamma_il = exp(G_i - G_l).
 

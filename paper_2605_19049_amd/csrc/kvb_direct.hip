@@ -1,116 +1,11 @@
-// kvb_direct: kvb_direct_mfma_kernel (16-bit inputs, d = 128) and kvb_direct_kernel (fp32 inputs and the other
-// head sizes).
+// kvb_direct: kvb_direct_mfma_kernel (16-bit inputs, d = 128) and kvb_direct_rows_kernel (fp32 inputs and the
+// other head sizes).
 #include "kvb_device.h"
 
 namespace kvb_impl {
 
-// ---------------------------------------------------------------------------
-// kvb_direct: the parallel form, Eq. 13, from a zero state.
-//   cK[i][l] = Gamma_il (k_i.k_l) (l < i)     cQ[i][l] = Gamma_il (q_i.k_l) (l <= i)
-//   u_i = beta_i ( v_i - sum_{l<i} cK[i][l] u_l )       (row i of A Diag(beta) V)
-//   o_i = scale * sum_{l<=i} cQ[i][l] u_l
-// ---------------------------------------------------------------------------
-template <int D, typename TIn, typename TRec, bool PAGED>
-__global__ __launch_bounds__(NT) void kvb_direct_kernel(const DirectArgs a)
-{
-    constexpr int LM = 64;   // longest context of this kernel
-    __shared__ float sK[LM][D + 1];
-    __shared__ float sQ[LM][D + 1];
-    __shared__ float cK[LM][LM + 1];
-    __shared__ float cQ[LM][LM + 1];
-    __shared__ float sU[LM][D];
-    __shared__ float sG[LM];
-    __shared__ float sB[LM];
-    __shared__ int sBlk[NW][MAX_BLOCKS];
-
-    const int tid = threadIdx.x;
-    const int lb = logical_block();
-    const int b = lb / a.Hv;
-    const int h = lb % a.Hv;
-    const int r = a.Hv / a.Hk;
-    const int hk = h / r;
-    const int Lmax = a.Lmax;
-
-    const int s = a.slot[b];
-    if (s < 0 || s >= a.st.n_slots)
-        return;
-    int L = a.len[b];
-    if (L < 0 || L > Lmax) {
-        L = Lmax;
-        if (tid == 0 && a.st.status)
-            atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
-    }
-    const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, a.cap, sBlk[tid / 64], tid % 64, load_block_id<PAGED>(a.st, s, tid % 64));
-    auto ru = [&](int l) { return pg.row(l, a.Hv, h); };
-    auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };
-    const TIn *qin = static_cast<const TIn *>(a.q);
-    const TIn *kin = static_cast<const TIn *>(a.k);
-    const TIn *vin = static_cast<const TIn *>(a.v);
-    const Out<TIn> out{a.out, a.out_wide != 0};
-
-    for (int idx = tid; idx < L * D; idx += NT) {
-        const int i = idx / D, e = idx % D;
-        const size_t o = (((size_t)b * Lmax + i) * a.Hk + hk) * D + e;
-        sK[i][e] = to_f32(kin[o]);
-        sQ[i][e] = to_f32(qin[o]);
-    }
-    if (tid < L) {
-        float run = 0.0f;
-        for (int t = 0; t <= tid; ++t)
-            run += a.g[((size_t)b * Lmax + t) * a.Hv + h];
-        sG[tid] = run;
-        sB[tid] = a.beta[((size_t)b * Lmax + tid) * a.Hv + h];
-    }
-    __syncthreads();
-
-    for (int p = tid; p < L * L; p += NT) {
-        const int i = p / L, l = p % L;
-        if (l <= i) {
-            float dkk = 0.0f, dqk = 0.0f;
-#pragma unroll 8
-            for (int e = 0; e < D; ++e) {
-                const float kl = sK[l][e];
-                dkk = fmaf(sK[i][e], kl, dkk);
-                dqk = fmaf(sQ[i][e], kl, dqk);
-            }
-            const float gam = expf(sG[i] - sG[l]);
-            cK[i][l] = gam * dkk;
-            cQ[i][l] = gam * dqk;
-        }
-    }
-    __syncthreads();
-
-    if (tid < D) {
-        for (int i = 0; i < L; ++i) {
-            const size_t row = ((size_t)b * Lmax + i) * a.Hv + h;
-            float acc = to_f32(vin[row * D + tid]);
-            float o = 0.0f;
-            for (int l = 0; l < i; ++l) {
-                const float ul = sU[l][tid];
-                acc = fmaf(-cK[i][l], ul, acc);
-                o = fmaf(cQ[i][l], ul, o);
-            }
-            // the record as it is stored is what every later use reads
-            const TRec ur_i = from_f32<TRec>(sB[i] * acc);
-            const float ui = to_f32(ur_i);
-            sU[i][tid] = ui;
-            o = fmaf(cQ[i][i], ui, o);
-            out.put1(row * D + tid, a.scale * o);
-            static_cast<TRec *>(a.st.buf_u)[ru(i) * D + tid] = ur_i;
-        }
-    }
-    if (tid < L)
-        a.st.buf_G[ru(tid)] = sG[tid];
-    if (h % r == 0) {
-        TIn *kb = static_cast<TIn *>(a.st.buf_k);
-        for (int idx = tid; idx < L * D; idx += NT) {
-            const int i = idx / D, e = idx % D;
-            kb[rk(i) * D + e] = kin[(((size_t)b * Lmax + i) * a.Hk + hk) * D + e];
-        }
-    }
-    if (h == 0 && tid == 0)
-        a.st.fill[s] = L;
-}
+// (HIP's uint4 is a struct: arrays of it can end up in scratch memory)
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // kvb_direct for 16-bit inputs (bf16 or fp16) and d = 128, on the matrix cores throughout.
@@ -441,7 +336,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     // make the passes take their round trips one after the other; a row past the context re-reads
     // the context's last row from the cache and is never used.  Reading the rows up to Lmax as they
     // are instead would cost a short context the traffic of a long one.)
-    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     u32x4_t kst[NB];
     const int srow = tid / 16, sc8 = tid % 16;
     const int col2 = 32 * wave + 2 * c16;
@@ -1084,6 +978,292 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
 }
 
 // ---------------------------------------------------------------------------
+// kvb_direct for fp32 inputs at any head size and for 16-bit inputs at d = 32 and 64 (contexts of up to 64
+// tokens): block row by block row,
+//     U_d = T_d ( beta V_d - sum_{e<d} N_de U_e ),      O_d = sum_{e<=d} M_de U_e,
+// all products with fp32 values on v_mfma_f32_16x16x4_f32 (exact products), T_d by unit_lower_inverse16, the
+// Gram tiles of 16-bit inputs on the 16-bit instruction.  With heads this small (or inputs this wide) a unit
+// is a chain of waits rather than of products, so the pieces of the kernel above would shorten nothing and
+// cost registers; what counts is that every input is requested at once and that no step is taken row by row.
+// 48 contexts of ~U(1,64), 8/16 heads of 64, bf16, with the fold (17 us of it): 204 -> 32 us a pass against the
+// kernel before it, which kept everything in LDS and solved row by row on the vector ALU.
+// ---------------------------------------------------------------------------
+// The 16 x 16 tile (rows of block d against rows of block e) in A-form: `rows` are the staged keys of block e,
+// `own` this lane's part of row 16 d + c16, 16 bytes a step.
+template <typename TIn, int D, int NST>
+__device__ __forceinline__ f32x4_t gram_rows(const TIn *rows, const u32x4_t (&own)[NST], int lq)
+{
+    f32x4_t c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < NST; ++st) {
+        const u32x4_t av = *reinterpret_cast<const u32x4_t *>(rows + (D / NST) * st + (D / NST / 4) * lq);
+        if constexpr (sizeof(TIn) == 2) {
+            c = mfma16x32<TIn>(__builtin_bit_cast(uint4, av), __builtin_bit_cast(uint4, own[st]), c);
+        } else {   // k = 16 st + 4 lq + v on both sides
+            const f32x4_t x = __builtin_bit_cast(f32x4_t, av), y = __builtin_bit_cast(f32x4_t, own[st]);
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0], y[0], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1], y[1], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[2], y[2], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[3], y[3], c, 0, 0, 0);
+        }
+    }
+    if constexpr (sizeof(TIn) == 4)
+        asm volatile("s_nop 10" : "+v"(c));   // (settled, as in settle() above; 11 wait states for the fp32 instruction)
+    return c;
+}
+
+template <int D, typename TIn, typename TRec, bool PAGED>
+// (register budgets: 4 workgroups per CU; fp32 rows of 128 take 55 KB of LDS, two)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4))) void kvb_direct_rows_kernel(
+    const int32_t *len_arg, int32_t Hv_arg, int32_t deal_arg, const DirectArgs a)
+{
+    // (leading arguments: see kvb_direct_mfma_kernel)
+    constexpr int LM = 64;   // longest context
+    constexpr int NB = LM / 16;
+    constexpr int NLOW = NB * (NB + 1) / 2, NKK = NB * (NB - 1) / 2;
+    constexpr int NC = D == 128 ? 2 : 1;          // column tiles per wave (d = 32: the last two waves have none)
+    constexpr int EPC = 16 / sizeof(TIn);         // elements per 16-byte chunk
+    constexpr int CPR = D / EPC;                  // chunks per row
+    constexpr int NPS = LM * CPR / NT;            // chunks of K per thread
+    constexpr int NST = D / (4 * EPC);            // steps of a Gram tile
+    constexpr int GS = D + EPC;                   // LDS row stride: consecutive rows start 4 banks apart
+    static_assert(NB == NW, "one diagonal block per wave");
+    __shared__ __attribute__((aligned(16))) TIn sK[LM * GS];
+    __shared__ float4 tN[NKK][64], tM[NLOW][64], tT[NB][64];   // -N_de (d > e), M_de, T_d in A-form, a lane's values together
+    constexpr bool R16 = sizeof(TRec) == 2;
+    __shared__ float4 tD[R16 ? NB : 1][64];                    // -N_dd
+    __shared__ __attribute__((aligned(16))) float sG[LM], sB[LM];
+    __shared__ int sBlk[NW][MAX_BLOCKS];
+
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;   // (a scalar)
+    const int c16 = lane % 16, lq = lane / 16;
+    const int lb = dealt_block(deal_arg);
+    const int b = lb / Hv_arg;
+    int L = len_arg[b];
+    __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
+    const int h = lb % Hv_arg;
+    const int r = a.Hv / a.Hk;
+    const int hk = h / r;
+    const int Lmax = a.Lmax;
+
+    const int s = a.slot[b];
+    if (s < 0 || s >= a.st.n_slots)
+        return;
+    if (L < 0 || L > Lmax) {
+        L = Lmax;
+        if (tid == 0 && a.st.status)
+            atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
+    }
+    if (L == 0) {
+        if (h == 0 && tid == 0)
+            a.st.fill[s] = 0;
+        return;
+    }
+    // ---- every input is requested at once (no branch around a load; a row past the context re-reads its last row)
+    const TIn *kbase = static_cast<const TIn *>(a.k) + ((size_t)b * Lmax * a.Hk + hk) * D;
+    const TIn *qbase = static_cast<const TIn *>(a.q) + ((size_t)b * Lmax * a.Hk + hk) * D;
+    const TIn *vbase = static_cast<const TIn *>(a.v) + ((size_t)b * Lmax * a.Hv + h) * D;
+    const uint32_t qk_stride = (uint32_t)a.Hk * D, v_stride = (uint32_t)a.Hv * D;
+    u32x4_t kst[NPS];
+    const int srow = tid / CPR, sch = tid % CPR;   // this thread's row within a pass of NT / CPR rows, and its chunk
+#pragma unroll
+    for (int p = 0; p < NPS; ++p)
+        kst[p] = *reinterpret_cast<const u32x4_t *>(kbase + (uint32_t)min(NT / CPR * p + srow, L - 1) * qk_stride + EPC * sch);
+    // pairs of blocks, dealt round-robin as in kvb_direct_mfma_kernel: t = wave + 4 n; t < 6 are k.k pairs, the rest q.k
+    constexpr uint32_t PDB = pack2(1, 2, 2, 3, 3, 3, 0, 1, 1, 2, 2, 2, 3, 3, 3, 3);
+    constexpr uint32_t PEB = pack2(0, 0, 1, 0, 1, 2, 0, 0, 1, 0, 1, 2, 0, 1, 2, 3);
+    auto PD = [](int t) { return (int)((PDB >> (2 * t)) & 3u); };
+    auto PE = [](int t) { return (int)((PEB >> (2 * t)) & 3u); };
+    u32x4_t qop[3][NST];   // n = 1 (waves 2, 3 only), 2, 3
+#pragma unroll
+    for (int n = 1; n < 4; ++n) {
+        const uint32_t o = (uint32_t)min(16 * PD(wave + NW * n) + c16, L - 1) * qk_stride + EPC * lq;
+#pragma unroll
+        for (int st = 0; st < NST; ++st)
+            qop[n - 1][st] = *reinterpret_cast<const u32x4_t *>(qbase + o + 4 * EPC * st);
+    }
+    const size_t gb_o = ((size_t)b * Lmax + min(lane, L - 1)) * a.Hv + h;
+    const float g_raw = a.g[gb_o], beta_raw = a.beta[gb_o];
+    // v in B-form: rows 16 d + 4 lq + v, columns col0 .. col0 + NC - 1
+    const bool has_cols = 16 * NC * wave < D;   // uniform
+    const int col0 = has_cols ? 16 * NC * wave + NC * c16 : 0;
+    struct VRow {
+        TIn x[NC];
+    } __attribute__((aligned(NC * sizeof(TIn))));
+    VRow v_raw[NB][4];
+#pragma unroll
+    for (int d = 0; d < NB; ++d)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            v_raw[d][v] = *reinterpret_cast<const VRow *>(vbase + (uint32_t)min(16 * d + 4 * lq + v, L - 1) * v_stride + col0);
+
+    const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, a.cap, sBlk[wave], lane, load_block_id<PAGED>(a.st, s, lane));
+    auto ru = [&](int l) { return pg.row(l, a.Hv, h); };
+    auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };
+    const Out<TIn> out{a.out, a.out_wide != 0};
+    const int nb = (L + 15) / 16;
+    auto tri = [](int d, int e) { return d * (d + 1) / 2 + e; };    // slot of pair d >= e
+    auto trn = [](int d, int e) { return d * (d - 1) / 2 + e; };    // slot of pair d > e
+
+    // stage K; the thread that loaded a piece of K also appends it to the buffer
+    TIn *kb = static_cast<TIn *>(a.st.buf_k);
+#pragma unroll
+    for (int p = 0; p < NPS; ++p) {
+        const int row = NT / CPR * p + srow;
+        *reinterpret_cast<u32x4_t *>(sK + row * GS + EPC * sch) = kst[p];
+        if (h % r == 0 && row < L)
+            *reinterpret_cast<u32x4_t *>(kb + rk(row) * D + EPC * sch) = kst[p];
+    }
+    // Cumulative log decay and beta.  Token by token: only differences G_i - G_l are used, nearby ones above all,
+    // and the roundings of a running sum cancel in them (a scan over the wave was 1.4 times further off in the
+    // outputs and the state).  The lane's sum takes part up to its own token.
+    if (wave == 0) {
+        const float gv = lane < L ? g_raw : 0.0f;
+        float run = 0.0f;
+        for (int t0 = 0; t0 < 16 * nb; t0 += 16) {
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                const float gt = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, gv), t0 + t));
+                run += t0 + t <= lane ? gt : 0.0f;
+            }
+        }
+        sG[lane] = run;
+        sB[lane] = lane < L ? beta_raw : 0.0f;
+        if (lane < L)
+            a.st.buf_G[ru(lane)] = run;
+    }
+    __syncthreads();
+
+    // ---- Gram tiles, weighted and masked at once (A-form: row i = 16 d + c16, column l = 16 e + 4 lq + v) ----
+    auto own_keys = [&](int d, u32x4_t(&x)[NST]) {
+#pragma unroll
+        for (int st = 0; st < NST; ++st)
+            x[st] = *reinterpret_cast<const u32x4_t *>(sK + (16 * d + c16) * GS + 4 * EPC * st + EPC * lq);
+    };
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const int t = wave + NW * n, d = PD(t), e = PE(t);
+        if (d < nb) {   // uniform
+            const bool isq = t >= 6;   // (implies n >= 1)
+            f32x4_t raw;
+            if (isq) {
+                raw = gram_rows<TIn, D, NST>(sK + (16 * e + c16) * GS, qop[n > 0 ? n - 1 : 0], lq);
+            } else {
+                u32x4_t own[NST];
+                own_keys(d, own);
+                raw = gram_rows<TIn, D, NST>(sK + (16 * e + c16) * GS, own, lq);
+            }
+            const int i = 16 * d + c16;
+            const float gi = sG[i];
+            const float si = isq ? 1.0f : -sB[i];
+            const float4 gl4 = *reinterpret_cast<const float4 *>(&sG[16 * e + 4 * lq]);
+            const float gl[4] = {gl4.x, gl4.y, gl4.z, gl4.w};
+            float o[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int l = 16 * e + 4 * lq + v;
+                const bool ok = i < L && (isq ? l <= i : l < i);
+                o[v] = ok ? si * expf(gi - gl[v]) * raw[v] : 0.0f;
+            }
+            if (isq)
+                tM[tri(d, e)][lane] = make_float4(o[0], o[1], o[2], o[3]);
+            else
+                tN[trn(d, e)][lane] = make_float4(o[0], o[1], o[2], o[3]);
+        }
+    }
+    // T_d = (I + N_dd)^-1 for d = wave.  The raw diagonal tile is symmetric: the same registers give both forms.
+    if (wave < nb) {
+        const int d = wave;
+        u32x4_t own[NST];
+        own_keys(d, own);
+        const f32x4_t gdiag = gram_rows<TIn, D, NST>(sK + (16 * d + c16) * GS, own, lq);
+        f32x4_t na, nbm, ia;
+        const float gc = sG[16 * d + c16], bc = sB[16 * d + c16];
+        const float4 gq4 = *reinterpret_cast<const float4 *>(&sG[16 * d + 4 * lq]);
+        const float4 bq4 = *reinterpret_cast<const float4 *>(&sB[16 * d + 4 * lq]);
+        const float gq[4] = {gq4.x, gq4.y, gq4.z, gq4.w}, bq[4] = {bq4.x, bq4.y, bq4.z, bq4.w};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int ia_i = 16 * d + c16, ia_l = 16 * d + 4 * lq + v;    // A-form indices
+            const int ib_i = ia_l, ib_l = ia_i;                            // B-form indices
+            na[v] = (ia_i < L && ia_l < ia_i) ? bc * expf(gc - gq[v]) * gdiag[v] : 0.0f;
+            nbm[v] = (ib_i < L && ib_l < ib_i) ? bq[v] * expf(gq[v] - gc) * gdiag[v] : 0.0f;
+            ia[v] = ia_i == ia_l ? 1.0f : 0.0f;
+        }
+        const f32x4_t p = unit_lower_inverse16(na, nbm, ia, c16, lq);
+        tT[d][lane] = make_float4(p[0], p[1], p[2], p[3]);
+        if constexpr (R16)
+            tD[d][lane] = make_float4(-na[0], -na[1], -na[2], -na[3]);
+    }
+    __syncthreads();
+
+    // ---- block forward substitution and outputs, this wave's columns ----
+    if (has_cols) {
+        const f32x4_t z4 = {0.f, 0.f, 0.f, 0.f};
+        auto tile = [&](const float4 &t) { return f32x4_t{t.x, t.y, t.z, t.w}; };
+        f32x4_t U[NB][NC];
+        const size_t outp = (((size_t)b * Lmax) * a.Hv + h) * D;
+        TRec *up = static_cast<TRec *>(a.st.buf_u);
+#pragma unroll
+        for (int d = 0; d < NB; ++d) {
+            if (d < nb) {   // uniform
+                f32x4_t acc[NC], o[NC];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    o[c] = z4;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        acc[c][v] = sB[16 * d + 4 * lq + v] * to_f32(v_raw[d][v].x[c]);   // (beta is zero beyond the context)
+                }
+#pragma unroll
+                for (int e = 0; e < d; ++e) {
+                    const f32x4_t nn = tile(tN[trn(d, e)][lane]), mm = tile(tM[tri(d, e)][lane]);
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        acc[c] = mm16(nn, U[e][c], acc[c]);
+                        o[c] = mm16(mm, U[e][c], o[c]);
+                    }
+                }
+                const f32x4_t tt = tile(tT[d][lane]), mm = tile(tM[tri(d, d)][lane]);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    U[d][c] = mm16(tt, acc[c], z4);
+                    if constexpr (R16) {
+                        // Later blocks and this block's outputs read the records as stored, and so do the rows of
+                        // the block themselves: once more, U = acc - N_dd U, from the rounded values (without it the
+                        // outputs are 3 % further from 64 bits).
+                        auto round_all = [&](f32x4_t x) {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                x[v] = rounded_to<TRec>(x[v]);
+                            return x;
+                        };
+                        U[d][c] = round_all(mm16(tile(tD[d][lane]), round_all(U[d][c]), acc[c]));
+                    }
+                    o[c] = mm16(mm, U[d][c], o[c]);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 16 * d + 4 * lq + v;
+                    if (i < L) {
+                        const size_t oo = outp + (uint32_t)i * v_stride + col0, uo = ru(i) * D + col0;
+                        if constexpr (NC == 2) {
+                            out.put2(oo, a.scale * o[0][v], a.scale * o[1][v]);
+                            store2(up + uo, U[d][0][v], U[d][1][v]);
+                        } else {
+                            out.put1(oo, a.scale * o[0][v]);
+                            store1(up + uo, U[d][0][v]);
+                        }
+                    }
+                }
+            }
+        }
+    }
+    if (h == 0 && tid == 0)
+        a.st.fill[s] = L;
+}
+
+// ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
 int launch_direct(int dk, int in_dtype, int rec_dtype, const DirectArgs &a, int blocks, hipStream_t stream)
@@ -1099,11 +1279,15 @@ int launch_direct(int dk, int in_dtype, int rec_dtype, const DirectArgs &a, int 
             else
                 launch(kvb_direct_mfma_kernel<TIn, TRec, false, false>, blocks, stream, a.len, a.Hv, deal_of(a, blocks), a);
         });
-    if (a.Lmax > 64)   // the plain kernel holds a 64-token context in LDS
+    if (a.Lmax > 64)   // the block-row kernel holds a 64-token context in LDS
         return KVB_EUNSUPPORTED;
     return dispatch(dk, in_dtype, rec_dtype, [&]<int D, typename TIn, typename TRec>() {
-        if constexpr (!(D == 128 && sizeof(TIn) == 2))
-            LAUNCH_PAGED(blocks, stream, a, kvb_direct_kernel<D, TIn, TRec);
+        if constexpr (!(D == 128 && sizeof(TIn) == 2)) {
+            if (a.st.block_table)
+                launch(kvb_direct_rows_kernel<D, TIn, TRec, true>, blocks, stream, a.len, a.Hv, deal_of(a, blocks), a);
+            else
+                launch(kvb_direct_rows_kernel<D, TIn, TRec, false>, blocks, stream, a.len, a.Hv, deal_of(a, blocks), a);
+        }
     });
 }
 

@@ -31,3 +31,16 @@ def test_direct_every_unit_is_taken_once(B, Hk, Hv, Lmax):
     e = _direct_case(B=B, Hk=Hk, Hv=Hv, d=128, Lmax=Lmax, cap=Lmax, in_dtype="bf16", seed=810 + B + Lmax)
     say("direct, B=%d heads %d/%d Lmax=%d: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((B, Hk, Hv, Lmax) + e))
     H.check(e, "bf16", what="dealt units")
+
+
+@pytest.mark.parametrize("d, in_dtype, rec_dtype", [(d, i, r) for d in (32, 64) for i, r in TYPES + [("f32", "f32")]]
+                         + [(128, "f32", "f32")])
+def test_direct_block_rows(d, in_dtype, rec_dtype):
+    """The block-row kernel around every block of 16 rows, contiguous and paged (its bound is the 1e-5 of fp32
+    workloads wherever records and outputs are fp32: accurate exponentials and exact products)."""
+    lens = np.array([0, 1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64], np.int32)
+    for block_size in (None, 8):
+        e = _direct_case(B=len(lens), Hk=2, Hv=4, d=d, Lmax=64, cap=64, in_dtype=in_dtype, seed=820 + d, lens=lens,
+                         then_decode=False, rec_dtype=rec_dtype, out_dtype=rec_dtype, block_size=block_size)
+        say("direct, block rows, d=%d %s/%s: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((d, in_dtype, rec_dtype) + e))
+        H.check(e, "f32" if rec_dtype == "f32" else in_dtype, rec_dtype, "block rows")
