@@ -38,8 +38,9 @@ __device__ __forceinline__ float group_sum(float x)
 // the state tile it already holds in registers and writes it back, which saves the second
 // kernel's re-read of the state.
 template <int D, typename TIn, typename TRec, int TM, int WREC, bool HAS_STATE, bool FUSE, bool STREAM, bool PAGED>
-// (register budget: the 64-record decode variants sit at the edge of three workgroups per CU; hold them there)
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TM == 1 && WREC == 64 && HAS_STATE ? 3 : 1)))
+// (register budget: the 64-record decode variants sit at the edge of three workgroups per CU; hold them there,
+// and those with the matrix-core update, which would spread the state over accumulation registers)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TM == 1 && HAS_STATE && (WREC == 64 || (FUSE && D == 128 && sizeof(TIn) == 2)) ? 3 : 1)))
 void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg,
                                                       const StepArgs a)
 {
@@ -59,6 +60,11 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     constexpr bool TAIL = WREC >= 64;
     constexpr int LT = 16;                 // records per LDS tile of the fused state update
     constexpr int EPT = LT * D / NT;
+    // the fused state update runs on the matrix cores (see fold_tile)
+    constexpr bool MFOLD = FUSE && D == 128 && sizeof(TIn) == 2;
+    constexpr int KPC = __is_same(TIn, f16_t) ? 2 : 1;   // bf16 pieces of a key
+    constexpr int UPC = 3;                               // bf16 pieces of a weighted delta value
+    constexpr int FS = 24;                               // halves per staged row: 16 records + padding (16-byte reads)
     // state loads issued before the fill is known (the 64-record window keeps the records first:
     // holding it across the state pass costs a workgroup per CU)
     constexpr bool EARLY = TM == 1 && HAS_STATE && WREC <= 32;
@@ -71,9 +77,12 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     __shared__ float cK[TM][NC];     // Gamma_il (k_i.k_l), 0 for l >= f+i
     __shared__ float cQ[TM][NC];     // Gamma_il (q_i.k_l), 0 for l >  f+i
     __shared__ __attribute__((aligned(16))) float red[NW][TM][2][D];
-    __shared__ __attribute__((aligned(16))) float kh[FUSE ? LT : 1][D];  // Gamma_fl k_l tile
+    __shared__ __attribute__((aligned(16))) float kh[FUSE && !MFOLD ? LT : 1][D];  // Gamma_fl k_l tile
     __shared__ int sBlk[NW][MAX_BLOCKS];
-    __shared__ __attribute__((aligned(16))) float uu[FUSE ? LT : 1][D];  // u_l tile
+    __shared__ __attribute__((aligned(16))) float uu[FUSE && !MFOLD ? LT : 1][D];  // u_l tile
+    __shared__ float wF[MFOLD ? NC : 1];                                           // Gamma_fl
+    __shared__ __attribute__((aligned(16))) uint16_t kT[MFOLD ? KPC : 1][MFOLD ? D : 1][FS];  // pieces of k_l, by state row
+    __shared__ __attribute__((aligned(16))) uint16_t uT[MFOLD ? UPC : 1][MFOLD ? D : 1][FS];  // of Gamma_fl u_l, by column
 
     const int tid = threadIdx.x;
     const int lb = logical_block(nblocks_arg);
@@ -285,6 +294,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                 const float w = expf(Gc[0] - Gl[p]);
                 cK[0][l] = w * dkk;
                 cQ[0][l] = w * dq;
+                if constexpr (MFOLD)
+                    wF[l] = w;
             }
         }
         if constexpr (TAIL) {
@@ -319,6 +330,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                             const float w = expf(Gc[0] - Gt[x]);
                             cK[0][l] = w * dkk;
                             cQ[0][l] = w * dq;
+                            if constexpr (MFOLD)
+                                wF[l] = w;
                         }
                     }
                 }
@@ -554,124 +567,228 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
         const int m = f + 1;
         if (m >= a.threshold) {   // uniform over the workgroup (and over the request)
             const float gam = expf(Gc[0]);
+            if constexpr (MFOLD) {
+                // The rank-m update on the matrix cores, 16 records a step.  A thread holds rows
+                // rg + 8 p (p = 0..15, rg = 2 wave + lane / 32) of columns 4 c4 + e: for each e that is
+                // the accumulator of a 32 x 32 tile, its column index c4 = lane % 32 and its row index
+                // 8 (p / 4) + 4 (lane / 32) + p % 4, so the state is updated where it already lies and
+                // nothing crosses waves but the two staged factors.  The factors are exact: Gamma u is cut
+                // into three bf16 pieces (24 bits), a key is one bf16 value or, from fp16, two (11 bits;
+                // bf16 also has the exponent range that a large delta value needs), products are summed in
+                // fp32.  The vector ALU took 4096 cycles a wave for 16 records, the chain that ended every launch
+                // in which some request folds.  13 requests of 8 heads, C = 32, fp16, 16 steps: 120 -> 99 us;
+                // 64 of 32 heads, C = 16, bf16: 483 -> 475 us; 1 of 32: 76.1 -> 74.9 us.  (500 of 32 at C = 64:
+                // the same 1072 us, its launches wait for memory.)
+                // The records of a tile go to contraction slots 2 (r % 8) + r / 8, so that the two a thread
+                // stages share a word.
+                f32x16_t acc[4];
 #pragma unroll
-            for (int p = 0; p < NPASS; ++p) {
-                sreg[p].x *= gam; sreg[p].y *= gam; sreg[p].z *= gam; sreg[p].w *= gam;
-            }
-            // one LDS tile of LT records: record f itself comes from this workgroup's registers
-            auto inject_new = [&](int l0) {
-                if (f >= l0 && f < l0 + LT) {
-                    if (grp == 0) {
+                for (int p = 0; p < NPASS; ++p) {
+                    acc[0][p] = gam * sreg[p].x;
+                    acc[1][p] = gam * sreg[p].y;
+                    acc[2][p] = gam * sreg[p].z;
+                    acc[3][p] = gam * sreg[p].w;
+                }
+                if (tid < D)
+                    sKs[0][tid] = u_new;   // (the state rows were weighted long ago)
+                const int lane = tid % 64, wv = tid / 64;
+                // kx: elements 8 sub .. + 7 of key l0 + grp; u0, u1: columns 4 c4 .. + 3 of records l0 + rg, + 8
+                auto fold_tile = [&](int l0, const Raw8<TIn> &kx, const float4 &u0, const float4 &u1) {
+                    __syncthreads();
+                    {
+                        const int l = l0 + grp, at = 2 * (grp % 8) + grp / 8;
+                        float kf[8];
+                        unpack8(kx, kf);
 #pragma unroll
-                        for (int e = 0; e < 8; ++e)
-                            kh[f - l0][8 * sub + e] = k8[e];
+                        for (int e = 0; e < 8; ++e) {
+                            const float x = l < f ? kf[e] : l == f ? k8[e] : 0.0f;
+                            const int row = 32 * (e / 2) + 8 * (sub / 4) + 4 * (e % 2) + sub % 4;
+                            const uint32_t top = __float_as_uint(x) & 0xFFFF0000u;
+                            kT[0][row][at] = (uint16_t)(top >> 16);
+                            if constexpr (KPC == 2)
+                                kT[KPC - 1][row][at] = (uint16_t)(__float_as_uint(x - __uint_as_float(top)) >> 16);
+                        }
+                        const float *un = &sKs[0][4 * c4];
+                        const int la = l0 + rg, lb8 = la + 8;
+                        const float wa = la < f ? wF[la] : 0.0f, wb = lb8 < f ? wF[lb8] : 0.0f;
+                        const float xa[4] = {u0.x, u0.y, u0.z, u0.w}, xb[4] = {u1.x, u1.y, u1.z, u1.w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float nw = un[e];
+                            float ra = la < f ? wa * xa[e] : la == f ? nw : 0.0f;
+                            float rb = lb8 < f ? wb * xb[e] : lb8 == f ? nw : 0.0f;
+#pragma unroll
+                            for (int q = 0; q < UPC; ++q) {   // the leading 8 bits of what is left; the rest is exact
+                                const uint32_t ta = __float_as_uint(ra) & 0xFFFF0000u, tb = __float_as_uint(rb) & 0xFFFF0000u;
+                                *reinterpret_cast<uint32_t *>(&uT[q][32 * e + c4][2 * rg]) = (ta >> 16) | tb;
+                                ra -= __uint_as_float(ta);
+                                rb -= __uint_as_float(tb);
+                            }
+                        }
                     }
-                    if (tid < D)
-                        uu[f - l0][tid] = u_new;
-                }
-            };
-            auto apply_tile = [&](int l0) {
-                const int nl = min(LT, m - l0);
-                for (int l = 0; l < nl; ++l) {
-                    const float4 u = *reinterpret_cast<const float4 *>(&uu[l][4 * c4]);
+                    __syncthreads();
+                    bf16x8_t ka[KPC];
 #pragma unroll
-                    for (int p = 0; p < NPASS; ++p)
-                        fma4(sreg[p], kh[l][rg + RPP * p], u);
-                }
-            };
-            int l_done = 0;
-            if constexpr (NG == LT && 2 * RPP == LT && WREC <= 32) {
-                // d = 128: a window pass of keys is exactly one tile, two passes of delta values
-                // fill it, so the tiles inside the register window need no second trip to memory
-                // (not for the 64-record window: keeping it alive this long costs a workgroup per CU)
+                    for (int x = 0; x < KPC; ++x)
+                        ka[x] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(&kT[x][32 * wv + lane % 32][8 * (lane / 32)]));
 #pragma unroll
-                for (int p = 0; p < KP; ++p) {
-                    if (LT * p < m) {   // uniform
+                    for (int q = UPC - 1; q >= 0; --q)   // smallest pieces first
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const bf16x8_t ub8 = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(&uT[q][32 * e + lane % 32][8 * (lane / 32)]));
+#pragma unroll
+                            for (int x = KPC - 1; x >= 0; --x)
+                                acc[e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[x], ub8, acc[e], 0, 0, 0);
+                        }
+                };
+                if constexpr (WREC <= 32) {   // the whole buffer is in registers: a key pass is one tile, two passes of u fill it
+#pragma unroll
+                    for (int p = 0; p < KP; ++p)
+                        if (LT * p < m)   // uniform
+                            fold_tile(LT * p, kl_raw[p], ur[2 * p], ur[2 * p + 1]);
+                } else {
+                    // (holding the 64-record window this long costs a workgroup per CU: its records come back
+                    // from memory, the next tile requested before this one is applied.  Requests are clamped;
+                    // rows >= f are not used)
+                    const int lmax = f > 0 ? f - 1 : 0;
+                    Raw8<TIn> kq;
+                    Raw4<TRec> ua, ub4;
+                    auto request = [&](int l0) {
+                        kq = load_raw8(kb + rk(min(l0 + grp, lmax)) * D + 8 * sub);
+                        ua = load_raw4(ub + ru(min(l0 + rg, lmax)) * D + 4 * c4);
+                        ub4 = load_raw4(ub + ru(min(l0 + rg + 8, lmax)) * D + 4 * c4);
+                    };
+                    request(0);
+                    for (int l0 = 0; l0 < m; l0 += LT) {
+                        const Raw8<TIn> kc = kq;
+                        const float4 u0 = unpack4(ua), u1 = unpack4(ub4);
+                        request(l0 + LT);   // (past the last tile: a valid record, dropped)
+                        fold_tile(l0, kc, u0, u1);
+                    }
+                }
+#pragma unroll
+                for (int p = 0; p < NPASS; ++p)
+                    sreg[p] = make_float4(acc[0][p], acc[1][p], acc[2][p], acc[3][p]);
+            } else {
+#pragma unroll
+                for (int p = 0; p < NPASS; ++p) {
+                    sreg[p].x *= gam; sreg[p].y *= gam; sreg[p].z *= gam; sreg[p].w *= gam;
+                }
+                // one LDS tile of LT records: record f itself comes from this workgroup's registers
+                auto inject_new = [&](int l0) {
+                    if (f >= l0 && f < l0 + LT) {
+                        if (grp == 0) {
+#pragma unroll
+                            for (int e = 0; e < 8; ++e)
+                                kh[f - l0][8 * sub + e] = k8[e];
+                        }
+                        if (tid < D)
+                            uu[f - l0][tid] = u_new;
+                    }
+                };
+                auto apply_tile = [&](int l0) {
+                    const int nl = min(LT, m - l0);
+                    for (int l = 0; l < nl; ++l) {
+                        const float4 u = *reinterpret_cast<const float4 *>(&uu[l][4 * c4]);
+#pragma unroll
+                        for (int p = 0; p < NPASS; ++p)
+                            fma4(sreg[p], kh[l][rg + RPP * p], u);
+                    }
+                };
+                int l_done = 0;
+                if constexpr (NG == LT && 2 * RPP == LT && WREC <= 32) {
+                    // d = 128: a window pass of keys is exactly one tile, two passes of delta values
+                    // fill it, so the tiles inside the register window need no second trip to memory
+                    // (not for the 64-record window: keeping it alive this long costs a workgroup per CU)
+#pragma unroll
+                    for (int p = 0; p < KP; ++p) {
+                        if (LT * p < m) {   // uniform
+                            __syncthreads();
+                            const int l = LT * p + grp;
+                            float kx[8];
+                            unpack8(kl_raw[p], kx);
+                            const float w = l < f ? expf(Gc[0] - Gl[p]) : 0.0f;
+                            if (l != f) {   // row f of the tile belongs to inject_new
+#pragma unroll
+                                for (int e = 0; e < 8; ++e)
+                                    kh[grp][8 * sub + e] = l < f ? w * kx[e] : 0.0f;
+                            }
+#pragma unroll
+                            for (int jj = 0; jj < 2; ++jj) {
+                                const int lu = LT * p + RPP * jj + rg;
+                                const float4 u = ur[2 * p + jj];
+                                if (lu != f)
+                                    *reinterpret_cast<float4 *>(&uu[RPP * jj + rg][4 * c4]) =
+                                        lu < f ? u : make_float4(0.f, 0.f, 0.f, 0.f);
+                            }
+                            inject_new(LT * p);
+                            __syncthreads();
+                            apply_tile(LT * p);
+                        }
+                    }
+                    l_done = LT * KP;
+                }
+                if constexpr (NG == LT) {
+                  if (l_done < m) {   // uniform
+                    // records before f come back from memory (written by earlier calls): thread (grp, sub)
+                    // brings 8 elements of record l0 + grp, and the next tile is requested before this
+                    // one is applied, so its round trip hides under the multiply-adds
+                    const int lmax = f > 0 ? f - 1 : 0;   // requests are clamped; rows >= f are not used
+                    int lr = min(l_done + grp, lmax);
+                    size_t rowr = ru(lr);
+                    Raw8<TIn> kq = load_raw8(kb + rk(lr) * D + 8 * sub);
+                    Raw8<TRec> uq = load_raw8(ub + rowr * D + 8 * sub);
+                    float Gq = Gbuf[rowr];
+                    for (int l0 = l_done; l0 < m; l0 += LT) {
                         __syncthreads();
-                        const int l = LT * p + grp;
-                        float kx[8];
-                        unpack8(kl_raw[p], kx);
-                        const float w = l < f ? expf(Gc[0] - Gl[p]) : 0.0f;
+                        const int l = l0 + grp;
                         if (l != f) {   // row f of the tile belongs to inject_new
+                            float kx[8];
+                            unpack8(kq, kx);
+                            const float w = l < f ? expf(Gc[0] - Gq) : 0.0f;
 #pragma unroll
                             for (int e = 0; e < 8; ++e)
                                 kh[grp][8 * sub + e] = l < f ? w * kx[e] : 0.0f;
+                            // (component by component: a select between two float4 objects is compiled
+                            // as a select between their addresses, which puts them in scratch memory)
+                            const bool in = l < f;
+                            float ux[8];
+                            unpack8(uq, ux);
+                            *reinterpret_cast<float4 *>(&uu[grp][8 * sub]) = make_float4(
+                                in ? ux[0] : 0.0f, in ? ux[1] : 0.0f, in ? ux[2] : 0.0f, in ? ux[3] : 0.0f);
+                            *reinterpret_cast<float4 *>(&uu[grp][8 * sub + 4]) = make_float4(
+                                in ? ux[4] : 0.0f, in ? ux[5] : 0.0f, in ? ux[6] : 0.0f, in ? ux[7] : 0.0f);
                         }
-#pragma unroll
-                        for (int jj = 0; jj < 2; ++jj) {
-                            const int lu = LT * p + RPP * jj + rg;
-                            const float4 u = ur[2 * p + jj];
-                            if (lu != f)
-                                *reinterpret_cast<float4 *>(&uu[RPP * jj + rg][4 * c4]) =
-                                    lu < f ? u : make_float4(0.f, 0.f, 0.f, 0.f);
-                        }
-                        inject_new(LT * p);
+                        inject_new(l0);
+                        // (the request past the last tile re-reads a valid record and is dropped)
+                        lr = min(l0 + LT + grp, lmax);
+                        rowr = ru(lr);
+                        kq = load_raw8(kb + rk(lr) * D + 8 * sub);
+                        uq = load_raw8(ub + rowr * D + 8 * sub);
+                        Gq = Gbuf[rowr];
                         __syncthreads();
-                        apply_tile(LT * p);
+                        apply_tile(l0);
                     }
-                }
-                l_done = LT * KP;
-            }
-            if constexpr (NG == LT) {
-              if (l_done < m) {   // uniform
-                // records before f come back from memory (written by earlier calls): thread (grp, sub)
-                // brings 8 elements of record l0 + grp, and the next tile is requested before this
-                // one is applied, so its round trip hides under the multiply-adds
-                const int lmax = f > 0 ? f - 1 : 0;   // requests are clamped; rows >= f are not used
-                int lr = min(l_done + grp, lmax);
-                size_t rowr = ru(lr);
-                Raw8<TIn> kq = load_raw8(kb + rk(lr) * D + 8 * sub);
-                Raw8<TRec> uq = load_raw8(ub + rowr * D + 8 * sub);
-                float Gq = Gbuf[rowr];
-                for (int l0 = l_done; l0 < m; l0 += LT) {
-                    __syncthreads();
-                    const int l = l0 + grp;
-                    if (l != f) {   // row f of the tile belongs to inject_new
-                        float kx[8];
-                        unpack8(kq, kx);
-                        const float w = l < f ? expf(Gc[0] - Gq) : 0.0f;
+                  }
+                } else {
+                    for (int l0 = l_done; l0 < m; l0 += LT) {
+                        __syncthreads();
+                        // records before f come back from memory (written by earlier calls)
 #pragma unroll
-                        for (int e = 0; e < 8; ++e)
-                            kh[grp][8 * sub + e] = l < f ? w * kx[e] : 0.0f;
-                        // (component by component: a select between two float4 objects is compiled
-                        // as a select between their addresses, which puts them in scratch memory)
-                        const bool in = l < f;
-                        float ux[8];
-                        unpack8(uq, ux);
-                        *reinterpret_cast<float4 *>(&uu[grp][8 * sub]) = make_float4(
-                            in ? ux[0] : 0.0f, in ? ux[1] : 0.0f, in ? ux[2] : 0.0f, in ? ux[3] : 0.0f);
-                        *reinterpret_cast<float4 *>(&uu[grp][8 * sub + 4]) = make_float4(
-                            in ? ux[4] : 0.0f, in ? ux[5] : 0.0f, in ? ux[6] : 0.0f, in ? ux[7] : 0.0f);
-                    }
-                    inject_new(l0);
-                    // (the request past the last tile re-reads a valid record and is dropped)
-                    lr = min(l0 + LT + grp, lmax);
-                    rowr = ru(lr);
-                    kq = load_raw8(kb + rk(lr) * D + 8 * sub);
-                    uq = load_raw8(ub + rowr * D + 8 * sub);
-                    Gq = Gbuf[rowr];
-                    __syncthreads();
-                    apply_tile(l0);
-                }
-              }
-            } else {
-                for (int l0 = l_done; l0 < m; l0 += LT) {
-                    __syncthreads();
-                    // records before f come back from memory (written by earlier calls)
-#pragma unroll
-                    for (int x = 0; x < EPT; ++x) {
-                        const int idx = tid + NT * x, l = l0 + idx / D, e = idx % D;
-                        if (l < f) {
-                            kh[idx / D][e] = expf(Gc[0] - Gbuf[ru(l)]) * to_f32(kb[rk(l) * D + e]);
-                            uu[idx / D][e] = to_f32(ub[ru(l) * D + e]);
-                        } else if (l > f) {
-                            kh[idx / D][e] = 0.0f;
-                            uu[idx / D][e] = 0.0f;
+                        for (int x = 0; x < EPT; ++x) {
+                            const int idx = tid + NT * x, l = l0 + idx / D, e = idx % D;
+                            if (l < f) {
+                                kh[idx / D][e] = expf(Gc[0] - Gbuf[ru(l)]) * to_f32(kb[rk(l) * D + e]);
+                                uu[idx / D][e] = to_f32(ub[ru(l) * D + e]);
+                            } else if (l > f) {
+                                kh[idx / D][e] = 0.0f;
+                                uu[idx / D][e] = 0.0f;
+                            }
                         }
+                        inject_new(l0);
+                        __syncthreads();
+                        apply_tile(l0);
                     }
-                    inject_new(l0);
-                    __syncthreads();
-                    apply_tile(l0);
                 }
             }
             float4 *sw = reinterpret_cast<float4 *>(a.st.state + unit * D * D);

@@ -6,6 +6,8 @@ import numpy as np
 import pytest
 
 import harness as H
+from harness import oracle
+from paper_2605_19049_amd import synth
 from test_gpu_parity import _direct_case, say
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +46,25 @@ def test_direct_block_rows(d, in_dtype, rec_dtype):
                          then_decode=False, rec_dtype=rec_dtype, out_dtype=rec_dtype, block_size=block_size)
         say("direct, block rows, d=%d %s/%s: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((d, in_dtype, rec_dtype) + e))
         H.check(e, "f32" if rec_dtype == "f32" else in_dtype, rec_dtype, "block rows")
+
+
+@pytest.mark.parametrize("in_dtype, rec_dtype", TYPES)
+@pytest.mark.parametrize("C", [1, 2, 15, 16, 17, 31, 32, 33, 48, 64, 65, 128])
+def test_fused_update_tiles(in_dtype, rec_dtype, C):
+    """The state update inside kvb_decode_flush around every 16-record tile and register window.  With fp32
+    records the state is 1e5 times its usual size, so the delta values leave the range of fp16: the errors are
+    relative, so the bounds stay what they are."""
+    rng = np.random.default_rng(830 + C)
+    S0 = H.prefix_state(rng, 2, 2, 4, 128, 128, in_dtype, 16)
+    if rec_dtype == "f32":
+        S0 = S0 * np.float32(1e5)
+    tok = synth.token_stream(rng, 2, C + 3, 2, 4, 128, 128, in_dtype)
+    lay = H.Layer(2, 2, 4, 128, 128, cap=C, in_dtype=in_dtype, scale=128 ** -0.5, rec_dtype=rec_dtype)
+    o, u, S, _ = H.run_decode(lay, S0, tok, C, final_flush=False, fused=True)
+    o_ref, u_ref, _ = oracle.kvb_decode_expected(S0, tok["q"], tok["k"], tok["v"], tok["g"], tok["beta"], scale=128 ** -0.5)
+    # (the state holds what was folded: the first floor((C + 3) / C) * C tokens)
+    n = (C + 3) // C * C
+    _, _, S_ref = oracle.kvb_decode_expected(S0, *(tok[x][:, :n] for x in ("q", "k", "v", "g", "beta")), scale=128 ** -0.5)
+    e = (H.rel_err(o, o_ref), H.rel_err(u, u_ref), H.rel_err(S, S_ref))
+    say("fused update, %s/%s C=%d: rel err out/u/state %.2e %.2e %.2e" % ((in_dtype, rec_dtype, C) + e))
+    H.check(e, in_dtype, rec_dtype, "fused update")
