@@ -5,7 +5,7 @@
 //                        (input type, record type) by kvb_step_f32.hip, kvb_step_bf16.hip,
 //                        kvb_step_bf16_r16.hip, kvb_step_f16.hip, kvb_step_f16_r16.hip
 //   kvb_verify_kernel.h  kvb_verify_mfma_kernel; instantiated by kvb_verify_bf16.hip, kvb_verify_f16.hip
-//   kvb_flush.hip        kvb_flush_mfma_kernel, kvb_flush_kernel, kvb_compact_kernel
+//   kvb_flush.hip        kvb_flush_mfma_kernel, kvb_flush_rows_kernel, kvb_compact_kernel
 //   kvb_direct.hip       kvb_direct_mfma_kernel, kvb_direct_rows_kernel
 //   kvb_api.hip          argument checks, the extern "C" entry points, the kernel timer
 //
@@ -24,7 +24,7 @@
 //   kvb_verify_mfma_kernel  verify, 16-bit inputs / d = 128: matrix cores; a wave owns 32 dv columns
 //   kvb_flush_mfma_kernel   deferred state update, 16-bit inputs / d = 128: matrix cores on exact
 //                           16-bit pieces of the fp32 factor
-//   kvb_flush_kernel        the same for the other types and head sizes: vector ALUs
+//   kvb_flush_rows_kernel   the same for the other types and head sizes: fp32 matrix instruction
 //   kvb_direct_mfma_kernel  short contexts, 16-bit inputs / d = 128: matrix cores throughout
 //   kvb_direct_rows_kernel  short contexts, other types and head sizes: fp32 matrix instruction, block row by block row
 //

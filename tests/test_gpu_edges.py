@@ -68,3 +68,18 @@ def test_fused_update_tiles(in_dtype, rec_dtype, C):
     e = (H.rel_err(o, o_ref), H.rel_err(u, u_ref), H.rel_err(S, S_ref))
     say("fused update, %s/%s C=%d: rel err out/u/state %.2e %.2e %.2e" % ((in_dtype, rec_dtype, C) + e))
     H.check(e, in_dtype, rec_dtype, "fused update")
+
+
+@pytest.mark.parametrize("d, in_dtype, rec_dtype", [(128, "f32", "f32"), (64, "f32", "f32"), (64, "bf16", "f32"), (32, "f16", "f16")])
+@pytest.mark.parametrize("C, block_size", [(9, None), (95, None), (128, 8)])
+def test_flush_rows_chunks(d, in_dtype, rec_dtype, C, block_size):
+    """kvb_flush off the 16-bit matrix instruction: remainders of a chunk of records, and several chunks."""
+    rng = np.random.default_rng(840 + C)
+    S0 = H.prefix_state(rng, 2, 2, 4, d, d, in_dtype, 16)
+    tok = synth.token_stream(rng, 2, C + 3, 2, 4, d, d, in_dtype)
+    lay = H.Layer(2, 2, 4, d, d, cap=C, in_dtype=in_dtype, scale=d ** -0.5, rec_dtype=rec_dtype, block_size=block_size)
+    o, u, S, _ = H.run_decode(lay, S0, tok, C, fused=False)
+    o_ref, u_ref, S_ref = oracle.kvb_decode_expected(S0, tok["q"], tok["k"], tok["v"], tok["g"], tok["beta"], scale=d ** -0.5)
+    e = (H.rel_err(o, o_ref), H.rel_err(u, u_ref), H.rel_err(S, S_ref))
+    say("flush rows, d=%d %s/%s C=%d: rel err out/u/state %.2e %.2e %.2e" % ((d, in_dtype, rec_dtype, C) + e))
+    H.check(e, in_dtype, rec_dtype, "flush rows")
