@@ -129,12 +129,13 @@ int step_common(const kvb_shape *sh, const kvb_store *st, const int32_t *slot, i
     const int blocks = sh->B * sh->Hv;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     g_launch_status = hipSuccess;
-    if (sh->dk == 128 && sh->in_dtype != KVB_F32 && T > 1)   // several drafts: the matrix-core kernel
-        rc = dispatch_types16(sh->in_dtype, sh->rec_dtype,
-                              [&]<typename TIn, typename TRec>() { launch_verify_typed<TIn, TRec>(a, blocks, hs); });
+    if (T > 1)   // several drafts: the matrix-core kernel (the head size was checked above)
+        rc = dispatch_types(sh->in_dtype, sh->rec_dtype, [&]<typename TIn, typename TRec>() {
+            launch_verify_typed<TIn, TRec>(sh->dk, a, blocks, hs);
+        });
     else
         rc = dispatch_types(sh->in_dtype, sh->rec_dtype, [&]<typename TIn, typename TRec>() {
-            launch_step_typed<TIn, TRec>(sh->dk, a, blocks, hs);   // (the head size was checked above)
+            launch_step_typed<TIn, TRec>(sh->dk, a, blocks, hs);
         });
     if (rc != KVB_OK)
         return rc;

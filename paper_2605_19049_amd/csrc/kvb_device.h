@@ -1,10 +1,10 @@
 // kvb -- KVBuffer-style Gated DeltaNet decoding, HIP kernels for gfx950 behind the C ABI of
 // include/kvb.h.  This header holds what the translation units share: device helpers, the
 // argument structs of the kernels, and the launch plumbing.
-//   kvb_step_kernel.h    kvb_step_kernel (decode and the vector-ALU verify); instantiated per
+//   kvb_step_kernel.h    kvb_step_kernel (decode); instantiated per
 //                        (input type, record type) by kvb_step_f32.hip, kvb_step_bf16.hip,
 //                        kvb_step_bf16_r16.hip, kvb_step_f16.hip, kvb_step_f16_r16.hip
-//   kvb_verify_kernel.h  kvb_verify_mfma_kernel; instantiated by kvb_verify_bf16.hip, kvb_verify_f16.hip
+//   kvb_verify_kernel.h  kvb_verify_mfma_kernel; instantiated by kvb_verify_bf16.hip, _f16.hip, _f32.hip
 //   kvb_flush.hip        kvb_flush_mfma_kernel, kvb_flush_rows_kernel, kvb_compact_kernel
 //   kvb_direct.hip       kvb_direct_mfma_kernel, kvb_direct_rows_kernel
 //   kvb_api.hip          argument checks, the extern "C" entry points, the kernel timer
@@ -19,9 +19,9 @@
 // d = 128) is streamed exactly once per call.  Besides the state a unit needs
 // its buffered keys k_l, delta values u_l and cumulative log decays G_l (paper
 // App. A.1, the paragraph after Eq. 16), a few KB.
-//   kvb_step_kernel         decode (T = 1) and generic verify: vector ALUs; a thread owns
+//   kvb_step_kernel         decode, one token: vector ALUs; a thread owns
 //                           4 adjacent dv columns of 16 state rows (16-byte loads)
-//   kvb_verify_mfma_kernel  verify, 16-bit inputs / d = 128: matrix cores; a wave owns 32 dv columns
+//   kvb_verify_mfma_kernel  verify: matrix cores; a wave owns 32 dv columns (16 at d <= 64)
 //   kvb_flush_mfma_kernel   deferred state update, 16-bit inputs / d = 128: matrix cores on exact
 //                           16-bit pieces of the fp32 factor
 //   kvb_flush_rows_kernel   the same for the other types and head sizes: fp32 matrix instruction
@@ -586,7 +586,7 @@ int dispatch(int dk, int in_dtype, int rec_dtype, F &&f)
 template <typename TIn, typename TRec>
 int launch_step_typed(int dk, const StepArgs &a, int blocks, hipStream_t stream);   // kvb_step_*.hip, one unit per pair
 template <typename TIn, typename TRec>
-void launch_verify_typed(const StepArgs &a, int blocks, hipStream_t stream);        // kvb_verify_*.hip (16-bit inputs, d = 128)
+void launch_verify_typed(int dk, const StepArgs &a, int blocks, hipStream_t stream);   // kvb_verify_*.hip, one unit per input type
 int launch_flush(int dk, int in_dtype, int rec_dtype, const FlushArgs &a, int blocks, hipStream_t stream);    // kvb_flush.hip
 int launch_compact(int dk, int in_dtype, int rec_dtype, const CompactArgs &a, int blocks, hipStream_t stream);
 int launch_direct(int dk, int in_dtype, int rec_dtype, const DirectArgs &a, int blocks, hipStream_t stream);  // kvb_direct.hip

@@ -1,6 +1,6 @@
-// kvb_step_kernel: kvb_decode, kvb_decode_flush and the vector-ALU kvb_verify / kvb_verify_tree, with its
-// launch helpers.  Template code only; kvb_step_bf16.hip and kvb_step_f32.hip instantiate it for their
-// input type (two translation units, so that they compile side by side).
+// kvb_step_kernel: kvb_decode and kvb_decode_flush (and kvb_verify of a single draft), with its launch
+// helpers.  Template code only; kvb_step_*.hip instantiate it per (input type, record type), so that they
+// compile side by side.
 #ifndef KVB_STEP_KERNEL_H
 #define KVB_STEP_KERNEL_H
 
@@ -9,17 +9,15 @@
 namespace kvb_impl {
 
 // ---------------------------------------------------------------------------
-// kvb_decode (TM == 1) and kvb_verify (TM >= T): rows f..f+T-1 of the chunkwise
-// form, Eq. 15/16.  Per (b,h):
-//   accU_i = -gamma_i k_i S0 - sum_{l<f} Gamma_il (k_i.k_l) u_l
-//   accO_i =  gamma_i q_i S0 + sum_{l<f} Gamma_il (q_i.k_l) u_l
+// kvb_decode: row f of the chunkwise form, Eq. 16.  Per (b,h):
+//   accU = -gamma k S0 - sum_{l<f} Gamma_l (k.k_l) u_l
+//   accO =  gamma q S0 + sum_{l<f} Gamma_l (q.k_l) u_l
 // are accumulated over state rows and buffered records alike (both are "rows"
-// weighted by a per-row scalar), reduced across the workgroup, and the T new
-// rows are then finished by forward substitution among themselves.
+// weighted by a per-row scalar) and reduced across the workgroup.
 //
 // Load order is the point of this kernel.  The memory counter retires loads
-// in issue order, so the few small loads whose values are needed first (new
-// q/k rows, the buffered records of a WREC-record window, v) are issued
+// in issue order, so the few small loads whose values are needed first (the new
+// q/k rows, v; with the 64-record window also the buffered records) are issued
 // before the 64 KB state tile; the dot products and the LDS exchange then run
 // while the state is still in flight.
 // ---------------------------------------------------------------------------
@@ -37,10 +35,10 @@ __device__ __forceinline__ float group_sum(float x)
 // workgroup applies the deferred update S <- gamma_f S0 + sum_{l<=f} Gamma_fl k_l^T u_l to
 // the state tile it already holds in registers and writes it back, which saves the second
 // kernel's re-read of the state.
-template <int D, typename TIn, typename TRec, int TM, int WREC, bool HAS_STATE, bool FUSE, bool STREAM, bool PAGED>
+template <int D, typename TIn, typename TRec, int WREC, bool HAS_STATE, bool FUSE, bool STREAM, bool PAGED>
 // (register budget: the 64-record decode variants sit at the edge of three workgroups per CU; hold them there,
 // and those with the matrix-core update, which would spread the state over accumulation registers)
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TM == 1 && HAS_STATE && (WREC == 64 || (FUSE && D == 128 && sizeof(TIn) == 2)) ? 3 : 1)))
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(HAS_STATE && (WREC == 64 || (FUSE && D == 128 && sizeof(TIn) == 2)) ? 3 : 1)))
 void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg,
                                                       const StepArgs a)
 {
@@ -55,7 +53,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     constexpr int NG = NT / GL;      // records handled per pass of the dot-product phase
     constexpr int KP = (WREC + NG - 1) / NG;    // key passes held in registers
     constexpr int UP = (WREC + RPP - 1) / RPP;  // delta-value passes held in registers
-    constexpr int NC = KVB_MAX_CAP + TM;
+    constexpr int NC = KVB_MAX_CAP + 1;
     // the two smaller window tiers are only launched when the whole buffer fits the window
     constexpr bool TAIL = WREC >= 64;
     constexpr int LT = 16;                 // records per LDS tile of the fused state update
@@ -67,16 +65,14 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     constexpr int FS = 24;                               // halves per staged row: 16 records + padding (16-byte reads)
     // state loads issued before the fill is known (the 64-record window keeps the records first:
     // holding it across the state pass costs a workgroup per CU)
-    constexpr bool EARLY = TM == 1 && HAS_STATE && WREC <= 32;
-    static_assert(!FUSE || (TM == 1 && HAS_STATE), "the fused update belongs to kvb_decode with a state");
+    constexpr bool EARLY = HAS_STATE && WREC <= 32;
+    static_assert(!FUSE || HAS_STATE, "the fused update belongs to kvb_decode with a state");
 
-    __shared__ __attribute__((aligned(16))) float sKs[TM][D];  // -gamma_i k_i (state-row weights for accU)
-    __shared__ __attribute__((aligned(16))) float sQs[TM][D];  //  gamma_i q_i
-    __shared__ __attribute__((aligned(16))) float rK[TM][D];   // raw new rows
-    __shared__ __attribute__((aligned(16))) float rQ[TM][D];
-    __shared__ float cK[TM][NC];     // Gamma_il (k_i.k_l), 0 for l >= f+i
-    __shared__ float cQ[TM][NC];     // Gamma_il (q_i.k_l), 0 for l >  f+i
-    __shared__ __attribute__((aligned(16))) float red[NW][TM][2][D];
+    __shared__ __attribute__((aligned(16))) float sKs[D];  // -gamma k (state-row weights for accU)
+    __shared__ __attribute__((aligned(16))) float sQs[D];  //  gamma q
+    __shared__ float cK[NC];     // Gamma_l (k.k_l) of record l
+    __shared__ float cQ[NC];     // Gamma_l (q.k_l), and q.k of the token itself at l = f
+    __shared__ __attribute__((aligned(16))) float red[NW][2][D];
     __shared__ __attribute__((aligned(16))) float kh[FUSE && !MFOLD ? LT : 1][D];  // Gamma_fl k_l tile
     __shared__ int sBlk[NW][MAX_BLOCKS];
     __shared__ __attribute__((aligned(16))) float uu[FUSE && !MFOLD ? LT : 1][D];  // u_l tile
@@ -92,7 +88,6 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     const int h = lb % Hv_arg;
     const int r = a.Hv / a.Hk;
     const int hk = h / r;
-    const int T = TM == 1 ? 1 : a.T;
     const int cap = a.cap;
     if (s < 0 || s >= a.st.n_slots)
         return;
@@ -113,24 +108,18 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     // All vector loads of this kernel are issued as raw bits from always-valid addresses (an
     // index past the fill is clamped to record 0 and its value ignored), with no branch and
     // no conversion in between, so nothing waits before the state tile is in flight.
-    // new rows: each thread's 8-element slice of q_i, k_i (TM > 1: thread idx -> row idx / (D/8))
-    const int nr_i = TM == 1 ? 0 : min(tid / (D / 8), T - 1);
-    const int nr_e = TM == 1 ? sub : tid % (D / 8);
-    const size_t nr_o = (((size_t)b * T + nr_i) * a.Hk + hk) * D + 8 * nr_e;
+    // the new rows: each thread's 8-element slice of q, k
+    const size_t nr_o = ((size_t)b * a.Hk + hk) * D + 8 * sub;
     const Raw8<TIn> q_raw = load_raw8(qin + nr_o);
     const Raw8<TIn> k_raw = load_raw8(kin + nr_o);
-    TIn v_raw[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-        v_raw[i] = vin[(((size_t)b * T + min(i, T - 1)) * a.Hv + h) * D + tid % D];
+    const TIn v_raw = vin[((size_t)b * a.Hv + h) * D + tid % D];
 
     // ---- 2. the state tile goes in flight ------------------------------------
     // Decoding one token (EARLY): the state's address needs the slot only, so its loads go out
     // before the fill count is known.  Each dependent scalar load costs microseconds while the
     // chip is streaming, and this takes one of them off the path to the first state byte.  The
     // buffered records, whose addresses do need the fill, follow the state and are consumed
-    // after it.  The multi-row variants keep the records ahead of the state, since their
-    // dot-product phase is long enough to be worth hiding under the state's flight.
+    // after it.  The 64-record window keeps them ahead of the state.
     // (scheduling fences: the instruction scheduler must not reorder loads across them; the
     // memory counter retires loads in issue order)
     float4 sreg[NPASS];
@@ -146,23 +135,11 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     if constexpr (EARLY)
         issue_state();
 
-    // per-row scalars (uniform); requested together with the fill, after the state loads,
+    // scalars of the token (uniform); requested together with the fill, after the state loads,
     // so that no scalar wait stands between the slot and the first state byte
-    float gnew[TM], bet[TM];
-    int par[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const size_t o = ((size_t)b * T + min(i, T - 1)) * a.Hv + h;
-        gnew[i] = i < T ? a.g[o] : 0.0f;
-        bet[i] = i < T ? a.beta[o] : 0.0f;
-        par[i] = i - 1;
-        if constexpr (TM > 1) {
-            const int pl = a.parent[(size_t)b * T + min(i, T - 1)];
-            par[i] = a.tree ? pl : i - 1;
-        }
-    }
+    const float gnew = a.g[(size_t)b * a.Hv + h], bet = a.beta[(size_t)b * a.Hv + h];
     const int f = a.st.fill[s] & FILL_MASK;
-    if (f + T > cap) {
+    if (f + 1 > cap) {
         if (tid == 0) {
             if (a.st.status)
                 atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
@@ -174,34 +151,11 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[tid / 64], tid % 64, blk_id);
     auto ru = [&](int l) { return pg.row(l, a.Hv, h); };    // row of record l in buf_u / buf_G
     auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };   // row of record l in buf_k
-    // cumulative log decay of the new rows (uniform)
-    // Gc[i]: cumulative log decay of new row i along its own root path (a chain unless the
-    // drafts form a tree); anc[i]: bit j set iff new row j is a strict ancestor of row i.
-    // A parent index that does not precede its child is taken as -1 and flagged.
-    float Gc[TM];
-    int anc[TM];
+    // cumulative log decay of the new row (uniform)
+    float Gc;
     float G_prev = f > 0 ? Gbuf[ru(f - 1)] : 0.0f;
-    auto finish_Gc = [&]() {
-        bool bad = false;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            float base = G_prev;
-            int am = 0;
-            bad = bad || (i < T && (par[i] < -1 || par[i] >= i));
-#pragma unroll
-            for (int j = 0; j < i; ++j) {
-                const bool is_parent = par[i] == j;
-                base = is_parent ? Gc[j] : base;
-                am = is_parent ? (anc[j] | (1 << j)) : am;
-            }
-            Gc[i] = base + gnew[i];
-            anc[i] = am;
-        }
-        if (TM > 1 && bad && tid == 0 && a.st.status)
-            atomicOr(&a.st.status[s], KVB_STATUS_BADPATH);
-    };
     if constexpr (!EARLY)
-        finish_Gc();
+        Gc = G_prev + gnew;
     // window of buffered records
     Raw8<TIn> kl_raw[KP];
     float Gl[KP];
@@ -230,20 +184,15 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     float q8[8], k8[8];
     unpack8(q_raw, q8);
     unpack8(k_raw, k8);
-    float4 accU[TM], accO[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        accU[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        accO[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    if constexpr (TM == 1) {
+    float4 accU = make_float4(0.f, 0.f, 0.f, 0.f), accO = make_float4(0.f, 0.f, 0.f, 0.f);
+    {
         // EARLY applies gamma after the sum over state rows (Gc comes back behind the state)
-        const float gw = EARLY ? 1.0f : expf(Gc[0]);
+        const float gw = EARLY ? 1.0f : expf(Gc);
         if (grp == 0) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                sKs[0][8 * sub + e] = -gw * k8[e];
-                sQs[0][8 * sub + e] = gw * q8[e];
+                sKs[8 * sub + e] = -gw * k8[e];
+                sQs[8 * sub + e] = gw * q8[e];
             }
         }
         float dqk = 0.0f;
@@ -252,8 +201,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
             dqk = fmaf(q8[e], k8[e], dqk);
         dqk = group_sum<GL>(dqk);
         if (tid == 0) {
-            cK[0][f] = 0.0f;
-            cQ[0][f] = dqk;
+            cK[f] = 0.0f;
+            cQ[f] = dqk;
         }
         if constexpr (EARLY) {
             // the state rows are consumed first, in the order they were issued; the records
@@ -263,19 +212,19 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 #pragma unroll
             for (int p = 0; p < NPASS; ++p) {
                 const int row = rg + RPP * p;
-                fma4(accU[0], sKs[0][row], sreg[p]);
-                fma4(accO[0], sQs[0][row], sreg[p]);
+                fma4(accU, sKs[row], sreg[p]);
+                fma4(accO, sQs[row], sreg[p]);
             }
             // pins the sums (and everything derived from G_prev, a load younger than the
             // state) to this point: pure arithmetic is otherwise free to drift across the fences
-            asm volatile("" : "+v"(accU[0].x), "+v"(accU[0].y), "+v"(accU[0].z), "+v"(accU[0].w),
-                              "+v"(accO[0].x), "+v"(accO[0].y), "+v"(accO[0].z), "+v"(accO[0].w),
+            asm volatile("" : "+v"(accU.x), "+v"(accU.y), "+v"(accU.z), "+v"(accU.w),
+                              "+v"(accO.x), "+v"(accO.y), "+v"(accO.z), "+v"(accO.w),
                               "+v"(G_prev));
             __builtin_amdgcn_sched_barrier(0);
-            finish_Gc();
-            const float gam = expf(Gc[0]);
-            accU[0].x *= gam; accU[0].y *= gam; accU[0].z *= gam; accU[0].w *= gam;
-            accO[0].x *= gam; accO[0].y *= gam; accO[0].z *= gam; accO[0].w *= gam;
+            Gc = G_prev + gnew;
+            const float gam = expf(Gc);
+            accU.x *= gam; accU.y *= gam; accU.z *= gam; accU.w *= gam;
+            accO.x *= gam; accO.y *= gam; accO.z *= gam; accO.w *= gam;
         }
 #pragma unroll
         for (int p = 0; p < KP; ++p) {
@@ -291,9 +240,9 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
             dkk = group_sum<GL>(dkk);
             dq = group_sum<GL>(dq);
             if (sub == 0 && l < f) {
-                const float w = expf(Gc[0] - Gl[p]);
-                cK[0][l] = w * dkk;
-                cQ[0][l] = w * dq;
+                const float w = expf(Gc - Gl[p]);
+                cK[l] = w * dkk;
+                cQ[l] = w * dq;
                 if constexpr (MFOLD)
                     wF[l] = w;
             }
@@ -327,97 +276,14 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                         dkk = group_sum<GL>(dkk);
                         dq = group_sum<GL>(dq);
                         if (sub == 0 && l < f) {
-                            const float w = expf(Gc[0] - Gt[x]);
-                            cK[0][l] = w * dkk;
-                            cQ[0][l] = w * dq;
+                            const float w = expf(Gc - Gt[x]);
+                            cK[l] = w * dkk;
+                            cQ[l] = w * dq;
                             if constexpr (MFOLD)
                                 wF[l] = w;
                         }
                     }
                 }
-            }
-        }
-    } else {
-        if (tid < T * (D / 8)) {
-            float gam = 0.0f;
-#pragma unroll
-            for (int j = 0; j < TM; ++j)
-                if (j == nr_i)
-                    gam = expf(Gc[j]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                rK[nr_i][8 * nr_e + e] = k8[e];
-                rQ[nr_i][8 * nr_e + e] = q8[e];
-                sKs[nr_i][8 * nr_e + e] = -gam * k8[e];
-                sQs[nr_i][8 * nr_e + e] = gam * q8[e];
-            }
-        }
-        __syncthreads();   // rK, rQ visible
-        // buffered records, all T new rows at once
-        auto rows_vs_record = [&](const float(&kx)[8], float Gx, int l) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                if (i < T) {
-                    float dkk = 0.0f, dq = 0.0f;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        dkk = fmaf(kx[e], rK[i][8 * sub + e], dkk);
-                        dq = fmaf(kx[e], rQ[i][8 * sub + e], dq);
-                    }
-                    dkk = group_sum<GL>(dkk);
-                    dq = group_sum<GL>(dq);
-                    if (sub == 0 && l < f) {
-                        const float w = expf(Gc[i] - Gx);
-                        cK[i][l] = w * dkk;
-                        cQ[i][l] = w * dq;
-                    }
-                }
-            }
-        };
-#pragma unroll
-        for (int p = 0; p < KP; ++p) {
-            float kx[8];
-            unpack8(kl_raw[p], kx);
-            rows_vs_record(kx, Gl[p], grp + NG * p);
-        }
-        for (int l0 = KP * NG; TAIL && l0 < f; l0 += NG) {
-            const int l = l0 + grp;
-            float kx[8];
-            float Gx = 0.0f;
-            if (l < f) {
-                load8(kb + rk(l) * D + 8 * sub, kx);
-                Gx = Gbuf[ru(l)];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    kx[e] = 0.0f;
-            }
-            rows_vs_record(kx, Gx, l);
-        }
-        // new rows against each other: pair (i, j <= i) -> columns f+j of row i
-        for (int pr = grp; pr < T * T; pr += NG) {
-            const int i = pr / T, j = pr % T;
-            float dkk = 0.0f, dq = 0.0f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float kj = rK[j][8 * sub + e];
-                dkk = fmaf(kj, rK[i][8 * sub + e], dkk);
-                dq = fmaf(kj, rQ[i][8 * sub + e], dq);
-            }
-            dkk = group_sum<GL>(dkk);
-            dq = group_sum<GL>(dq);
-            if (sub == 0) {
-                float Gi = 0.0f, Gj = 0.0f;
-                int ai = 0;
-#pragma unroll
-                for (int x = 0; x < TM; ++x) {
-                    if (x == i) { Gi = Gc[x]; ai = anc[x]; }
-                    if (x == j) Gj = Gc[x];
-                }
-                const bool above = (ai >> j) & 1;   // row j is a strict ancestor of row i
-                const float w = (above || j == i) ? expf(Gi - Gj) : 0.0f;
-                cK[i][f + j] = above ? w * dkk : 0.0f;
-                cQ[i][f + j] = w * dq;
             }
         }
     }
@@ -430,13 +296,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
         const int l = rg + RPP * j;
         ur[j] = unpack4(ur_raw[j]);
         if (l < f) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                if (i < T) {
-                    fma4(accU[i], -cK[i][l], ur[j]);
-                    fma4(accO[i], cQ[i][l], ur[j]);
-                }
-            }
+            fma4(accU, -cK[l], ur[j]);
+            fma4(accO, cQ[l], ur[j]);
         }
     }
     if constexpr (TAIL) {
@@ -459,13 +320,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                 for (int j = 0; j < 4; ++j) {
                     const int l = (UP + x0 + j) * RPP + rg;
                     if (x0 + j < UT && l < f) {
-#pragma unroll
-                        for (int i = 0; i < TM; ++i) {
-                            if (i < T) {
-                                fma4(accU[i], -cK[i][l], ut[j]);
-                                fma4(accO[i], cQ[i][l], ut[j]);
-                            }
-                        }
+                        fma4(accU, -cK[l], ut[j]);
+                        fma4(accO, cQ[l], ut[j]);
                     }
                 }
             }
@@ -475,98 +331,57 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 #pragma unroll
         for (int p = 0; p < NPASS; ++p) {
             const int row = rg + RPP * p;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                if (i < T) {
-                    fma4(accU[i], sKs[i][row], sreg[p]);
-                    fma4(accO[i], sQs[i][row], sreg[p]);
-                }
-            }
+            fma4(accU, sKs[row], sreg[p]);
+            fma4(accO, sQs[row], sreg[p]);
         }
     }
 
     // ---- 5. reduce over the row groups: shuffles inside the wave, LDS across waves
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        if (i < T) {
-#pragma unroll
-            for (int off = LPR; off < 64; off <<= 1) {
-                accU[i].x += __shfl_xor(accU[i].x, off);
-                accU[i].y += __shfl_xor(accU[i].y, off);
-                accU[i].z += __shfl_xor(accU[i].z, off);
-                accU[i].w += __shfl_xor(accU[i].w, off);
-                accO[i].x += __shfl_xor(accO[i].x, off);
-                accO[i].y += __shfl_xor(accO[i].y, off);
-                accO[i].z += __shfl_xor(accO[i].z, off);
-                accO[i].w += __shfl_xor(accO[i].w, off);
-            }
-        }
+    for (int off = LPR; off < 64; off <<= 1) {
+        accU.x += __shfl_xor(accU.x, off);
+        accU.y += __shfl_xor(accU.y, off);
+        accU.z += __shfl_xor(accU.z, off);
+        accU.w += __shfl_xor(accU.w, off);
+        accO.x += __shfl_xor(accO.x, off);
+        accO.y += __shfl_xor(accO.y, off);
+        accO.z += __shfl_xor(accO.z, off);
+        accO.w += __shfl_xor(accO.w, off);
     }
     {
         const int wave = tid / 64, lane = tid % 64;
         if (lane < LPR) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                if (i < T) {
-                    *reinterpret_cast<float4 *>(&red[wave][i][0][4 * lane]) = accU[i];
-                    *reinterpret_cast<float4 *>(&red[wave][i][1][4 * lane]) = accO[i];
-                }
-            }
+            *reinterpret_cast<float4 *>(&red[wave][0][4 * lane]) = accU;
+            *reinterpret_cast<float4 *>(&red[wave][1][4 * lane]) = accO;
         }
     }
     __syncthreads();
 
-    // ---- 6. finish the T new rows (forward substitution), write results -----
+    // ---- 6. finish the new row, write results --------------------------------
     float u_new = 0.0f;
     if (tid < D) {
-        float uprev[TM];
+        float au = 0.0f, ao = 0.0f;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            if (i < T) {
-                float au = 0.0f, ao = 0.0f;
-#pragma unroll
-                for (int w = 0; w < NW; ++w) {
-                    au += red[w][i][0][tid];
-                    ao += red[w][i][1][tid];
-                }
-                const size_t row = ((size_t)b * T + i) * a.Hv + h;
-                float acc = to_f32(v_raw[i]) + au;
-#pragma unroll
-                for (int j = 0; j < TM; ++j)
-                    if (j < i)
-                        acc = fmaf(-cK[i][f + j], uprev[j], acc);
-                // the record as it is stored is what every later use reads, this token's output included
-                const TRec ur_i = from_f32<TRec>(bet[i] * acc);
-                const float ui = to_f32(ur_i);
-#pragma unroll
-                for (int j = 0; j < TM; ++j)
-                    if (j < i)
-                        ao = fmaf(cQ[i][f + j], uprev[j], ao);
-                ao = fmaf(cQ[i][f + i], ui, ao);
-                uprev[i] = ui;
-                u_new = ui;
-                out.put1(row * D + tid, a.scale * ao);
-                static_cast<TRec *>(a.st.buf_u)[ru(f + i) * D + tid] = ur_i;
-            }
+        for (int w = 0; w < NW; ++w) {
+            au += red[w][0][tid];
+            ao += red[w][1][tid];
         }
+        // the record as it is stored is what every later use reads, this token's output included
+        const TRec ur_new = from_f32<TRec>(bet * (to_f32(v_raw) + au));
+        u_new = to_f32(ur_new);
+        ao = fmaf(cQ[f], u_new, ao);
+        out.put1(((size_t)b * a.Hv + h) * D + tid, a.scale * ao);
+        static_cast<TRec *>(a.st.buf_u)[ru(f) * D + tid] = ur_new;
     }
-    if (tid < T) {
-        float gv = 0.0f;
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-            if (j == tid)
-                gv = Gc[j];
-        a.st.buf_G[ru(f + tid)] = gv;
-    }
-    if (h % r == 0 && tid < T * (D / 8)) {   // the threads that loaded the new k rows store them
-        TIn *kw = static_cast<TIn *>(a.st.buf_k) + rk(f + nr_i) * D;
-        store_raw8(kw + 8 * nr_e, k_raw);
-    }
-    int new_fill = f + T;
+    if (tid == 0)
+        a.st.buf_G[ru(f)] = Gc;
+    if (h % r == 0 && tid < D / 8)   // the threads that loaded the new k row store it
+        store_raw8(static_cast<TIn *>(a.st.buf_k) + rk(f) * D + 8 * sub, k_raw);
+    int new_fill = f + 1;
     if constexpr (FUSE) {
         const int m = f + 1;
         if (m >= a.threshold) {   // uniform over the workgroup (and over the request)
-            const float gam = expf(Gc[0]);
+            const float gam = expf(Gc);
             if constexpr (MFOLD) {
                 // The rank-m update on the matrix cores, 16 records a step.  A thread holds rows
                 // rg + 8 p (p = 0..15, rg = 2 wave + lane / 32) of columns 4 c4 + e: for each e that is
@@ -590,7 +405,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                     acc[3][p] = gam * sreg[p].w;
                 }
                 if (tid < D)
-                    sKs[0][tid] = u_new;   // (the state rows were weighted long ago)
+                    sKs[tid] = u_new;   // (the state rows were weighted long ago)
                 const int lane = tid % 64, wv = tid / 64;
                 // kx: elements 8 sub .. + 7 of key l0 + grp; u0, u1: columns 4 c4 .. + 3 of records l0 + rg, + 8
                 auto fold_tile = [&](int l0, const Raw8<TIn> &kx, const float4 &u0, const float4 &u1) {
@@ -608,7 +423,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                             if constexpr (KPC == 2)
                                 kT[KPC - 1][row][at] = (uint16_t)(__float_as_uint(x - __uint_as_float(top)) >> 16);
                         }
-                        const float *un = &sKs[0][4 * c4];
+                        const float *un = &sKs[4 * c4];
                         const int la = l0 + rg, lb8 = la + 8;
                         const float wa = la < f ? wF[la] : 0.0f, wb = lb8 < f ? wF[lb8] : 0.0f;
                         const float xa[4] = {u0.x, u0.y, u0.z, u0.w}, xb[4] = {u1.x, u1.y, u1.z, u1.w};
@@ -707,7 +522,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                             const int l = LT * p + grp;
                             float kx[8];
                             unpack8(kl_raw[p], kx);
-                            const float w = l < f ? expf(Gc[0] - Gl[p]) : 0.0f;
+                            const float w = l < f ? expf(Gc - Gl[p]) : 0.0f;
                             if (l != f) {   // row f of the tile belongs to inject_new
 #pragma unroll
                                 for (int e = 0; e < 8; ++e)
@@ -745,7 +560,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                         if (l != f) {   // row f of the tile belongs to inject_new
                             float kx[8];
                             unpack8(kq, kx);
-                            const float w = l < f ? expf(Gc[0] - Gq) : 0.0f;
+                            const float w = l < f ? expf(Gc - Gq) : 0.0f;
 #pragma unroll
                             for (int e = 0; e < 8; ++e)
                                 kh[grp][8 * sub + e] = l < f ? w * kx[e] : 0.0f;
@@ -778,7 +593,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                         for (int x = 0; x < EPT; ++x) {
                             const int idx = tid + NT * x, l = l0 + idx / D, e = idx % D;
                             if (l < f) {
-                                kh[idx / D][e] = expf(Gc[0] - Gbuf[ru(l)]) * to_f32(kb[rk(l) * D + e]);
+                                kh[idx / D][e] = expf(Gc - Gbuf[ru(l)]) * to_f32(kb[rk(l) * D + e]);
                                 uu[idx / D][e] = to_f32(ub[ru(l) * D + e]);
                             } else if (l > f) {
                                 kh[idx / D][e] = 0.0f;
@@ -812,70 +627,51 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 // ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
-template <int D, typename TIn, typename TRec, int TM, int WREC>
+template <int D, typename TIn, typename TRec, int WREC>
 void launch_step_s(const StepArgs &a, int blocks, hipStream_t stream)
 {
     // (a branch inside the kernel around the state loads would make the compiler's wait
     // counters conservative at the join, so these are compile-time variants)
     const bool st = a.stream_state != 0 && D == 128;   // the small head sizes are not tuned: no streaming variant
-    if constexpr (TM == 1) {
-        if (a.threshold > 0) {
-            if constexpr (D == 128) {
-                if (st) {
-                    LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, 1, WREC, true, true, true);
-                    return;
-                }
+    if (a.threshold > 0) {
+        if constexpr (D == 128) {
+            if (st) {
+                LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, true, true);
+                return;
             }
-            LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, 1, WREC, true, true, false);
-            return;
         }
+        LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, true, false);
+        return;
     }
     if (!a.st.state) {
-        LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, TM, WREC, false, false, false);
+        LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, false, false, false);
         return;
     }
     if constexpr (D == 128) {
         if (st) {
-            LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, TM, WREC, true, false, true);
+            LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, false, true);
             return;
         }
     }
-    LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, TM, WREC, true, false, false);
+    LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, false, false);
 }
 
-template <int D, typename TIn, typename TRec, int TM>
+template <int D, typename TIn, typename TRec>
 void launch_step_w(const StepArgs &a, int blocks, hipStream_t stream)
 {
     // Register window of buffered records.  For d = 128 the smallest tier that holds the
     // whole buffer is used; the smaller head sizes only carry the general (64 + tail) tier.
     if constexpr (D == 128) {
         if (a.cap <= 16) {
-            launch_step_s<D, TIn, TRec, TM, 16>(a, blocks, stream);
+            launch_step_s<D, TIn, TRec, 16>(a, blocks, stream);
             return;
         }
         if (a.cap <= 32) {
-            launch_step_s<D, TIn, TRec, TM, 32>(a, blocks, stream);
+            launch_step_s<D, TIn, TRec, 32>(a, blocks, stream);
             return;
         }
     }
-    launch_step_s<D, TIn, TRec, TM, 64>(a, blocks, stream);
-}
-
-template <int D, typename TIn, typename TRec>
-void launch_step_t(const StepArgs &a, int blocks, hipStream_t stream)
-{
-    if (a.T == 1) {
-        launch_step_w<D, TIn, TRec, 1>(a, blocks, stream);
-        return;
-    }
-    // several drafts with 16-bit inputs and d = 128 belong to kvb_verify_mfma_kernel; the
-    // vector-ALU variants are not compiled for that pair
-    if constexpr (!(D == 128 && sizeof(TIn) == 2)) {
-        if (a.T <= 4)
-            launch_step_w<D, TIn, TRec, 4>(a, blocks, stream);
-        else
-            launch_step_w<D, TIn, TRec, 8>(a, blocks, stream);
-    }
+    launch_step_s<D, TIn, TRec, 64>(a, blocks, stream);
 }
 
 // All head sizes of one (input type, record type) pair.
@@ -884,13 +680,13 @@ int launch_step_typed(int dk, const StepArgs &a, int blocks, hipStream_t stream)
 {
     switch (dk) {
     case 32:
-        launch_step_t<32, TIn, TRec>(a, blocks, stream);
+        launch_step_w<32, TIn, TRec>(a, blocks, stream);
         return KVB_OK;
     case 64:
-        launch_step_t<64, TIn, TRec>(a, blocks, stream);
+        launch_step_w<64, TIn, TRec>(a, blocks, stream);
         return KVB_OK;
     case 128:
-        launch_step_t<128, TIn, TRec>(a, blocks, stream);
+        launch_step_w<128, TIn, TRec>(a, blocks, stream);
         return KVB_OK;
     }
     return KVB_EUNSUPPORTED;

@@ -3,7 +3,7 @@
 
 namespace kvb_impl {
 
-template void launch_verify_typed<bf16_t, float>(const StepArgs &a, int blocks, hipStream_t stream);
-template void launch_verify_typed<bf16_t, bf16_t>(const StepArgs &a, int blocks, hipStream_t stream);
+template void launch_verify_typed<bf16_t, float>(int dk, const StepArgs &a, int blocks, hipStream_t stream);
+template void launch_verify_typed<bf16_t, bf16_t>(int dk, const StepArgs &a, int blocks, hipStream_t stream);
 
 }  // namespace kvb_impl

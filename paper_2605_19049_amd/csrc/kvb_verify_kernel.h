@@ -1,5 +1,5 @@
-// kvb_verify_mfma_kernel: kvb_verify / kvb_verify_tree for 16-bit inputs and d = 128.  Template code
-// only; kvb_verify_bf16.hip and kvb_verify_f16.hip instantiate it for their input type.
+// kvb_verify_mfma_kernel: kvb_verify / kvb_verify_tree.  Template code
+// only; kvb_verify_bf16.hip, kvb_verify_f16.hip and kvb_verify_f32.hip instantiate it for their input type.
 #ifndef KVB_VERIFY_KERNEL_H
 #define KVB_VERIFY_KERNEL_H
 
@@ -7,32 +7,124 @@
 
 namespace kvb_impl {
 
+// N adjacent columns of a state row or a delta-value row, converted and as raw bits.
+template <int N>
+struct Cols {
+    float x[N];
+};
+template <bool STREAM, int N>
+__device__ __forceinline__ Cols<N> load_cols(const float *p)
+{
+    if constexpr (N == 2) {
+        const float2 t = load_state2<STREAM>(p);
+        return Cols<N>{{t.x, t.y}};
+    } else {
+        return Cols<N>{{*p}};
+    }
+}
+template <typename T, int N>
+struct RawCols {
+    Raw2<T> w;
+};
+template <typename T>
+struct RawCols<T, 1> {
+    T w;
+};
+template <int N, typename T>
+__device__ __forceinline__ RawCols<T, N> load_raw_cols(const T *p)
+{
+    if constexpr (N == 2)
+        return RawCols<T, N>{load_raw2(p)};
+    else
+        return RawCols<T, N>{*p};
+}
+template <typename T, int N>
+__device__ __forceinline__ Cols<N> unpack_cols(const RawCols<T, N> &r)
+{
+    if constexpr (N == 2) {
+        const float2 t = unpack2r(r.w);
+        return Cols<N>{{t.x, t.y}};
+    } else {
+        return Cols<N>{{to_f32(r.w)}};
+    }
+}
+
+// 16 bytes of a key or query row as fp32, and a 16 x 16 tile of dot products: a lane holds the same
+// pieces of row lm of both factors, so which element a contraction slot stands for is free.
+template <typename T, int N>
+__device__ __forceinline__ void unpack_piece(const uint4 &w, float (&o)[N])
+{
+    if constexpr (sizeof(T) == 2) {
+        unpack8(Raw8<T>{w}, o);
+    } else {
+        o[0] = __uint_as_float(w.x); o[1] = __uint_as_float(w.y); o[2] = __uint_as_float(w.z); o[3] = __uint_as_float(w.w);
+    }
+}
+template <typename T, int N>
+__device__ __forceinline__ f32x4_t dot_tile(const uint4 (&a)[N], const uint4 (&b)[N])
+{
+    f32x4_t c = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int st = 0; st < N; ++st)
+            c = mfma16x32<T>(a[st], b[st], c);
+        return c;
+    } else {   // (short chains: see CHAINS below)
+#pragma unroll
+        for (int s0 = 0; s0 < N; s0 += 4) {
+            f32x4_t e[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                e[x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int st = s0; st < s0 + 4 && st < N; ++st) {
+                e[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[st].x), __uint_as_float(b[st].x), e[0], 0, 0, 0);
+                e[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[st].y), __uint_as_float(b[st].y), e[1], 0, 0, 0);
+                e[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[st].z), __uint_as_float(b[st].z), e[2], 0, 0, 0);
+                e[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[st].w), __uint_as_float(b[st].w), e[3], 0, 0, 0);
+            }
+            c += (e[0] + e[1]) + (e[2] + e[3]);
+        }
+        return c;
+    }
+}
+
 // ---------------------------------------------------------------------------
-// kvb_verify for 16-bit inputs (bf16 or fp16) and d = 128, on the matrix cores.
+// kvb_verify on the matrix cores.
 //
 // With T drafts the step is a pair of small dense contractions (Sec. 3.3, Eq. 7; Eq. 15):
 //   stage 1   C1[m][l] = W[m] . k_l        W = [k_0..k_7 ; q_0..q_7] (16 x dk, 16-bit),
-//             l over the buffered and the new keys  -> v_mfma_f32_16x16x32_{bf16,f16}
+//             l over the buffered and the new keys  -> v_mfma_f32_16x16x32_{bf16,f16}; fp32 keys: 16x16x4_f32
 //   stage 2   acc[m][:] = sum_rows sW[row][m] S0[row][:] + sum_{l<f} cW[l][m] u_l[:]
 //             (16 x (dk + f)) . ((dk + f) x dv), fp32 operands -> v_mfma_f32_16x16x4_f32
 // where sW[row][m] = -gamma_i k_i[row] (m = i) or gamma_i q_i[row] (m = 8 + i) and
 // cW[l][m] = -/+ Gamma_il C1[m][l].  The cost of stage 2 does not depend on T <= 8.
-// Each wave owns 32 dv columns for all rows, so no reduction across waves is needed; a
-// lane loads 2 adjacent columns of 4 consecutive rows' worth of lanes (16 lanes x 8 B =
-// one 128-byte line per row).  MFMA layouts: see kvb_direct_mfma_kernel; for 16x16x4 fp32
+// Each wave owns D / 4 dv columns (d = 32: two waves own 16) for all rows, so no reduction
+// across waves is needed; at d = 128 a lane loads 2 adjacent columns (16 lanes x 8 B = one
+// 128-byte line per row).  MFMA layouts: see kvb_direct_mfma_kernel; for 16x16x4 fp32
 // lane l supplies A[l%16][l/16] and B[l/16][l%16] and receives C[4*(l/16)+v][l%16].
+// fp32 inputs and the head sizes 32 and 64 came here from the vector ALU, where every draft cost its own
+// multiply-adds for every state row and record.  Verify and commit, 24 requests of 16 heads, fp32, 5 drafts:
+// 31.5 -> 21.1 us; with the commit's own move off the vector ALU, 150 of 16 heads, fp32, 3 drafts: 100 -> 68 us;
+// 200 of 32, d = 64, 4 drafts: 92 -> 55 us.
 // ---------------------------------------------------------------------------
-template <typename TIn, typename TRec, int WREC, bool HAS_STATE, bool STREAM, bool PAGED>
-// (register budgets: 4 waves per SIMD with a record window of 16 or 32, 3 with the 64-record window)
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(!HAS_STATE ? 1 : WREC <= 32 ? 4 : 3)))
+template <int D, typename TIn, typename TRec, int WREC, bool HAS_STATE, bool STREAM, bool PAGED>
+// (register budgets: 4 waves per SIMD with a record window of 16 or 32, 3 with the 64-record window or with
+// fp32 keys of 128, whose operands take twice the registers)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(!HAS_STATE ? 1 : (WREC <= 32 ? 4 : 3) - (D * sizeof(TIn) > 256))))
 void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg, const StepArgs a)
 {
     // (the three leading arguments repeat a.slot, a.Hv and the grid size: preloaded into scalar registers
     // at wave launch, so that the load of slot[b] does not wait for the fetch of the argument block)
-    constexpr int D = 128;
+    constexpr int CT = D == 128 ? 2 : 1;                      // adjacent columns of a lane
+    constexpr int WC = 16 * CT;                               // columns of a wave
+    constexpr int NWC = D / WC;                               // waves that own columns (d = 32: the other two repeat them)
+    constexpr int EW = 16 / (int)sizeof(TIn);                 // elements of a 16-byte piece of a key row
+    constexpr int NWA = D / (4 * EW);                         // pieces of a row that a lane holds (lq 0..3 side by side)
     constexpr int TMX = KVB_MAX_DRAFTS;                       // 8
     constexpr int NTILE = (KVB_MAX_CAP + TMX + 15) / 16;      // key tiles of 16 (9)
-    constexpr int NTW = ((WREC + TMX + 15) / 16 + NW - 1) / NW;  // tiles per wave held in registers
+    // tiles per wave held in registers
+    constexpr int NTW = D * sizeof(TIn) > 256 ? 1 : ((WREC + TMX + 15) / 16 + NW - 1) / NW;
     constexpr int WQ = WREC / 4;                              // record quads held in registers
     constexpr bool TAIL = WREC >= 64;
     constexpr bool EARLY = HAS_STATE;   // state loads issued before the fill is known
@@ -68,18 +160,18 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     const int blk_id = load_block_id<PAGED>(a.st, s, lane);
 
     const int lm = lane % 16, lq = lane / 16;   // MFMA row/column index and k index of this lane
-    const int col2 = 32 * wave + 2 * lm;
+    const int col2 = WC * (wave % NWC) + CT * lm;
 
     // ---- 1. loads that need only the request index: raw bits, clamped addresses, no branches
-    // row lm of W (draft lm % 8; k for lm < 8, q above), k-chunk lq of each 32-wide step
+    // row lm of W (draft lm % 8; k for lm < 8, q above), piece lq of each four
     const int wi = min(lm % 8, T - 1);
-    const TIn *wrow = (lm < 8 ? kin : qin) + (((size_t)b * T + wi) * a.Hk + hk) * D + 8 * lq;
-    uint4 wa[4];
+    const TIn *wrow = (lm < 8 ? kin : qin) + (((size_t)b * T + wi) * a.Hk + hk) * D + EW * lq;
+    uint4 wa[NWA];
 #pragma unroll
-    for (int st = 0; st < 4; ++st)
-        wa[st] = *reinterpret_cast<const uint4 *>(wrow + 32 * st);
+    for (int st = 0; st < NWA; ++st)
+        wa[st] = *reinterpret_cast<const uint4 *>(wrow + 4 * EW * st);
 
-    // ---- 2. the state: rows 4 st + lq, the wave's 32 columns -----------------
+    // ---- 2. the state: rows 4 st + lq, the wave's columns --------------------
     // EARLY: the state's address needs the slot only, so its loads go out before the fill is
     // known and before the long scalar prologue; the records follow and are consumed after the
     // state (the decay gamma_i of row i is then applied to the finished sum over state rows).
@@ -87,19 +179,10 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     // register pair as soon as its quad has gone through the matrix cores: 32 registers less, which
     // is what lets a fourth workgroup onto each CU (the kernel is bound by how well its waves hide
     // each other's waits, not by bytes in flight).
-    constexpr int WIN = EARLY ? 16 : D / 4;
-    float2 sreg[WIN];
+    constexpr int WIN = EARLY && D == 128 ? 16 : D / 4;
+    Cols<CT> sreg[WIN];
     const float *sp = a.st.state + (HAS_STATE ? unit * D * D + col2 : 0);
-    auto load_quad = [&](int st) {
-        const float2 *p = reinterpret_cast<const float2 *>(sp + (size_t)(4 * st + lq) * D);
-        if constexpr (STREAM) {
-            typedef float v2f __attribute__((ext_vector_type(2)));
-            const v2f t = __builtin_nontemporal_load(reinterpret_cast<const v2f *>(p));
-            return make_float2(t.x, t.y);
-        } else {
-            return *p;
-        }
-    };
+    auto load_quad = [&](int st) { return load_cols<STREAM, CT>(sp + (size_t)(4 * st + lq) * D); };
     auto issue_state = [&]() {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -132,7 +215,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     int par_raw = a.parent[(size_t)b * T + min(lane % 8, T - 1)];
     float G_prev = f > 0 ? Gbuf[ru(f - 1)] : 0.0f;
     // keys of this wave's tiles (buffered first, then the new ones)
-    uint4 kt[NTW][4];
+    uint4 kt[NTW][NWA];
     float Gn[NTW];
 #pragma unroll
     for (int x = 0; x < NTW; ++x) {
@@ -141,19 +224,19 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
                               : kin + (((size_t)b * T + min(max(n - f, 0), T - 1)) * a.Hk + hk) * D;
         Gn[x] = Gbuf[ru(n < f ? n : 0)];
 #pragma unroll
-        for (int st = 0; st < 4; ++st)
-            kt[x][st] = *reinterpret_cast<const uint4 *>(kp + 8 * lq + 32 * st);
+        for (int st = 0; st < NWA; ++st)
+            kt[x][st] = *reinterpret_cast<const uint4 *>(kp + EW * lq + 4 * EW * st);
     }
     // buffered delta values: quad sq = records 4 sq .. 4 sq + 3, this lane: record 4 sq + lq,
-    // columns 32 wave + 2 lm, + 1
-    Raw2<TRec> uq[WQ];
+    // columns col2 (d = 128: and the next)
+    RawCols<TRec, CT> uq[WQ];
 #pragma unroll
     for (int sq = 0; sq < WQ; ++sq) {
         const int l = 4 * sq + lq;
-        uq[sq] = load_raw2(ub + ru(l < f ? l : 0) * D + col2);
+        uq[sq] = load_raw_cols<CT>(ub + ru(l < f ? l : 0) * D + col2);
     }
-    // v of this wave's columns (used by lanes 0..31 in the last stage)
-    const int colf = 32 * wave + lane % 32;
+    // v of this wave's columns (used by its first WC lanes in the last stage)
+    const int colf = WC * (wave % NWC) + lane % WC;
     TIn v_raw[TMX];
 #pragma unroll
     for (int i = 0; i < TMX; ++i)
@@ -224,37 +307,74 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         finish_Gc();
 
     // ---- 4. weights of the state rows ------------------------------------------
-    f32x4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+    // The sums.  One chain of multiply-adds holds a rounding of the whole sum for each of its terms, which for fp32
+    // inputs and the small head sizes showed against the vector ALU's row groups; there two chains run for SETTLE
+    // contraction steps and are then added to the total (24 requests, fp32, 5 drafts: 1.2e-7 off 64 bits like the
+    // vector ALU, one chain 2.2e-7).
+    constexpr bool CHAINS = !(D == 128 && sizeof(TIn) == 2);
+    constexpr int NACC = CHAINS ? 2 : 1, SETTLE = D == 128 ? 8 : 4;
+    f32x4_t acc[CT], part[NACC][CT];
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int n = 0; n < NACC; ++n)
+            part[n][t] = acc[t];
+    }
+    auto add = [&](int step, int t, float w, float x) {
+        f32x4_t &c = CHAINS ? part[step % NACC][t] : acc[t];
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(w, x, c, 0, 0, 0);
+    };
+    auto settle = [&]() {
+        if constexpr (CHAINS) {
+#pragma unroll
+            for (int t = 0; t < CT; ++t) {
+                acc[t] += part[0][t] + part[NACC - 1][t];
+                part[0][t] = part[NACC - 1][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+    };
     const bool live = lm % 8 < T;
     {
-        // the chunk this lane holds for step == wave covers state rows 32 wave + 8 lq .. + 7
-        float x[8];
-        unpack8(Raw8<TIn>{wa[0]}, x);
-#pragma unroll
-        for (int st = 1; st < 4; ++st) {
-            float y[8];
-            unpack8(Raw8<TIn>{wa[st]}, y);
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                x[e] = wave == st ? y[e] : x[e];
-        }
         float gam;
         if constexpr (EARLY)
             gam = live ? 1.0f : 0.0f;
         else
             gam = live ? expf(GcLm) : 0.0f;
         const float sg = lm < 8 ? -gam : gam;
+        // piece st of the rows belongs to wave st % 4 and covers state rows 4 EW st + EW lq ..
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-            sW[32 * wave + 8 * lq + e][lm] = sg * x[e];
+        for (int g = 0; g < NWA; g += NW) {
+            // (component by component: a select between two uint4 objects is compiled as a select
+            // between their addresses, which puts them in scratch memory)
+            uint4 mine = wa[g];
+#pragma unroll
+            for (int j = 1; j < NW; ++j) {
+                const uint4 other = wa[g + j < NWA ? g + j : g];
+                mine.x = wave == j ? other.x : mine.x;
+                mine.y = wave == j ? other.y : mine.y;
+                mine.z = wave == j ? other.z : mine.z;
+                mine.w = wave == j ? other.w : mine.w;
+            }
+            if (g + wave < NWA) {   // uniform
+                float x[EW];
+                unpack_piece<TIn>(mine, x);
+#pragma unroll
+                for (int e = 0; e < EW; ++e)
+                    sW[4 * EW * (g + wave) + EW * lq + e][lm] = sg * x[e];
+            }
+        }
     }
     auto state_rows = [&]() {
 #pragma unroll
         for (int st = 0; st < D / 4; ++st) {
             const float aw = sW[4 * st + lq][lm];
-            const float2 sv = sreg[st % WIN];
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw, sv.x, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw, sv.y, acc1, 0, 0, 0);
+            const Cols<CT> sv = sreg[st % WIN];
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+                add(st, t, aw, sv.x[t]);
+            if (st % SETTLE == SETTLE - 1)
+                settle();
             if (st + WIN < D / 4) {   // the freed registers take the quad WIN further on
                 __builtin_amdgcn_sched_barrier(0);
                 sreg[st % WIN] = load_quad(st + WIN);
@@ -268,7 +388,9 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         state_rows();
         // pins the sums, and whatever derives from the loads younger than the state, to this
         // point: pure arithmetic is otherwise free to drift across the fences
-        asm volatile("" : "+v"(acc0), "+v"(acc1), "+v"(G_prev), "+v"(g_raw), "+v"(beta_mine), "+v"(par_raw));
+        if constexpr (CT == 2)
+            asm volatile("" : "+v"(acc[CT - 1]));
+        asm volatile("" : "+v"(acc[0]), "+v"(G_prev), "+v"(g_raw), "+v"(beta_mine), "+v"(par_raw));
         __builtin_amdgcn_sched_barrier(0);
         finish_Gc();
         // acc*[v] is row m = 4 lq + v = draft m % 8: apply its gamma
@@ -276,18 +398,16 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         for (int v = 0; v < 4; ++v) {
             const int i = (4 * lq + v) % 8;
             const float gam = i < T ? expf(GcRow[v]) : 0.0f;
-            acc0[v] *= gam;
-            acc1[v] *= gam;
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+                acc[t][v] *= gam;
         }
     }
 
     // ---- 5. stage 1: decayed dot products with every buffered and new key -------
     // Gkey: cumulative log decay of key n of the tile (a buffered one from memory, a new one from above)
-    auto key_tile = [&](int tile, const uint4(&kk)[4], float Gkey) {
-        f32x4_t c1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int st = 0; st < 4; ++st)
-            c1 = mfma16x32<TIn>(wa[st], kk[st], c1);
+    auto key_tile = [&](int tile, const uint4(&kk)[NWA], float Gkey) {
+        const f32x4_t c1 = dot_tile<TIn>(wa, kk);
         // this lane: rows m = 4 lq + v of W against key n
         const int n = 16 * tile + lm;
         float o[4];
@@ -298,8 +418,8 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             // a buffered key is seen by every draft; a new one by its descendants (q rows: and by itself)
             const bool above = n >= f && ((ancRow[v] >> min(n - f, 31)) & 1);
             const bool ok = i < T && n < nrec && (n < f || above || (isq && n - f == i));
-            const float w = ok ? expf(GcRow[v] - Gkey) : 0.0f;
-            o[v] = (isq ? w : -w) * c1[v];
+            const float w = expf(GcRow[v] - Gkey);
+            o[v] = ok ? (isq ? w : -w) * c1[v] : 0.0f;
         }
         *reinterpret_cast<float4 *>(&cW[n][4 * lq]) = make_float4(o[0], o[1], o[2], o[3]);
     };
@@ -313,10 +433,10 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         const int n = 16 * tile + lm;
         const TIn *kp = n < f ? kb + rk(min(n, cap - 1)) * D
                               : kin + (((size_t)b * T + min(max(n - f, 0), T - 1)) * a.Hk + hk) * D;
-        uint4 kk[4];
+        uint4 kk[NWA];
 #pragma unroll
-        for (int st = 0; st < 4; ++st)
-            kk[st] = *reinterpret_cast<const uint4 *>(kp + 8 * lq + 32 * st);
+        for (int st = 0; st < NWA; ++st)
+            kk[st] = *reinterpret_cast<const uint4 *>(kp + EW * lq + 4 * EW * st);
         const float Gb = Gbuf[ru(n < f ? n : 0)];
         key_tile(tile, kk, n < f ? Gb : sGc[wave][min(max(n - f, 0), TMX - 1)]);
     }
@@ -329,37 +449,47 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         if (sq < nquad) {   // uniform
             const bool ok = 4 * sq + lq < f;
             const float aw = cW[4 * sq + lq][lm];
-            const float2 uv = unpack2r(uq[sq]);
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw, ok ? uv.x : 0.0f, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw, ok ? uv.y : 0.0f, acc1, 0, 0, 0);
+            const Cols<CT> uv = unpack_cols(uq[sq]);
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+                add(sq, t, aw, ok ? uv.x[t] : 0.0f);
+            if (sq % SETTLE == SETTLE - 1)
+                settle();
         }
     }
     // records beyond the register window: four quads to a round trip (requested together, clamped)
     for (int s0 = WQ; TAIL && s0 < nquad; s0 += 4) {
-        Raw2<TRec> u4r[4];
+        RawCols<TRec, CT> u4r[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int l = 4 * (s0 + j) + lq;
-            u4r[j] = load_raw2(ub + ru(l < f ? l : 0) * D + col2);
+            u4r[j] = load_raw_cols<CT>(ub + ru(l < f ? l : 0) * D + col2);
         }
-        float2 u4[4];
+        Cols<CT> u4[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            u4[j] = unpack2r(u4r[j]);
+            u4[j] = unpack_cols(u4r[j]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int l = 4 * (s0 + j) + lq;   // < 4 * 35 + 4 = 144 rows of cW
             if (s0 + j < nquad) {   // uniform
                 const float aw = cW[l][lm];
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw, l < f ? u4[j].x : 0.0f, acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw, l < f ? u4[j].y : 0.0f, acc1, 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < CT; ++t)
+                    add(j, t, aw, l < f ? u4[j].x[t] : 0.0f);
             }
         }
     }
-    // acc*[v] = row m = 4 lq + v, column col2 (+1)
+    settle();
+    // acc[t][v] = row m = 4 lq + v, column col2 + t
+    if (wave < NWC)   // uniform
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-        *reinterpret_cast<float2 *>(&fin[4 * lq + v][col2]) = make_float2(acc0[v], acc1[v]);
+        for (int v = 0; v < 4; ++v) {
+            if constexpr (CT == 2)
+                *reinterpret_cast<float2 *>(&fin[4 * lq + v][col2]) = make_float2(acc[0][v], acc[CT - 1][v]);
+            else
+                fin[4 * lq + v][col2] = acc[0][v];
+        }
     __syncthreads();
 
     // ---- 5. the T new rows among themselves; results ---------------------------
@@ -371,7 +501,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         vf[i] = to_f32(v_raw[i]);
         asm volatile("" : "+v"(vf[i]));
     }
-    if (lane < 32) {
+    if (lane < WC && wave < NWC) {
         // every LDS value of the substitution is fetched up front (independent reads, one
         // round trip for all) rather than one by one along the serial chain
         float fu[TMX], fo[TMX], ck[TMX][TMX], cq[TMX][TMX];
@@ -422,7 +552,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         }
     }
     __syncthreads();
-    // results leave as whole 512-byte rows, 16 bytes per lane: T rows of u, then T rows of out
+    // results leave as whole rows, 16 bytes per lane: T rows of u, then T rows of out
     for (int idx = tid; idx < 2 * T * (D / 4); idx += NT) {
         const int rr = idx / (D / 4), c4 = idx % (D / 4);
         const bool is_u = rr < T;
@@ -436,37 +566,62 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     if (tid < T)
         a.st.buf_G[ru(f + tid)] = GcTid;
     if (h % r == 0 && wave == 0 && lm < T) {   // lanes holding k rows store them
-        TIn *kw = static_cast<TIn *>(a.st.buf_k) + rk(f + lm) * D + 8 * lq;
+        TIn *kw = static_cast<TIn *>(a.st.buf_k) + rk(f + lm) * D + EW * lq;
 #pragma unroll
-        for (int st = 0; st < 4; ++st)
-            *reinterpret_cast<uint4 *>(kw + 32 * st) = wa[st];
+        for (int st = 0; st < NWA; ++st)
+            *reinterpret_cast<uint4 *>(kw + 4 * EW * st) = wa[st];
     }
 }
 
 // ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
-template <typename TIn, typename TRec, int WREC>
+template <int D, typename TIn, typename TRec, int WREC>
 void launch_verify_w(const StepArgs &a, int blocks, hipStream_t stream)
 {
-    if (!a.st.state)
-        LAUNCH_LEAD(blocks, stream, a, kvb_verify_mfma_kernel<TIn, TRec, WREC, false, false);
-    else if (a.stream_state)
-        LAUNCH_LEAD(blocks, stream, a, kvb_verify_mfma_kernel<TIn, TRec, WREC, true, true);
+    if (!a.st.state) {
+        LAUNCH_LEAD(blocks, stream, a, kvb_verify_mfma_kernel<D, TIn, TRec, WREC, false, false);
+        return;
+    }
+    if constexpr (D == 128) {   // (the small head sizes are not tuned: no streaming variant)
+        if (a.stream_state) {
+            LAUNCH_LEAD(blocks, stream, a, kvb_verify_mfma_kernel<D, TIn, TRec, WREC, true, true);
+            return;
+        }
+    }
+    LAUNCH_LEAD(blocks, stream, a, kvb_verify_mfma_kernel<D, TIn, TRec, WREC, true, false);
+}
+
+template <int D, typename TIn, typename TRec>
+void launch_verify_d(const StepArgs &a, int blocks, hipStream_t stream)
+{
+    // record window: a request that fits has fill <= cap - T
+    if constexpr (D == 128) {
+        if (a.cap - a.T <= 16) {
+            launch_verify_w<D, TIn, TRec, 16>(a, blocks, stream);
+            return;
+        }
+    }
+    if (a.cap - a.T <= 32)
+        launch_verify_w<D, TIn, TRec, 32>(a, blocks, stream);
     else
-        LAUNCH_LEAD(blocks, stream, a, kvb_verify_mfma_kernel<TIn, TRec, WREC, true, false);
+        launch_verify_w<D, TIn, TRec, 64>(a, blocks, stream);
 }
 
 template <typename TIn, typename TRec>
-void launch_verify_typed(const StepArgs &a, int blocks, hipStream_t stream)
+void launch_verify_typed(int dk, const StepArgs &a, int blocks, hipStream_t stream)
 {
-    // record window: a request that fits has fill <= cap - T
-    if (a.cap - a.T <= 16)
-        launch_verify_w<TIn, TRec, 16>(a, blocks, stream);
-    else if (a.cap - a.T <= 32)
-        launch_verify_w<TIn, TRec, 32>(a, blocks, stream);
-    else
-        launch_verify_w<TIn, TRec, 64>(a, blocks, stream);
+    switch (dk) {   // (checked by the caller)
+    case 32:
+        launch_verify_d<32, TIn, TRec>(a, blocks, stream);
+        break;
+    case 64:
+        launch_verify_d<64, TIn, TRec>(a, blocks, stream);
+        break;
+    case 128:
+        launch_verify_d<128, TIn, TRec>(a, blocks, stream);
+        break;
+    }
 }
 
 }  // namespace kvb_impl

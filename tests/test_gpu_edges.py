@@ -8,7 +8,7 @@ import pytest
 import harness as H
 from harness import oracle
 from paper_2605_19049_amd import synth
-from test_gpu_parity import _direct_case, say
+from test_gpu_parity import _direct_case, _tree_case, _verify_case, say
 
 pytestmark = pytest.mark.gpu
 
@@ -83,3 +83,15 @@ def test_flush_rows_chunks(d, in_dtype, rec_dtype, C, block_size):
     e = (H.rel_err(o, o_ref), H.rel_err(u, u_ref), H.rel_err(S, S_ref))
     say("flush rows, d=%d %s/%s C=%d: rel err out/u/state %.2e %.2e %.2e" % ((d, in_dtype, rec_dtype, C) + e))
     H.check(e, in_dtype, rec_dtype, "flush rows")
+
+
+@pytest.mark.parametrize("d, in_dtype, rec_dtype", [(d, i, r) for d in (32, 64) for i, r in TYPES + [("f32", "f32")]]
+                         + [(128, "f32", "f32")])
+@pytest.mark.parametrize("C, T", [(1, 2), (16, 4), (30, 8), (60, 3), (120, 8)])
+def test_verify_windows(d, in_dtype, rec_dtype, C, T):
+    """kvb_verify and kvb_verify_tree off the 16-bit d = 128 path, in every record window and beyond it."""
+    for block_size, case in ((None, _verify_case), (8, _tree_case)):
+        cap = -(-(C - 1 + T) // 8) * 8
+        e = case(5, 2, 6, d, C, cap, T, in_dtype, seed=850 + C, block_size=block_size, rec_dtype=rec_dtype)
+        say("verify windows, d=%d %s/%s C=%d T=%d: %s" % (d, in_dtype, rec_dtype, C, T, e))
+        H.check(e, in_dtype, rec_dtype, "verify windows")
