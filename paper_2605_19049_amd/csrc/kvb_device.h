@@ -1,7 +1,7 @@
 // kvb -- KVBuffer-style Gated DeltaNet decoding, HIP kernels for gfx950 behind the C ABI of
 // include/kvb.h.  This header holds what the translation units share: device helpers, the
 // argument structs of the kernels, and the launch plumbing.
-//   kvb_step_kernel.h    kvb_step_kernel (decode); instantiated per
+//   kvb_step_kernel.h    kvb_step_kernel and kvb_buffer_step_kernel (decode); instantiated per
 //                        (input type, record type) by kvb_step_f32.hip, kvb_step_bf16.hip,
 //                        kvb_step_bf16_r16.hip, kvb_step_f16.hip, kvb_step_f16_r16.hip
 //   kvb_verify_kernel.h  kvb_verify_mfma_kernel; instantiated by kvb_verify_bf16.hip, _f16.hip, _f32.hip
@@ -21,6 +21,7 @@
 // App. A.1, the paragraph after Eq. 16), a few KB.
 //   kvb_step_kernel         decode, one token: vector ALUs; a thread owns
 //                           4 adjacent dv columns of 16 state rows (16-byte loads)
+//   kvb_buffer_step_kernel  decode without a state: one workgroup per (b, one or two v-heads of a qk-head)
 //   kvb_verify_mfma_kernel  verify: matrix cores; a wave owns 32 dv columns (16 at d <= 64)
 //   kvb_flush_mfma_kernel   deferred state update, 16-bit inputs / d = 128: matrix cores on exact
 //                           16-bit pieces of the fp32 factor

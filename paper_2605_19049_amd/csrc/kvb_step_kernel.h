@@ -1,4 +1,4 @@
-// kvb_step_kernel: kvb_decode and kvb_decode_flush (and kvb_verify of a single draft), with its launch
+// kvb_step_kernel and kvb_buffer_step_kernel: kvb_decode and kvb_decode_flush (and kvb_verify of a single draft), with their launch
 // helpers.  Template code only; kvb_step_*.hip instantiate it per (input type, record type), so that they
 // compile side by side.
 #ifndef KVB_STEP_KERNEL_H
@@ -35,10 +35,10 @@ __device__ __forceinline__ float group_sum(float x)
 // workgroup applies the deferred update S <- gamma_f S0 + sum_{l<=f} Gamma_fl k_l^T u_l to
 // the state tile it already holds in registers and writes it back, which saves the second
 // kernel's re-read of the state.
-template <int D, typename TIn, typename TRec, int WREC, bool HAS_STATE, bool FUSE, bool STREAM, bool PAGED>
+template <int D, typename TIn, typename TRec, int WREC, bool FUSE, bool STREAM, bool PAGED>
 // (register budget: the 64-record decode variants sit at the edge of three workgroups per CU; hold them there,
 // and those with the matrix-core update, which would spread the state over accumulation registers)
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(HAS_STATE && (WREC == 64 || (FUSE && D == 128 && sizeof(TIn) == 2)) ? 3 : 1)))
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WREC == 64 || (FUSE && D == 128 && sizeof(TIn) == 2) ? 3 : 1)))
 void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg,
                                                       const StepArgs a)
 {
@@ -65,8 +65,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     constexpr int FS = 24;                               // halves per staged row: 16 records + padding (16-byte reads)
     // state loads issued before the fill is known (the 64-record window keeps the records first:
     // holding it across the state pass costs a workgroup per CU)
-    constexpr bool EARLY = HAS_STATE && WREC <= 32;
-    static_assert(!FUSE || HAS_STATE, "the fused update belongs to kvb_decode with a state");
+    constexpr bool EARLY = WREC <= 32;
 
     __shared__ __attribute__((aligned(16))) float sKs[D];  // -gamma k (state-row weights for accU)
     __shared__ __attribute__((aligned(16))) float sQs[D];  //  gamma q
@@ -172,7 +171,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
         const int l = rg + RPP * j;
         ur_raw[j] = load_raw4(ub + ru(l < f ? l : 0) * D + 4 * c4);
     }
-    if constexpr (HAS_STATE && !EARLY)
+    if constexpr (!EARLY)
         issue_state();
     __builtin_amdgcn_sched_barrier(0);
     // youngest memory operation of the wave: nothing waits for it before the very end
@@ -327,7 +326,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
             }
         }
     }
-    if constexpr (HAS_STATE && !EARLY) {
+    if constexpr (!EARLY) {
 #pragma unroll
         for (int p = 0; p < NPASS; ++p) {
             const int row = rg + RPP * p;
@@ -625,6 +624,201 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 }
 
 // ---------------------------------------------------------------------------
+// kvb_decode without a state (Sec. 3.4, Eq. 14): the buffer is all there is to read, so a workgroup of a single
+// v-head moves a few KB and lives on its chain of loads (slot, fill, records) and exchanges.  HB v-heads of a key
+// head share a workgroup: the keys are read and multiplied once for them, and their chains run side by side.
+// The records go in blocks of WREC: keys, decays and delta values of a block are requested together, one round
+// trip for each block that the fill reaches.
+// Rule (launch_buffer_step): two heads a workgroup as soon as that leaves one for every CU; below, the halves of
+// the chip that would stay idle are worth more.  Passes beyond the fill load a valid record and compute nothing.
+// 128 requests of 32 heads, fp16 records: 8 records 21.9 -> 14.4 us, 60 23.5 -> 21.5, 110 35.3 -> 33.1; fp32 records:
+// 21.3 -> 16.1, 32.2 -> 29.4, 48.9 -> 48.2; 32 requests, fp32 keys, 1..60 records: 12.6 -> 8.3; 8 requests (one head a
+// workgroup): 6.8 -> 6.4.
+// ---------------------------------------------------------------------------
+template <int D, typename TIn, typename TRec, int HB, bool PAGED>
+__global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot_arg, int32_t nu_arg, int32_t nblocks_arg,
+                                                             const StepArgs a)
+{
+    // (leading arguments: as in kvb_step_kernel, with the workgroups of a request in the place of its heads)
+    constexpr int LPR = D / 4;       // lanes covering one record with 4 elements each
+    constexpr int RPP = NT / LPR;    // delta-value rows per pass
+    constexpr int GL = D / 8;        // lanes sharing one key dot product (8 elements each)
+    constexpr int NG = NT / GL;      // keys per pass
+    constexpr int WREC = NG > 64 ? NG : 64;
+    constexpr int KP = WREC / NG, UP = WREC / RPP;
+    constexpr int NC = (KVB_MAX_CAP + WREC) / WREC * WREC;
+    static_assert(GL >= HB && HB * D <= NT, "a lane of each key group and a column of each head to a thread");
+
+    __shared__ float cK[HB][NC];     // Gamma_l (k.k_l) of record l
+    __shared__ float cQ[HB][NC];     // Gamma_l (q.k_l)
+    __shared__ float sQK;            // q.k of the token itself
+    __shared__ __attribute__((aligned(16))) float red[NW][HB][2][D];
+    __shared__ int sBlk[NW][MAX_BLOCKS];
+
+    const int tid = threadIdx.x;
+    const int lb = logical_block(nblocks_arg);
+    const int b = lb / nu_arg;
+    const int s = slot_arg[b];
+    __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
+    const int r = a.Hv / a.Hk;
+    const int per = (r + HB - 1) / HB;   // workgroups of a key head
+    const int hk = lb % nu_arg / per;
+    const int h0 = hk * r + lb % nu_arg % per * HB, hlast = hk * r + r - 1;
+    const int nh = min(HB, hlast - h0 + 1);
+    const int cap = a.cap;
+    if (s < 0 || s >= a.st.n_slots)
+        return;
+
+    const int rg = tid / LPR, c4 = tid % LPR;
+    const int grp = tid / GL, sub = tid % GL;
+    const int jw = min(sub, nh - 1);         // head whose weights this lane makes (lanes sub < nh write them)
+    const int jc = min(tid / D, nh - 1);     // head whose column tid % D this thread finishes
+    const float *Gbuf = a.st.buf_G;
+    const TIn *kb = static_cast<const TIn *>(a.st.buf_k);
+    TRec *ub = static_cast<TRec *>(a.st.buf_u);
+    const Out<TIn> out{a.out, a.out_wide != 0};
+    const int blk_id = load_block_id<PAGED>(a.st, s, tid % 64);
+
+    // loads that need only the request
+    const size_t nr_o = ((size_t)b * a.Hk + hk) * D + 8 * sub;
+    const Raw8<TIn> q_raw = load_raw8(static_cast<const TIn *>(a.q) + nr_o);
+    const Raw8<TIn> k_raw = load_raw8(static_cast<const TIn *>(a.k) + nr_o);
+    const TIn v_raw = static_cast<const TIn *>(a.v)[((size_t)b * a.Hv + h0 + jc) * D + tid % D];
+    const float bet = a.beta[(size_t)b * a.Hv + h0 + jc];
+    const float g_w = a.g[(size_t)b * a.Hv + h0 + jw];
+    const int f = a.st.fill[s] & FILL_MASK;
+    if (f + 1 > cap) {
+        if (tid == 0) {
+            if (a.st.status)
+                atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
+            if (a.advance)
+                publish_fill(&a.st.fill[s], nu_arg, f);
+        }
+        return;
+    }
+    const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[tid / 64], tid % 64, blk_id);
+    auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };            // row of record l in buf_k
+    auto ru = [&](int l, int j) { return pg.row(l, a.Hv, h0 + j); };   // of head h0 + j in buf_u / buf_G
+    // cumulative log decay of the new row, of head h0 + jw
+    const float Gc = (f > 0 ? Gbuf[ru(f - 1, jw)] : 0.0f) + g_w;
+
+    float q8[8], k8[8];
+    float4 accU[HB], accO[HB];
+#pragma unroll
+    for (int j = 0; j < HB; ++j)
+        accU[j] = accO[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    unpack8(q_raw, q8);
+    unpack8(k_raw, k8);
+    int ticket = 0;
+    for (int l0 = 0; l0 == 0 || l0 < f; l0 += WREC) {   // uniform
+        // raw bits from always-valid addresses: an index past the fill is clamped to record 0, its value ignored
+        Raw8<TIn> kl_raw[KP];
+        float Gl[KP];
+        Raw4<TRec> ur_raw[HB][UP];
+#pragma unroll
+        for (int p = 0; p < KP; ++p) {
+            const int l = l0 + grp + NG * p, lc = l < f ? l : 0;
+            kl_raw[p] = load_raw8(kb + rk(lc) * D + 8 * sub);
+            Gl[p] = Gbuf[ru(lc, jw)];
+        }
+#pragma unroll
+        for (int p = 0; p < UP; ++p) {
+            const int l = l0 + rg + RPP * p, lc = l < f ? l : 0;
+#pragma unroll
+            for (int j = 0; j < HB; ++j)
+                ur_raw[j][p] = load_raw4(ub + ru(lc, min(j, nh - 1)) * D + 4 * c4);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (l0 == 0 && a.advance && tid == 0)
+            ticket = take_ticket(&a.st.fill[s]);
+#pragma unroll
+        for (int p = 0; p < KP; ++p) {
+            const int l = l0 + grp + NG * p;
+            if (l0 + NG * p >= f)   // uniform: nothing of this pass is live
+                break;
+            float kx[8];
+            unpack8(kl_raw[p], kx);
+            float dkk = 0.0f, dq = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                dkk = fmaf(kx[e], k8[e], dkk);
+                dq = fmaf(kx[e], q8[e], dq);
+            }
+            dkk = group_sum<GL>(dkk);
+            dq = group_sum<GL>(dq);
+            if (sub < nh && l < f) {
+                const float w = expf(Gc - Gl[p]);
+                cK[sub][l] = w * dkk;
+                cQ[sub][l] = w * dq;
+            }
+        }
+        __syncthreads();   // (blocks write disjoint parts of cK, cQ)
+#pragma unroll
+        for (int p = 0; p < UP; ++p) {
+            const int l = l0 + rg + RPP * p;
+            if (l0 + RPP * p >= f)   // uniform
+                break;
+#pragma unroll
+            for (int j = 0; j < HB; ++j) {
+                const float4 u = unpack4(ur_raw[j][p]);
+                if (l < f) {
+                    fma4(accU[j], -cK[j][l], u);
+                    fma4(accO[j], cQ[j][l], u);
+                }
+            }
+        }
+    }
+    float dqk = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        dqk = fmaf(q8[e], k8[e], dqk);
+    dqk = group_sum<GL>(dqk);
+    if (tid == 0)
+        sQK = dqk;
+
+    // reduce over the row groups: shuffles inside the wave, LDS across waves
+#pragma unroll
+    for (int j = 0; j < HB; ++j) {
+#pragma unroll
+        for (int off = LPR; off < 64; off <<= 1) {
+            accU[j].x += __shfl_xor(accU[j].x, off);
+            accU[j].y += __shfl_xor(accU[j].y, off);
+            accU[j].z += __shfl_xor(accU[j].z, off);
+            accU[j].w += __shfl_xor(accU[j].w, off);
+            accO[j].x += __shfl_xor(accO[j].x, off);
+            accO[j].y += __shfl_xor(accO[j].y, off);
+            accO[j].z += __shfl_xor(accO[j].z, off);
+            accO[j].w += __shfl_xor(accO[j].w, off);
+        }
+        if (tid % 64 < LPR) {
+            *reinterpret_cast<float4 *>(&red[tid / 64][j][0][4 * (tid % 64)]) = accU[j];
+            *reinterpret_cast<float4 *>(&red[tid / 64][j][1][4 * (tid % 64)]) = accO[j];
+        }
+    }
+    __syncthreads();
+    if (tid < nh * D) {
+        const int col = tid % D;
+        float au = 0.0f, ao = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            au += red[w][jc][0][col];
+            ao += red[w][jc][1][col];
+        }
+        // the record as it is stored is what every later use reads, this token's output included
+        const TRec ur_new = from_f32<TRec>(bet * (to_f32(v_raw) + au));
+        ao = fmaf(sQK, to_f32(ur_new), ao);
+        out.put1(((size_t)b * a.Hv + h0 + jc) * D + col, a.scale * ao);
+        ub[ru(f, jc) * D + col] = ur_new;
+    }
+    if (tid < nh)   // (grp == 0, sub == tid)
+        a.st.buf_G[ru(f, jw)] = Gc;
+    if (h0 == hk * r && tid < D / 8)   // the threads that loaded the new k row store it
+        store_raw8(static_cast<TIn *>(a.st.buf_k) + rk(f) * D + 8 * sub, k_raw);
+    if (a.advance && tid == 0)
+        publish_if_last(&a.st.fill[s], ticket, nu_arg, f + 1);
+}
+
+// ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int WREC>
@@ -636,29 +830,49 @@ void launch_step_s(const StepArgs &a, int blocks, hipStream_t stream)
     if (a.threshold > 0) {
         if constexpr (D == 128) {
             if (st) {
-                LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, true, true);
+                LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, true);
                 return;
             }
         }
-        LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, true, false);
-        return;
-    }
-    if (!a.st.state) {
-        LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, false, false, false);
+        LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, false);
         return;
     }
     if constexpr (D == 128) {
         if (st) {
-            LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, false, true);
+            LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, false, true);
             return;
         }
     }
-    LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, false, false);
+    LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, false, false);
+}
+
+template <int D, typename TIn, typename TRec, int HB>
+void launch_buffer_step_h(const StepArgs &a, int B, hipStream_t stream)
+{
+    const int32_t nu = a.Hk * ((a.Hv / a.Hk + HB - 1) / HB);   // workgroups of a request
+    if (a.st.block_table)
+        launch(kvb_buffer_step_kernel<D, TIn, TRec, HB, true>, B * nu, stream, a.slot, nu, B * nu, a);
+    else
+        launch(kvb_buffer_step_kernel<D, TIn, TRec, HB, false>, B * nu, stream, a.slot, nu, B * nu, a);
+}
+
+template <int D, typename TIn, typename TRec>
+void launch_buffer_step(const StepArgs &a, int blocks, hipStream_t stream)
+{
+    const int B = blocks / a.Hv;
+    if (a.Hv > a.Hk && blocks >= 2 * 256)
+        launch_buffer_step_h<D, TIn, TRec, 2>(a, B, stream);
+    else
+        launch_buffer_step_h<D, TIn, TRec, 1>(a, B, stream);
 }
 
 template <int D, typename TIn, typename TRec>
 void launch_step_w(const StepArgs &a, int blocks, hipStream_t stream)
 {
+    if (!a.st.state) {
+        launch_buffer_step<D, TIn, TRec>(a, blocks, stream);
+        return;
+    }
     // Register window of buffered records.  For d = 128 the smallest tier that holds the
     // whole buffer is used; the smaller head sizes only carry the general (64 + tail) tier.
     if constexpr (D == 128) {

@@ -95,3 +95,20 @@ def test_verify_windows(d, in_dtype, rec_dtype, C, T):
         e = case(5, 2, 6, d, C, cap, T, in_dtype, seed=850 + C, block_size=block_size, rec_dtype=rec_dtype)
         say("verify windows, d=%d %s/%s C=%d T=%d: %s" % (d, in_dtype, rec_dtype, C, T, e))
         H.check(e, in_dtype, rec_dtype, "verify windows")
+
+
+@pytest.mark.parametrize("B, Hk, Hv, d, in_dtype, rec_dtype", [(45, 4, 12, 128, "f16", "f16"), (45, 4, 12, 128, "bf16", "f32"), (33, 4, 16, 64, "f32", "f32"),
+                                                                (130, 4, 4, 32, "bf16", "bf16"), (20, 1, 2, 128, "f16", "f32"), (20, 2, 10, 32, "f32", "f32")])
+@pytest.mark.parametrize("block_size", [None, 8])
+def test_decode_from_the_buffer_alone(B, Hk, Hv, d, in_dtype, rec_dtype, block_size):
+    """One and two heads to a workgroup, head ratios that two does not divide, fills around each block of records."""
+    Lmax, cap = (127, 128) if d == 128 else (64, 72)
+    edges = [0, 1, 7, 8, 16, 17, 63, 64] + ([65, 80, 100, 127] if d == 128 else [])
+    lens = np.resize(np.array(edges, np.int32), B)
+    e = _direct_case(B=B, Hk=Hk, Hv=Hv, d=d, Lmax=Lmax, cap=cap, in_dtype=in_dtype, seed=870 + B, lens=lens,
+                     rec_dtype=rec_dtype, out_dtype=rec_dtype, block_size=block_size)
+    say("buffer alone, B=%d heads %d/%d d=%d %s/%s: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((B, Hk, Hv, d, in_dtype, rec_dtype) + e))
+    # (the state folded afterwards is the flush tests' matter.  Its error is measured against an RMS that a third of
+    # the requests, with 0 or 1 record, pull down: fp32 sums of 65 records may stand 65 * 2^-24 * max / RMS = 4e-6 *
+    # max / RMS off, above 1e-5 here)
+    H.check(e[:3], in_dtype, rec_dtype, "buffer alone")
