@@ -63,7 +63,7 @@ def parse():
 
 def kernel_name(w, fused, types):
     win = 16 if w.cap <= 16 else 32 if w.cap <= 32 else 64
-    return "kvb_step_kernel<%d,%s,rec=%s,TM=1,W=%d,state%s> (%s)" % (
+    return "kvb_step_kernel<%d,%s,rec=%s,W=%d%s> (%s)" % (
         w.dk, types[0], types[1], win, ",fused" if fused else "", "kvb_decode_flush" if fused else "kvb_decode")
 
 

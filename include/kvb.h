@@ -56,8 +56,8 @@ extern "C" {
  * allowed rec_dtype / out_dtype) is the pair the kernels are built and measured for: matrix-
  * instruction kernels for kvb_verify, kvb_verify_tree, kvb_flush and kvb_direct, the streaming
  * decode kernel for kvb_decode / kvb_decode_flush.  KVB_F32 inputs at any head size, and
- * d = 32 or 64 with any input type, run vector-ALU kernels (kvb_direct: the fp32 matrix
- * instruction): same results, and kvb_direct is limited to 64 tokens there. */
+ * d = 32 or 64 with any input type, run on the fp32 matrix instruction (single-token decoding:
+ * the vector ALU): same results, and kvb_direct is limited to 64 tokens there. */
 
 #define KVB_MAX_CAP        128 /* largest `cap` (the paper buffers at most d records, Sec. 3.4) */
 #define KVB_MAX_DRAFTS       8 /* largest T of kvb_verify (Sec. 4.2 sweeps up to 8)             */
