@@ -418,8 +418,13 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             // a buffered key is seen by every draft; a new one by its descendants (q rows: and by itself)
             const bool above = n >= f && ((ancRow[v] >> min(n - f, 31)) & 1);
             const bool ok = i < T && n < nrec && (n < f || above || (isq && n - f == i));
-            const float w = expf(GcRow[v] - Gkey);
-            o[v] = ok ? (isq ? w : -w) * c1[v] : 0.0f;
+            if constexpr (CHAINS) {   // (what is masked stays out whatever its product is, as on the vector ALU)
+                const float w = expf(GcRow[v] - Gkey);
+                o[v] = ok ? (isq ? w : -w) * c1[v] : 0.0f;
+            } else {
+                const float w = ok ? expf(GcRow[v] - Gkey) : 0.0f;
+                o[v] = (isq ? w : -w) * c1[v];
+            }
         }
         *reinterpret_cast<float4 *>(&cW[n][4 * lq]) = make_float4(o[0], o[1], o[2], o[3]);
     };
