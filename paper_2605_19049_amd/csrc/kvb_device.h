@@ -308,23 +308,32 @@ __device__ __forceinline__ void fma4(float4 &acc, float c, const float4 &x)
     acc.w = fmaf(c, x.w, acc.w);
 }
 
-// The workgroups of one request share fill[slot].  Each reads it (low 16 bits)
-// when it starts and takes a ticket (bits 16..) when it has finished; the
-// workgroup holding the last ticket knows every other one has read the word and
-// stores the new plain value.  Relaxed ordering is enough and matters: a
-// workgroup's read of the word has long completed when it takes its ticket
-// (its value fed address computations), the store depends on the ticket's
-// return value, and nothing else is communicated through the word.  Acquire /
-// release ordering at device scope would make every workgroup write back and
-// invalidate its L2, which costs more than the kernel's whole memory traffic.
+// The workgroups of one request share fill[slot].  Every wave reads it (low 16 bits) when it
+// starts, and its value decides a branch; then comes a barrier, and behind it the workgroup's
+// first thread takes a ticket (bits 16..), so a ticket says that ALL waves of its workgroup have
+// read the word.  The workgroup holding the last ticket therefore knows that no read is
+// outstanding and stores the new plain value.  (Without the barrier wave 0 could publish while
+// another wave of the workgroup, or of one that has its ticket already, had yet to read: that
+// wave would take the new fill for the old one.)  The barrier is bare: it waits for the
+// waves, not for their memory operations.  Relaxed ordering is enough and matters: the reads have
+// completed when the ticket is taken (their values decided branches), the store depends on the
+// ticket's return value, and nothing else is communicated through the word.  Acquire / release
+// ordering at device scope would make every workgroup write back and invalidate its L2, which
+// costs more than the kernel's whole memory traffic.
 //
 // The ticket is taken once the workgroup's loads are in flight (take_ticket), so that its
-// round trip overlaps the streaming, and is looked at only at the very end.
+// round trip overlaps the streaming, and is looked at only at the very end.  take_ticket and
+// publish_fill hold the barrier: every thread of the workgroup calls them.
+__device__ __forceinline__ int take_ticket_read(int32_t *word)   // every wave is known to have read the word
+{
+    return threadIdx.x == 0 ? __hip_atomic_fetch_add(word, TICKET_ONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+}
 __device__ __forceinline__ int take_ticket(int32_t *word)
 {
-    return __hip_atomic_fetch_add(word, TICKET_ONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_barrier();
+    return take_ticket_read(word);
 }
-__device__ __forceinline__ void publish_if_last(int32_t *word, int ticket, int nwg, int new_fill)
+__device__ __forceinline__ void publish_if_last(int32_t *word, int ticket, int nwg, int new_fill)   // thread 0
 {
     // Opaque to the optimiser: otherwise the shift below is hoisted next to the atomic and
     // the wave waits there for the ticket (and for every load it issued before it).
@@ -334,7 +343,9 @@ __device__ __forceinline__ void publish_if_last(int32_t *word, int ticket, int n
 }
 __device__ __forceinline__ void publish_fill(int32_t *word, int nwg, int new_fill)
 {
-    publish_if_last(word, take_ticket(word), nwg, new_fill);
+    const int ticket = take_ticket(word);
+    if (threadIdx.x == 0)
+        publish_if_last(word, ticket, nwg, new_fill);
 }
 
 __device__ __forceinline__ void store_raw8(float *p, const Raw8<float> &r)

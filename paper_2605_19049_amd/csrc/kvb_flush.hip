@@ -68,7 +68,7 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     // (no state: a KV-only context, Sec. 3.4 -- the call then only commits accepted drafts)
     const bool do_flush = a.st.state != nullptr && m >= a.threshold && m > 0;
     if (!do_flush) {
-        if (m != f && tid == 0)   // fill only moves when something was accepted
+        if (m != f)   // fill only moves when something was accepted
             publish_fill(&a.st.fill[s], a.Hv, m);
         return;
     }
@@ -110,9 +110,7 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
         for (int v = 0; v < 4; ++v)
             copy_row<CT>(sreg[rt][v], sp + (size_t)(RW + RT * (4 * lq + v) + rt) * D);
     __builtin_amdgcn_sched_barrier(0);
-    int ticket = 0;
-    if (tid == 0)
-        ticket = take_ticket(&a.st.fill[s]);
+    const int ticket = take_ticket(&a.st.fill[s]);
 
     // the sums, apart from the state, so that nothing waits for it before the end
     f32x4_t acc[RT][CT];
@@ -232,7 +230,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     }
     const bool do_flush = a.st.state != nullptr && m >= a.threshold && m > 0;
     if (!do_flush) {
-        if (m != f && tid == 0)
+        if (m != f)
             publish_fill(&a.st.fill[s], a.Hv, m);
         return;
     }
@@ -279,9 +277,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 #pragma unroll
     for (int rt = 0; rt < WIN; ++rt)
         issue_state(rt);
-    int ticket = 0;
-    if (tid == 0)
-        ticket = take_ticket(&a.st.fill[s]);
+    const int ticket = take_ticket(&a.st.fill[s]);
 
     // B operands of a chunk: piece p of Gamma_l u_l[col2 + t], 8 records to a lane
     uint4 bop[2][NP];

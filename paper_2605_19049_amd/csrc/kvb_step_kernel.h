@@ -139,12 +139,10 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     const float gnew = a.g[(size_t)b * a.Hv + h], bet = a.beta[(size_t)b * a.Hv + h];
     const int f = a.st.fill[s] & FILL_MASK;
     if (f + 1 > cap) {
-        if (tid == 0) {
-            if (a.st.status)
-                atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
-            if (a.advance)
-                publish_fill(&a.st.fill[s], a.Hv, f);
-        }
+        if (tid == 0 && a.st.status)
+            atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
+        if (a.advance)
+            publish_fill(&a.st.fill[s], a.Hv, f);
         return;
     }
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[tid / 64], tid % 64, blk_id);
@@ -175,8 +173,9 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
         issue_state();
     __builtin_amdgcn_sched_barrier(0);
     // youngest memory operation of the wave: nothing waits for it before the very end
+    // (EARLY: behind the barrier that it needs anyway, below)
     int ticket = 0;
-    if (a.advance && tid == 0)
+    if (!EARLY && a.advance)
         ticket = take_ticket(&a.st.fill[s]);
 
     // ---- 3. decayed dot products of the new rows with every earlier key ----
@@ -207,6 +206,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
             // the state rows are consumed first, in the order they were issued; the records
             // (younger loads) are not touched before the last state row has been used
             __syncthreads();
+            if (a.advance)
+                ticket = take_ticket_read(&a.st.fill[s]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int p = 0; p < NPASS; ++p) {
@@ -688,12 +689,10 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
     const float g_w = a.g[(size_t)b * a.Hv + h0 + jw];
     const int f = a.st.fill[s] & FILL_MASK;
     if (f + 1 > cap) {
-        if (tid == 0) {
-            if (a.st.status)
-                atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
-            if (a.advance)
-                publish_fill(&a.st.fill[s], nu_arg, f);
-        }
+        if (tid == 0 && a.st.status)
+            atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
+        if (a.advance)
+            publish_fill(&a.st.fill[s], nu_arg, f);
         return;
     }
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[tid / 64], tid % 64, blk_id);
@@ -729,7 +728,7 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
                 ur_raw[j][p] = load_raw4(ub + ru(lc, min(j, nh - 1)) * D + 4 * c4);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (l0 == 0 && a.advance && tid == 0)
+        if (l0 == 0 && a.advance)
             ticket = take_ticket(&a.st.fill[s]);
 #pragma unroll
         for (int p = 0; p < KP; ++p) {

@@ -1,0 +1,112 @@
+"""Orderings that the kernels depend on and that no result shows reliably, checked on the machine code of the built
+library along every path of every kernel (no GPU needed)."""
+import os
+import re
+import shutil
+import subprocess
+from concurrent.futures import ProcessPoolExecutor
+
+import pytest
+
+from paper_2605_19049_amd import kvb
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+TARGET = re.compile(r"<[^>+]*\+0x([0-9a-f]+)>")
+
+
+def code_objects(tmp):
+    """The gfx950 code objects of libkvb.so, disassembled: one list of lines each."""
+    lib = os.path.join(tmp, "libkvb.so")
+    shutil.copyfile(kvb.LIB_PATH, lib)
+    subprocess.run([OBJDUMP, "--offloading", lib], check=True, stdout=subprocess.DEVNULL, cwd=tmp)
+    return sorted(os.path.join(tmp, f) for f in os.listdir(tmp) if f.endswith("gfx950"))
+
+
+def kernels(path):
+    """(name, [instruction text], [address]) of every kernel of a code object."""
+    text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", path], check=True, stdout=subprocess.PIPE, text=True).stdout
+    name, ins, adr, base = None, [], [], 0
+    for line in text.splitlines():
+        if line.endswith(">:"):
+            if name:
+                yield name, ins, adr
+            name, ins, adr, base = line.split("<")[1][:-2], [], [], int(line.split()[0], 16)
+        elif line.startswith("\t") and "//" in line:   # (not the mark of skipped padding)
+            body, _, tail = line.partition("//")
+            body = body.strip()
+            t = TARGET.search(tail)
+            if t and body.startswith(("s_branch", "s_cbranch")):
+                body = "%s -> %d" % (body.split()[0], base + int(t.group(1), 16))
+            ins.append(body)
+            adr.append(int(tail.split(":")[0], 16))
+    if name:
+        yield name, ins, adr
+
+
+def blocks(ins, adr):
+    """Basic blocks as (first, last + 1, successors by block number); block 0 is the entry."""
+    at = {a: i for i, a in enumerate(adr)}
+    starts, target = {0}, {}
+    for i, x in enumerate(ins):
+        if "->" in x:
+            target[i] = at[int(x.split()[-1])]
+            starts.update((target[i], i + 1))
+        elif x.startswith("s_endpgm"):
+            starts.add(i + 1)
+        assert not x.startswith(("s_setpc", "s_swappc")), x
+    starts = sorted(s for s in starts if s < len(ins))
+    number = {s: n for n, s in enumerate(starts)}
+    res = []
+    for n, s in enumerate(starts):
+        end = starts[n + 1] if n + 1 < len(starts) else len(ins)
+        last, succ = ins[end - 1], []
+        if "->" in last:
+            succ.append(number[target[end - 1]])
+        if not last.startswith(("s_branch", "s_endpgm")) and end < len(ins):
+            succ.append(number[end])
+        res.append((s, end, succ))
+    return res
+
+
+def unordered_tickets(ins, adr):
+    """Ticket atomics that some path reaches without a workgroup barrier."""
+    bl = blocks(ins, adr)
+    bad, seen, todo = [], {0}, [0]
+    while todo:
+        first, end, succ = bl[todo.pop()]
+        for i in range(first, end):
+            if ins[i].startswith("s_barrier"):
+                break
+            if ins[i].startswith("global_atomic_add"):
+                bad.append(ins[i])
+        else:
+            for s in succ:
+                if s not in seen:
+                    seen.add(s)
+                    todo.append(s)
+    return bad
+
+
+def scan(path):
+    res = []
+    for name, ins, adr in kernels(path):
+        res.append((name, len(ins), any(x.startswith("global_atomic_add") for x in ins), unordered_tickets(ins, adr)))
+    return res
+
+
+@pytest.fixture(scope="module")
+def scanned(tmp_path_factory):
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no llvm-objdump")
+    files = code_objects(str(tmp_path_factory.mktemp("isa")))
+    with ProcessPoolExecutor(4) as pool:
+        return [r for one in pool.map(scan, files) for r in one]
+
+
+def test_tickets_follow_a_barrier(scanned):
+    """Each wave reads fill[slot] for itself, and the workgroup with the last ticket replaces it: a ticket may only be
+    taken when every wave of the workgroup has read.  The barrier stands behind the branch on the value read."""
+    with_ticket = [r for r in scanned if r[2]]
+    assert len(with_ticket) > 100, len(with_ticket)
+    bad = [(r[0], r[3]) for r in with_ticket if r[3]]
+    assert not bad, "%d kernels, e.g. %s" % (len(bad), bad[0])
