@@ -118,6 +118,161 @@ __device__ __forceinline__ void settle(f32x4_t &x, f32x4_t &y)
     asm volatile("s_nop 7" : "+v"(x), "+v"(y));
 }
 
+// One step of a 16 x 16 Gram tile in A-form (rows of block d against rows of block e): 16 bytes of row 16 e + c16 and of
+// row 16 d + c16; fp32: contraction slot lq of instruction v stands for element 4 lq + v on both sides.
+template <typename TIn>
+__device__ __forceinline__ f32x4_t gram_step(const u32x4_t &row, const u32x4_t &own, f32x4_t c)
+{
+    if constexpr (sizeof(TIn) == 2) {
+        c = mfma16x32<TIn>(__builtin_bit_cast(uint4, row), __builtin_bit_cast(uint4, own), c);
+    } else {
+        const f32x4_t x = __builtin_bit_cast(f32x4_t, row), y = __builtin_bit_cast(f32x4_t, own);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[v], y[v], c, 0, 0, 0);
+    }
+    return c;
+}
+
+// ---------------------------------------------------------------------------
+// Contexts whose result is not finite.
+//
+// The kernels below multiply whole 16 x 16 tiles, zeros above the diagonal included, and those for 16-bit inputs
+// cut fp32 values into 16-bit pieces.  For finite values in range that changes nothing.  But 0 * Inf and the second
+// piece of Inf are NaN, so an infinity or a NaN in one token's key or value would reach earlier tokens, an infinite
+// value would become NaN, and a fp16 piece has no value beyond 65504 (queries and keys need not be normalised, and a
+// fp32 delta value may be larger).  All of these end in an output that is not finite: an output tile sums over the
+// whole diagonal tile of delta values, and whatever an infinity meets stays infinite or becomes NaN.  So a wave whose
+// outputs are all finite is done, and one that has produced anything else solves its columns again with this
+// function, where a row sees exactly the rows before it:
+//     u_i = beta_i ( v_i - sum_{l<i} Gamma_il (k_i.k_l) u_l )     o_i = sum_{l<=i} Gamma_il (q_i.k_l) u_l
+// with fp32 products: Gram tiles and the products with earlier blocks on the matrix cores (every entry of those tiles
+// belongs to the sum), the 16 rows of a diagonal block one after the other.  Nothing is staged: keys and queries come
+// from the inputs again, earlier delta values from the records, which the same lane has written.  A wave needs nothing
+// from the others, so this is no barrier's business.
+// col0: the first of the lane's NC adjacent columns; sG, sB: cumulative log decays and betas of the context; ru: row of
+// a record in buf_u.
+// ---------------------------------------------------------------------------
+template <int D, int NC, typename TIn, typename TRec, typename RowOf>
+__device__ __forceinline__ void solve_by_token(const DirectArgs &a, int b, int h, int L, int col0, const float *sG, const float *sB,
+                                               const RowOf &ru, int lane)
+{
+    constexpr int EPC = 16 / sizeof(TIn);   // elements of 16 bytes
+    // (opaque: nothing computed for the kernel's own work stays in a register for this)
+    asm volatile("" : "+v"(lane), "+v"(col0), "+s"(b), "+s"(h), "+s"(L));
+    const int c16 = lane % 16, lq = lane / 16;
+    const int hk = h / (a.Hv / a.Hk);
+    const TIn *kbase = static_cast<const TIn *>(a.k) + ((size_t)b * a.Lmax * a.Hk + hk) * D;
+    const TIn *qbase = static_cast<const TIn *>(a.q) + ((size_t)b * a.Lmax * a.Hk + hk) * D;
+    const TIn *vbase = static_cast<const TIn *>(a.v) + ((size_t)b * a.Lmax * a.Hv + h) * D + col0;
+    const uint32_t qk_stride = (uint32_t)a.Hk * D, v_stride = (uint32_t)a.Hv * D;
+    const Out<TIn> out{a.out, a.out_wide != 0};
+    const size_t outp = (((size_t)b * a.Lmax) * a.Hv + h) * D + col0;
+    TRec *up = static_cast<TRec *>(a.st.buf_u) + col0;
+#pragma unroll 1
+    for (int d = 0; 16 * d < L; ++d) {
+        const int i = 16 * d + c16;   // this lane's row of the tiles in A-form
+        const float gi = sG[i];
+        const uint32_t own = (uint32_t)min(i, L - 1) * qk_stride + EPC * lq;
+        f32x4_t acc[NC], o[NC];   // B-form: rows 16 d + 4 lq + v
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            o[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                acc[c][v] = to_f32(vbase[(uint32_t)min(16 * d + 4 * lq + v, L - 1) * v_stride + c]);
+        }
+        auto tiles = [&](int e, f32x4_t &n, f32x4_t &m) {   // -Gamma (k.k) below the diagonal, Gamma (q.k) up to it
+            const uint32_t row = (uint32_t)min(16 * e + c16, L - 1) * qk_stride + EPC * lq;
+            n = m = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1   // (few registers: this must not cost the kernel anything)
+            for (int o = 0; o < D; o += 4 * EPC) {
+                const u32x4_t kr = *reinterpret_cast<const u32x4_t *>(kbase + row + o);
+                n = gram_step<TIn>(kr, *reinterpret_cast<const u32x4_t *>(kbase + own + o), n);
+                m = gram_step<TIn>(kr, *reinterpret_cast<const u32x4_t *>(qbase + own + o), m);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int l = 16 * e + 4 * lq + v;
+                const float w = expf(gi - sG[l]);
+                n[v] = i < L && l < i ? -w * n[v] : 0.0f;
+                m[v] = i < L && l <= i ? w * m[v] : 0.0f;
+            }
+        };
+        f32x4_t n, m;
+#pragma unroll 1
+        for (int e = 0; e < d; ++e) {
+            tiles(e, n, m);
+            f32x4_t u[NC];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+                    u[c][v] = to_f32(up[ru(16 * e + 4 * lq + v) * D + c]);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                acc[c] = mm16(n, u[c], acc[c]);
+                o[c] = mm16(m, u[c], o[c]);
+            }
+        }
+        tiles(d, n, m);
+        // the rows of the block: row 4 g + x is held by the lanes lq = g, entry (row, 4 g + x) of a tile in A-form by
+        // lane 16 g + row
+        f32x4_t ub[NC];
+#pragma unroll 1
+        for (int g = 0; g < 4; ++g) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                float nc[4], mc[4];   // column 4 g + x, of the lane's own rows
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    nc[v] = __shfl(n[x], 16 * g + 4 * lq + v);
+                    mc[v] = __shfl(m[x], 16 * g + 4 * lq + v);
+                }
+                const float beta = sB[16 * d + 4 * g + x];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    // the record as it is stored is what every later use reads
+                    const float u = __shfl(rounded_to<TRec>(beta * acc[c][x]), 16 * g + c16);
+                    if (lq == g)
+                        ub[c][x] = u;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        if (4 * lq + v > 4 * g + x)
+                            acc[c][v] = fmaf(nc[v], u, acc[c][v]);
+                        if (4 * lq + v >= 4 * g + x)
+                            o[c][v] = fmaf(mc[v], u, o[c][v]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = 16 * d + 4 * lq + v;
+            if (row < L) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    out.put1(outp + (uint32_t)row * v_stride + c, a.scale * o[c][v]);
+                    store1(up + ru(row) * D + c, ub[c][v]);
+                }
+            }
+        }
+    }
+}
+// The largest magnitude so far, NaN once there was one.
+__device__ __forceinline__ float largest(float so_far, const f32x4_t &x)
+{
+    auto max3 = [](float a, float b, float c) {   // (v_maximum3_f32, which hands NaN on)
+        return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, __builtin_fabsf(b)), __builtin_fabsf(c));
+    };
+    return max3(max3(so_far, x[0], x[1]), x[2], x[3]);
+}
+__device__ __forceinline__ bool all_finite(float largest)
+{
+    // (as bits: the compiler turned "< Inf" into "!= Inf", which NaN passes)
+    return __all(__float_as_uint(largest) < 0x7F800000u);
+}
+
 // ---------------------------------------------------------------------------
 // Pieces.  A fp32 value x is cut into NP values of the 16-bit input type, x = x_1 + ... + x_NP
 // (+ a remainder below 2^-24 |x| for three bf16 pieces, 2^-22 |x| for two fp16 pieces), each
@@ -645,6 +800,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     f32x4_t ukeep[LONG && RECUT ? NB : 1][2];
     const size_t outp = (((size_t)b * Lmax) * a.Hv + h) * D;
     TRec *up = static_cast<TRec *>(a.st.buf_u);
+    float big = 0.0f;   // largest output
 #pragma unroll
     for (int d = 0; d < NB; ++d) {
         if (d < nb) {   // uniform
@@ -698,6 +854,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                 for (int c = 0; c < 2; ++c)
                     o[c] = mm16_pieces<TP, NP, NPU>(mp, upc[e][c], o[c]);
             }
+            big = largest(largest(big, o[0]), o[1]);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int i = 16 * d + 4 * lq + v;
@@ -962,6 +1119,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                         }
                     }
                     settle(o1[e][0], o1[e][1]);
+                    big = largest(largest(big, o1[e][0]), o1[e][1]);
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int i = LM + 16 * e + 4 * lq + v;
@@ -973,6 +1131,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
             }
         }
     }
+    if (!all_finite(big))
+        solve_by_token<D, 2, TIn, TRec>(a, b, h, L, col2, sG, sB, ru, lane);
     if (h == 0 && tid == 0)
         a.st.fill[s] = L;
 }
@@ -995,18 +1155,8 @@ __device__ __forceinline__ f32x4_t gram_rows(const TIn *rows, const u32x4_t (&ow
 {
     f32x4_t c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int st = 0; st < NST; ++st) {
-        const u32x4_t av = *reinterpret_cast<const u32x4_t *>(rows + (D / NST) * st + (D / NST / 4) * lq);
-        if constexpr (sizeof(TIn) == 2) {
-            c = mfma16x32<TIn>(__builtin_bit_cast(uint4, av), __builtin_bit_cast(uint4, own[st]), c);
-        } else {   // k = 16 st + 4 lq + v on both sides
-            const f32x4_t x = __builtin_bit_cast(f32x4_t, av), y = __builtin_bit_cast(f32x4_t, own[st]);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0], y[0], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1], y[1], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[2], y[2], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[3], y[3], c, 0, 0, 0);
-        }
-    }
+    for (int st = 0; st < NST; ++st)
+        c = gram_step<TIn>(*reinterpret_cast<const u32x4_t *>(rows + (D / NST) * st + (D / NST / 4) * lq), own[st], c);
     if constexpr (sizeof(TIn) == 4)
         asm volatile("s_nop 10" : "+v"(c));   // (settled, as in settle() above; 11 wait states for the fp32 instruction)
     return c;
@@ -1204,6 +1354,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2
         f32x4_t U[NB][NC];
         const size_t outp = (((size_t)b * Lmax) * a.Hv + h) * D;
         TRec *up = static_cast<TRec *>(a.st.buf_u);
+        float big = 0.0f;   // largest output
 #pragma unroll
         for (int d = 0; d < NB; ++d) {
             if (d < nb) {   // uniform
@@ -1241,6 +1392,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2
                         U[d][c] = round_all(mm16(tile(tD[d][lane]), round_all(U[d][c]), acc[c]));
                     }
                     o[c] = mm16(mm, U[d][c], o[c]);
+                    big = largest(big, o[c]);
                 }
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
@@ -1258,6 +1410,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2
                 }
             }
         }
+        if (!all_finite(big))
+            solve_by_token<D, NC, TIn, TRec>(a, b, h, L, col0, sG, sB, ru, lane);
     }
     if (h == 0 && tid == 0)
         a.st.fill[s] = L;

@@ -1,0 +1,137 @@
+"""Infinities, NaN and values beyond the range of fp16: a result is what the formulas give token by token and element by
+element, so a bad token reaches nothing that does not depend on it.
+
+The oracle here is the chunkwise form (App. A.1, Eq. 16) in fp64 with every sum over exactly the terms that the formula
+names; what has to agree is which elements are finite, +Inf, -Inf or NaN, and the finite ones to the usual bound.
+"""
+import numpy as np
+import pytest
+import torch
+
+import harness as H
+from harness import oracle
+from paper_2605_19049_amd import synth
+from test_gpu_parity import say
+
+pytestmark = pytest.mark.gpu
+
+TYPES = [("bf16", "f32"), ("f16", "f32"), ("bf16", "bf16"), ("f16", "f16")]
+OTHERS = [(d, i, r) for d in (32, 64) for i, r in TYPES + [("f32", "f32")]] + [(128, "f32", "f32")]
+
+
+def as_stored(x, rec_dtype):
+    return torch.from_numpy(np.asarray(x)).to(torch.float32).to(H.TORCH_DT[rec_dtype]).double().numpy()
+
+
+def dot(a, b):
+    """a [n, d] . b [m, d] -> [n, m], every product by itself."""
+    return (a[:, None, :] * b[None, :, :]).sum(-1)
+
+
+def rows(S0, rec, q, k, v, g, beta, scale, rec_dtype):
+    """One head: new tokens after the records rec = (k [f,d], u [f,d], G [f]) on the state S0 (None: no state).
+    Returns o [T,d] and all records."""
+    K, U, G = rec
+    f, o = len(G), []
+    for i in range(len(g)):
+        G = np.append(G, (G[-1] if len(G) else 0.0) + g[i])
+        w = np.exp(G[-1] - G)
+        acc, out = v[i].copy(), np.zeros_like(v[i])
+        if S0 is not None:
+            acc = acc - (np.exp(G[-1]) * k[i][:, None] * S0).sum(0)
+            out = (np.exp(G[-1]) * q[i][:, None] * S0).sum(0)
+        if len(K):
+            acc = acc - ((w[:-1] * dot(k[i:i + 1], K)[0])[:, None] * U).sum(0)
+            out = out + ((w[:-1] * dot(q[i:i + 1], K)[0])[:, None] * U).sum(0)
+        K = np.vstack([K, k[i:i + 1]])
+        U = np.vstack([U, as_stored(beta[i] * acc, rec_dtype)[None]])
+        o.append(scale * (out + (q[i] * k[i]).sum() * U[-1]))
+    return np.array(o).reshape(len(g), -1), (K, U, G)
+
+
+def kind(x):
+    """0 finite, 1 +Inf, 2 -Inf, 3 NaN."""
+    x = np.asarray(x)
+    return np.where(np.isnan(x), 3, np.where(x == np.inf, 1, np.where(x == -np.inf, 2, 0)))
+
+
+def compare(got, want, in_dtype, rec_dtype, what):
+    k_got, k_want = kind(got), kind(want)
+    assert np.array_equal(k_got, k_want), "%s: %d of %d elements are finite / infinite / NaN in the wrong place" % (
+        what, (k_got != k_want).sum(), k_got.size)
+    m = k_want == 0
+    if m.any():
+        e = H.rel_err(np.asarray(got)[m], np.asarray(want)[m])
+        say("%s: %d finite of %d, rel err %.2e" % (what, m.sum(), m.size, e))
+        assert e < H.tol_for(in_dtype, rec_dtype), (what, e)
+
+
+def empty(d):
+    return np.zeros((0, d)), np.zeros((0, d)), np.zeros(0)
+
+
+@pytest.fixture(autouse=True)
+def quiet():
+    with np.errstate(all="ignore"):
+        yield
+
+
+def poison(tok, b, what, j, d):
+    x = {"v": (b, j, 0, d // 3), "k": (b, j, 0, 5), "q": (b, j, 0, 5)}.get(what[0])
+    tok[what[0]][x] = {"inf": np.inf, "-inf": -np.inf, "nan": np.nan}[what[1]]
+
+
+DIRECT = [(d, i, r, L) for d, i, r in OTHERS for L in (64,)] + [(128, i, r, L) for i, r in TYPES for L in (64, 100)]
+
+
+@pytest.mark.parametrize("d, in_dtype, rec_dtype, Lmax", DIRECT)
+def test_direct_bad_tokens(d, in_dtype, rec_dtype, Lmax):
+    """A bad value or key changes its own token and later ones; a bad query its own output alone."""
+    kinds = [(x, y) for x in "vk" for y in ("inf", "-inf", "nan")] + [("q", "nan")]
+    at = [21, 37, 6, 20, 41, 59, 33] if Lmax == 64 else [21, 70, 90, 20, 77, 98, 69]
+    B, Hk, Hv = len(kinds) + 1, 1, 2
+    rng = np.random.default_rng(900 + d + Lmax)
+    tok = synth.token_stream(rng, B, Lmax, Hk, Hv, d, d, in_dtype)
+    for b, w in enumerate(kinds):
+        poison(tok, b, w, at[b], d)
+    lens = np.array([Lmax, Lmax - 7, Lmax, Lmax - 3, Lmax, Lmax, 40 if Lmax == 64 else 71, Lmax], np.int32)
+    lay = H.Layer(B, Hk, Hv, d, d, cap=Lmax, in_dtype=in_dtype, with_state=False, rec_dtype=rec_dtype)
+    out = lay.new_out(B, Lmax, Hv, d, fill=0.0)
+    lay.direct(H.dev(lens), Lmax, H.upload_tokens(tok, in_dtype), out)
+    torch.cuda.synchronize()
+    got = H.host(out)
+    for b in range(B):
+        n = lens[b]
+        u_got = lay.u_records(b, 0, n)
+        for h in range(Hv):
+            o, (_, u, _) = rows(None, empty(d), *(tok[x].astype(np.float64)[b, :n, 0 if x in "qk" else h] for x in ("q", "k", "v", "g", "beta")),
+                                1.0, rec_dtype)
+            name = "direct d=%d %s/%s Lmax=%d, %s, head %d" % (d, in_dtype, rec_dtype, Lmax, kinds[b] if b < len(kinds) else "clean", h)
+            compare(got[b, :n, h], o, in_dtype, rec_dtype, name + ", outputs")
+            compare(u_got[h], u, in_dtype, rec_dtype, name + ", records")
+
+
+@pytest.mark.parametrize("rec_dtype", ["f32", "f16"])
+@pytest.mark.parametrize("Lmax", [9, 40, 64, 100])
+def test_direct_beyond_the_range_of_fp16(rec_dtype, Lmax):
+    """Weighted q.k products and (with fp32 records) delta values above 65504 from fp16 inputs below it."""
+    rng = np.random.default_rng(910 + Lmax)
+    B, Hk, Hv, d = 5, 2, 4, 128
+    tok = synth.token_stream(rng, B, Lmax, Hk, Hv, d, d, "f16")
+    tok["q"] = synth.round_to_fp16(70000.0 * tok["k"])
+    if rec_dtype == "f32":
+        tok["v"] = synth.round_to_fp16(np.clip(30000.0 * tok["v"], -65504, 65504))
+        tok["beta"][:] = 1.0
+    lens = np.array([Lmax, Lmax - 1, Lmax // 2, 1, Lmax], np.int32)
+    lay = H.Layer(B, Hk, Hv, d, d, cap=Lmax, in_dtype="f16", with_state=False, rec_dtype=rec_dtype)
+    out = lay.new_out(B, Lmax, Hv, d, fill=float("nan"))
+    lay.direct(H.dev(lens), Lmax, H.upload_tokens(tok, "f16"), out)
+    torch.cuda.synchronize()
+    o_ref, u_ref, _ = oracle.kvb_direct_expected(tok["q"], tok["k"], tok["v"], tok["g"], tok["beta"], lens)
+    ok = ~np.isnan(o_ref)
+    u_got = np.stack([lay.u_records(b, 0, Lmax) for b in range(B)]).transpose(0, 2, 1, 3)
+    if rec_dtype == "f32" and Lmax > 9:
+        assert np.abs(u_ref[ok]).max() > 65520
+    e = H.rel_err(H.host(out)[ok], o_ref[ok]), H.rel_err(u_got[ok], u_ref[ok])
+    say("direct beyond fp16, rec=%s Lmax=%d: rel err out/u %.2e %.2e" % ((rec_dtype, Lmax) + e))
+    H.check(e, "f16", rec_dtype, "beyond fp16")
