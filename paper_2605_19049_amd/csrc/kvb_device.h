@@ -272,6 +272,24 @@ __device__ __forceinline__ f32x4_t mfma16x32(const uint4 &a, const uint4 &b, con
                                                       c, 0, 0, 0);
 }
 
+// Whether the matrix products of a wave came out finite: cut into 16-bit pieces, or multiplied as whole tiles with
+// their zeros, an infinity or a value out of range becomes NaN, and every kernel of that kind then does the wave's part
+// again in fp32 over the exact terms.  largest: the largest magnitude so far, NaN once there was one.
+__device__ __forceinline__ float largest(float so_far, float x, float y)
+{
+    // (v_maximum3_f32, which hands NaN on)
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(so_far, __builtin_fabsf(x)), __builtin_fabsf(y));
+}
+__device__ __forceinline__ float largest(float so_far, const f32x4_t &x)
+{
+    return largest(largest(so_far, x[0], x[1]), x[2], x[3]);
+}
+__device__ __forceinline__ bool all_finite(float largest)
+{
+    // (as bits: the compiler turned "< Inf" into "!= Inf", which NaN passes)
+    return __all(__float_as_uint(largest) < 0x7F800000u);
+}
+
 // One 16-byte piece of the state tile.  STREAM: non-temporal load, for a state that will
 // not be read again before the last-level cache has turned over (measured on MI355X:
 // +14% at 1 GiB of state per call, -5% at 128 MiB, which the 256 MB cache keeps).

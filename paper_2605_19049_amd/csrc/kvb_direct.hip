@@ -259,19 +259,6 @@ __device__ __forceinline__ void solve_by_token(const DirectArgs &a, int b, int h
         }
     }
 }
-// The largest magnitude so far, NaN once there was one.
-__device__ __forceinline__ float largest(float so_far, const f32x4_t &x)
-{
-    auto max3 = [](float a, float b, float c) {   // (v_maximum3_f32, which hands NaN on)
-        return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, __builtin_fabsf(b)), __builtin_fabsf(c));
-    };
-    return max3(max3(so_far, x[0], x[1]), x[2], x[3]);
-}
-__device__ __forceinline__ bool all_finite(float largest)
-{
-    // (as bits: the compiler turned "< Inf" into "!= Inf", which NaN passes)
-    return __all(__float_as_uint(largest) < 0x7F800000u);
-}
 
 // ---------------------------------------------------------------------------
 // Pieces.  A fp32 value x is cut into NP values of the 16-bit input type, x = x_1 + ... + x_NP

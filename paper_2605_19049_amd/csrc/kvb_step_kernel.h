@@ -377,10 +377,13 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
         a.st.buf_G[ru(f)] = Gc;
     if (h % r == 0 && tid < D / 8)   // the threads that loaded the new k row store it
         store_raw8(static_cast<TIn *>(a.st.buf_k) + rk(f) * D + 8 * sub, k_raw);
-    int new_fill = f + 1;
+    const int m = f + 1;
+    const bool fold = FUSE && m >= a.threshold;   // uniform over the workgroup (and over the request)
+    // (ahead of the fold, which has no register to spare for the ticket: what the word orders are reads of itself)
+    if (a.advance && tid == 0)
+        publish_if_last(&a.st.fill[s], ticket, a.Hv, fold ? 0 : m);
     if constexpr (FUSE) {
-        const int m = f + 1;
-        if (m >= a.threshold) {   // uniform over the workgroup (and over the request)
+        if (fold) {
             const float gam = expf(Gc);
             if constexpr (MFOLD) {
                 // The rank-m update on the matrix cores, 16 records a step.  A thread holds rows
@@ -394,6 +397,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                 // in which some request folds.  13 requests of 8 heads, C = 32, fp16, 16 steps: 120 -> 99 us;
                 // 64 of 32 heads, C = 16, bf16: 483 -> 475 us; 1 of 32: 76.1 -> 74.9 us.  (500 of 32 at C = 64:
                 // the same 1072 us, its launches wait for memory.)
+                // Pieces of an infinity are NaN: a wave whose result is not finite folds again on the vector ALU.
                 // The records of a tile go to contraction slots 2 (r % 8) + r / 8, so that the two a thread
                 // stages share a word.
                 f32x16_t acc[4];
@@ -481,9 +485,40 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                         fold_tile(l0, kc, u0, u1);
                     }
                 }
+                float big = 0.0f;
 #pragma unroll
-                for (int p = 0; p < NPASS; ++p)
+                for (int p = 0; p < NPASS; ++p) {
+                    big = largest(largest(big, acc[0][p], acc[1][p]), acc[2][p], acc[3][p]);
                     sreg[p] = make_float4(acc[0][p], acc[1][p], acc[2][p], acc[3][p]);
+                }
+                if (__builtin_expect(!all_finite(big), 0)) {   // (the state, the records and the new token as the formula has them)
+                    // (everything from an opaque thread index: nothing is kept in a register for this)
+                    int t = tid;
+                    asm volatile("" : "+v"(t));
+                    const int row0 = t / LPR, col0 = t % LPR * 4;
+                    Pages<PAGED> pq = pg;
+                    pq.tab = sBlk[t / 64];
+                    const float gs = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, gam)));
+                    const float *sp = a.st.state + unit * D * D + (size_t)row0 * D + col0;
+#pragma unroll
+                    for (int p = 0; p < NPASS; ++p) {
+                        sreg[p] = *reinterpret_cast<const float4 *>(sp + (size_t)RPP * p * D);
+                        sreg[p].x *= gs; sreg[p].y *= gs; sreg[p].z *= gs; sreg[p].w *= gs;
+                    }
+#pragma unroll 1
+                    for (int l = 0; l < m; ++l) {
+                        const TIn *kp = (l < f ? kb + pq.row(l, a.Hk, hk) * D : kin + ((size_t)b * a.Hk + hk) * D) + row0;
+                        float4 u = *reinterpret_cast<const float4 *>(&sKs[col0]);
+                        float w = 1.0f;
+                        if (l < f) {   // uniform
+                            u = unpack4(load_raw4(ub + pq.row(l, a.Hv, h) * D + col0));
+                            w = wF[l];
+                        }
+#pragma unroll
+                        for (int p = 0; p < NPASS; ++p)
+                            fma4(sreg[p], w * to_f32(kp[RPP * p]), u);
+                    }
+                }
             } else {
 #pragma unroll
                 for (int p = 0; p < NPASS; ++p) {
@@ -617,11 +652,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                     sw[(size_t)(rg + RPP * p) * LPR + c4] = sreg[p];
                 }
             }
-            new_fill = 0;
         }
     }
-    if (a.advance && tid == 0)
-        publish_if_last(&a.st.fill[s], ticket, a.Hv, new_fill);
 }
 
 // ---------------------------------------------------------------------------

@@ -49,6 +49,14 @@ def rows(S0, rec, q, k, v, g, beta, scale, rec_dtype):
     return np.array(o).reshape(len(g), -1), (K, U, G)
 
 
+def folded(S0, rec):
+    K, U, G = rec
+    S = np.exp(G[-1]) * S0
+    for k, u, w in zip(K, U, np.exp(G[-1] - G)):
+        S = S + w * k[:, None] * u[None, :]
+    return S
+
+
 def kind(x):
     """0 finite, 1 +Inf, 2 -Inf, 3 NaN."""
     x = np.asarray(x)
@@ -135,3 +143,52 @@ def test_direct_beyond_the_range_of_fp16(rec_dtype, Lmax):
     e = H.rel_err(H.host(out)[ok], o_ref[ok]), H.rel_err(u_got[ok], u_ref[ok])
     say("direct beyond fp16, rec=%s Lmax=%d: rel err out/u %.2e %.2e" % ((rec_dtype, Lmax) + e))
     H.check(e, "f16", rec_dtype, "beyond fp16")
+
+
+def fill_buffers(lay, rng, f, d, in_dtype, rec_dtype):
+    """f random records for every request, and what was put there as float64."""
+    B, Hk, Hv = lay.B, lay.Hk, lay.Hv
+    t = synth.token_stream(rng, B, max(f, 1), Hk, Hv, d, d, in_dtype)
+    k, u, G = t["k"][:, :f], as_stored(0.6 * t["v"][:, :f], rec_dtype), np.cumsum(t["g"][:, :f].astype(np.float32), 1)
+    return k.astype(np.float64), u, G
+
+
+def put_buffers(lay, k, u, G, f):
+    lay.ds.buf_k[:, :, :f] = torch.from_numpy(k).float().cuda().transpose(1, 2).to(lay.ds.buf_k.dtype)
+    lay.ds.buf_u[:, :, :f] = torch.from_numpy(u).float().cuda().transpose(1, 2).to(lay.ds.buf_u.dtype)
+    lay.ds.buf_G[:, :, :f] = torch.from_numpy(np.asarray(G, np.float32)).cuda().transpose(1, 2)
+    lay.ds.fill.fill_(f)
+
+
+@pytest.mark.parametrize("in_dtype, rec_dtype", TYPES)
+@pytest.mark.parametrize("f", [0, 6, 24, 40, 70])
+def test_fused_update_bad_records(in_dtype, rec_dtype, f):
+    """kvb_decode_flush with an infinity or a NaN in a buffered record, or in the new token."""
+    d, Hk, Hv = 128, 1, 2
+    cases = ["u inf", "u nan", "k inf", "v inf", "v -inf", "new k inf", "clean"]
+    B = len(cases)
+    rng = np.random.default_rng(930 + f)
+    S0 = H.prefix_state(rng, B, Hk, Hv, d, d, in_dtype, 16)
+    tok = {x: y[:, 0] for x, y in synth.token_stream(rng, B, 1, Hk, Hv, d, d, in_dtype).items()}
+    lay = H.Layer(B, Hk, Hv, d, d, cap=max(8, -(-(f + 1) // 8) * 8), in_dtype=in_dtype, rec_dtype=rec_dtype)
+    k, u, G = fill_buffers(lay, rng, f, d, in_dtype, rec_dtype)
+    if f:
+        u[0, f // 2, 0, 11] = np.inf
+        u[1, f - 1, 1, 12] = np.nan
+        k[2, f // 3, 0, 7] = np.inf
+    tok["v"][3, 0, 20] = np.inf
+    tok["v"][4, 1, 21] = -np.inf
+    tok["k"][5, 0, 9] = np.inf
+    put_buffers(lay, k, u, G, f)
+    lay.set_state(S0)
+    out = lay.new_out(B, Hv, d)
+    lay.decode_flush(H.upload_tokens(tok, in_dtype), out, f + 1)
+    torch.cuda.synchronize()
+    S, got = lay.get_state(), H.host(out)
+    for b in range(B):
+        for h in range(Hv):
+            args = [tok[x].astype(np.float64)[b, 0 if x in "qk" else h][None] for x in ("q", "k", "v", "g", "beta")]
+            o, rec = rows(S0[b, h].astype(np.float64), (k[b, :, 0], u[b, :, h], G[b, :, h].astype(np.float64)), *args, 1.0, rec_dtype)
+            name = "fused update %s/%s f=%d, %s, head %d" % (in_dtype, rec_dtype, f, cases[b], h)
+            compare(got[b, h], o[0], in_dtype, rec_dtype, name + ", output")
+            compare(S[b, h], folded(S0[b, h].astype(np.float64), rec), in_dtype, rec_dtype, name + ", state")
