@@ -131,7 +131,7 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
                 float kf[RT], uf[CT];
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt)
-                    kf[rt] = to_f32(x.k[j][rt]);
+                    kf[rt] = in ? to_f32(x.k[j][rt]) : 0.0f;   // (both factors: 0 * Inf is NaN)
 #pragma unroll
                 for (int t = 0; t < CT; ++t)
                     uf[t] = in ? w * to_f32(x.u[j][t]) : 0.0f;

@@ -192,3 +192,29 @@ def test_fused_update_bad_records(in_dtype, rec_dtype, f):
             name = "fused update %s/%s f=%d, %s, head %d" % (in_dtype, rec_dtype, f, cases[b], h)
             compare(got[b, h], o[0], in_dtype, rec_dtype, name + ", output")
             compare(S[b, h], folded(S0[b, h].astype(np.float64), rec), in_dtype, rec_dtype, name + ", state")
+
+
+@pytest.mark.parametrize("d, in_dtype, rec_dtype", OTHERS)
+@pytest.mark.parametrize("m", [1, 5, 30, 43])
+def test_flush_rows_bad_records(d, in_dtype, rec_dtype, m):
+    """kvb_flush off the 16-bit d = 128 path with an infinity or a NaN in a record, the first one above all."""
+    Hk, Hv = 1, 2
+    cases = ["k inf", "k nan", "u inf", "u nan", "clean"]
+    B = len(cases)
+    rng = np.random.default_rng(940 + m)
+    S0 = H.prefix_state(rng, B, Hk, Hv, d, d, in_dtype, 16)
+    lay = H.Layer(B, Hk, Hv, d, d, cap=48, in_dtype=in_dtype, rec_dtype=rec_dtype)
+    k, u, G = fill_buffers(lay, rng, m, d, in_dtype, rec_dtype)
+    k[0, 0, 0, 3] = np.inf
+    k[1, m // 2, 0, 4] = np.nan
+    u[2, m - 1, 0, 5] = np.inf
+    u[3, 0, 1, 6] = np.nan
+    put_buffers(lay, k, u, G, m)
+    lay.set_state(S0)
+    lay.flush(1)
+    torch.cuda.synchronize()
+    S = lay.get_state()
+    for b in range(B):
+        for h in range(Hv):
+            want = folded(S0[b, h].astype(np.float64), (k[b, :, 0], u[b, :, h], G[b, :, h].astype(np.float64)))
+            compare(S[b, h], want, in_dtype, rec_dtype, "flush rows d=%d %s/%s m=%d, %s, head %d" % (d, in_dtype, rec_dtype, m, cases[b], h))
