@@ -453,7 +453,9 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     for (int sq = 0; sq < WQ; ++sq) {
         if (sq < nquad) {   // uniform
             const bool ok = 4 * sq + lq < f;
-            const float aw = cW[4 * sq + lq][lm];
+            float aw = cW[4 * sq + lq][lm];
+            if constexpr (CHAINS)   // (past the records the row holds a draft's weights: 0 * Inf is NaN)
+                aw = ok ? aw : 0.0f;
             const Cols<CT> uv = unpack_cols(uq[sq]);
 #pragma unroll
             for (int t = 0; t < CT; ++t)
@@ -478,7 +480,9 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         for (int j = 0; j < 4; ++j) {
             const int l = 4 * (s0 + j) + lq;   // < 4 * 35 + 4 = 144 rows of cW
             if (s0 + j < nquad) {   // uniform
-                const float aw = cW[l][lm];
+                float aw = cW[l][lm];
+                if constexpr (CHAINS)
+                    aw = l < f ? aw : 0.0f;
 #pragma unroll
                 for (int t = 0; t < CT; ++t)
                     add(j, t, aw, l < f ? u4[j].x[t] : 0.0f);

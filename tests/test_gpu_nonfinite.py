@@ -218,3 +218,34 @@ def test_flush_rows_bad_records(d, in_dtype, rec_dtype, m):
         for h in range(Hv):
             want = folded(S0[b, h].astype(np.float64), (k[b, :, 0], u[b, :, h], G[b, :, h].astype(np.float64)))
             compare(S[b, h], want, in_dtype, rec_dtype, "flush rows d=%d %s/%s m=%d, %s, head %d" % (d, in_dtype, rec_dtype, m, cases[b], h))
+
+
+@pytest.mark.parametrize("d, in_dtype, rec_dtype", OTHERS)
+@pytest.mark.parametrize("f", [0, 5, 39, 70])
+def test_verify_bad_drafts(d, in_dtype, rec_dtype, f):
+    """kvb_verify off the 16-bit d = 128 path: a bad draft changes itself and the drafts after it."""
+    Hk, Hv, T = 1, 2, 5
+    cases = [("v", "inf"), ("v", "nan"), ("k", "inf"), ("k", "nan"), ("q", "nan"), None]
+    B = len(cases)
+    rng = np.random.default_rng(950 + f)
+    S0 = H.prefix_state(rng, B, Hk, Hv, d, d, in_dtype, 16)
+    tok = synth.token_stream(rng, B, T, Hk, Hv, d, d, in_dtype)
+    for b, w in enumerate(cases):
+        if w:
+            poison(tok, b, w, 2, d)
+    lay = H.Layer(B, Hk, Hv, d, d, cap=80, in_dtype=in_dtype, rec_dtype=rec_dtype)
+    k, u, G = fill_buffers(lay, rng, f, d, in_dtype, rec_dtype)
+    put_buffers(lay, k, u, G, f)
+    lay.set_state(S0)
+    out = lay.new_out(B, T, Hv, d)
+    lay.verify(T, H.upload_tokens(tok, in_dtype), out)
+    torch.cuda.synchronize()
+    got = H.host(out)
+    for b in range(B):
+        u_got = lay.u_records(b, f, f + T)
+        for h in range(Hv):
+            args = [tok[x].astype(np.float64)[b, :, 0 if x in "qk" else h] for x in ("q", "k", "v", "g", "beta")]
+            o, rec = rows(S0[b, h].astype(np.float64), (k[b, :, 0], u[b, :, h], G[b, :, h].astype(np.float64)), *args, 1.0, rec_dtype)
+            name = "verify d=%d %s/%s f=%d, %s, head %d" % (d, in_dtype, rec_dtype, f, cases[b], h)
+            compare(got[b, :, h], o, in_dtype, rec_dtype, name + ", outputs")
+            compare(u_got[h], rec[1][f:], in_dtype, rec_dtype, name + ", records")
