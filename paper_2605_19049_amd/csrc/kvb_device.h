@@ -272,6 +272,31 @@ __device__ __forceinline__ f32x4_t mfma16x32(const uint4 &a, const uint4 &b, con
                                                       c, 0, 0, 0);
 }
 
+// Waits until the matrix instructions that produce these values have written them.  The compiler
+// inserts such waits itself, but where a block of matrix instructions is skipped by a branch it looked back
+// along the path through that block only, and the other path read a register before its sum had arrived; sums
+// that end in such blocks are therefore settled by hand before anything else reads them.  (The wait states from
+// a matrix instruction to a vector read of its result: 16-bit 16x16x32 8, fp32 16x16x4 10.)
+constexpr int SETTLE_16BIT = 8, SETTLE_FP32 = 10;
+template <int STATES>
+__device__ __forceinline__ void settle(f32x4_t &x)
+{
+    asm volatile("s_nop %1" : "+v"(x) : "n"(STATES - 1));
+}
+template <int STATES>
+__device__ __forceinline__ void settle(f32x4_t &x, f32x4_t &y)
+{
+    asm volatile("s_nop %2" : "+v"(x), "+v"(y) : "n"(STATES - 1));
+}
+template <int STATES, int N>
+__device__ __forceinline__ void settle(f32x4_t (&x)[N][2])
+{
+    settle<STATES>(x[0][0], x[0][1]);   // (volatile: the ones below stay behind it)
+#pragma unroll
+    for (int i = 1; i < N; ++i)
+        asm volatile("" : "+v"(x[i][0]), "+v"(x[i][1]));
+}
+
 // Whether the matrix products of a wave came out finite: cut into 16-bit pieces, or multiplied as whole tiles with
 // their zeros, an infinity or a value out of range becomes NaN, and every kernel of that kind then does the wave's part
 // again in fp32 over the exact terms.  largest: the largest magnitude so far, NaN once there was one.

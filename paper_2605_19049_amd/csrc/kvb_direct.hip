@@ -99,25 +99,6 @@ __device__ __forceinline__ f32x4_t gram16(const TIn *arow, const TIn *brow, int 
     return c;
 }
 
-// Waits until the matrix instructions that produce these values have written them (8 wait states cover
-// the 16-bit 16x16x32 instruction).  The compiler inserts such waits itself, but where a block of matrix
-// instructions is skipped by a branch it looked back along the path through that block only, and the
-// other path read a register before its sum had arrived; sums that end in such blocks are therefore
-// settled by hand before anything else reads them.
-template <int N>
-__device__ __forceinline__ void settle(f32x4_t (&x)[N][2])
-{
-    asm volatile("s_nop 7" : "+v"(x[0][0]));   // (volatile: the ones below stay behind it)
-#pragma unroll
-    for (int i = 0; i < 2 * N; ++i)
-        if (i > 0)
-            asm volatile("" : "+v"(x[i / 2][i % 2]));
-}
-__device__ __forceinline__ void settle(f32x4_t &x, f32x4_t &y)
-{
-    asm volatile("s_nop 7" : "+v"(x), "+v"(y));
-}
-
 // One step of a 16 x 16 Gram tile in A-form (rows of block d against rows of block e): 16 bytes of row 16 e + c16 and of
 // row 16 d + c16; fp32: contraction slot lq of instruction v stands for element 4 lq + v on both sides.
 template <typename TIn>
@@ -898,7 +879,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                         n = mfma16x32<TIn>(av, __builtin_bit_cast(uint4, ko[st]), n);
                         m = mfma16x32<TIn>(av, __builtin_bit_cast(uint4, qo[st]), m);
                     }
-                    settle(n, m);
+                    settle<SETTLE_16BIT>(n, m);
                 };
                 const float gi = sG[i1], bi = sB[i1];
                 auto weigh = [&](int l0, const f32x4_t &x, float si, bool strict) {
@@ -1008,7 +989,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
             for (int d = 0; d < NB; ++d)
                 x[d][0] = x[d][1] = z4;
             cross_product(x);   // (N' is stored negated)
-            settle(x);
+            settle<SETTLE_16BIT>(x);
 #pragma unroll
             for (int d = 0; d < NB; ++d)
 #pragma unroll
@@ -1034,7 +1015,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                 for (int c = 0; c < 2; ++c)
                     o1[d][c] = u1[d][c] = z4;
             cross_product(o1);
-            settle(o1);
+            settle<SETTLE_16BIT>(o1);
 #pragma unroll
             for (int e = 0; e < NB; ++e) {
                 if (e < nb1) {   // uniform
@@ -1054,7 +1035,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                                 u1[d][c] = mm16_pieces<TP, NP, NP>(ap, xp[c], u1[d][c]);
                         }
                     }
-                    settle(u1[e][0], u1[e][1]);
+                    settle<SETTLE_16BIT>(u1[e][0], u1[e][1]);
                     if constexpr (sizeof(TRec) == 2) {
 #pragma unroll
                         for (int c = 0; c < 2; ++c)
@@ -1105,7 +1086,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                                 o1[d][c] = mm16_pieces<TP, NP, NPU>(mp, up1[c], o1[d][c]);
                         }
                     }
-                    settle(o1[e][0], o1[e][1]);
+                    settle<SETTLE_16BIT>(o1[e][0], o1[e][1]);
                     big = largest(largest(big, o1[e][0]), o1[e][1]);
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
@@ -1145,7 +1126,7 @@ __device__ __forceinline__ f32x4_t gram_rows(const TIn *rows, const u32x4_t (&ow
     for (int st = 0; st < NST; ++st)
         c = gram_step<TIn>(*reinterpret_cast<const u32x4_t *>(rows + (D / NST) * st + (D / NST / 4) * lq), own[st], c);
     if constexpr (sizeof(TIn) == 4)
-        asm volatile("s_nop 10" : "+v"(c));   // (settled, as in settle() above; 11 wait states for the fp32 instruction)
+        settle<SETTLE_FP32>(c);
     return c;
 }
 

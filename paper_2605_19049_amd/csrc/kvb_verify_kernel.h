@@ -110,8 +110,9 @@ __device__ __forceinline__ f32x4_t dot_tile(const uint4 (&a)[N], const uint4 (&b
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int WREC, bool HAS_STATE, bool STREAM, bool PAGED>
 // (register budgets: 4 waves per SIMD with a record window of 16 or 32, 3 with the 64-record window or with
-// fp32 keys of 128, whose operands take twice the registers)
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(!HAS_STATE ? 1 : (WREC <= 32 ? 4 : 3) - (D * sizeof(TIn) > 256))))
+// fp32 keys of 128, whose operands take twice the registers; without a state 2, which keeps the sums out of the
+// accumulation registers, where settle() could not hold them)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(!HAS_STATE ? 2 : (WREC <= 32 ? 4 : 3) - (D * sizeof(TIn) > 256))))
 void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg, const StepArgs a)
 {
     // (the three leading arguments repeat a.slot, a.Hv and the grid size: preloaded into scalar registers
@@ -325,7 +326,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         f32x4_t &c = CHAINS ? part[step % NACC][t] : acc[t];
         c = __builtin_amdgcn_mfma_f32_16x16x4f32(w, x, c, 0, 0, 0);
     };
-    auto settle = [&]() {
+    auto add_chains = [&]() {
         if constexpr (CHAINS) {
 #pragma unroll
             for (int t = 0; t < CT; ++t) {
@@ -374,7 +375,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             for (int t = 0; t < CT; ++t)
                 add(st, t, aw, sv.x[t]);
             if (st % SETTLE == SETTLE - 1)
-                settle();
+                add_chains();
             if (st + WIN < D / 4) {   // the freed registers take the quad WIN further on
                 __builtin_amdgcn_sched_barrier(0);
                 sreg[st % WIN] = load_quad(st + WIN);
@@ -461,7 +462,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             for (int t = 0; t < CT; ++t)
                 add(sq, t, aw, ok ? uv.x[t] : 0.0f);
             if (sq % SETTLE == SETTLE - 1)
-                settle();
+                add_chains();
         }
     }
     // records beyond the register window: four quads to a round trip (requested together, clamped)
@@ -489,7 +490,15 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             }
         }
     }
-    settle();
+    // (the blocks above end the sums, and a branch may skip any of them)
+    if constexpr (!CHAINS) {
+        settle<SETTLE_FP32>(acc[0], acc[CT - 1]);
+    } else {
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+            settle<SETTLE_FP32>(part[0][t], part[NACC - 1][t]);
+        add_chains();
+    }
     // acc[t][v] = row m = 4 lq + v, column col2 + t
     if (wave < NWC)   // uniform
 #pragma unroll

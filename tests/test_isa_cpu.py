@@ -1,5 +1,6 @@
 """Orderings that the kernels depend on and that no result shows reliably, checked on the machine code of the built
 library along every path of every kernel (no GPU needed)."""
+import functools
 import os
 import re
 import shutil
@@ -12,6 +13,7 @@ from paper_2605_19049_amd import kvb
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 TARGET = re.compile(r"<[^>+]*\+0x([0-9a-f]+)>")
+REG = re.compile(r"\b([va])(?:(\d+)\b|\[(\d+):(\d+)\])")
 
 
 def code_objects(tmp):
@@ -87,10 +89,73 @@ def unordered_tickets(ins, adr):
     return bad
 
 
+@functools.lru_cache(None)
+def regs(operands):
+    """Bit mask of the vector registers in an operand text (accumulation registers above the others)."""
+    m = 0
+    for kind, one, lo, hi in REG.findall(operands):
+        lo, hi = (int(one), int(one)) if one else (int(lo), int(hi))
+        m |= ((1 << (hi - lo + 1)) - 1) << (lo + (256 if kind == "a" else 0))
+    return m
+
+
+def mfma_wait(op):
+    """Wait states between a matrix instruction and a read of its result: its passes of 4 cycles and 2 (fp32), or 4
+    (16-bit types)."""
+    return {"v_mfma_f32_16x16x4_f32": 8 + 2, "v_mfma_f32_16x16x32_bf16": 4 + 4, "v_mfma_f32_16x16x32_f16": 4 + 4,
+            "v_mfma_f32_32x32x16_bf16": 8 + 4}[op]
+
+
+@functools.lru_cache(None)
+def effect(x):
+    """(issue slots, mask of what is read before the slot ends, mask of matrix results, their wait)."""
+    op, _, rest = x.partition(" ")
+    if op == "s_nop":
+        return int(rest.split()[0], 0) + 1, 0, 0, 0
+    ops = rest.split(", ")
+    if op.startswith("v_mfma"):   # (the accumulator input is forwarded)
+        return 1, regs(ops[1]) | regs(ops[2]), regs(ops[0]), mfma_wait(op)
+    if op.startswith("v_") or any(x in op for x in ("_load_", "_read", "permute", "swizzle")):
+        return 1, regs(", ".join(ops[1:])), 0, 0
+    if op.startswith(("ds_", "global_", "buffer_", "scratch_", "flat_")):
+        return 1, regs(rest), 0, 0
+    return 1, 0, 0, 0
+
+
+def early_reads(ins, adr):
+    """Instructions that some path lets read a matrix result before the wait states it needs."""
+    bl = blocks(ins, adr)
+    state, bad = {0: frozenset()}, set()
+    todo = [0]
+    while todo:
+        n = todo.pop()
+        first, end, succ = bl[n]
+        pending = dict(state[n])   # result mask -> wait states still needed
+        for i in range(first, end):
+            slots, read, made, wait = effect(ins[i])
+            if pending:
+                if read and any(read & m for m in pending):
+                    bad.add((i, ins[i]))
+                pending = {m: w - slots for m, w in pending.items() if w > slots}
+            if made:
+                pending[made] = wait
+        out = frozenset(pending.items())
+        for s in succ:
+            old = dict(state.get(s, ()))
+            new = dict(old)
+            for m, w in out:
+                new[m] = max(w, new.get(m, 0))
+            if s not in state or new != old:
+                state[s] = frozenset(new.items())
+                todo.append(s)
+    return sorted(bad)
+
+
 def scan(path):
     res = []
     for name, ins, adr in kernels(path):
-        res.append((name, len(ins), any(x.startswith("global_atomic_add") for x in ins), unordered_tickets(ins, adr)))
+        res.append((name, len(ins), any(x.startswith("global_atomic_add") for x in ins), unordered_tickets(ins, adr),
+                    early_reads(ins, adr)))
     return res
 
 
@@ -110,3 +175,9 @@ def test_tickets_follow_a_barrier(scanned):
     assert len(with_ticket) > 100, len(with_ticket)
     bad = [(r[0], r[3]) for r in with_ticket if r[3]]
     assert not bad, "%d kernels, e.g. %s" % (len(bad), bad[0])
+
+
+def test_matrix_results_are_waited_for(scanned):
+    """No path reads the result of a matrix instruction before the wait states it needs."""
+    bad = [(r[0], r[4][:3]) for r in scanned if r[4]]
+    assert not bad, "%d kernels, e.g. %s" % (len(bad), bad[:2])
