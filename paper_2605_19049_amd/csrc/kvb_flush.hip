@@ -171,7 +171,10 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 // relative) are far below the 2^-9 rounding a bf16 record already carries.  fp16 pieces carry
 // 11 bits: two give 22 bits (2^-23 relative, the rounding of fp32 itself is 2^-24); a piece
 // below the fp16 range (6e-8) is dropped, an absolute error that small against delta values
-// of order one.  The 16-bit instruction runs at 16 times the rate of the fp32 matrix
+// of order one.  A fp32 record may be larger than a fp16 piece can be (65504): a column that holds such a
+// value is scaled by a power of two before it is cut, and its sums are scaled back (SCALED; three bf16 pieces
+// of the record and two of the key, exact without a scale, cost 92 us instead of 76 for 64 requests of 32
+// heads and 128 records, the scale 78).  The 16-bit instruction runs at 16 times the rate of the fp32 matrix
 // instruction, so even three products come at about 5 times that rate and 10 times the rate
 // of plain vector-ALU FMAs, which is what bounds the vector-ALU kernel above from 16 records on.
 //
@@ -204,6 +207,8 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     constexpr int CH = 32;   // records per chunk
     // pieces of the fp32 factor (see above)
     constexpr int NP = (__is_same(TIn, bf16_t) && sizeof(TRec) == 4) ? 3 : 2;
+    // fp16 pieces of fp32 records: out of range is scaled (see above)
+    constexpr bool SCALED = __is_same(TIn, f16_t) && sizeof(TRec) == 4;
     __shared__ int sBlk[NW][MAX_BLOCKS];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;   // (a scalar)
@@ -279,8 +284,14 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
         issue_state(rt);
     const int ticket = take_ticket(&a.st.fill[s]);
 
-    // B operands of a chunk: piece p of Gamma_l u_l[col2 + t], 8 records to a lane
+    // B operands of a chunk: piece p of Gamma_l u_l[col2 + t], 8 records to a lane.  down, up: the power of two that
+    // column t is cut at and its inverse, the same in the four lanes that hold the column
     uint4 bop[2][NP];
+    float down[2] = {1.0f, 1.0f}, up[2] = {1.0f, 1.0f};
+    f32x4_t acc[MULTI ? 8 : 1][2];   // the sums, where they persist
+#pragma unroll
+    for (int rt = 0; rt < (MULTI ? 8 : 1); ++rt)
+        acc[rt][0] = acc[rt][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     auto build_b = [&](int c) {
         float w[8];
         float2 uf[8];
@@ -289,12 +300,39 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
             w[j] = CH * c + 8 * lq + j < m ? expf(Glast - Graw[j]) : 0.0f;
             uf[j] = unpack2r(uraw[j]);
         }
+        if constexpr (SCALED) {
+            float big = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                big = largest(big, w[j] * uf[j].x * down[0], w[j] * uf[j].y * down[1]);
+            if (__any(big > 65504.0f)) {   // (NaN is none of this)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    float most = 0.0f;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        most = fmaxf(most, fabsf(w[j] * (t ? uf[j].y : uf[j].x)));
+                    most = fmaxf(most, __shfl_xor(most, 16));
+                    most = fmaxf(most, __shfl_xor(most, 32));
+                    const int e = (int)(__float_as_uint(most) >> 23);   // 2^(e - 127) <= most < 2^(e - 126)
+                    if (most * down[t] > 65504.0f && e < 255) {
+                        const float to = __uint_as_float((uint32_t)(127 + 127 + 14 - e) << 23);   // most * to < 2^15
+                        const float by = to * up[t];
+#pragma unroll
+                        for (int rt = 0; rt < (MULTI ? 8 : 1); ++rt)
+                            acc[rt][t] *= by;
+                        down[t] = to;
+                        up[t] = __uint_as_float((uint32_t)(127 + e - 127 - 14) << 23);
+                    }
+                }
+            }
+        }
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             float r[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-                r[j] = w[j] * (t ? uf[j].y : uf[j].x);
+                r[j] = w[j] * (t ? uf[j].y : uf[j].x) * down[t];
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
                 // the leading significand bits of what is left; the rest is exact in fp32
@@ -347,8 +385,8 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             float2 o;
-            o.x = fmaf(gam, sreg[rt % WIN][v].x, c0[v]);
-            o.y = fmaf(gam, sreg[rt % WIN][v].y, c1[v]);
+            o.x = fmaf(gam, sreg[rt % WIN][v].x, c0[v] * up[0]);
+            o.y = fmaf(gam, sreg[rt % WIN][v].y, c1[v] * up[1]);
             if constexpr (STREAM)
                 store2_nt(sp + (size_t)(32 * lq + 8 * v + rt) * D, o.x, o.y);
             else
@@ -368,10 +406,6 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
             finish(rt, c0, c1);
         }
     } else {
-        f32x4_t acc[8][2];
-#pragma unroll
-        for (int rt = 0; rt < 8; ++rt)
-            acc[rt][0] = acc[rt][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         const int nchunk = (m + CH - 1) / CH;
         for (int c = 0; c < nchunk; ++c) {
             if (c > 0)

@@ -145,6 +145,20 @@ def test_direct_beyond_the_range_of_fp16(rec_dtype, Lmax):
     H.check(e, "f16", rec_dtype, "beyond fp16")
 
 
+@pytest.mark.parametrize("C", [5, 16, 33, 70])
+def test_flush_beyond_the_range_of_fp16(C):
+    """kvb_decode, then kvb_flush: fp32 records of fp16 tokens on a state 1e8 times its usual size."""
+    rng = np.random.default_rng(920 + C)
+    S0 = H.prefix_state(rng, 2, 2, 4, 128, 128, "f16", 16) * np.float32(1e8)
+    tok = synth.token_stream(rng, 2, C + 3, 2, 4, 128, 128, "f16")
+    lay = H.Layer(2, 2, 4, 128, 128, cap=C, in_dtype="f16", scale=128 ** -0.5)
+    o, u, S, _ = H.run_decode(lay, S0, tok, C, fused=False)
+    o_ref, u_ref, S_ref = oracle.kvb_decode_expected(S0, tok["q"], tok["k"], tok["v"], tok["g"], tok["beta"], scale=128 ** -0.5)
+    e = (H.rel_err(o, o_ref), H.rel_err(u, u_ref), H.rel_err(S, S_ref))
+    say("flush beyond fp16, C=%d: rel err out/u/state %.2e %.2e %.2e" % ((C,) + e))
+    H.check(e, "f16", what="flush beyond fp16")
+
+
 def fill_buffers(lay, rng, f, d, in_dtype, rec_dtype):
     """f random records for every request, and what was put there as float64."""
     B, Hk, Hv = lay.B, lay.Hk, lay.Hv
@@ -158,6 +172,41 @@ def put_buffers(lay, k, u, G, f):
     lay.ds.buf_u[:, :, :f] = torch.from_numpy(u).float().cuda().transpose(1, 2).to(lay.ds.buf_u.dtype)
     lay.ds.buf_G[:, :, :f] = torch.from_numpy(np.asarray(G, np.float32)).cuda().transpose(1, 2)
     lay.ds.fill.fill_(f)
+
+
+@pytest.mark.parametrize("m, paged", [(3, False), (32, False), (33, True), (100, False), (128, True)])
+def test_flush_columns_of_their_own_size(m, paged):
+    """fp16 keys, fp32 records: columns from 0.1 to 1e9 side by side, growing from record to record; every column of the
+    state to the usual bound against its own size."""
+    d, Hk, Hv, B = 128, 2, 4, 3
+    rng = np.random.default_rng(925 + m)
+    cap = max(8, -(-m // 8) * 8)
+    lay = H.Layer(B, Hk, Hv, d, d, cap=cap, in_dtype="f16", block_size=8 if paged else None)
+    k, u, G = fill_buffers(lay, rng, m, d, "f16", "f32")
+    size = 10.0 ** rng.uniform(-1, 9, (B, 1, Hv, d))
+    u = as_stored(u * size * 1.05 ** np.arange(m)[None, :, None, None], "f32")
+    S0 = (rng.standard_normal((B, Hv, d, d)) * size.transpose(0, 2, 1, 3)).astype(np.float32)
+    if paged:
+        bs = lay.ds.block_size
+        blk = lay.ds.block_table.long()[:, torch.arange(m, device="cuda") // bs]
+        off = (torch.arange(m, device="cuda") % bs).expand(B, m)
+        lay.ds.buf_k[blk, :, off] = H.dev(k.astype(np.float32), "f16")
+        lay.ds.buf_u[blk, :, off] = H.dev(u.astype(np.float32))
+        lay.ds.buf_G[blk, :, off] = H.dev(G.astype(np.float32))
+        lay.ds.fill.fill_(m)
+    else:
+        put_buffers(lay, k, u, G, m)
+    lay.set_state(S0)
+    lay.flush(1)
+    torch.cuda.synchronize()
+    S, worst = lay.get_state().astype(np.float64), 0.0
+    for b in range(B):
+        for h in range(Hv):
+            want = folded(S0[b, h].astype(np.float64), (k[b, :, h // 2], u[b, :, h], G[b, :, h].astype(np.float64)))
+            rms = np.sqrt((want ** 2).mean(0))
+            worst = max(worst, np.nan_to_num((np.abs(S[b, h] - want).max(0) / rms).max(), nan=np.inf))
+    say("flush, columns of their own size, m=%d: worst column %.2e" % (m, worst))
+    H.check(worst, "f16", what="columns of their own size")
 
 
 @pytest.mark.parametrize("in_dtype, rec_dtype", TYPES)
