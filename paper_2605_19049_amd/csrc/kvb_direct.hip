@@ -242,13 +242,6 @@ __device__ __forceinline__ void solve_by_token(const DirectArgs &a, int b, int h
 }
 
 // ---------------------------------------------------------------------------
-// Pieces.  A fp32 value x is cut into NP values of the 16-bit input type, x = x_1 + ... + x_NP
-// (+ a remainder below 2^-24 |x| for three bf16 pieces, 2^-22 |x| for two fp16 pieces), each
-// the leading bits of what is left, so that a product of two fp32 tiles becomes a few products
-// of 16-bit tiles on v_mfma_f32_16x16x32, which runs at 16 times the rate of the fp32 matrix
-// instruction.  take_piece handles two values at once and returns their pieces packed in one
-// word (first value in the low half); the two arguments become the remainders.
-// ---------------------------------------------------------------------------
 // Which unit a workgroup takes.  Workgroup ids go round the 8 XCDs.  The work of a unit grows with its
 // context, so the heads of a request are dealt over all XCDs, one qk-head with its `deal` v-heads (which
 // share keys and queries through the XCD's L2) at a time; with whole requests on one XCD, as the kernels
@@ -270,6 +263,14 @@ inline int deal_of(const DirectArgs &a, int blocks)
     return blocks % (8 * r) == 0 ? r : 0;
 }
 
+// ---------------------------------------------------------------------------
+// Pieces.  A fp32 value x is cut into NP values of the 16-bit input type, x = x_1 + ... + x_NP
+// (+ a remainder below 2^-24 |x| for three bf16 pieces, 2^-22 |x| for two fp16 pieces), each
+// what is left rounded to nearest, so that a product of two fp32 tiles becomes a few products
+// of 16-bit tiles on v_mfma_f32_16x16x32, which runs at 16 times the rate of the fp32 matrix
+// instruction.  take_piece handles two values at once and returns their pieces packed in one
+// word (first value in the low half); the two arguments become the remainders.
+// ---------------------------------------------------------------------------
 template <typename T>
 constexpr int pieces_of_f32() { return __is_same(T, bf16_t) ? 3 : 2; }
 
@@ -277,10 +278,12 @@ template <typename T>
 __device__ __forceinline__ uint32_t take_piece(float &a, float &b)
 {
     if constexpr (__is_same(T, bf16_t)) {
-        const uint32_t ua = __builtin_bit_cast(uint32_t, a), ub = __builtin_bit_cast(uint32_t, b);
-        a -= __builtin_bit_cast(float, ua & 0xFFFF0000u);   // exact
-        b -= __builtin_bit_cast(float, ub & 0xFFFF0000u);
-        return __builtin_amdgcn_perm(ub, ua, 0x07060302u);   // (ua >> 16) | (ub & 0xFFFF0000)
+        typedef float f32x2_t __attribute__((ext_vector_type(2)));
+        typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+        const uint32_t p = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+        a -= __uint_as_float(p << 16);   // exact
+        b -= __uint_as_float(p & 0xFFFF0000u);
+        return p;
     } else {
         const f16_t ha = from_f32<f16_t>(a), hb = from_f32<f16_t>(b);
         a -= to_f32(ha);   // exact
@@ -307,7 +310,10 @@ __device__ __forceinline__ void split_tile(const f32x4_t &x, uint2 (&p)[NP])
 // pieces in B-form (NPY = 1: Y is exactly representable in the 16-bit type).  One instruction
 // contracts over 32 slots; a lane's 8 slots are its 4 contraction indices taken twice, so an
 // instruction adds two piece products X_a Y_b + X_c Y_d.  Three instructions give the six
-// products down to 2^-16 of the leading one (all that matter for a fp32 result).
+// products down to 2^-16 of the leading one.  The three that are left out, X2 Y3 + X3 Y2 + X3 Y3, are at most
+// 5.4e-8 of the product and 6e-9 rms, without a bias (4 million pairs of normal values; the rounding of a fp32
+// product is up to 6e-8, 2.5e-8 rms): that needs the pieces rounded to nearest.  Cut off instead, every piece has the
+// sign of its value and they add up: 4.3e-7, 6e-8 rms, 4e-8 on the average.
 template <typename T, int NPX, int NPY>
 __device__ __forceinline__ f32x4_t mm16_pieces(const uint2 (&x)[NPX], const uint2 (&y)[NPY], f32x4_t acc)
 {
@@ -424,6 +430,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     __shared__ __attribute__((aligned(16))) float sG[LONG ? 2 * LM : LM];
     __shared__ __attribute__((aligned(16))) float sB[LONG ? 2 * LM : LM];
     __shared__ int sBlk[NW][MAX_BLOCKS];
+    // LONG: the first two weighted query tiles of each block row of the second panel, kept for its end (a lane's values
+    // together, written and read by the same lane; 160 KB hold three workgroups with them)
+    __shared__ float4 sM[LONG ? 7 : 1][64];
     TIn *sK = reinterpret_cast<TIn *>(region);
     auto pieceA = [&](int tile, int p) { return reinterpret_cast<uint2 *>(region + (tile * NP + p) * 512); };
     auto pieceM = [&](int tile, int p) { return reinterpret_cast<uint2 *>(region + X_BYTES + (tile * NP + p) * 512); };
@@ -908,6 +917,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                             else   // (the diagonal tile stays raw: diagonal_inverse weighs it in both forms)
                                 gd1 = n1[e];
                             m1[e] = weigh(LM + 16 * e + 4 * lq, m1[e], 1.0f, false);
+                            if (e < 2)
+                                sM[4 * e + wave - e][lane] = make_float4(m1[e][0], m1[e][1], m1[e][2], m1[e][3]);
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);
@@ -977,13 +988,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
             // ---- X = V_1 - N' U_0 beside the first half of the inverse
             // (v in B-form: rows LM + 16 d + 4 lq + v, this lane's two columns; needed at the end only)
             uint32_t v1_raw[NB][4];
+            auto request_v1 = [&]() {
 #pragma unroll
-            for (int d = 0; d < NB; ++d)
+                for (int d = 0; d < NB; ++d)
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    v1_raw[d][v] = *reinterpret_cast<const uint32_t *>(
-                        vbase + (uint32_t)min(LM + 16 * d + 4 * lq + v, L - 1) * v_stride + col2);
+                    for (int v = 0; v < 4; ++v)
+                        v1_raw[d][v] = *reinterpret_cast<const uint32_t *>(
+                            vbase + (uint32_t)min(LM + 16 * d + 4 * lq + v, L - 1) * v_stride + col2);
+            };
             inverse_first_half(nb1, t_own);
+            __builtin_amdgcn_sched_barrier(0);
+            request_v1();
             f32x4_t x[NB][2];
 #pragma unroll
             for (int d = 0; d < NB; ++d)
@@ -1058,6 +1073,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                 for (int e = 0; e < NB; ++e) {
                     if (e <= wave) {
                         uint2 pc[NP];
+                        if (e < 2) {
+                            const float4 t = sM[4 * e + wave - e][lane];
+                            m1[e] = f32x4_t{t.x, t.y, t.z, t.w};
+                        }
                         split_tile<TP, NP>(m1[e], pc);
 #pragma unroll
                         for (int p = 0; p < NP; ++p)
@@ -1099,7 +1118,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
             }
         }
     }
-    if (!all_finite(big))
+    if (__builtin_expect(!all_finite(big), 0))
         solve_by_token<D, 2, TIn, TRec>(a, b, h, L, col2, sG, sB, ru, lane);
     if (h == 0 && tid == 0)
         a.st.fill[s] = L;

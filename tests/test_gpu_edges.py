@@ -112,3 +112,32 @@ def test_decode_from_the_buffer_alone(B, Hk, Hv, d, in_dtype, rec_dtype, block_s
     # the requests, with 0 or 1 record, pull down: fp32 sums of 65 records may stand 65 * 2^-24 * max / RMS = 4e-6 *
     # max / RMS off, above 1e-5 here; the vector-ALU kernels that this path ran on before read 1.2e-5 too)
     H.check(e[:3], in_dtype, rec_dtype, "buffer alone")
+
+
+@pytest.mark.parametrize("in_dtype, Lmax", [("bf16", 64), ("bf16", 128), ("f16", 128)])
+def test_direct_products_of_full_fp32_factors(in_dtype, Lmax):
+    """Outputs that are one product (q_i.k_0) u_0 of two factors with all 24 bits: three pieces to a factor, of whose nine
+    products six are formed.  Rounded to nearest, the three that are left out are at most 5.4e-8 of the product (4 million
+    pairs of normal values) and have no sign of their own; three sums in fp32 add 2^-24 each: 2.4e-7.  Cut off instead of
+    rounded they are 4.3e-7, 4e-8 on the average."""
+    rng = np.random.default_rng(880)
+    Hk, Hv, d = 4, 8, 128
+    tok = {x: np.zeros((1, Lmax, Hk if x in "qk" else Hv, d), np.float32) for x in "qkv"}
+    tok["g"], tok["beta"] = np.zeros((1, Lmax, Hv), np.float32), np.zeros((1, Lmax, Hv), np.float32)
+
+    def eight_bits(*size):   # 1 .. 2, exact in both types
+        return (rng.integers(128, 256, size) / 128.0).astype(np.float32)
+    # q.k = a c + b d: a c a multiple of 2^-14, b d one of 2^-22, their sum below 4
+    tok["k"][0, 0, :, 0], tok["k"][0, 0, :, 1] = eight_bits(Hk), eight_bits(Hk) / 256
+    tok["q"][0, :, :, 0], tok["q"][0, :, :, 1] = eight_bits(Lmax, Hk), eight_bits(Lmax, Hk)
+    tok["v"][0, 0] = eight_bits(Hv, d) * rng.choice([-1, 1], (Hv, d))
+    tok["beta"][0, 0] = rng.uniform(0.5, 1, Hv)
+    lay = H.Layer(1, Hk, Hv, d, d, cap=Lmax, in_dtype=in_dtype, with_state=False)
+    out = lay.new_out(1, Lmax, Hv, d, fill=float("nan"))
+    lay.direct(H.dev(np.array([Lmax], np.int32)), Lmax, H.upload_tokens(tok, in_dtype), out)
+    u0 = lay.u_records(0, 0, 1)[:, 0].astype(np.float64)                                          # [Hv, d]
+    qk = (tok["q"][0].astype(np.float64) * tok["k"][0, 0].astype(np.float64)).sum(-1)             # [Lmax, Hk]
+    want = np.repeat(qk, Hv // Hk, 1)[:, :, None] * u0
+    e = (H.host(out)[0].astype(np.float64) - want) / want
+    say("direct, full fp32 factors, %s Lmax=%d: error max %.2e mean %.2e" % (in_dtype, Lmax, np.abs(e).max(), e.mean()))
+    assert np.abs(e).max() < 2.4e-7 and abs(e.mean()) < 1e-8, (np.abs(e).max(), e.mean())
