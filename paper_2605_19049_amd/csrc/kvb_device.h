@@ -413,6 +413,30 @@ __device__ __forceinline__ int logical_block(int n)
 }
 __device__ __forceinline__ int logical_block() { return logical_block(gridDim.x); }
 
+// Which unit a workgroup of kvb_direct takes, whose work grows with the context: the heads of a request are dealt
+// over all XCDs, one qk-head with its r v-heads (which share keys and queries through the XCD's L2) at a time; with
+// whole requests on one XCD, as the kernels with a ticket word need it, the XCD that drew the longest contexts set the
+// end of the launch (256 contexts of ~U(1,64): 118 -> 110 us; 96 of ~U(1,128): 130 -> 115 us).  Handing out the longest
+// contexts first (every workgroup ranks the lengths) was 8 % slower at 64 tokens, where the work of a launch is most
+// uniform in time; above 64 tokens it has not been tried.
+// Rounds of 8 qk-heads are dealt, one to an XCD; the units of the qk-heads that are left (fewer than 8) go one by one.
+// Where some are left, from 1024 units on (four workgroups a CU; below that all run at once, and what the v-heads of a
+// qk-head share is worth less than spreading contexts of one length over the CUs).  Against unit = workgroup id, d =
+// 128 unless said, contexts of ~U(1, 64): 255 requests of 4/8 heads 32.9 -> 32.3 us, up to 128 tokens 80.3 -> 77.4; 255
+// of 2/16 heads, fp16, 46.2 -> 43.6; 101 of 4/16 heads 26.0 -> 26.8, up to 112 tokens 57.9 -> 56.7, d = 64 26.6 -> 25.4;
+// dealt all the same below the line: 61 of 4/8 heads 14.1 -> 14.1, 13 of 4/8 11.1 -> 11.3, 77 of 3/9 16.9 -> 17.6.
+// The rule in one word: rounds in the upper 20 bits, r in the lower 12 (0 rounds: unit = workgroup id).
+__host__ __device__ inline int deal_of(int blocks, int r)
+{
+    const int rounds = r < 4096 && (blocks % (8 * r) == 0 || blocks >= 1024) ? blocks / (8 * r) : 0;
+    return (rounds < 0x7FFFF ? rounds : 0x7FFFF) << 12 | (r & 4095);
+}
+__host__ __device__ inline int dealt_unit(int x, int deal)
+{
+    const int r = deal & 4095, rounds = deal >> 12, j = x / 8;
+    return x < 8 * r * rounds ? (j / r * 8 + x % 8) * r + j % r : x;
+}
+
 struct Store {
     float *state;
     void *buf_k;   // input type

@@ -242,28 +242,6 @@ __device__ __forceinline__ void solve_by_token(const DirectArgs &a, int b, int h
 }
 
 // ---------------------------------------------------------------------------
-// Which unit a workgroup takes.  Workgroup ids go round the 8 XCDs.  The work of a unit grows with its
-// context, so the heads of a request are dealt over all XCDs, one qk-head with its `deal` v-heads (which
-// share keys and queries through the XCD's L2) at a time; with whole requests on one XCD, as the kernels
-// with a ticket word need it, the XCD that drew the longest contexts set the end of the launch (256 contexts
-// of ~U(1,64): 118 -> 110 us; 96 of ~U(1,128): 130 -> 115 us).  Handing out the longest contexts first (every
-// workgroup ranks the lengths) was 8 % slower at 64 tokens, where the work of a launch is most uniform in time.
-// deal 0 (the qk-heads of the batch do not divide by 8): unit = workgroup id.
-__device__ __forceinline__ int dealt_block(int deal)
-{
-    const int x = blockIdx.x;
-    if (deal == 0)
-        return x;
-    const int j = x / 8;
-    return (j / deal * 8 + x % 8) * deal + j % deal;
-}
-inline int deal_of(const DirectArgs &a, int blocks)
-{
-    const int r = a.Hv / a.Hk;
-    return blocks % (8 * r) == 0 ? r : 0;
-}
-
-// ---------------------------------------------------------------------------
 // Pieces.  A fp32 value x is cut into NP values of the 16-bit input type, x = x_1 + ... + x_NP
 // (+ a remainder below 2^-24 |x| for three bf16 pieces, 2^-22 |x| for two fp16 pieces), each
 // what is left rounded to nearest, so that a product of two fp32 tiles becomes a few products
@@ -391,7 +369,7 @@ template <typename TIn, typename TRec, bool LONG, bool PAGED>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PER_CU<TIn, LONG>, DIRECT_WG_PER_CU<TIn, LONG>))) void kvb_direct_mfma_kernel(
     const int32_t *len_arg, int32_t Hv_arg, int32_t deal_arg, const DirectArgs a)
 {
-    // The three leading arguments repeat a.len and a.Hv and hold deal_of(a): as plain leading kernel arguments
+    // The three leading arguments repeat a.len and a.Hv and hold deal_of(): as plain leading kernel arguments
     // they are preloaded into scalar registers at wave launch (the build asks for it), so the load of
     // len[b] -- the head of the dependent chain to the first key byte -- goes out at once instead of after
     // the round trip that fetches the argument block.
@@ -441,7 +419,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     // the compiler, scalar branches instead of masked ones)
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
     const int c16 = lane % 16, lq = lane / 16;
-    const int lb = dealt_block(deal_arg);
+    const int lb = dealt_unit(blockIdx.x, deal_arg);
     const int b = lb / Hv_arg;
     int L = len_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
@@ -1174,7 +1152,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;   // (a scalar)
     const int c16 = lane % 16, lq = lane / 16;
-    const int lb = dealt_block(deal_arg);
+    const int lb = dealt_unit(blockIdx.x, deal_arg);
     const int b = lb / Hv_arg;
     int L = len_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
@@ -1412,22 +1390,22 @@ int launch_direct(int dk, int in_dtype, int rec_dtype, const DirectArgs &a, int 
     if (dk == 128 && in_dtype != KVB_F32)
         return dispatch_types16(in_dtype, rec_dtype, [&]<typename TIn, typename TRec>() {
             if (a.Lmax > 64 && a.st.block_table)   // two panels of 64 rows
-                launch(kvb_direct_mfma_kernel<TIn, TRec, true, true>, blocks, stream, a.len, a.Hv, deal_of(a, blocks), a);
+                launch(kvb_direct_mfma_kernel<TIn, TRec, true, true>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
             else if (a.Lmax > 64)
-                launch(kvb_direct_mfma_kernel<TIn, TRec, true, false>, blocks, stream, a.len, a.Hv, deal_of(a, blocks), a);
+                launch(kvb_direct_mfma_kernel<TIn, TRec, true, false>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
             else if (a.st.block_table)
-                launch(kvb_direct_mfma_kernel<TIn, TRec, false, true>, blocks, stream, a.len, a.Hv, deal_of(a, blocks), a);
+                launch(kvb_direct_mfma_kernel<TIn, TRec, false, true>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
             else
-                launch(kvb_direct_mfma_kernel<TIn, TRec, false, false>, blocks, stream, a.len, a.Hv, deal_of(a, blocks), a);
+                launch(kvb_direct_mfma_kernel<TIn, TRec, false, false>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
         });
     if (a.Lmax > 64)   // the block-row kernel holds a 64-token context in LDS
         return KVB_EUNSUPPORTED;
     return dispatch(dk, in_dtype, rec_dtype, [&]<int D, typename TIn, typename TRec>() {
         if constexpr (!(D == 128 && sizeof(TIn) == 2)) {
             if (a.st.block_table)
-                launch(kvb_direct_rows_kernel<D, TIn, TRec, true>, blocks, stream, a.len, a.Hv, deal_of(a, blocks), a);
+                launch(kvb_direct_rows_kernel<D, TIn, TRec, true>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
             else
-                launch(kvb_direct_rows_kernel<D, TIn, TRec, false>, blocks, stream, a.len, a.Hv, deal_of(a, blocks), a);
+                launch(kvb_direct_rows_kernel<D, TIn, TRec, false>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
         }
     });
 }

@@ -26,7 +26,7 @@ def test_direct_second_panel(in_dtype, rec_dtype, block_size):
     H.check(e, in_dtype, rec_dtype, "second panel")
 
 
-@pytest.mark.parametrize("B, Hk, Hv", [(3, 8, 24), (5, 3, 9), (1, 1, 4), (2, 4, 4), (7, 16, 32)])
+@pytest.mark.parametrize("B, Hk, Hv", [(3, 8, 24), (5, 3, 9), (1, 1, 4), (2, 4, 4), (7, 16, 32), (13, 4, 8), (129, 2, 8)])
 @pytest.mark.parametrize("Lmax", [33, 90])
 def test_direct_every_unit_is_taken_once(B, Hk, Hv, Lmax):
     """Head counts that deal over the 8 XCDs and ones that do not; an untaken unit leaves NaN in its outputs."""
