@@ -108,10 +108,11 @@ def test_decode_from_the_buffer_alone(B, Hk, Hv, d, in_dtype, rec_dtype, block_s
     e = _direct_case(B=B, Hk=Hk, Hv=Hv, d=d, Lmax=Lmax, cap=cap, in_dtype=in_dtype, seed=870 + B, lens=lens,
                      rec_dtype=rec_dtype, out_dtype=rec_dtype, block_size=block_size)
     say("buffer alone, B=%d heads %d/%d d=%d %s/%s: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((B, Hk, Hv, d, in_dtype, rec_dtype) + e))
-    # (the state folded afterwards is the flush tests' matter.  Its error is measured against an RMS that a quarter of
-    # the requests, with 0 or 1 record, pull down: fp32 sums of 65 records may stand 65 * 2^-24 * max / RMS = 4e-6 *
-    # max / RMS off, above 1e-5 here; the vector-ALU kernels that this path ran on before read 1.2e-5 too)
-    H.check(e[:3], in_dtype, rec_dtype, "buffer alone")
+    # fp32: the state folded afterwards is a sum of up to 65 records, each off by 2^-24 of its size, and the error is
+    # measured against an RMS that a quarter of the requests, with 0 or 1 record, pull down: the largest element is 13.5
+    # times the RMS (d = 64) and 12.0 (d = 32) in the oracle's states
+    H.check(e if in_dtype != "f32" else e[:3], in_dtype, rec_dtype, "buffer alone")
+    assert in_dtype != "f32" or e[3] < 65 * 2.0 ** -24 * 13.6, e
 
 
 @pytest.mark.parametrize("in_dtype, Lmax", [("bf16", 64), ("bf16", 128), ("f16", 128)])
