@@ -664,9 +664,20 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 // trip for each block that the fill reaches.
 // Rule (launch_buffer_step): two heads a workgroup as soon as that leaves one for every CU; below, the halves of
 // the chip that would stay idle are worth more.  Passes beyond the fill load a valid record and compute nothing.
-// 128 requests of 32 heads, fp16 records: 8 records 21.9 -> 14.4 us, 60 23.5 -> 21.5, 110 35.3 -> 33.1; fp32 records:
-// 21.3 -> 16.1, 32.2 -> 29.4, 48.9 -> 48.2; 32 requests, fp32 keys, 1..60 records: 12.6 -> 8.3; 8 requests (one head a
-// workgroup): 6.8 -> 6.4.
+// Against kvb_step_kernel, which had this path before, d = 128, 128 requests of 32 heads, fp16 records: 8 records
+// 21.9 -> 14.4 us, 60 23.5 -> 21.5, 110 35.3 -> 33.1; fp32 records: 21.3 -> 16.1, 32.2 -> 29.4, 48.9 -> 48.2.
+// One head a workgroup / two, 32 heads, us a call, each request at its own fill:
+//                           0..60 records                          0..10 records       0..119 records
+//   requests                16           32           128          32           128    128
+//   d = 128, bf16 / fp32    10.6 /  8.0  12.6 /  9.9  21.3 / 20.7  11.3 / 8.1  16.3 / 14.5  32.3 / 33.3
+//   d = 128, fp16 / fp16    10.4 /  9.1  12.5 /  9.9  18.7 / 17.4  11.2 / 7.8  16.4 / 13.0  25.9 / 25.3
+//   d = 64,  bf16 / fp32    10.7 /  7.8  11.0 /  8.1  17.1 / 13.4  10.9 / 8.0  16.1 / 11.3  20.7 / 19.5
+//   d = 64,  fp32           10.7 /  7.8  11.3 /  8.0  17.7 / 14.9  11.2 / 7.9  16.3 / 11.6  21.1 / 20.7
+//   d = 32,  fp16 / fp16    10.2 /  7.6  10.8 /  7.9  16.6 / 11.3  10.7 / 7.8  16.0 / 10.8  16.8 / 13.0
+//   d = 32,  fp32           10.5 /  7.6  10.8 /  8.0  16.4 / 11.4  10.7 / 7.8  16.5 / 11.2  18.0 / 15.8
+// 8 requests (256 units), 0..60 records, d = 128: 7.4 / 7.3 with bf16 / fp32, 7.1 / 7.7 with fp16; d = 64 7.3 / 6.2,
+// d = 32 7.1 / 6.0: the line lies where two heads are better with every size and type (but the fp32 records of 128
+// requests at 0..119).
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int HB, bool PAGED>
 __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot_arg, int32_t nu_arg, int32_t nblocks_arg,
