@@ -129,7 +129,11 @@ typedef struct kvb_store {
 
 /*
  * All compute calls take `slot`: device int32 [B], the store slot of request b.
- * A slot must not appear twice in one call.  state, buf_k, buf_u, q, k, v and
+ * A slot must not appear twice in one call.  Infinities and NaN reach what the formulas pass
+ * them to, with two exceptions for 16-bit inputs at d = 128: kvb_flush makes NaN of the state
+ * column of an infinite delta value and of the state row of an infinite key (kvb_decode_flush
+ * keeps them infinite), and in kvb_verify / kvb_verify_tree a draft whose key is not finite may
+ * make the request's other drafts NaN.  state, buf_k, buf_u, q, k, v and
  * out must be 16-byte aligned; the int32 / float vectors 4-byte aligned.
  */
 
@@ -240,9 +244,13 @@ int kvb_compact(const kvb_shape *shape, const kvb_store *store, const int32_t *s
  *   out   device [B, Lmax, Hv, dv] out_dtype; rows >= len[b] are not written
  * len[b] outside 0..Lmax is clamped to Lmax with KVB_STATUS_OVERFLOW.
  * With a 16-bit rec_dtype the outputs read the records as stored (rounded), like everywhere
- * else; the delta values themselves are solved for in fp32 before they are rounded -- all
- * rows at once up to 64 tokens, 64 rows at a time above that (d = 128) -- so a row's delta
- * value does not see the rounding of the rows solved with it.
+ * else; a row's delta value reads the stored records of the rows solved before it, and the
+ * rows solved with it as follows.  d = 128: 64 rows are solved for in fp32 and rounded
+ * afterwards, so none sees the rounding of the others.  d = 32 and 64: 16 rows are solved for in
+ * fp32, and once more from the rounded values of that first solution; the second solution is
+ * rounded and stored (it differs from solving row by row only where rounding the first one
+ * differs from rounding the second).
+ * A head of a context whose outputs are not all finite is solved token by token (slower).
  */
 int kvb_direct(const kvb_shape *shape, const kvb_store *store, const int32_t *slot,
                const int32_t *len, int32_t Lmax,

@@ -12,10 +12,10 @@
 // Element types (Sec. 4.1: 16-bit vectors and records beside a fp32 state): TIn is the type of
 // q, k, v and of the buffered keys (float, bf16_t or f16_t), TRec that of the buffered delta
 // values (float, or TIn when that is 16-bit); outputs are fp32 or TIn, chosen at run time at the
-// final store.  All arithmetic is fp32.
+// final store.  All arithmetic is fp32, or on 16-bit pieces of fp32 values with fp32 sums.
 //
-// Work decomposition (every kernel): one 256-thread workgroup per (request b,
-// v-head h); the committed state S0[dk][dv] (fp32, dv contiguous, 64 KB at
+// Work decomposition: one 256-thread workgroup per (request b, v-head h), in
+// kvb_buffer_step_kernel per request and one or two v-heads; the committed state S0[dk][dv] (fp32, dv contiguous, 64 KB at
 // d = 128) is streamed exactly once per call.  Besides the state a unit needs
 // its buffered keys k_l, delta values u_l and cumulative log decays G_l (paper
 // App. A.1, the paragraph after Eq. 16), a few KB.

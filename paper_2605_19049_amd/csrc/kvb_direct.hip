@@ -337,8 +337,9 @@ __device__ __forceinline__ f32x4_t mm16_pieces(const uint2 (&x)[NPX], const uint
 //     A_10 = -T_1 N_10 T_0                     A_32 = -T_3 N_32 T_2
 //     W = C P^-1:  W_20 = (N_20 - N_21 T_1 N_10) T_0    W_21 = N_21 T_1      (same for row 3)
 //     A_20 = -T_2 W_20   A_21 = -T_2 W_21   A_30 = -(A_32 W_20 + T_3 W_30)   A_31 = -(A_32 W_21 + T_3 W_31)
-// Every entry of A is a key-to-key product through a chain of contractions (I - beta k^T k), so
-// it is bounded by 1 whatever the keys: forming the inverse loses nothing here.  The four waves
+// Every entry of A is a key-to-key product through a chain of factors (I - beta k^T k); where these
+// contract (beta |k|^2 <= 2, so for normalised keys, however they are correlated) it is bounded by
+// |k|^2: forming the inverse loses nothing here.  The four waves
 // share this work tile by tile; tiles cross LDS row-major, so that a reader takes them in
 // A-form (one 16-byte read) or in B-form (four 4-byte reads, the transposed access).
 //
@@ -355,14 +356,15 @@ __device__ __forceinline__ f32x4_t mm16_pieces(const uint2 (&x)[NPX], const uint
 // does.  A context of up to 64 tokens in a LONG launch leaves after the first panel.  The line to LONG
 // lies at Lmax = 64 because the 64-row kernel is the faster one there (four or five workgroups per CU
 // instead of three).  Bound by the issue of vector and matrix instructions at three long-lived waves per
-// SIMD.  96 contexts of ~U(1,128), 32 heads, bf16 with fp32 records: 192 -> 130 us against the kernel
+// SIMD.  96 contexts of ~U(1,128), 32 heads, bf16 with fp32 records: 192 -> 130 us (without the fold) against the kernel
 // before it (8 block rows solved one after the other with fp32 matrix instructions); 128 of ~U(1,100),
 // fp16 throughout: 193 -> 127 us.  Two workgroups per CU without any spill were 5 % slower than three that
-// spill 32 words of the weighted query tiles; pieces of U_0 kept in registers instead of cut again: two fit.
+// spill (with fp32 records 19 words for bf16 and 12 for fp16, with 16-bit records 9 and 8; paged 12, 12, 0, 0);
+// pieces of U_0 kept in registers instead of cut again: two fit.
 // ---------------------------------------------------------------------------
 // Workgroups per CU: the two fp16 pieces need 28 KB of LDS and 92 registers, which leaves room for
 // five (6 % faster than four on ragged lengths); the three bf16 pieces need 36 KB and 124.
-// LONG: 46 KB and 168 registers, three.
+// LONG: 53 KB and 168 registers, three.
 template <typename T, bool LONG>
 constexpr int DIRECT_WG_PER_CU = LONG ? 3 : __is_same(T, f16_t) ? 5 : 4;
 template <typename TIn, typename TRec, bool LONG, bool PAGED>
