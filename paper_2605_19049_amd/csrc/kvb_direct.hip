@@ -1130,8 +1130,10 @@ __device__ __forceinline__ f32x4_t gram_rows(const TIn *rows, const u32x4_t (&ow
 }
 
 template <int D, typename TIn, typename TRec, bool PAGED>
-// (register budgets: 4 workgroups per CU; fp32 rows of 128 take 55 KB of LDS, two)
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4))) void kvb_direct_rows_kernel(
+// (register budgets: 4 workgroups per CU; fp32 rows of 128 take 55 KB of LDS, two; 16-bit rows of 32 with fp32 records
+// 26 KB, and six were 6 % faster than five at 500 requests of 32 heads)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
+    D == 128 ? 2 : D == 32 && sizeof(TIn) == 2 && sizeof(TRec) == 4 ? 6 : 4))) void kvb_direct_rows_kernel(
     const int32_t *len_arg, int32_t Hv_arg, int32_t deal_arg, const DirectArgs a)
 {
     // (leading arguments: see kvb_direct_mfma_kernel)
