@@ -105,8 +105,8 @@ typedef struct kvb_store {
     float   *buf_G;   /* device [n_slots, Hv, cap]     fp32                                 */
     int32_t *fill;    /* device [n_slots]; 0..cap between calls.  While a call that changes
                          fill runs, bits 16.. of the word count the workgroups that have
-                         read it; the last one stores the new fill, so the word is a plain
-                         count again when the call's kernel ends.                           */
+                         read it; the last one brings it back to a plain count, which it is
+                         again when the call's kernel ends.                                 */
     int32_t *status;  /* device [n_slots] sticky KVB_STATUS_* bits, or NULL                 */
     int32_t  n_slots; /* slots in the arrays above; requests whose slot is outside
                          0..n_slots-1 are skipped                                           */

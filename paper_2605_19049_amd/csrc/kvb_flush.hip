@@ -55,10 +55,11 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     if (s < 0 || s >= a.st.n_slots)
         return;
     const int blk_id = load_block_id<PAGED>(a.st, s, lane);
-    const int f = a.st.fill[s] & FILL_MASK;
+    const int word = a.st.fill[s];
     int nacc = a.accepted ? a.accepted[b] : 0;
     if (nacc < 0)
         nacc = 0;
+    const int f = fill_before_commit(word, nacc);
     int m = f + nacc;
     if (m > cap) {
         m = cap;
@@ -68,8 +69,11 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     // (no state: a KV-only context, Sec. 3.4 -- the call then only commits accepted drafts)
     const bool do_flush = a.st.state != nullptr && m >= a.threshold && m > 0;
     if (!do_flush) {
-        if (m != f)   // fill only moves when something was accepted
+        // (fill only moves when something was accepted)
+        if (m != f + nacc)
             publish_fill(&a.st.fill[s], a.Hv, m);
+        else if (nacc > 0)
+            advance_fill(&a.st.fill[s], h == 0, a.Hv, nacc);
         return;
     }
     const size_t unit = (size_t)s * a.Hv + h;
@@ -232,10 +236,11 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 
     if (s < 0 || s >= a.st.n_slots)
         return;
-    const int f = a.st.fill[s] & FILL_MASK;
+    const int word = a.st.fill[s];
     int nacc = a.accepted ? a.accepted[b] : 0;
     if (nacc < 0)
         nacc = 0;
+    const int f = fill_before_commit(word, nacc);
     int m = f + nacc;
     if (m > cap) {
         m = cap;
@@ -244,8 +249,10 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     }
     const bool do_flush = a.st.state != nullptr && m >= a.threshold && m > 0;
     if (!do_flush) {
-        if (m != f)
+        if (m != f + nacc)
             publish_fill(&a.st.fill[s], a.Hv, m);
+        else if (nacc > 0)
+            advance_fill(&a.st.fill[s], h == 0, a.Hv, nacc);
         return;
     }
     const size_t unit = (size_t)s * a.Hv + h;

@@ -137,12 +137,10 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     // scalars of the token (uniform); requested together with the fill, after the state loads,
     // so that no scalar wait stands between the slot and the first state byte
     const float gnew = a.g[(size_t)b * a.Hv + h], bet = a.beta[(size_t)b * a.Hv + h];
-    const int f = a.st.fill[s] & FILL_MASK;
+    const int f = fill_before(a.st.fill[s], a.threshold - 1);
     if (f + 1 > cap) {
         if (tid == 0 && a.st.status)
             atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
-        if (a.advance)
-            publish_fill(&a.st.fill[s], a.Hv, f);
         return;
     }
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[tid / 64], tid % 64, blk_id);
@@ -172,11 +170,11 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     if constexpr (!EARLY)
         issue_state();
     __builtin_amdgcn_sched_barrier(0);
-    // youngest memory operation of the wave: nothing waits for it before the very end
-    // (EARLY: behind the barrier that it needs anyway, below)
-    int ticket = 0;
-    if (!EARLY && a.advance)
-        ticket = take_ticket(&a.st.fill[s]);
+    // (uniform over the workgroup, and over the request.  A buffer that was due earlier: its fill does not follow from 0)
+    const bool fold = FUSE && f + 1 >= a.threshold, overdue = FUSE && f + 1 > a.threshold;
+    // youngest memory operation of the wave (EARLY: behind the barrier that it needs anyway, below)
+    if (!EARLY && a.advance && !overdue)
+        advance_fill(&a.st.fill[s], h == 0, a.Hv, fold ? -f : 1);
 
     // ---- 3. decayed dot products of the new rows with every earlier key ----
     float q8[8], k8[8];
@@ -206,8 +204,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
             // the state rows are consumed first, in the order they were issued; the records
             // (younger loads) are not touched before the last state row has been used
             __syncthreads();
-            if (a.advance)
-                ticket = take_ticket_read(&a.st.fill[s]);
+            if (a.advance && !overdue)
+                advance_fill_read(&a.st.fill[s], h == 0, a.Hv, fold ? -f : 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int p = 0; p < NPASS; ++p) {
@@ -378,10 +376,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     if (h % r == 0 && tid < D / 8)   // the threads that loaded the new k row store it
         store_raw8(static_cast<TIn *>(a.st.buf_k) + rk(f) * D + 8 * sub, k_raw);
     const int m = f + 1;
-    const bool fold = FUSE && m >= a.threshold;   // uniform over the workgroup (and over the request)
-    // (ahead of the fold, which has no register to spare for the ticket: what the word orders are reads of itself)
-    if (a.advance && tid == 0)
-        publish_if_last(&a.st.fill[s], ticket, a.Hv, fold ? 0 : m);
+    if (overdue)
+        publish_fill(&a.st.fill[s], a.Hv, 0);
     if constexpr (FUSE) {
         if (fold) {
             const float gam = expf(Gc);
@@ -730,12 +726,10 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
     const TIn v_raw = static_cast<const TIn *>(a.v)[((size_t)b * a.Hv + h0 + jc) * D + tid % D];
     const float bet = a.beta[(size_t)b * a.Hv + h0 + jc];
     const float g_w = a.g[(size_t)b * a.Hv + h0 + jw];
-    const int f = a.st.fill[s] & FILL_MASK;
+    const int f = fill_before(a.st.fill[s], 0);
     if (f + 1 > cap) {
         if (tid == 0 && a.st.status)
             atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
-        if (a.advance)
-            publish_fill(&a.st.fill[s], nu_arg, f);
         return;
     }
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[tid / 64], tid % 64, blk_id);
@@ -751,7 +745,6 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
         accU[j] = accO[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     unpack8(q_raw, q8);
     unpack8(k_raw, k8);
-    int ticket = 0;
     for (int l0 = 0; l0 == 0 || l0 < f; l0 += WREC) {   // uniform
         // raw bits from always-valid addresses: an index past the fill is clamped to record 0, its value ignored
         Raw8<TIn> kl_raw[KP];
@@ -772,7 +765,7 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
         }
         __builtin_amdgcn_sched_barrier(0);
         if (l0 == 0 && a.advance)
-            ticket = take_ticket(&a.st.fill[s]);
+            advance_fill(&a.st.fill[s], lb % nu_arg == 0, nu_arg, 1);
 #pragma unroll
         for (int p = 0; p < KP; ++p) {
             const int l = l0 + grp + NG * p;
@@ -856,8 +849,6 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
         a.st.buf_G[ru(f, jw)] = Gc;
     if (h0 == hk * r && tid < D / 8)   // the threads that loaded the new k row store it
         store_raw8(static_cast<TIn *>(a.st.buf_k) + rk(f) * D + 8 * sub, k_raw);
-    if (a.advance && tid == 0)
-        publish_if_last(&a.st.fill[s], ticket, nu_arg, f + 1);
 }
 
 // ---------------------------------------------------------------------------

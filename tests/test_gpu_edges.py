@@ -4,6 +4,7 @@ The bounds are harness.check's: the parity bound of the types and, with fp32 rec
 """
 import numpy as np
 import pytest
+import torch
 
 import harness as H
 from harness import oracle
@@ -142,3 +143,35 @@ def test_direct_products_of_full_fp32_factors(in_dtype, Lmax):
     e = (H.host(out)[0].astype(np.float64) - want) / want
     say("direct, full fp32 factors, %s Lmax=%d: error max %.2e mean %.2e" % (in_dtype, Lmax, np.abs(e).max(), e.mean()))
     assert np.abs(e).max() < 2.4e-7 and abs(e.mean()) < 1e-8, (np.abs(e).max(), e.mean())
+
+
+@pytest.mark.parametrize("d, in_dtype, cap", [(128, "bf16", 16), (128, "f16", 64), (64, "bf16", 64), (128, "f32", 32)])
+@pytest.mark.parametrize("Hk, Hv", [(1, 1), (2, 4)])
+def test_fold_of_an_overdue_buffer(d, in_dtype, cap, Hk, Hv):
+    """kvb_decode_flush whose threshold lies below, at and above the records that a request holds with its new token:
+    every fill is a plain count again, and the state that a last kvb_flush completes is the recurrence's."""
+    rng = np.random.default_rng(880 + cap + Hv)
+    fills, C = np.array([0, 4, 5, 6, cap - 1, 3], np.int32), 6
+    B, n = len(fills), int(fills.max()) + 1
+    S0 = H.prefix_state(rng, B, Hk, Hv, d, d, in_dtype, 8)
+    tok = synth.token_stream(rng, B, n, Hk, Hv, d, d, in_dtype)
+    dtok = H.upload_tokens(tok, in_dtype)
+    lay = H.Layer(B, Hk, Hv, d, d, cap, in_dtype)
+    lay.set_state(S0)
+    out = lay.new_out(B, Hv, d)
+    for t in range(n - 1):   # request b joins so that all end at token n - 1
+        who = np.flatnonzero(fills >= n - 1 - t)
+        view = {x: y[torch.from_numpy(who).cuda(), t].contiguous() for x, y in dtok.items()}
+        lay.decode(view, lay.new_out(len(who), Hv, d), slot=lay.slot[torch.from_numpy(who).cuda()].contiguous(), B=len(who))
+    assert np.array_equal(lay.fill(), fills)
+    lay.decode_flush(H.step_view(dtok, n - 1), out, C)
+    assert np.array_equal(lay.fill(), np.where(fills + 1 >= C, 0, fills + 1))
+    lay.flush(1)
+    assert np.array_equal(lay.fill(), np.zeros(B, np.int32)) and not lay.status().any()
+    errs = []
+    for b in range(B):
+        own = {x: y[b:b + 1, n - 1 - fills[b]:] for x, y in tok.items()}
+        o, _, S, _ = oracle.gdn_sequence(S0[b:b + 1].astype(np.float64), own["q"], own["k"], own["v"], own["g"], own["beta"])
+        errs += [H.rel_err(H.host(out[b]), o[0, -1]), H.rel_err(lay.get_state()[b], S[0])]
+    say("overdue buffer, d=%d %s: rel err %.2e" % (d, in_dtype, max(errs)))
+    H.check(errs, in_dtype, what="overdue buffer")
