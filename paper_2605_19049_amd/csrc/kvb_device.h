@@ -508,6 +508,26 @@ struct Pages {
         return ((size_t)blk(l) * H + head) * bs + off(l);
     }
 };
+// The records of one head as an array of rows of E elements (a scalar address and 32 bits of offset where the rows of a
+// slot are contiguous: with 64-bit arithmetic for each load a wave alone on its SIMD spends a microsecond on addresses).
+template <int E, typename T, bool PAGED>
+struct Rows {
+    T *p;   // contiguous: record 0 of the head; paged: the pool
+    Pages<PAGED> pg;
+    int H, head;
+    __device__ __forceinline__ T *at(int l, int e) const   // element e of record l
+    {
+        if constexpr (PAGED)
+            return p + pg.row(l, H, head) * E + e;
+        else
+            return reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(p) + (uint32_t)((l * E + e) * (int)sizeof(T)));
+    }
+};
+template <int E, bool PAGED, typename T>
+__device__ __forceinline__ Rows<E, T, PAGED> make_rows(T *pool, const Pages<PAGED> &pg, int H, int head)
+{
+    return Rows<E, T, PAGED>{PAGED ? pool : pool + ((size_t)pg.s * H + head) * pg.bs * E, pg, H, head};
+}
 // The lane's entry of the block-table row (lanes >= max_blocks repeat the last entry).
 template <bool PAGED>
 __device__ __forceinline__ int load_block_id(const Store &st, int s, int lane)
@@ -612,18 +632,10 @@ void launch(void (*kernel)(Params...), int blocks, hipStream_t stream, const Arg
 }
 
 // Picks the paged or the contiguous instance of a kernel template whose last parameter is PAGED;
-// the arguments after `a` are the kernel's name and its leading template arguments.
-#define LAUNCH_PAGED(blocks, stream, a, ...)                          \
-    do {                                                              \
-        if ((a).st.block_table)                                       \
-            launch(__VA_ARGS__, true>, blocks, stream, a);            \
-        else                                                          \
-            launch(__VA_ARGS__, false>, blocks, stream, a);           \
-    } while (0)
-
-// The same for kernels that take (slot, Hv, grid size) as three plain leading arguments ahead of the
-// argument struct: the build preloads the first kernel-argument words into scalar registers at wave
-// launch, so the load of slot[b] -- the head of every dependent chain -- goes out at once.
+// the arguments after `a` are the kernel's name and its leading template arguments.  They take
+// (slot, Hv, grid size) as three plain leading arguments ahead of the argument struct: the build preloads the first
+// kernel-argument words into scalar registers at wave launch, so the load of slot[b] -- the head of every dependent
+// chain -- goes out at once.
 #define LAUNCH_LEAD(blocks, stream, a, ...)                                            \
     do {                                                                               \
         if ((a).st.block_table)                                                        \

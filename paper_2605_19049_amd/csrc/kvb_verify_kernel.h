@@ -107,6 +107,9 @@ __device__ __forceinline__ f32x4_t dot_tile(const uint4 (&a)[N], const uint4 (&b
 // multiply-adds for every state row and record.  Verify and commit, 24 requests of 16 heads, fp32, 5 drafts:
 // 31.5 -> 21.1 us; with the commit's own move off the vector ALU, 150 of 16 heads, fp32, 3 drafts: 100 -> 68 us;
 // 200 of 32, d = 64, 4 drafts: 92 -> 55 us.
+// With a workgroup to a CU, every phase is as long as its instructions: the drafts' decays are worked out a draft to a
+// lane (draft after draft in scalar registers took 1.0 us, now 0.23) and record addresses are 32-bit offsets: 7 requests
+// of 32 heads, 8 tree drafts, fp16, with compaction and commit, 24.5 -> 23.9 us (every workgroup 8.8 -> 7.8).
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int WREC, bool HAS_STATE, bool STREAM, bool PAGED>
 // (register budgets: 4 waves per SIMD with a record window of 16 or 32, 3 with the 64-record window or with
@@ -135,7 +138,8 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     __shared__ __attribute__((aligned(16))) float cW[NTILE * 16][16];
     __shared__ __attribute__((aligned(16))) float fin[16][D];
     __shared__ int sBlk[NW][MAX_BLOCKS];
-    __shared__ float sGc[TAIL ? NW : 1][TMX];   // per-wave table for the keys beyond the register window
+    __shared__ __attribute__((aligned(16))) float sGc[NW][TMX], sGam[NW][TMX];   // by draft: G and exp(G), each wave's own copy
+    __shared__ __attribute__((aligned(16))) int sAnc[NW][TMX];                   // ancestors
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;   // (a scalar)
     const int lb = logical_block(nblocks_arg);
@@ -154,9 +158,6 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     const TIn *qin = static_cast<const TIn *>(a.q);
     const TIn *kin = static_cast<const TIn *>(a.k);
     const TIn *vin = static_cast<const TIn *>(a.v);
-    const float *Gbuf = a.st.buf_G;                          // record l of this head: Gbuf[ru(l)]
-    const TIn *kb = static_cast<const TIn *>(a.st.buf_k);    //                        kb + rk(l) * D
-    const TRec *ub = static_cast<const TRec *>(a.st.buf_u);  //                        ub + ru(l) * D
     const Out<TIn> out{a.out, a.out_wide != 0};
     const int blk_id = load_block_id<PAGED>(a.st, s, lane);
 
@@ -171,6 +172,14 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
 #pragma unroll
     for (int st = 0; st < NWA; ++st)
         wa[st] = *reinterpret_cast<const uint4 *>(wrow + 4 * EW * st);
+
+    // scalars of draft lane % 8, one vector load each (a scalar load per draft costs a round trip each while the chip
+    // is streaming)
+    const int di = lane % 8;
+    const uint32_t go = (uint32_t)min(di, T - 1) * a.Hv;
+    float g_raw = (a.g + (size_t)b * T * a.Hv + h)[go];
+    float beta_mine = (a.beta + (size_t)b * T * a.Hv + h)[go];
+    int par_raw = a.parent[(size_t)b * T + min(di, T - 1)];
 
     // ---- 2. the state: rows 4 st + lq, the wave's columns --------------------
     // EARLY: the state's address needs the slot only, so its loads go out before the fill is
@@ -203,30 +212,30 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     }
     const int nrec = f + T;
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[wave], lane, blk_id);
-    auto ru = [&](int l) { return pg.row(l, a.Hv, h); };
-    auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };
+    const auto krec = make_rows<D>(static_cast<TIn *>(a.st.buf_k), pg, a.Hk, hk);
+    const auto urec = make_rows<D>(static_cast<TRec *>(a.st.buf_u), pg, a.Hv, h);
+    const auto Grec = make_rows<1>(a.st.buf_G, pg, a.Hv, h);
+    const TIn *knew = kin + ((size_t)b * T * a.Hk + hk) * D;
+    // 16-byte piece lq of key n of the chunk, a buffered one or a new one
+    auto key_at = [&](int n) {
+        return n < f ? krec.at(min(n, cap - 1), EW * lq)
+                     : knew + (uint32_t)(min(max(n - f, 0), T - 1) * a.Hk * D + EW * lq);
+    };
     const int ntile = (nrec + 15) / 16;
 
     // ---- 3. loads that need the fill ------------------------------------------
-    // per-draft scalars of draft lane % 8, one vector load each (a scalar load per draft costs
-    // a round trip each while the chip is streaming)
-    const size_t go = ((size_t)b * T + min(lane % 8, T - 1)) * a.Hv + h;
-    float g_raw = a.g[go];
-    float beta_mine = a.beta[go];
-    int par_raw = a.parent[(size_t)b * T + min(lane % 8, T - 1)];
-    float G_prev = f > 0 ? Gbuf[ru(f - 1)] : 0.0f;
+    float G_prev = f > 0 ? *Grec.at(f - 1, 0) : 0.0f;
     // keys of this wave's tiles (buffered first, then the new ones)
     uint4 kt[NTW][NWA];
     float Gn[NTW];
 #pragma unroll
     for (int x = 0; x < NTW; ++x) {
         const int n = 16 * (wave + NW * x) + lm;
-        const TIn *kp = n < f ? kb + rk(n) * D
-                              : kin + (((size_t)b * T + min(max(n - f, 0), T - 1)) * a.Hk + hk) * D;
-        Gn[x] = Gbuf[ru(n < f ? n : 0)];
+        const TIn *kp = key_at(n);
+        Gn[x] = *Grec.at(n < f ? n : 0, 0);
 #pragma unroll
         for (int st = 0; st < NWA; ++st)
-            kt[x][st] = *reinterpret_cast<const uint4 *>(kp + EW * lq + 4 * EW * st);
+            kt[x][st] = *reinterpret_cast<const uint4 *>(kp + 4 * EW * st);
     }
     // buffered delta values: quad sq = records 4 sq .. 4 sq + 3, this lane: record 4 sq + lq,
     // columns col2 (d = 128: and the next)
@@ -234,75 +243,66 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
 #pragma unroll
     for (int sq = 0; sq < WQ; ++sq) {
         const int l = 4 * sq + lq;
-        uq[sq] = load_raw_cols<CT>(ub + ru(l < f ? l : 0) * D + col2);
+        uq[sq] = load_raw_cols<CT>(static_cast<const TRec *>(urec.at(l < f ? l : 0, col2)));
     }
     // v of this wave's columns (used by its first WC lanes in the last stage)
     const int colf = WC * (wave % NWC) + lane % WC;
+    const TIn *vrow = vin + ((size_t)b * T * a.Hv + h) * D;
     TIn v_raw[TMX];
 #pragma unroll
     for (int i = 0; i < TMX; ++i)
-        v_raw[i] = vin[(((size_t)b * T + min(i, T - 1)) * a.Hv + h) * D + colf];
+        v_raw[i] = vrow[(uint32_t)(min(i, T - 1) * a.Hv * D + colf)];
     __builtin_amdgcn_sched_barrier(0);
 
-    // Cumulative log decays and betas of the drafts as wave-uniform values read from the lanes
-    // that loaded them.  Whatever a lane needs by a draft index of its own is selected here,
-    // while the running sum is in a register: an array indexed at run time would live in
-    // scratch memory, whose loads share the counter of the state loads.
-    float bet[TMX];
-    float GcRow[4];      // of the draft of accumulator row 4 lq + v: draft v (lq even) or 4 + v (lq odd)
-    float GcLm = 0.0f;   // of draft lm % 8 (the row of W this lane loaded)
-    float GcTid = 0.0f;  // of draft tid (the lane that stores it)
-    float GcKey[NTW];    // of the new key this lane holds in window tile x, if it holds one
+    // Drafts form a chain (kvb_verify) or a tree (kvb_verify_tree): the decay of a draft runs along its own root path,
+    // and bit j of its mask is set iff draft j is a strict ancestor.  Lane i of every eight works out draft i: the sum
+    // over the ancestors in the order of the path (which is that of their indices), the ancestors by following parents
+    // packed four bits a draft.  A parent index that does not precede its child is taken as -1 and flagged.
+    int anc = (1 << di) - 1;
+    asm volatile("" : "+v"(par_raw));   // (its load stays above, out of the branch)
+    if (a.tree) {   // uniform
+        const bool bad = par_raw < -1 || par_raw >= di;
+        const int up = bad ? 0 : par_raw + 1;   // parent + 1
+        uint32_t parents = 0;                   // of draft j in bits 4 (j + 1) ..
 #pragma unroll
-    for (int x = 0; x < NTW; ++x)
-        GcKey[x] = 0.0f;
-    // Drafts form a chain (kvb_verify) or a tree (kvb_verify_tree): the decay of draft i runs
-    // along its own root path, and anc_i has bit j set iff draft j is a strict ancestor of i.
-    // A parent index that does not precede its child is taken as -1 and flagged.
-    int ancRow[4];       // ancestor bits of the draft of accumulator row 4 lq + v
-    auto finish_Gc = [&]() {
-        float Gi[TMX];   // wave-uniform; constant indices only
-        int anc[TMX];
-        bool bad = false;
-        const bool tree = a.tree != 0;   // uniform; no load sits behind this branch
+        for (int j = 0; j < TMX - 1; ++j)
+            parents |= (uint32_t)__builtin_amdgcn_readlane(up, j) << (4 * (j + 1));
+        anc = 0;
+        uint32_t at = up;
 #pragma unroll
-        for (int i = 0; i < TMX; ++i) {
-            const float gi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, g_raw), i));
-            bet[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, beta_mine), i));
-            float base = i > 0 ? Gi[i > 0 ? i - 1 : 0] : G_prev;   // chain: the previous draft
-            int am = (1 << i) - 1;
-            if (tree) {
-                const int pi = __builtin_amdgcn_readlane(par_raw, i);
-                bad = bad || (i < T && (pi < -1 || pi >= i));
-                base = G_prev;
-                am = 0;
-#pragma unroll
-                for (int j = 0; j < i; ++j) {
-                    const bool is_parent = pi == j;
-                    base = is_parent ? Gi[j] : base;
-                    am = is_parent ? (anc[j] | (1 << j)) : am;
-                }
-            }
-            const float run = base + (i < T ? gi : 0.0f);
-            Gi[i] = run;
-            anc[i] = am;
-            if (i < 4) {
-                GcRow[i] = run;
-                ancRow[i] = am;
-            } else {
-                GcRow[i - 4] = lq % 2 ? run : GcRow[i - 4];
-                ancRow[i - 4] = lq % 2 ? am : ancRow[i - 4];
-            }
-            GcLm = lm % 8 == i ? run : GcLm;
-            GcTid = tid == i ? run : GcTid;
-#pragma unroll
-            for (int x = 0; x < NTW; ++x)
-                GcKey[x] = 16 * (wave + NW * x) + lm - f == i ? run : GcKey[x];
-            if (TAIL && lane == 0)
-                sGc[wave][i] = run;
+        for (int j = 0; j < TMX - 1; ++j) {
+            anc |= (1 << at) >> 1;
+            at = parents >> (4 * at) & 15u;
         }
-        if (bad && tid == 0 && a.st.status)
+        if (__any(bad && di < T) && tid == 0 && a.st.status)
             atomicOr(&a.st.status[s], KVB_STATUS_BADPATH);
+    }
+    // Whatever a lane needs of other drafts it reads from the wave's table in LDS (an array indexed at run time would
+    // live in scratch memory, whose loads share the counter of the state loads).
+    float bet[TMX];      // betas, wave-uniform
+    float GcMine;        // of draft lane % 8, the row of W that this lane loaded
+    float GcRow[4];      // of the draft of accumulator row 4 lq + v: draft v (lq even) or 4 + v (lq odd)
+    int ancRow[4];       // its ancestors
+    auto finish_Gc = [&]() {
+        const int path = anc | 1 << di;
+        float run = G_prev;
+#pragma unroll
+        for (int j = 0; j < TMX; ++j) {
+            const float gj = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, g_raw), j));
+            bet[j] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, beta_mine), j));
+            run += path >> j & 1 ? gj : 0.0f;
+        }
+        GcMine = run;
+        if (lane < TMX) {
+            sGc[wave][lane] = run;
+            sGam[wave][lane] = lane < T ? expf(run) : 0.0f;
+            sAnc[wave][lane] = anc;
+        }
+        __builtin_amdgcn_wave_barrier();   // (the same wave reads them)
+        const float4 G4 = *reinterpret_cast<const float4 *>(&sGc[wave][4 * (lq % 2)]);
+        const int4 A4 = *reinterpret_cast<const int4 *>(&sAnc[wave][4 * (lq % 2)]);
+        GcRow[0] = G4.x; GcRow[1] = G4.y; GcRow[2] = G4.z; GcRow[3] = G4.w;
+        ancRow[0] = A4.x; ancRow[1] = A4.y; ancRow[2] = A4.z; ancRow[3] = A4.w;
     };
     if constexpr (!EARLY)
         finish_Gc();
@@ -341,7 +341,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         if constexpr (EARLY)
             gam = live ? 1.0f : 0.0f;
         else
-            gam = live ? expf(GcLm) : 0.0f;
+            gam = live ? expf(GcMine) : 0.0f;
         const float sg = lm < 8 ? -gam : gam;
         // piece st of the rows belongs to wave st % 4 and covers state rows 4 EW st + EW lq ..
 #pragma unroll
@@ -391,18 +391,14 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         // point: pure arithmetic is otherwise free to drift across the fences
         if constexpr (CT == 2)
             asm volatile("" : "+v"(acc[CT - 1]));
-        asm volatile("" : "+v"(acc[0]), "+v"(G_prev), "+v"(g_raw), "+v"(beta_mine), "+v"(par_raw));
+        asm volatile("" : "+v"(acc[0]), "+v"(G_prev), "+v"(g_raw), "+v"(beta_mine));
         __builtin_amdgcn_sched_barrier(0);
         finish_Gc();
         // acc*[v] is row m = 4 lq + v = draft m % 8: apply its gamma
+        const f32x4_t gam = *reinterpret_cast<const f32x4_t *>(&sGam[wave][4 * (lq % 2)]);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int i = (4 * lq + v) % 8;
-            const float gam = i < T ? expf(GcRow[v]) : 0.0f;
-#pragma unroll
-            for (int t = 0; t < CT; ++t)
-                acc[t][v] *= gam;
-        }
+        for (int t = 0; t < CT; ++t)
+            acc[t] *= gam;
     }
 
     // ---- 5. stage 1: decayed dot products with every buffered and new key -------
@@ -429,22 +425,24 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         }
         *reinterpret_cast<float4 *>(&cW[n][4 * lq]) = make_float4(o[0], o[1], o[2], o[3]);
     };
+    auto key_G = [&](int n, float buffered) {   // (the read without a condition, then the select)
+        const float fresh = sGc[wave][min(max(n - f, 0), TMX - 1)];
+        return n < f ? buffered : fresh;
+    };
 #pragma unroll
     for (int x = 0; x < NTW; ++x) {
         const int tile = wave + NW * x;
         if (tile < ntile)
-            key_tile(tile, kt[x], 16 * tile + lm < f ? Gn[x] : GcKey[x]);
+            key_tile(tile, kt[x], key_G(16 * tile + lm, Gn[x]));
     }
     for (int tile = wave + NW * NTW; TAIL && tile < ntile; tile += NW) {   // keys beyond the register window
         const int n = 16 * tile + lm;
-        const TIn *kp = n < f ? kb + rk(min(n, cap - 1)) * D
-                              : kin + (((size_t)b * T + min(max(n - f, 0), T - 1)) * a.Hk + hk) * D;
+        const TIn *kp = key_at(n);
         uint4 kk[NWA];
 #pragma unroll
         for (int st = 0; st < NWA; ++st)
-            kk[st] = *reinterpret_cast<const uint4 *>(kp + EW * lq + 4 * EW * st);
-        const float Gb = Gbuf[ru(n < f ? n : 0)];
-        key_tile(tile, kk, n < f ? Gb : sGc[wave][min(max(n - f, 0), TMX - 1)]);
+            kk[st] = *reinterpret_cast<const uint4 *>(kp + 4 * EW * st);
+        key_tile(tile, kk, key_G(n, *Grec.at(n < f ? n : 0, 0)));
     }
     __syncthreads();
 
@@ -471,7 +469,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int l = 4 * (s0 + j) + lq;
-            u4r[j] = load_raw_cols<CT>(ub + ru(l < f ? l : 0) * D + col2);
+            u4r[j] = load_raw_cols<CT>(static_cast<const TRec *>(urec.at(l < f ? l : 0, col2)));
         }
         Cols<CT> u4[4];
 #pragma unroll
@@ -577,14 +575,14 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         const int i = is_u ? rr : rr - T;
         const float4 val = *reinterpret_cast<const float4 *>(&fin[is_u ? i : 8 + i][4 * c4]);
         if (is_u)   // (already rounded to the record type: the conversion is exact)
-            store4(static_cast<TRec *>(a.st.buf_u) + ru(f + i) * D + 4 * c4, val);
+            store4(urec.at(f + i, 4 * c4), val);
         else
             out.put4((((size_t)b * T + i) * a.Hv + h) * D + 4 * c4, val);
     }
     if (tid < T)
-        a.st.buf_G[ru(f + tid)] = GcTid;
+        *Grec.at(f + tid, 0) = GcMine;   // (lane = draft)
     if (h % r == 0 && wave == 0 && lm < T) {   // lanes holding k rows store them
-        TIn *kw = static_cast<TIn *>(a.st.buf_k) + rk(f + lm) * D + EW * lq;
+        TIn *kw = krec.at(f + lm, EW * lq);
 #pragma unroll
         for (int st = 0; st < NWA; ++st)
             *reinterpret_cast<uint4 *>(kw + 4 * EW * st) = wa[st];
