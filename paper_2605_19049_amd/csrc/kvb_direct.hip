@@ -321,6 +321,70 @@ __device__ __forceinline__ f32x4_t mm16_pieces(const uint2 (&x)[NPX], const uint
 }
 
 // ---------------------------------------------------------------------------
+// Longest contexts first.  The work of a launch grows with the contexts faster than linearly, and in the order of the
+// batch a launch of up to 128 tokens ended with whatever long contexts had come last.  Every workgroup therefore sorts
+// the lengths of the batch, by counting, into classes of 16 tokens (the blocks that the kernel works in; the order of the
+// batch inside a class) and takes the p-th request of that order: one vector load of lengths in the place of the scalar
+// one, a barrier and a scan over 64 counts.  96 contexts of ~U(1, 128), 32 heads, with the fold 236 -> 227.5 us; 128 of
+// ~U(1, 100), fp16, and 16 steps from the buffer 482 -> 476.  More than MAX_RANKED requests keep their order: their
+// launch is many times as long as its end.  Up to 64 tokens: not sorted, see deal_of.
+// lead: Hv, or with its sign bit set a batch of B (<= MAX_RANKED) requests to be sorted in bits 16.., Hv in the rest.
+// ---------------------------------------------------------------------------
+constexpr int MAX_RANKED = 2 * NT;
+__host__ __device__ inline int rank_lead(int B, int Hv, bool rank)
+{
+    return rank && B > 1 && B <= MAX_RANKED && Hv < 65536 ? (int)(0x80000000u | (uint32_t)B << 16 | (uint32_t)Hv) : Hv;
+}
+// inclusive sum over the wave
+__device__ __forceinline__ int wave_sum(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);   // row_bcast 15 to rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);   // row_bcast 31 to rows 2 and 3
+    return x;
+}
+// The request at place p, and its length as it stands in len.
+__device__ __forceinline__ int ranked_request(const int32_t *len, int B, int Lmax, int p, int wave, int lane, int &L,
+                                              int *sLen /* [MAX_RANKED] */, int *sCount /* [64] */)
+{
+    auto class_of = [&](int l) {   // 0: the longest
+        const int n = l < 0 || l > Lmax ? Lmax : l;
+        return 7 - min(max(n - 1, 0) / 16, 7);
+    };
+    int l[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+        l[x] = len[min(NT * x + 64 * wave + lane, B - 1)];
+    int count = 0;   // lane 2 k + x: requests of class k among the 64 of this wave and half
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const int i = NT * x + 64 * wave + lane, c = i < B ? class_of(l[x]) : -1;
+        sLen[i] = l[x];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int n = __popcll(__ballot(c == k));
+            count = lane == 2 * k + x ? n : count;
+        }
+    }
+    if (lane < 16)
+        sCount[8 * (lane / 2) + 4 * (lane % 2) + wave] = count;   // by class, then in the order of the batch
+    __syncthreads();
+    const int n = sCount[lane], upto = wave_sum(n);
+    const int e = __builtin_ctzll(__ballot(upto > p));
+    const int nth = p - __builtin_amdgcn_readlane(upto - n, e);
+    const int first = NT * (e % 8 / 4) + 64 * (e % 4);
+    const int mine = sLen[first + lane];
+    const uint64_t in_class = __ballot(first + lane < B && class_of(mine) == e / 8);
+    const bool hit = (in_class >> lane & 1) && (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(in_class >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in_class, 0)) == nth;
+    const int at = __builtin_ctzll(__ballot(hit));
+    L = __builtin_amdgcn_readlane(mine, at);
+    return first + at;
+}
+
+// ---------------------------------------------------------------------------
 // kvb_direct for 16-bit inputs, d = 128 and contexts of up to 64 tokens.
 //
 // With N_il = beta_i Gamma_il (k_i.k_l) (l < i) and M_il = Gamma_il (q_i.k_l) (l <= i) the
@@ -369,9 +433,9 @@ template <typename T, bool LONG>
 constexpr int DIRECT_WG_PER_CU = LONG ? 3 : __is_same(T, f16_t) ? 5 : 4;
 template <typename TIn, typename TRec, bool LONG, bool PAGED>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PER_CU<TIn, LONG>, DIRECT_WG_PER_CU<TIn, LONG>))) void kvb_direct_mfma_kernel(
-    const int32_t *len_arg, int32_t Hv_arg, int32_t deal_arg, const DirectArgs a)
+    const int32_t *len_arg, int32_t lead_arg, int32_t deal_arg, const DirectArgs a)
 {
-    // The three leading arguments repeat a.len and a.Hv and hold deal_of(): as plain leading kernel arguments
+    // The three leading arguments hold a.len, rank_lead() and deal_of(): as plain leading kernel arguments
     // they are preloaded into scalar registers at wave launch (the build asks for it), so the load of
     // len[b] -- the head of the dependent chain to the first key byte -- goes out at once instead of after
     // the round trip that fetches the argument block.
@@ -422,10 +486,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
     const int c16 = lane % 16, lq = lane / 16;
     const int lb = dealt_unit(blockIdx.x, deal_arg);
-    const int b = lb / Hv_arg;
-    int L = len_arg[b];
+    const int Hv = lead_arg < 0 ? lead_arg & 0xFFFF : lead_arg;
+    int b = lb / Hv, L;
+    if (LONG && lead_arg < 0) {   // uniform
+        // (its tables lie where nothing is written before the barrier behind the staged keys)
+        static_assert(!LONG || REGION_BYTES >= STAGE_BYTES + 4 * (MAX_RANKED + 64), "room for the lengths");
+        int *tables = reinterpret_cast<int *>(region + STAGE_BYTES);
+        b = ranked_request(len_arg, lead_arg >> 16 & 0x7FFF, a.Lmax, b, wave, lane, L, tables, tables + MAX_RANKED);
+    } else {
+        L = len_arg[b];
+    }
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int h = lb % Hv_arg;
+    const int h = lb % Hv;
     const int r = a.Hv / a.Hk;
     const int hk = h / r;
     const int Lmax = a.Lmax;
@@ -1391,12 +1463,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
 // ---------------------------------------------------------------------------
 int launch_direct(int dk, int in_dtype, int rec_dtype, const DirectArgs &a, int blocks, hipStream_t stream)
 {
+    const int32_t lead = rank_lead(blocks / a.Hv, a.Hv, a.Lmax > 64);
     if (dk == 128 && in_dtype != KVB_F32)
         return dispatch_types16(in_dtype, rec_dtype, [&]<typename TIn, typename TRec>() {
             if (a.Lmax > 64 && a.st.block_table)   // two panels of 64 rows
-                launch(kvb_direct_mfma_kernel<TIn, TRec, true, true>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
+                launch(kvb_direct_mfma_kernel<TIn, TRec, true, true>, blocks, stream, a.len, lead, deal_of(blocks, a.Hv / a.Hk), a);
             else if (a.Lmax > 64)
-                launch(kvb_direct_mfma_kernel<TIn, TRec, true, false>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
+                launch(kvb_direct_mfma_kernel<TIn, TRec, true, false>, blocks, stream, a.len, lead, deal_of(blocks, a.Hv / a.Hk), a);
             else if (a.st.block_table)
                 launch(kvb_direct_mfma_kernel<TIn, TRec, false, true>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
             else

@@ -175,3 +175,15 @@ def test_fold_of_an_overdue_buffer(d, in_dtype, cap, Hk, Hv):
         errs += [H.rel_err(H.host(out[b]), o[0, -1]), H.rel_err(lay.get_state()[b], S[0])]
     say("overdue buffer, d=%d %s: rel err %.2e" % (d, in_dtype, max(errs)))
     H.check(errs, in_dtype, what="overdue buffer")
+
+
+@pytest.mark.parametrize("B", [2, 63, 65, 255, 257, 512, 513])
+def test_direct_longest_first(B):
+    """Batches around the wave, workgroup and table sizes of the sort by length, every class of lengths among them;
+    an untaken unit leaves NaN in its outputs."""
+    rng = np.random.default_rng(890 + B)
+    lens = rng.integers(0, 129, B).astype(np.int32)
+    lens[:2] = [0, 128]
+    e = _direct_case(B=B, Hk=1, Hv=1, d=128, Lmax=128, cap=128, in_dtype="bf16", seed=891 + B, lens=lens, then_decode=False)
+    say("direct, longest first, B=%d: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((B,) + e))
+    H.check(e, "bf16", what="longest first")
