@@ -247,6 +247,14 @@ struct Out {
                 store2_nt(static_cast<TIn *>(p) + i, x, y);
         }
     }
+    // element i0 + i, i0 a scalar (64-bit) and i the lane's (its byte offset in 32 bits)
+    __device__ __forceinline__ void put2_nt(size_t i0, uint32_t i, float x, float y) const
+    {
+        if (sizeof(TIn) == 4 || wide)
+            store2_nt(reinterpret_cast<float *>(static_cast<char *>(p) + 4 * i0 + 4 * i), x, y);
+        else if constexpr (sizeof(TIn) == 2)
+            store2_nt(reinterpret_cast<TIn *>(static_cast<char *>(p) + 2 * i0 + 2 * i), x, y);
+    }
     __device__ __forceinline__ void put4(size_t i, const float4 &v) const
     {
         if constexpr (sizeof(TIn) == 4) {
@@ -512,15 +520,24 @@ struct Pages {
 // slot are contiguous: with 64-bit arithmetic for each load a wave alone on its SIMD spends a microsecond on addresses).
 template <int E, typename T, bool PAGED>
 struct Rows {
+    using Byte = std::conditional_t<std::is_const_v<T>, const char, char>;
     T *p;   // contiguous: record 0 of the head; paged: the pool
     Pages<PAGED> pg;
     int H, head;
+    __device__ __forceinline__ T *at(int l0, int l, int e) const   // of record l0 + l, l0 a scalar
+    {
+        if constexpr (PAGED)
+            return at(l0 + l, e);
+        else
+            return reinterpret_cast<T *>(reinterpret_cast<Byte *>(p + l0 * E) + (uint32_t)((l * E + e) * (int)sizeof(T)));
+    }
     __device__ __forceinline__ T *at(int l, int e) const   // element e of record l
     {
         if constexpr (PAGED)
             return p + pg.row(l, H, head) * E + e;
         else
-            return reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(p) + (uint32_t)((l * E + e) * (int)sizeof(T)));
+            // (through a byte pointer: through an integer the compiler loses the address space and emits flat accesses)
+            return reinterpret_cast<T *>(reinterpret_cast<Byte *>(p) + (uint32_t)((l * E + e) * (int)sizeof(T)));
     }
 };
 template <int E, bool PAGED, typename T>

@@ -21,12 +21,25 @@ namespace kvb_impl {
 // before the 64 KB state tile; the dot products and the LDS exchange then run
 // while the state is still in flight.
 // ---------------------------------------------------------------------------
+// The sum over groups of N adjacent lanes, in every lane: permutations inside a row of 16 lanes ride on the additions,
+// where shuffles through LDS are a chain of round trips.  16 steps of kvb_decode_flush: one request 71.6 -> 67.5 us, 13
+// of 8 heads, fp16, 97.6 -> 92.4; 4 steps of 500 requests with 64-record buffers 1062 -> 948.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x)
+{
+    const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true);
+    return x + __builtin_bit_cast(float, y);
+}
 template <int N>
 __device__ __forceinline__ float group_sum(float x)
 {
-#pragma unroll
-    for (int off = 1; off < N; off <<= 1)
-        x += __shfl_xor(x, off);
+    static_assert(N == 4 || N == 8 || N == 16);
+    x = dpp_add<0xB1>(x);        // quad_perm 1 0 3 2
+    x = dpp_add<0x4E>(x);        // quad_perm 2 3 0 1
+    if constexpr (N > 4)
+        x = dpp_add<0x141>(x);   // mirrored in 8 lanes: the other four
+    if constexpr (N > 8)
+        x = dpp_add<0x140>(x);   // mirrored in 16: the other eight
     return x;
 }
 
@@ -97,9 +110,6 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     const TIn *qin = static_cast<const TIn *>(a.q);
     const TIn *kin = static_cast<const TIn *>(a.k);
     const TIn *vin = static_cast<const TIn *>(a.v);
-    const float *Gbuf = a.st.buf_G;                              // record l of this head: Gbuf[ru(l)]
-    const TIn *kb = static_cast<const TIn *>(a.st.buf_k);        //                        kb + rk(l) * D
-    const TRec *ub = static_cast<const TRec *>(a.st.buf_u);      //                        ub + ru(l) * D
     const Out<TIn> out{a.out, a.out_wide != 0};
     const int blk_id = load_block_id<PAGED>(a.st, s, tid % 64);
 
@@ -113,6 +123,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     const Raw8<TIn> k_raw = load_raw8(kin + nr_o);
     const TIn v_raw = vin[((size_t)b * a.Hv + h) * D + tid % D];
 
+    const int word = a.st.fill[s];
     // ---- 2. the state tile goes in flight ------------------------------------
     // Decoding one token (EARLY): the state's address needs the slot only, so its loads go out
     // before the fill count is known.  Each dependent scalar load costs microseconds while the
@@ -137,18 +148,42 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     // scalars of the token (uniform); requested together with the fill, after the state loads,
     // so that no scalar wait stands between the slot and the first state byte
     const float gnew = a.g[(size_t)b * a.Hv + h], bet = a.beta[(size_t)b * a.Hv + h];
-    const int f = fill_before(a.st.fill[s], a.threshold - 1);
+    // while the fill is on its way: the new rows as weights of the state rows (EARLY applies gamma after the sum over
+    // state rows; Gc comes back behind the state)
+    float q8[8], k8[8], dqk = 0.0f;
+    auto stage_rows = [&](float gw) {
+        unpack8(q_raw, q8);
+        unpack8(k_raw, k8);
+        if (grp == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                sKs[8 * sub + e] = -gw * k8[e];
+                sQs[8 * sub + e] = gw * q8[e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            dqk = fmaf(q8[e], k8[e], dqk);
+        dqk = group_sum<GL>(dqk);
+    };
+    if constexpr (EARLY) {
+        __builtin_amdgcn_sched_barrier(0);
+        stage_rows(1.0f);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const int f = fill_before(word, a.threshold - 1);
     if (f + 1 > cap) {
         if (tid == 0 && a.st.status)
             atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
         return;
     }
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[tid / 64], tid % 64, blk_id);
-    auto ru = [&](int l) { return pg.row(l, a.Hv, h); };    // row of record l in buf_u / buf_G
-    auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };   // row of record l in buf_k
+    const auto krec = make_rows<D>(static_cast<TIn *>(a.st.buf_k), pg, a.Hk, hk);
+    const auto urec = make_rows<D>(static_cast<TRec *>(a.st.buf_u), pg, a.Hv, h);
+    const auto Grec = make_rows<1>(a.st.buf_G, pg, a.Hv, h);
     // cumulative log decay of the new row (uniform)
     float Gc;
-    float G_prev = f > 0 ? Gbuf[ru(f - 1)] : 0.0f;
+    float G_prev = f > 0 ? *Grec.at(f - 1, 0) : 0.0f;
     if constexpr (!EARLY)
         Gc = G_prev + gnew;
     // window of buffered records
@@ -158,14 +193,14 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     for (int p = 0; p < KP; ++p) {
         const int l = grp + NG * p;
         const int lc = l < f ? l : 0;
-        kl_raw[p] = load_raw8(kb + rk(lc) * D + 8 * sub);
-        Gl[p] = Gbuf[ru(lc)];
+        kl_raw[p] = load_raw8(krec.at(lc, 8 * sub));
+        Gl[p] = *Grec.at(lc, 0);
     }
     Raw4<TRec> ur_raw[UP];
 #pragma unroll
     for (int j = 0; j < UP; ++j) {
         const int l = rg + RPP * j;
-        ur_raw[j] = load_raw4(ub + ru(l < f ? l : 0) * D + 4 * c4);
+        ur_raw[j] = load_raw4(urec.at(l < f ? l : 0, 4 * c4));
     }
     if constexpr (!EARLY)
         issue_state();
@@ -177,25 +212,10 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
         advance_fill(&a.st.fill[s], h == 0, a.Hv, fold ? -f : 1);
 
     // ---- 3. decayed dot products of the new rows with every earlier key ----
-    float q8[8], k8[8];
-    unpack8(q_raw, q8);
-    unpack8(k_raw, k8);
     float4 accU = make_float4(0.f, 0.f, 0.f, 0.f), accO = make_float4(0.f, 0.f, 0.f, 0.f);
     {
-        // EARLY applies gamma after the sum over state rows (Gc comes back behind the state)
-        const float gw = EARLY ? 1.0f : expf(Gc);
-        if (grp == 0) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                sKs[8 * sub + e] = -gw * k8[e];
-                sQs[8 * sub + e] = gw * q8[e];
-            }
-        }
-        float dqk = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            dqk = fmaf(q8[e], k8[e], dqk);
-        dqk = group_sum<GL>(dqk);
+        if constexpr (!EARLY)
+            stage_rows(expf(Gc));
         if (tid == 0) {
             cK[f] = 0.0f;
             cQ[f] = dqk;
@@ -256,8 +276,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                 for (int x = 0; x < KT; ++x) {
                     const int l = (KP + x) * NG + grp;
                     const int lc = l < f ? l : 0;
-                    kt_raw[x] = load_raw8(kb + rk(lc) * D + 8 * sub);
-                    Gt[x] = Gbuf[ru(lc)];
+                    kt_raw[x] = load_raw8(krec.at(lc, 8 * sub));
+                    Gt[x] = *Grec.at(lc, 0);
                 }
 #pragma unroll
                 for (int x = 0; x < KT; ++x) {
@@ -308,7 +328,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int l = (UP + x0 + j) * RPP + rg;
-                    ut_raw[j] = load_raw4(ub + ru(l < f ? l : 0) * D + 4 * c4);
+                    ut_raw[j] = load_raw4(urec.at(l < f ? l : 0, 4 * c4));
                 }
                 float4 ut[4];
 #pragma unroll
@@ -369,12 +389,12 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
         u_new = to_f32(ur_new);
         ao = fmaf(cQ[f], u_new, ao);
         out.put1(((size_t)b * a.Hv + h) * D + tid, a.scale * ao);
-        static_cast<TRec *>(a.st.buf_u)[ru(f) * D + tid] = ur_new;
+        *urec.at(f, tid) = ur_new;
     }
     if (tid == 0)
-        a.st.buf_G[ru(f)] = Gc;
+        *Grec.at(f, 0) = Gc;
     if (h % r == 0 && tid < D / 8)   // the threads that loaded the new k row store it
-        store_raw8(static_cast<TIn *>(a.st.buf_k) + rk(f) * D + 8 * sub, k_raw);
+        store_raw8(krec.at(f, 8 * sub), k_raw);
     const int m = f + 1;
     if (overdue)
         publish_fill(&a.st.fill[s], a.Hv, 0);
@@ -469,9 +489,9 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                     Raw8<TIn> kq;
                     Raw4<TRec> ua, ub4;
                     auto request = [&](int l0) {
-                        kq = load_raw8(kb + rk(min(l0 + grp, lmax)) * D + 8 * sub);
-                        ua = load_raw4(ub + ru(min(l0 + rg, lmax)) * D + 4 * c4);
-                        ub4 = load_raw4(ub + ru(min(l0 + rg + 8, lmax)) * D + 4 * c4);
+                        kq = load_raw8(krec.at(min(l0 + grp, lmax), 8 * sub));
+                        ua = load_raw4(urec.at(min(l0 + rg, lmax), 4 * c4));
+                        ub4 = load_raw4(urec.at(min(l0 + rg + 8, lmax), 4 * c4));
                     };
                     request(0);
                     for (int l0 = 0; l0 < m; l0 += LT) {
@@ -503,11 +523,11 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                     }
 #pragma unroll 1
                     for (int l = 0; l < m; ++l) {
-                        const TIn *kp = (l < f ? kb + pq.row(l, a.Hk, hk) * D : kin + ((size_t)b * a.Hk + hk) * D) + row0;
+                        const TIn *kp = (l < f ? static_cast<const TIn *>(a.st.buf_k) + pq.row(l, a.Hk, hk) * D : kin + ((size_t)b * a.Hk + hk) * D) + row0;
                         float4 u = *reinterpret_cast<const float4 *>(&sKs[col0]);
                         float w = 1.0f;
                         if (l < f) {   // uniform
-                            u = unpack4(load_raw4(ub + pq.row(l, a.Hv, h) * D + col0));
+                            u = unpack4(load_raw4(static_cast<const TRec *>(a.st.buf_u) + pq.row(l, a.Hv, h) * D + col0));
                             w = wF[l];
                         }
 #pragma unroll
@@ -581,10 +601,9 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                     // one is applied, so its round trip hides under the multiply-adds
                     const int lmax = f > 0 ? f - 1 : 0;   // requests are clamped; rows >= f are not used
                     int lr = min(l_done + grp, lmax);
-                    size_t rowr = ru(lr);
-                    Raw8<TIn> kq = load_raw8(kb + rk(lr) * D + 8 * sub);
-                    Raw8<TRec> uq = load_raw8(ub + rowr * D + 8 * sub);
-                    float Gq = Gbuf[rowr];
+                    Raw8<TIn> kq = load_raw8(krec.at(lr, 8 * sub));
+                    Raw8<TRec> uq = load_raw8(urec.at(lr, 8 * sub));
+                    float Gq = *Grec.at(lr, 0);
                     for (int l0 = l_done; l0 < m; l0 += LT) {
                         __syncthreads();
                         const int l = l0 + grp;
@@ -608,10 +627,9 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                         inject_new(l0);
                         // (the request past the last tile re-reads a valid record and is dropped)
                         lr = min(l0 + LT + grp, lmax);
-                        rowr = ru(lr);
-                        kq = load_raw8(kb + rk(lr) * D + 8 * sub);
-                        uq = load_raw8(ub + rowr * D + 8 * sub);
-                        Gq = Gbuf[rowr];
+                        kq = load_raw8(krec.at(lr, 8 * sub));
+                        uq = load_raw8(urec.at(lr, 8 * sub));
+                        Gq = *Grec.at(lr, 0);
                         __syncthreads();
                         apply_tile(l0);
                     }
@@ -624,8 +642,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
                         for (int x = 0; x < EPT; ++x) {
                             const int idx = tid + NT * x, l = l0 + idx / D, e = idx % D;
                             if (l < f) {
-                                kh[idx / D][e] = expf(Gc - Gbuf[ru(l)]) * to_f32(kb[rk(l) * D + e]);
-                                uu[idx / D][e] = to_f32(ub[ru(l) * D + e]);
+                                kh[idx / D][e] = expf(Gc - *Grec.at(l, 0)) * to_f32(*krec.at(l, e));
+                                uu[idx / D][e] = to_f32(*urec.at(l, e));
                             } else if (l > f) {
                                 kh[idx / D][e] = 0.0f;
                                 uu[idx / D][e] = 0.0f;
@@ -656,24 +674,34 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 // kvb_decode without a state (Sec. 3.4, Eq. 14): the buffer is all there is to read, so a workgroup of a single
 // v-head moves a few KB and lives on its chain of loads (slot, fill, records) and exchanges.  HB v-heads of a key
 // head share a workgroup: the keys are read and multiplied once for them, and their chains run side by side.
-// The records go in blocks of WREC: keys, decays and delta values of a block are requested together, one round
-// trip for each block that the fill reaches.
-// Rule (launch_buffer_step): two heads a workgroup as soon as that leaves one for every CU; below, the halves of
-// the chip that would stay idle are worth more.  Passes beyond the fill load a valid record and compute nothing.
-// Against kvb_step_kernel, which had this path before, d = 128, 128 requests of 32 heads, fp16 records: 8 records
-// 21.9 -> 14.4 us, 60 23.5 -> 21.5, 110 35.3 -> 33.1; fp32 records: 21.3 -> 16.1, 32.2 -> 29.4, 48.9 -> 48.2.
+// The records go in blocks of 64: keys, decays and delta values of a block are requested together, one round
+// trip for each block that the fill reaches.  With 16-bit inputs the dot products of 16 records with the new key and
+// query are one product on the matrix cores per 32 dimensions, rows k and q of which every lane group holds, so that a
+// lane ends up with both of its record for the head whose weights it makes.  128 contexts of up to 100 tokens, 32 heads,
+// fp16, 16 steps: 476 us with the dots on the vector ALU, sums by shuffles through LDS and 64-bit record addresses, 447
+// without the three.
+// Rule (launch_buffer_step): two heads a workgroup from as many units on as leave the CUs busy; below, the halves of
+// the chip that would stay idle are worth more.  What two heads save besides keys are additions to the fill word, which
+// pass one at a time (about 10 ns each) where the slots of a batch share a 128-byte line, as the slots here do.
+// Passes beyond the fill load a valid record and compute nothing.
 // One head a workgroup / two, 32 heads, us a call, each request at its own fill:
 //                           0..60 records                          0..10 records       0..119 records
 //   requests                16           32           128          32           128    128
-//   d = 128, bf16 / fp32    10.6 /  8.0  12.6 /  9.9  21.3 / 20.7  11.3 / 8.1  16.3 / 14.5  32.3 / 33.3
-//   d = 128, fp16 / fp16    10.4 /  9.1  12.5 /  9.9  18.7 / 17.4  11.2 / 7.8  16.4 / 13.0  25.9 / 25.3
-//   d = 64,  bf16 / fp32    10.7 /  7.8  11.0 /  8.1  17.1 / 13.4  10.9 / 8.0  16.1 / 11.3  20.7 / 19.5
-//   d = 64,  fp32           10.7 /  7.8  11.3 /  8.0  17.7 / 14.9  11.2 / 7.9  16.3 / 11.6  21.1 / 20.7
-//   d = 32,  fp16 / fp16    10.2 /  7.6  10.8 /  7.9  16.6 / 11.3  10.7 / 7.8  16.0 / 10.8  16.8 / 13.0
-//   d = 32,  fp32           10.5 /  7.6  10.8 /  8.0  16.4 / 11.4  10.7 / 7.8  16.5 / 11.2  18.0 / 15.8
-// 8 requests (256 units), 0..60 records, d = 128: 7.4 / 7.3 with bf16 / fp32, 7.1 / 7.7 with fp16; d = 64 7.3 / 6.2,
-// d = 32 7.1 / 6.0: the line lies where two heads are better with every size and type (but the fp32 records of 128
-// requests at 0..119).
+//   d = 128, bf16 / fp32    10.2 /  7.6  10.5 /  8.2  20.4 / 19.0  10.2 / 7.7  16.1 / 12.7  30.6 / 31.2
+//   d = 128, fp16 / fp16     9.8 /  7.1  10.4 /  7.9  19.0 / 15.7  10.1 / 7.2  15.9 / 11.9  25.7 / 23.2
+//   d = 64,  bf16 / fp32    10.0 /  7.3  10.7 /  7.7  15.8 / 12.7  10.5 / 7.4  14.4 / 10.2  17.7 / 17.7
+//   d = 64,  fp32           10.0 /  7.3  10.7 /  7.5  16.4 / 14.1  10.4 / 7.4  14.6 / 10.4  19.1 / 19.7
+//   d = 32,  fp16 / fp16     9.9 /  7.2  10.8 /  7.5  14.4 / 10.3  10.6 / 7.4  14.2 /  9.9  15.3 / 11.6
+//   d = 32,  fp32            9.9 /  7.2  10.3 /  7.5  14.6 / 10.6  10.4 / 7.4  14.4 / 10.3  16.0 / 14.8
+// Around the lines, 0..60 records (requests of 32 heads, or of 8 where marked):
+//   requests                2            4            13 of 8      30 of 8      6            8
+//   units                   64           128          104          240          192          256
+//   d = 128, bf16 / fp32    4.9 / 5.3    5.6 / 5.5    5.4 / 5.7    5.7 / 5.9    6.5 / 6.0    7.1 / 6.2
+//   d = 128, fp16 / fp16    4.8 / 5.3    5.2 / 5.4    5.2 / 5.6    5.8 / 5.8    6.1 / 5.8    6.8 / 6.0
+//   d = 128, fp32           4.9 / 5.7    5.6 / 5.9    5.3 / 6.1    5.6 / 6.3    6.4 / 6.3    7.0 / 6.3
+//   d = 64,  bf16 / fp32    4.6 / 4.8    5.4 / 5.0    5.1 / 5.0    5.4 / 5.1    6.2 / 5.4    6.9 / 5.7
+//   d = 32,  fp16 / fp16    4.6 / 4.8    5.4 / 5.0    5.1 / 4.9    5.4 / 5.0    6.2 / 5.4    6.8 / 5.7
+// The lines: 256 units at d = 128, 96 below.
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int HB, bool PAGED>
 __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot_arg, int32_t nu_arg, int32_t nblocks_arg,
@@ -684,13 +712,14 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
     constexpr int RPP = NT / LPR;    // delta-value rows per pass
     constexpr int GL = D / 8;        // lanes sharing one key dot product (8 elements each)
     constexpr int NG = NT / GL;      // keys per pass
-    constexpr int WREC = NG > 64 ? NG : 64;
-    constexpr int KP = WREC / NG, UP = WREC / RPP;
+    constexpr int WREC = 64;
+    constexpr bool MDOT = sizeof(TIn) == 2;      // dot products on the matrix instruction: a wave takes 16 records of a block
+    constexpr int NST = D / 32;                  // its steps
+    constexpr int KP = MDOT ? 1 : (WREC + NG - 1) / NG, UP = WREC / RPP;
     constexpr int NC = (KVB_MAX_CAP + WREC) / WREC * WREC;
-    static_assert(GL >= HB && HB * D <= NT, "a lane of each key group and a column of each head to a thread");
+    static_assert(GL >= HB && HB <= 4 && HB * D <= NT, "a lane of each key group and a column of each head to a thread");
 
-    __shared__ float cK[HB][NC];     // Gamma_l (k.k_l) of record l
-    __shared__ float cQ[HB][NC];     // Gamma_l (q.k_l)
+    __shared__ float2 cW[HB][NC];    // -Gamma_l (k.k_l) and Gamma_l (q.k_l) of record l
     __shared__ float sQK;            // q.k of the token itself
     __shared__ __attribute__((aligned(16))) float red[NW][HB][2][D];
     __shared__ int sBlk[NW][MAX_BLOCKS];
@@ -711,11 +740,10 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
 
     const int rg = tid / LPR, c4 = tid % LPR;
     const int grp = tid / GL, sub = tid % GL;
-    const int jw = min(sub, nh - 1);         // head whose weights this lane makes (lanes sub < nh write them)
+    const int lm = tid % 16, lq = tid % 64 / 16, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int own = MDOT ? lq : sub;         // lanes own < nh make the weights of head own
+    const int jw = min(own, nh - 1);
     const int jc = min(tid / D, nh - 1);     // head whose column tid % D this thread finishes
-    const float *Gbuf = a.st.buf_G;
-    const TIn *kb = static_cast<const TIn *>(a.st.buf_k);
-    TRec *ub = static_cast<TRec *>(a.st.buf_u);
     const Out<TIn> out{a.out, a.out_wide != 0};
     const int blk_id = load_block_id<PAGED>(a.st, s, tid % 64);
 
@@ -723,6 +751,14 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
     const size_t nr_o = ((size_t)b * a.Hk + hk) * D + 8 * sub;
     const Raw8<TIn> q_raw = load_raw8(static_cast<const TIn *>(a.q) + nr_o);
     const Raw8<TIn> k_raw = load_raw8(static_cast<const TIn *>(a.k) + nr_o);
+    // the rows k, q, k, q, .. as an operand of the matrix instruction
+    uint4 kq_op[MDOT ? NST : 1];
+    if constexpr (MDOT) {
+        const TIn *row = static_cast<const TIn *>(lm % 2 ? a.q : a.k) + ((size_t)b * a.Hk + hk) * D + 8 * lq;
+#pragma unroll
+        for (int st = 0; st < NST; ++st)
+            kq_op[st] = *reinterpret_cast<const uint4 *>(row + 32 * st);
+    }
     const TIn v_raw = static_cast<const TIn *>(a.v)[((size_t)b * a.Hv + h0 + jc) * D + tid % D];
     const float bet = a.beta[(size_t)b * a.Hv + h0 + jc];
     const float g_w = a.g[(size_t)b * a.Hv + h0 + jw];
@@ -733,10 +769,12 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
         return;
     }
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[tid / 64], tid % 64, blk_id);
-    auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };            // row of record l in buf_k
-    auto ru = [&](int l, int j) { return pg.row(l, a.Hv, h0 + j); };   // of head h0 + j in buf_u / buf_G
+    const auto krec = make_rows<D>(static_cast<TIn *>(a.st.buf_k), pg, a.Hk, hk);
+    // (of head h0; the next heads' records follow a block of cap or block_size records further on)
+    const auto urec = make_rows<D>(static_cast<TRec *>(a.st.buf_u), pg, a.Hv, h0);
+    const auto Grec = make_rows<1>(a.st.buf_G, pg, a.Hv, h0);
     // cumulative log decay of the new row, of head h0 + jw
-    const float Gc = (f > 0 ? Gbuf[ru(f - 1, jw)] : 0.0f) + g_w;
+    const float Gc = (f > 0 ? *Grec.at(f - 1, jw * pg.bs) : 0.0f) + g_w;
 
     float q8[8], k8[8];
     float4 accU[HB], accO[HB];
@@ -747,47 +785,69 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
     unpack8(k_raw, k8);
     for (int l0 = 0; l0 == 0 || l0 < f; l0 += WREC) {   // uniform
         // raw bits from always-valid addresses: an index past the fill is clamped to record 0, its value ignored
-        Raw8<TIn> kl_raw[KP];
+        Raw8<TIn> kl_raw[MDOT ? 1 : KP];
+        uint4 k_op[MDOT ? NST : 1];
         float Gl[KP];
         Raw4<TRec> ur_raw[HB][UP];
+        if constexpr (MDOT) {   // key row lm of the wave's 16 as the other operand
+            const int l = l0 + 16 * wave + lm, lc = l < f ? l : 0;
 #pragma unroll
-        for (int p = 0; p < KP; ++p) {
-            const int l = l0 + grp + NG * p, lc = l < f ? l : 0;
-            kl_raw[p] = load_raw8(kb + rk(lc) * D + 8 * sub);
-            Gl[p] = Gbuf[ru(lc, jw)];
+            for (int st = 0; st < NST; ++st)
+                k_op[st] = *reinterpret_cast<const uint4 *>(krec.at(lc, 8 * lq + 32 * st));
+            Gl[0] = *Grec.at(lc, jw * pg.bs);
+        } else {
+#pragma unroll
+            for (int p = 0; p < KP; ++p) {
+                const int l = l0 + grp + NG * p, lc = l < f ? l : 0;
+                kl_raw[p] = load_raw8(static_cast<const TIn *>(krec.at(lc, 8 * sub)));
+                Gl[p] = *Grec.at(lc, jw * pg.bs);
+            }
         }
 #pragma unroll
         for (int p = 0; p < UP; ++p) {
             const int l = l0 + rg + RPP * p, lc = l < f ? l : 0;
 #pragma unroll
             for (int j = 0; j < HB; ++j)
-                ur_raw[j][p] = load_raw4(ub + ru(lc, min(j, nh - 1)) * D + 4 * c4);
+                ur_raw[j][p] = load_raw4(static_cast<const TRec *>(urec.at(lc, min(j, nh - 1) * pg.bs * D + 4 * c4)));
         }
         __builtin_amdgcn_sched_barrier(0);
         if (l0 == 0 && a.advance)
             advance_fill(&a.st.fill[s], lb % nu_arg == 0, nu_arg, 1);
+        if constexpr (MDOT) {
+            if (l0 + 16 * wave < f) {   // uniform
+                // rows 4 lq + v of the product are k (v = 0) and q (v = 1) for every lq, its columns the records
+                f32x4_t dots = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int p = 0; p < KP; ++p) {
-            const int l = l0 + grp + NG * p;
-            if (l0 + NG * p >= f)   // uniform: nothing of this pass is live
-                break;
-            float kx[8];
-            unpack8(kl_raw[p], kx);
-            float dkk = 0.0f, dq = 0.0f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                dkk = fmaf(kx[e], k8[e], dkk);
-                dq = fmaf(kx[e], q8[e], dq);
+                for (int st = 0; st < NST; ++st)
+                    dots = mfma16x32<TIn>(kq_op[st], k_op[st], dots);
+                const int l = l0 + 16 * wave + lm;
+                const float w = expf(Gc - Gl[0]);
+                if (own < nh && l < f)
+                    cW[own][l] = make_float2(-w * dots[0], w * dots[1]);
             }
-            dkk = group_sum<GL>(dkk);
-            dq = group_sum<GL>(dq);
-            if (sub < nh && l < f) {
-                const float w = expf(Gc - Gl[p]);
-                cK[sub][l] = w * dkk;
-                cQ[sub][l] = w * dq;
+        } else {
+#pragma unroll
+            for (int p = 0; p < KP; ++p) {
+                const int l = l0 + grp + NG * p;
+                if (l0 + NG * p >= f)   // uniform: nothing of this pass is live
+                    break;
+                float kx[8];
+                unpack8(kl_raw[p], kx);
+                float dkk = 0.0f, dq = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    dkk = fmaf(kx[e], k8[e], dkk);
+                    dq = fmaf(kx[e], q8[e], dq);
+                }
+                dkk = group_sum<GL>(dkk);
+                dq = group_sum<GL>(dq);
+                if (own < nh && l < f) {
+                    const float w = expf(Gc - Gl[p]);
+                    cW[own][l] = make_float2(-w * dkk, w * dq);
+                }
             }
         }
-        __syncthreads();   // (blocks write disjoint parts of cK, cQ)
+        __syncthreads();   // (blocks write disjoint parts of cW)
 #pragma unroll
         for (int p = 0; p < UP; ++p) {
             const int l = l0 + rg + RPP * p;
@@ -797,8 +857,9 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
             for (int j = 0; j < HB; ++j) {
                 const float4 u = unpack4(ur_raw[j][p]);
                 if (l < f) {
-                    fma4(accU[j], -cK[j][l], u);
-                    fma4(accO[j], cQ[j][l], u);
+                    const float2 c = cW[j][l];
+                    fma4(accU[j], c.x, u);
+                    fma4(accO[j], c.y, u);
                 }
             }
         }
@@ -843,12 +904,12 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
         const TRec ur_new = from_f32<TRec>(bet * (to_f32(v_raw) + au));
         ao = fmaf(sQK, to_f32(ur_new), ao);
         out.put1(((size_t)b * a.Hv + h0 + jc) * D + col, a.scale * ao);
-        ub[ru(f, jc) * D + col] = ur_new;
+        *urec.at(f, jc * pg.bs * D + col) = ur_new;
     }
-    if (tid < nh)   // (grp == 0, sub == tid)
-        a.st.buf_G[ru(f, jw)] = Gc;
+    if (own < nh && (MDOT ? tid < 64 && lm == 0 : grp == 0))
+        *Grec.at(f, jw * pg.bs) = Gc;
     if (h0 == hk * r && tid < D / 8)   // the threads that loaded the new k row store it
-        store_raw8(static_cast<TIn *>(a.st.buf_k) + rk(f) * D + 8 * sub, k_raw);
+        store_raw8(krec.at(f, 8 * sub), k_raw);
 }
 
 // ---------------------------------------------------------------------------
@@ -893,7 +954,7 @@ template <int D, typename TIn, typename TRec>
 void launch_buffer_step(const StepArgs &a, int blocks, hipStream_t stream)
 {
     const int B = blocks / a.Hv;
-    if (a.Hv > a.Hk && blocks >= 2 * 256)
+    if (a.Hv > a.Hk && blocks >= (D == 128 ? 256 : 96))
         launch_buffer_step_h<D, TIn, TRec, 2>(a, B, stream);
     else
         launch_buffer_step_h<D, TIn, TRec, 1>(a, B, stream);

@@ -187,3 +187,32 @@ def test_direct_longest_first(B):
     e = _direct_case(B=B, Hk=1, Hv=1, d=128, Lmax=128, cap=128, in_dtype="bf16", seed=891 + B, lens=lens, then_decode=False)
     say("direct, longest first, B=%d: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((B,) + e))
     H.check(e, "bf16", what="longest first")
+
+
+@pytest.mark.parametrize("d, in_dtype, rec_dtype", [(128, i, r) for i, r in TYPES + [("f32", "f32")]]
+                         + [(64, "bf16", "f32"), (64, "f32", "f32"), (32, "f16", "f16")])
+@pytest.mark.parametrize("Hk, Hv, block_size", [(1, 2, None), (16, 48, None), (16, 32, 16)])
+def test_buffer_step_blocks(d, in_dtype, rec_dtype, Hk, Hv, block_size):
+    """kvb_decode without a state around every 16-record tile and 64-record block, with one and two v-heads a workgroup
+    (and an odd head left over), contiguous and paged: the token that joins fills[b] records, and the record it leaves."""
+    rng = np.random.default_rng(900 + d + Hv)
+    fills = np.array([0, 1, 15, 16, 17, 63, 64, 65, 127], np.int32)
+    B, n, cap = len(fills), 128, 128
+    tok = synth.token_stream(rng, B, n, Hk, Hv, d, d, in_dtype)
+    dtok = H.upload_tokens(tok, in_dtype)
+    lay = H.Layer(B, Hk, Hv, d, d, cap, in_dtype, with_state=False, rec_dtype=rec_dtype, out_dtype=rec_dtype, block_size=block_size)
+    for t in range(n - 1):   # request b joins so that all end at token n - 1
+        who = torch.from_numpy(np.flatnonzero(fills >= n - 1 - t)).cuda()
+        view = {x: y[who, t].contiguous() for x, y in dtok.items()}
+        lay.decode(view, lay.new_out(len(who), Hv, d), slot=lay.slot[who].contiguous(), B=len(who))
+    out = lay.new_out(B, Hv, d, fill=float("nan"))
+    lay.decode(H.step_view(dtok, n - 1), out)
+    torch.cuda.synchronize()
+    assert np.array_equal(lay.fill(), fills + 1) and lay.spare_clean()
+    errs = []
+    for b in range(B):
+        own = {x: y[b:b + 1, n - 1 - fills[b]:] for x, y in tok.items()}
+        o, u, _, _ = oracle.gdn_sequence(np.zeros((1, Hv, d, d)), own["q"], own["k"], own["v"], own["g"], own["beta"])
+        errs += [H.rel_err(H.host(out[b]), o[0, -1], lay.out_unit), H.rel_err(lay.u_records(b, 0, fills[b] + 1).transpose(1, 0, 2), u[0])]
+    say("buffer step, d=%d %s/%s %d/%d heads: rel err %.2e" % (d, in_dtype, rec_dtype, Hk, Hv, max(errs)))
+    H.check(errs, in_dtype, rec_dtype, "buffer step")
