@@ -78,11 +78,9 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     }
     const size_t unit = (size_t)s * a.Hv + h;
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[wave], lane, blk_id);
-    auto ru = [&](int l) { return pg.row(l, a.Hv, h); };
-    auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };
-    const float *Gbuf = a.st.buf_G;
-    const TIn *kb = static_cast<const TIn *>(a.st.buf_k);
-    const TRec *ub = static_cast<const TRec *>(a.st.buf_u);
+    const auto krec = make_rows<D>(static_cast<const TIn *>(a.st.buf_k), pg, a.Hk, hk);
+    const auto urec = make_rows<D>(static_cast<const TRec *>(a.st.buf_u), pg, a.Hv, h);
+    const auto Grec = make_rows<1>(static_cast<const float *>(a.st.buf_G), pg, a.Hv, h);
     const int RW = D == 128 ? 0 : 16 * RT * (wave / 2);                              // first row of the wave
     const int CW = D == 128 ? 16 * CT * wave : 16 * CT * (wave % 2);                 // and column
     const int row0 = RW + RT * lm, col0 = CW + CT * lm;
@@ -97,22 +95,25 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 #pragma unroll
         for (int j = 0; j < ST; ++j) {
             const int l = l0 + 4 * j + lq;
-            const size_t rl = ru(l < m ? l : 0), kl = rk(l < m ? l : 0);
-            copy_row<RT>(x.k[j], kb + kl * D + row0);
-            copy_row<CT>(x.u[j], ub + rl * D + col0);
-            x.G[j] = Gbuf[rl];
+            const int lc = l < m ? l : 0;
+            copy_row<RT>(x.k[j], krec.at(lc, row0));
+            copy_row<CT>(x.u[j], urec.at(lc, col0));
+            x.G[j] = *Grec.at(lc, 0);
         }
     };
-    const float Glast = Gbuf[ru(m - 1)];
+    const float Glast = *Grec.at(m - 1, 0);
     Chunk cur;
     load_chunk(0, cur);
-    float *sp = a.st.state + unit * D * D + col0;
+    // row r + RT 4 lq of the wave's columns: a scalar address and the lane's offset
+    float *sp = a.st.state + unit * D * D;
+    const uint32_t lane_at = (uint32_t)((RW + RT * 4 * lq) * D + col0) * 4;
+    auto state_at = [&](int r) { return reinterpret_cast<float *>(reinterpret_cast<char *>(sp + r * D) + lane_at); };
     float sreg[RT][4][CT];   // the lane's rows RW + RT (4 lq + v) + rt
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            copy_row<CT>(sreg[rt][v], sp + (size_t)(RW + RT * (4 * lq + v) + rt) * D);
+            copy_row<CT>(sreg[rt][v], state_at(RT * v + rt));
     __builtin_amdgcn_sched_barrier(0);
     const int ticket = take_ticket(&a.st.fill[s]);
 
@@ -165,7 +166,7 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 #pragma unroll
             for (int t = 0; t < CT; ++t)
                 o[t] = fmaf(gam, sreg[rt][v][t], acc[rt][t][v]);
-            copy_row<CT>(sp + (size_t)(RW + RT * (4 * lq + v) + rt) * D, o);
+            copy_row<CT>(state_at(RT * v + rt), o);
         }
     if (tid == 0)
         publish_if_last(&a.st.fill[s], ticket, a.Hv, 0);
@@ -257,12 +258,10 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     }
     const size_t unit = (size_t)s * a.Hv + h;
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[wave], lane, load_block_id<PAGED>(a.st, s, lane));
-    auto ru = [&](int l) { return pg.row(l, a.Hv, h); };
-    auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };
-    const float *Gbuf = a.st.buf_G;
-    const TIn *kb = static_cast<const TIn *>(a.st.buf_k);
-    const TRec *ub = static_cast<const TRec *>(a.st.buf_u);
-    const float Glast = Gbuf[ru(m - 1)];
+    const auto krec = make_rows<D>(static_cast<const TIn *>(a.st.buf_k), pg, a.Hk, hk);
+    const auto urec = make_rows<D>(static_cast<const TRec *>(a.st.buf_u), pg, a.Hv, h);
+    const auto Grec = make_rows<1>(static_cast<const float *>(a.st.buf_G), pg, a.Hv, h);
+    const float Glast = *Grec.at(m - 1, 0);
     const int col2 = 32 * wave + 2 * lm;
 
     // records 32 c + 8 lq + j of chunk c as raw bits; an index past m is clamped to record 0
@@ -275,9 +274,9 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
         for (int j = 0; j < 8; ++j) {
             const int l = CH * c + 8 * lq + j;
             const int lc = l < m ? l : 0;
-            kraw[j] = *reinterpret_cast<const uint4 *>(kb + rk(lc) * D + 8 * lm);
-            uraw[j] = load_raw2(ub + ru(lc) * D + col2);
-            Graw[j] = Gbuf[ru(lc)];
+            kraw[j] = *reinterpret_cast<const uint4 *>(krec.at(lc, 8 * lm));
+            uraw[j] = load_raw2(urec.at(lc, col2));
+            Graw[j] = *Grec.at(lc, 0);
         }
     };
     // first chunk, then the state tile: loads retire in issue order, and the products of the
@@ -287,12 +286,15 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     // State row tiles in flight: a window of 4 of the 8, refilled tile by tile as the results are
     // stored (all 8 in flight measured the same and cost a workgroup per CU).
     constexpr int WIN = 4;
-    float *sp = a.st.state + unit * D * D + col2;
+    // row r + 32 lq of the wave's columns: a scalar address and the lane's offset
+    float *sp = a.st.state + unit * D * D;
+    const uint32_t lane_at = (uint32_t)(32 * lq * D + col2) * 4;
+    auto state_at = [&](int r) { return reinterpret_cast<float *>(reinterpret_cast<char *>(sp + r * D) + lane_at); };
     float2 sreg[WIN][4];
     auto issue_state = [&](int rt) {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            sreg[rt % WIN][v] = load_state2<STREAM>(sp + (size_t)(32 * lq + 8 * v + rt) * D);
+            sreg[rt % WIN][v] = load_state2<STREAM>(state_at(8 * v + rt));
         __builtin_amdgcn_sched_barrier(0);   // issue in the order they are consumed
     };
 #pragma unroll
@@ -404,9 +406,9 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
             o.x = fmaf(gam, sreg[rt % WIN][v].x, c0[v] * up[0]);
             o.y = fmaf(gam, sreg[rt % WIN][v].y, c1[v] * up[1]);
             if constexpr (STREAM)
-                store2_nt(sp + (size_t)(32 * lq + 8 * v + rt) * D, o.x, o.y);
+                store2_nt(state_at(8 * v + rt), o.x, o.y);
             else
-                *reinterpret_cast<float2 *>(sp + (size_t)(32 * lq + 8 * v + rt) * D) = o;
+                *reinterpret_cast<float2 *>(state_at(8 * v + rt)) = o;
         }
         if (rt + WIN < 8) {
             __builtin_amdgcn_sched_barrier(0);
