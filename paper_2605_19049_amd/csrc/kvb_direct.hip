@@ -527,10 +527,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     const TIn *kbase = static_cast<const TIn *>(a.k) + ((size_t)b * Lmax * a.Hk + hk) * D;
     const TIn *qbase = static_cast<const TIn *>(a.q) + ((size_t)b * Lmax * a.Hk + hk) * D;
     const TIn *vbase = static_cast<const TIn *>(a.v) + ((size_t)b * Lmax * a.Hv + h) * D;
-    const uint32_t qk_stride = (uint32_t)a.Hk * D, v_stride = (uint32_t)a.Hv * D;
+    const uint32_t qk_stride = (uint32_t)a.Hk * (2 * D), v_stride = (uint32_t)a.Hv * (2 * D);   // bytes
+    // 16 rows from i0 on as a scalar address; a lane adds its own row (times the stride), cut off at the last row
+    auto row_at = [&](const TIn *base, uint32_t stride, int i0, uint32_t own, uint32_t in_row) {
+        const int r0 = min(i0, L - 1);   // (scalars)
+        const uint32_t last = (uint32_t)(L - 1 - r0) * stride;
+        return reinterpret_cast<const char *>(base) + (size_t)r0 * stride + (min(own, last) + in_row);
+    };
+    const uint32_t own_s = (uint32_t)srow * qk_stride, own_c = (uint32_t)c16 * qk_stride;
+    uint32_t own_v[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        own_v[v] = (uint32_t)(4 * lq + v) * v_stride;
 #pragma unroll
     for (int p = 0; p < NB; ++p)   // pass p = rows 16 p .. 16 p + 15, 16 bytes per thread
-        kst[p] = *reinterpret_cast<const u32x4_t *>(kbase + (uint32_t)min(16 * p + srow, L - 1) * qk_stride + 8 * sc8);
+        kst[p] = *reinterpret_cast<const u32x4_t *>(row_at(kbase, qk_stride, 16 * p, own_s, 16 * sc8));
     // Q is not staged: the waves read the rows of their q.k tiles straight from memory in the
     // operand layout of the matrix instruction (row 16 d + c16, k = 8 lq + 32 step); a block of
     // 16 query rows is 4 KB and is shared by at most 4 tiles, so the repeats hit in the caches.
@@ -542,23 +553,26 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     u32x4_t qop[3][4];   // n = 1 (waves 2, 3 only), 2, 3
 #pragma unroll
     for (int n = 1; n < 4; ++n) {
-        const uint32_t o = (uint32_t)min(16 * PD(wave + NW * n) + c16, L - 1) * qk_stride + 8 * lq;
+        const char *qrow = row_at(qbase, qk_stride, 16 * PD(wave + NW * n), own_c, 16 * lq);
 #pragma unroll
         for (int st = 0; st < 4; ++st)
-            qop[n - 1][st] = *reinterpret_cast<const u32x4_t *>(qbase + o + 32 * st);
+            qop[n - 1][st] = *reinterpret_cast<const u32x4_t *>(qrow + 64 * st);
     }
-    const size_t gb_o = ((size_t)b * Lmax + min(lane, L - 1)) * a.Hv + h;
-    float g_raw = a.g[gb_o], beta_raw = a.beta[gb_o];   // (every wave: a branch around a load costs more)
+    const size_t gb_o = (size_t)b * Lmax * a.Hv + h;
+    const uint32_t gb_l = (uint32_t)min(lane, L - 1) * a.Hv;
+    float g_raw = (a.g + gb_o)[gb_l], beta_raw = (a.beta + gb_o)[gb_l];   // (every wave: a branch around a load costs more)
     float g_raw1 = 0.0f, beta_raw1 = 0.0f;
     if constexpr (LONG) {
-        const size_t gb_o1 = ((size_t)b * Lmax + min(LM + lane, L - 1)) * a.Hv + h;
-        g_raw1 = a.g[gb_o1];
-        beta_raw1 = a.beta[gb_o1];
+        const uint32_t gb_l1 = (uint32_t)min(LM + lane, L - 1) * a.Hv;
+        g_raw1 = (a.g + gb_o)[gb_l1];
+        beta_raw1 = (a.beta + gb_o)[gb_l1];
     }
 
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, a.cap, sBlk[wave], lane, load_block_id<PAGED>(a.st, s, lane));
     auto ru = [&](int l) { return pg.row(l, a.Hv, h); };
-    auto rk = [&](int l) { return pg.row(l, a.Hk, hk); };
+    const auto krec = make_rows<D>(static_cast<TIn *>(a.st.buf_k), pg, a.Hk, hk);
+    const auto urec = make_rows<D>(static_cast<TRec *>(a.st.buf_u), pg, a.Hv, h);
+    const auto Grec = make_rows<1>(a.st.buf_G, pg, a.Hv, h);
     const Out<TIn> out{a.out, a.out_wide != 0};
     const int nb = ((LONG ? min(L, LM) : L) + 15) / 16;
     auto tri = [](int d, int e) { return d * (d + 1) / 2 + e; };    // slot of pair d >= e
@@ -611,16 +625,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
         sG[row] = gv;
         sB[row] = bv;
         if (row < L)
-            a.st.buf_G[ru(row)] = gv;
+            *Grec.at(row, 0) = gv;
     }
     // stage K; the thread that loaded a piece of K also appends it to the buffer
-    TIn *kb = static_cast<TIn *>(a.st.buf_k);
 #pragma unroll
     for (int p = 0; p < NB; ++p) {
         if (p < nb) {   // uniform
             *reinterpret_cast<u32x4_t *>(sK + (16 * p + srow) * GS + 8 * sc8) = kst[p];
             if (h % r == 0 && 16 * p + srow < L)
-                *reinterpret_cast<u32x4_t *>(kb + rk(16 * p + srow) * D + 8 * sc8) = kst[p];
+                *reinterpret_cast<u32x4_t *>(krec.at(16 * p, srow, 8 * sc8)) = kst[p];
         }
     }
     __syncthreads();
@@ -659,8 +672,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     for (int d = 0; d < NB; ++d)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            v_raw[d][v] = *reinterpret_cast<const uint32_t *>(
-                vbase + (uint32_t)min(16 * d + 4 * lq + v, L - 1) * v_stride + col2);
+            v_raw[d][v] = *reinterpret_cast<const uint32_t *>(row_at(vbase, v_stride, 16 * d, own_v[v], 2 * col2));
     // ---- weights and masks.  A-form element of tile (d, e): row i = 16 d + c16, column l = 16 e + 4 lq + v.
     // N tiles go to LDS in fp32 (they enter the inverse), M tiles are cut into pieces at once.
 #pragma unroll
@@ -827,8 +839,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     // three (16 registers less; they are cut again where they are used)
     constexpr bool RECUT = NPU > 2;
     f32x4_t ukeep[LONG && RECUT ? NB : 1][2];
+    // outputs: a scalar row 16 d + v, and the lane's rows 4 lq below it
     const size_t outp = (((size_t)b * Lmax) * a.Hv + h) * D;
-    TRec *up = static_cast<TRec *>(a.st.buf_u);
+    const uint32_t out_l = (uint32_t)(4 * lq) * a.Hv * D + col2;
+    auto out_row = [&](int i) { return outp + (size_t)i * a.Hv * D; };
     float big = 0.0f;   // largest output
 #pragma unroll
     for (int d = 0; d < NB; ++d) {
@@ -890,8 +904,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                 if (i < L) {
                     // (streaming stores: neither array is read again by this kernel, and lines that do not
                     // linger in the L2 leave it to the keys, queries and values that the heads of a request share)
-                    out.put2_nt(outp + ((uint32_t)i * v_stride + col2), a.scale * o[0][v], a.scale * o[1][v]);
-                    store2_nt(up + (ru(i) * D + col2), U[0][v], U[1][v]);
+                    out.put2_nt(out_row(16 * d + v), out_l, a.scale * o[0][v], a.scale * o[1][v]);
+                    store2_nt(urec.at(16 * d + v, 4 * lq, col2), U[0][v], U[1][v]);
                 }
             }
         }
@@ -902,14 +916,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
             // keys of both panels for staging (the first panel's again: their place in LDS was needed), and
             // this wave's 16 query rows in operand layout
             u32x4_t ks[2 * NB], qo[4];
+            // (the lane's row offsets again, opaque: kept from the first panel they cost registers all the way)
+            int row_s = srow, row_c = c16, row_q = lq;
+            asm volatile("" : "+v"(row_s), "+v"(row_c), "+v"(row_q));
 #pragma unroll
             for (int p = 0; p < 2 * NB; ++p)
-                ks[p] = *reinterpret_cast<const u32x4_t *>(kbase + (uint32_t)min(16 * p + srow, L - 1) * qk_stride + 8 * sc8);
+                ks[p] = *reinterpret_cast<const u32x4_t *>(row_at(kbase, qk_stride, 16 * p, (uint32_t)row_s * qk_stride, 16 * sc8));
             {
-                const uint32_t o = (uint32_t)min(LM + 16 * wave + c16, L - 1) * qk_stride + 8 * lq;
+                const char *qrow = row_at(qbase, qk_stride, LM + 16 * wave, (uint32_t)row_c * qk_stride, 16 * lq);
 #pragma unroll
                 for (int st = 0; st < 4; ++st)
-                    qo[st] = *reinterpret_cast<const u32x4_t *>(qbase + o + 32 * st);
+                    qo[st] = *reinterpret_cast<const u32x4_t *>(qrow + 64 * st);
             }
             __syncthreads();   // the first panel's pieces are no longer read
             TIn *sK1 = reinterpret_cast<TIn *>(region + STAGE_BYTES);
@@ -918,7 +935,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                 *reinterpret_cast<u32x4_t *>(sK + (16 * p + srow) * GS + 8 * sc8) = ks[p];
                 *reinterpret_cast<u32x4_t *>(sK1 + (16 * p + srow) * GS + 8 * sc8) = ks[NB + p];
                 if (h % r == 0 && LM + 16 * p + srow < L)
-                    *reinterpret_cast<u32x4_t *>(kb + rk(LM + 16 * p + srow) * D + 8 * sc8) = ks[NB + p];
+                    *reinterpret_cast<u32x4_t *>(krec.at(LM + 16 * p, srow, 8 * sc8)) = ks[NB + p];
             }
             __syncthreads();
 
@@ -1045,8 +1062,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                 for (int d = 0; d < NB; ++d)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        v1_raw[d][v] = *reinterpret_cast<const uint32_t *>(
-                            vbase + (uint32_t)min(LM + 16 * d + 4 * lq + v, L - 1) * v_stride + col2);
+                        v1_raw[d][v] = *reinterpret_cast<const uint32_t *>(row_at(vbase, v_stride, LM + 16 * d, (uint32_t)(4 * row_q + v) * v_stride, 2 * col2));
             };
             inverse_first_half(nb1, t_own);
             __builtin_amdgcn_sched_barrier(0);
@@ -1114,7 +1130,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                     for (int v = 0; v < 4; ++v) {
                         const int i = LM + 16 * e + 4 * lq + v;
                         if (i < L)
-                            store2_nt(up + (ru(i) * D + col2), u1[e][0][v], u1[e][1][v]);
+                            store2_nt(urec.at(LM + 16 * e + v, 4 * lq, col2), u1[e][0][v], u1[e][1][v]);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -1163,7 +1179,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                     for (int v = 0; v < 4; ++v) {
                         const int i = LM + 16 * e + 4 * lq + v;
                         if (i < L)
-                            out.put2_nt(outp + ((uint32_t)i * v_stride + col2), a.scale * o1[e][0][v], a.scale * o1[e][1][v]);
+                            out.put2_nt(out_row(LM + 16 * e + v), out_l, a.scale * o1[e][0][v], a.scale * o1[e][1][v]);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
