@@ -450,9 +450,8 @@ __device__ __forceinline__ int logical_block() { return logical_block(gridDim.x)
 // Which unit a workgroup of kvb_direct takes, whose work grows with the context: the heads of a request are dealt
 // over all XCDs, one qk-head with its r v-heads (which share keys and queries through the XCD's L2) at a time; with
 // whole requests on one XCD, as the kernels with a ticket word need it, the XCD that drew the longest contexts set the
-// end of the launch (256 contexts of ~U(1,64): 118 -> 110 us; 96 of ~U(1,128): 130 -> 115 us).  Handing out the longest
-// contexts first (every workgroup ranks the lengths) was 8 % slower at 64 tokens, where the work of a launch is most
-// uniform in time; above 64 tokens it has not been tried.
+// end of the launch (256 contexts of ~U(1,64): 118 -> 110 us; 96 of ~U(1,128): 130 -> 115 us).  The order of the requests is
+// another matter (longest_first in kvb_direct.hip).
 // Rounds of 8 qk-heads are dealt, one to an XCD; the units of the qk-heads that are left (fewer than 8) go one by one.
 // Where some are left, from 1024 units on (four workgroups a CU; below that all run at once, and what the v-heads of a
 // qk-head share is worth less than spreading contexts of one length over the CUs).  Against unit = workgroup id, d =

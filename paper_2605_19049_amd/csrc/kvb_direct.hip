@@ -322,15 +322,26 @@ __device__ __forceinline__ f32x4_t mm16_pieces(const uint2 (&x)[NPX], const uint
 
 // ---------------------------------------------------------------------------
 // Longest contexts first.  The work of a launch grows with the contexts faster than linearly, and in the order of the
-// batch a launch of up to 128 tokens ended with whatever long contexts had come last.  Every workgroup therefore sorts
-// the lengths of the batch, by counting, into classes of 16 tokens (the blocks that the kernel works in; the order of the
-// batch inside a class) and takes the p-th request of that order: one vector load of lengths in the place of the scalar
-// one, a barrier and a scan over 64 counts.  96 contexts of ~U(1, 128), 32 heads, with the fold 236 -> 227.5 us; 128 of
-// ~U(1, 100), fp16, and 16 steps from the buffer 482 -> 476.  More than MAX_RANKED requests keep their order: their
-// launch is many times as long as its end.  Up to 64 tokens: not sorted, see deal_of.
+// batch a launch ends with whatever long contexts have come last.  Every workgroup therefore sorts the lengths of the
+// batch, by counting, into classes of 16 tokens (the blocks that the kernels work in; the order of the batch inside a
+// class) and takes the p-th request of that order: one vector load of lengths in the place of the scalar one, a barrier
+// and a scan over 64 counts, 0.3 to 0.6 us.
 // lead: Hv, or with its sign bit set a batch of B (<= MAX_RANKED) requests to be sorted in bits 16.., Hv in the rest.
-// ---------------------------------------------------------------------------
+// Rule (longest_first), us a call in the order of the batch / sorted, 32 heads unless said:
+//   up to 128 tokens, d = 128: 96 contexts, bf16, 109 / 100; 128 of up to 100, fp16, 103 / 94; 400 of up to 112, fp16,
+//     473 / 451; 8 23.5 / 24.1; 4 29.0 / 29.6
+//   up to 64 tokens, d = 128, bf16: 256 contexts 105 / 106; 128 57 / 58; 96 46.6 / 47.6; 64 32.7 / 29.7; 24 16.7 / 16.4;
+//     16 16.5 / 15.2; 12 15.5 / 14.0; 8 12.8 / 13.4; fp16: 256 84 / 86; 96 37.9 / 37.8; 40 20.5 / 18.2; 8 11.7 / 12.2;
+//     heads of 8: 100 contexts 22.4 / 17.0, 45 13.6 / 13.1, 13 11.7 / 12.3
+//   up to 64 tokens, block rows: d = 64, heads of 16: 48 contexts 19.4 / 16.7, 100 32.0 / 27.7, 24 12.6 / 13.3, 8 9.4 / 10.2;
+//     500 of 32 heads and up to 40 139 / 153; fp32, d = 128: 40 48.2 / 43.8, 100 93 / 89; d = 32: 60 23.9 / 23.2
+// Below the lower lines all workgroups run at once; beyond the upper one the end is a small part of the launch, and
+// mixed lengths share the memory better (up to 128 tokens the work differs too much for that).
 constexpr int MAX_RANKED = 2 * NT;
+inline bool longest_first(int blocks, int Lmax, bool mfma)
+{
+    return blocks >= (mfma ? 320 : 512) && (Lmax > 64 || blocks <= 2560);
+}
 __host__ __device__ inline int rank_lead(int B, int Hv, bool rank)
 {
     return rank && B > 1 && B <= MAX_RANKED && Hv < 65536 ? (int)(0x80000000u | (uint32_t)B << 16 | (uint32_t)Hv) : Hv;
@@ -488,9 +499,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     const int lb = dealt_unit(blockIdx.x, deal_arg);
     const int Hv = lead_arg < 0 ? lead_arg & 0xFFFF : lead_arg;
     int b = lb / Hv, L;
-    if (LONG && lead_arg < 0) {   // uniform
+    if (__builtin_expect(lead_arg < 0, LONG)) {   // uniform
         // (its tables lie where nothing is written before the barrier behind the staged keys)
-        static_assert(!LONG || REGION_BYTES >= STAGE_BYTES + 4 * (MAX_RANKED + 64), "room for the lengths");
+        static_assert(REGION_BYTES >= STAGE_BYTES + 4 * (MAX_RANKED + 64), "room for the lengths");
         int *tables = reinterpret_cast<int *>(region + STAGE_BYTES);
         b = ranked_request(len_arg, lead_arg >> 16 & 0x7FFF, a.Lmax, b, wave, lane, L, tables, tables + MAX_RANKED);
     } else {
@@ -1222,7 +1233,7 @@ template <int D, typename TIn, typename TRec, bool PAGED>
 // 26 KB, and six were 6 % faster than five at 500 requests of 32 heads)
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     D == 128 ? 2 : D == 32 && sizeof(TIn) == 2 && sizeof(TRec) == 4 ? 6 : 4))) void kvb_direct_rows_kernel(
-    const int32_t *len_arg, int32_t Hv_arg, int32_t deal_arg, const DirectArgs a)
+    const int32_t *len_arg, int32_t lead_arg, int32_t deal_arg, const DirectArgs a)
 {
     // (leading arguments: see kvb_direct_mfma_kernel)
     constexpr int LM = 64;   // longest context
@@ -1245,10 +1256,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;   // (a scalar)
     const int c16 = lane % 16, lq = lane / 16;
     const int lb = dealt_unit(blockIdx.x, deal_arg);
-    const int b = lb / Hv_arg;
-    int L = len_arg[b];
+    const int Hv = lead_arg < 0 ? lead_arg & 0xFFFF : lead_arg;
+    int b = lb / Hv, L;
+    if (__builtin_expect(lead_arg < 0, 0)) {   // uniform
+        // (its tables lie where nothing is written before the barrier behind the staged keys)
+        static_assert(sizeof(tM) >= 4 * (MAX_RANKED + 64), "room for the lengths");
+        int *tables = reinterpret_cast<int *>(&tM[0][0]);
+        b = ranked_request(len_arg, lead_arg >> 16 & 0x7FFF, a.Lmax, b, wave, lane, L, tables, tables + MAX_RANKED);
+    } else {
+        L = len_arg[b];
+    }
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int h = lb % Hv_arg;
+    const int h = lb % Hv;
     const int r = a.Hv / a.Hk;
     const int hk = h / r;
     const int Lmax = a.Lmax;
@@ -1479,27 +1498,23 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
 // ---------------------------------------------------------------------------
 int launch_direct(int dk, int in_dtype, int rec_dtype, const DirectArgs &a, int blocks, hipStream_t stream)
 {
-    const int32_t lead = rank_lead(blocks / a.Hv, a.Hv, a.Lmax > 64);
-    if (dk == 128 && in_dtype != KVB_F32)
+    const bool mfma = dk == 128 && in_dtype != KVB_F32, sorted = longest_first(blocks, a.Lmax, mfma);
+    const int32_t lead = rank_lead(blocks / a.Hv, a.Hv, sorted), deal = deal_of(blocks, a.Hv / a.Hk);
+    auto start = [&](auto paged, auto contiguous) {
+        launch(a.st.block_table ? paged : contiguous, blocks, stream, a.len, lead, deal, a);
+    };
+    if (mfma)
         return dispatch_types16(in_dtype, rec_dtype, [&]<typename TIn, typename TRec>() {
-            if (a.Lmax > 64 && a.st.block_table)   // two panels of 64 rows
-                launch(kvb_direct_mfma_kernel<TIn, TRec, true, true>, blocks, stream, a.len, lead, deal_of(blocks, a.Hv / a.Hk), a);
-            else if (a.Lmax > 64)
-                launch(kvb_direct_mfma_kernel<TIn, TRec, true, false>, blocks, stream, a.len, lead, deal_of(blocks, a.Hv / a.Hk), a);
-            else if (a.st.block_table)
-                launch(kvb_direct_mfma_kernel<TIn, TRec, false, true>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
+            if (a.Lmax > 64)   // two panels of 64 rows
+                start(kvb_direct_mfma_kernel<TIn, TRec, true, true>, kvb_direct_mfma_kernel<TIn, TRec, true, false>);
             else
-                launch(kvb_direct_mfma_kernel<TIn, TRec, false, false>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
+                start(kvb_direct_mfma_kernel<TIn, TRec, false, true>, kvb_direct_mfma_kernel<TIn, TRec, false, false>);
         });
     if (a.Lmax > 64)   // the block-row kernel holds a 64-token context in LDS
         return KVB_EUNSUPPORTED;
     return dispatch(dk, in_dtype, rec_dtype, [&]<int D, typename TIn, typename TRec>() {
-        if constexpr (!(D == 128 && sizeof(TIn) == 2)) {
-            if (a.st.block_table)
-                launch(kvb_direct_rows_kernel<D, TIn, TRec, true>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
-            else
-                launch(kvb_direct_rows_kernel<D, TIn, TRec, false>, blocks, stream, a.len, a.Hv, deal_of(blocks, a.Hv / a.Hk), a);
-        }
+        if constexpr (!(D == 128 && sizeof(TIn) == 2))
+            start(kvb_direct_rows_kernel<D, TIn, TRec, true>, kvb_direct_rows_kernel<D, TIn, TRec, false>);
     });
 }
 

@@ -177,16 +177,17 @@ def test_fold_of_an_overdue_buffer(d, in_dtype, cap, Hk, Hv):
     H.check(errs, in_dtype, what="overdue buffer")
 
 
-@pytest.mark.parametrize("B", [2, 63, 65, 255, 257, 512, 513])
-def test_direct_longest_first(B):
+@pytest.mark.parametrize("d, Lmax, in_dtype", [(128, 128, "bf16"), (128, 64, "f16"), (64, 64, "bf16")])
+@pytest.mark.parametrize("B, Hv", [(2, 256), (63, 9), (65, 8), (255, 3), (257, 2), (512, 1), (513, 1)])
+def test_direct_longest_first(d, Lmax, in_dtype, B, Hv):
     """Batches around the wave, workgroup and table sizes of the sort by length, every class of lengths among them;
     an untaken unit leaves NaN in its outputs."""
     rng = np.random.default_rng(890 + B)
-    lens = rng.integers(0, 129, B).astype(np.int32)
-    lens[:2] = [0, 128]
-    e = _direct_case(B=B, Hk=1, Hv=1, d=128, Lmax=128, cap=128, in_dtype="bf16", seed=891 + B, lens=lens, then_decode=False)
-    say("direct, longest first, B=%d: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((B,) + e))
-    H.check(e, "bf16", what="longest first")
+    lens = rng.integers(0, Lmax + 1, B).astype(np.int32)
+    lens[:2] = [0, Lmax]
+    e = _direct_case(B=B, Hk=1, Hv=Hv, d=d, Lmax=Lmax, cap=Lmax, in_dtype=in_dtype, seed=891 + B, lens=lens, then_decode=False)
+    say("direct, longest first, d=%d B=%d: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((d, B) + e))
+    H.check(e, in_dtype, what="longest first")
 
 
 @pytest.mark.parametrize("d, in_dtype, rec_dtype", [(128, i, r) for i, r in TYPES + [("f32", "f32")]]
