@@ -433,12 +433,14 @@ __device__ __forceinline__ int ranked_request(const int32_t *len, int B, int Lma
 // instead of three).  Bound by the issue of vector and matrix instructions at three long-lived waves per
 // SIMD.  96 contexts of ~U(1,128), 32 heads, bf16 with fp32 records: 192 -> 130 us (without the fold) against the kernel
 // before it (8 block rows solved one after the other with fp32 matrix instructions); 128 of ~U(1,100),
-// fp16 throughout: 193 -> 127 us.  Two workgroups per CU without any spill were 5 % slower than three that
-// spill (with fp32 records 19 words for bf16 and 12 for fp16, with 16-bit records 9 and 8; paged 12, 12, 0, 0);
+// fp16 throughout: 193 -> 127 us.  Two workgroups per CU without any spill were 5 % slower than three that spill.  Token rows
+// are a scalar address and the lane's own row, whose offsets the second panel works out again: 64-bit addresses lane by
+// lane, kept from the first panel, made three workgroups spill 15 to 24 words (now one with fp32 records, none with 16-bit
+// ones): 96 contexts 100 -> 95 us (both sorted by length);
 // pieces of U_0 kept in registers instead of cut again: two fit.
 // ---------------------------------------------------------------------------
-// Workgroups per CU: the two fp16 pieces need 28 KB of LDS and 92 registers, which leaves room for
-// five (6 % faster than four on ragged lengths); the three bf16 pieces need 36 KB and 124.
+// Workgroups per CU: the two fp16 pieces need 28 KB of LDS and 95 registers, which leaves room for
+// five (6 % faster than four on ragged lengths); the three bf16 pieces need 36 KB and 118.
 // LONG: 53 KB and 168 registers, three.
 template <typename T, bool LONG>
 constexpr int DIRECT_WG_PER_CU = LONG ? 3 : __is_same(T, f16_t) ? 5 : 4;
@@ -498,19 +500,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     const int c16 = lane % 16, lq = lane / 16;
     const int lb = dealt_unit(blockIdx.x, deal_arg);
     const int Hv = lead_arg < 0 ? lead_arg & 0xFFFF : lead_arg;
-    int b = lb / Hv, L;
+    const int place = quotient(lb, Hv);   // of the request in the order of the launch
+    int b = place, L;
     if (__builtin_expect(lead_arg < 0, LONG)) {   // uniform
         // (its tables lie where nothing is written before the barrier behind the staged keys)
         static_assert(REGION_BYTES >= STAGE_BYTES + 4 * (MAX_RANKED + 64), "room for the lengths");
         int *tables = reinterpret_cast<int *>(region + STAGE_BYTES);
-        b = ranked_request(len_arg, lead_arg >> 16 & 0x7FFF, a.Lmax, b, wave, lane, L, tables, tables + MAX_RANKED);
+        b = ranked_request(len_arg, lead_arg >> 16 & 0x7FFF, a.Lmax, place, wave, lane, L, tables, tables + MAX_RANKED);
     } else {
         L = len_arg[b];
     }
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int h = lb % Hv;
-    const int r = a.Hv / a.Hk;
-    const int hk = h / r;
+    const int h = lb - place * Hv;
+    const int r = quotient(a.Hv, a.Hk);
+    const int hk = quotient(h, r);
     const int Lmax = a.Lmax;
 
     const int s = a.slot[b];
@@ -643,7 +646,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     for (int p = 0; p < NB; ++p) {
         if (p < nb) {   // uniform
             *reinterpret_cast<u32x4_t *>(sK + (16 * p + srow) * GS + 8 * sc8) = kst[p];
-            if (h % r == 0 && 16 * p + srow < L)
+            if (h == hk * r && 16 * p + srow < L)
                 *reinterpret_cast<u32x4_t *>(krec.at(16 * p, srow, 8 * sc8)) = kst[p];
         }
     }
@@ -945,7 +948,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
             for (int p = 0; p < NB; ++p) {
                 *reinterpret_cast<u32x4_t *>(sK + (16 * p + srow) * GS + 8 * sc8) = ks[p];
                 *reinterpret_cast<u32x4_t *>(sK1 + (16 * p + srow) * GS + 8 * sc8) = ks[NB + p];
-                if (h % r == 0 && LM + 16 * p + srow < L)
+                if (h == hk * r && LM + 16 * p + srow < L)
                     *reinterpret_cast<u32x4_t *>(krec.at(LM + 16 * p, srow, 8 * sc8)) = ks[NB + p];
             }
             __syncthreads();
@@ -1257,19 +1260,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     const int c16 = lane % 16, lq = lane / 16;
     const int lb = dealt_unit(blockIdx.x, deal_arg);
     const int Hv = lead_arg < 0 ? lead_arg & 0xFFFF : lead_arg;
-    int b = lb / Hv, L;
+    const int place = quotient(lb, Hv);   // of the request in the order of the launch
+    int b = place, L;
     if (__builtin_expect(lead_arg < 0, 0)) {   // uniform
         // (its tables lie where nothing is written before the barrier behind the staged keys)
         static_assert(sizeof(tM) >= 4 * (MAX_RANKED + 64), "room for the lengths");
         int *tables = reinterpret_cast<int *>(&tM[0][0]);
-        b = ranked_request(len_arg, lead_arg >> 16 & 0x7FFF, a.Lmax, b, wave, lane, L, tables, tables + MAX_RANKED);
+        b = ranked_request(len_arg, lead_arg >> 16 & 0x7FFF, a.Lmax, place, wave, lane, L, tables, tables + MAX_RANKED);
     } else {
         L = len_arg[b];
     }
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int h = lb % Hv;
-    const int r = a.Hv / a.Hk;
-    const int hk = h / r;
+    const int h = lb - place * Hv;
+    const int r = quotient(a.Hv, a.Hk);
+    const int hk = quotient(h, r);
     const int Lmax = a.Lmax;
 
     const int s = a.slot[b];
@@ -1337,7 +1341,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     for (int p = 0; p < NPS; ++p) {
         const int row = NT / CPR * p + srow;
         *reinterpret_cast<u32x4_t *>(sK + row * GS + EPC * sch) = kst[p];
-        if (h % r == 0 && row < L)
+        if (h == hk * r && row < L)
             *reinterpret_cast<u32x4_t *>(kb + rk(row) * D + EPC * sch) = kst[p];
     }
     // Cumulative log decay and beta.  Token by token: only differences G_i - G_l are used, nearby ones above all,

@@ -45,11 +45,11 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
     const int lm = lane % 16, lq = lane / 16;
     const int lb = logical_block(nblocks_arg);
-    const int b = lb / Hv_arg;
+    const int b = quotient(lb, Hv_arg);
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int h = lb % Hv_arg;
-    const int hk = h / (a.Hv / a.Hk);
+    const int h = lb - b * Hv_arg;
+    const int hk = quotient(h, quotient(a.Hv, a.Hk));
     const int cap = a.cap;
 
     if (s < 0 || s >= a.st.n_slots)
@@ -228,11 +228,11 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;   // (a scalar)
     const int lm = lane % 16, lq = lane / 16;
     const int lb = logical_block(nblocks_arg);
-    const int b = lb / Hv_arg;
+    const int b = quotient(lb, Hv_arg);
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int h = lb % Hv_arg;
-    const int hk = h / (a.Hv / a.Hk);
+    const int h = lb - b * Hv_arg;
+    const int hk = quotient(h, quotient(a.Hv, a.Hk));
     const int cap = a.cap;
 
     if (s < 0 || s >= a.st.n_slots)
@@ -458,11 +458,11 @@ __global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg
     static_assert(KVB_MAX_DRAFTS * PU <= NT && KVB_MAX_DRAFTS * PK <= NT, "a thread to each piece");
     __shared__ int sBlk[NW][MAX_BLOCKS];
     const int tid = threadIdx.x, lane = tid % 64;
-    const int b = blockIdx.x / Hv_arg;
+    const int b = quotient(blockIdx.x, Hv_arg);
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int h = blockIdx.x % Hv_arg;
-    const int r = a.Hv / a.Hk;
+    const int h = (int)blockIdx.x - b * Hv_arg;
+    const int r = quotient(a.Hv, a.Hk), hk = quotient(h, r);
     if (s < 0 || s >= a.st.n_slots)
         return;
     const int blk_id = load_block_id<PAGED>(a.st, s, lane);
@@ -480,10 +480,10 @@ __global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg
         return;
     }
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, a.cap, sBlk[tid / 64], lane, blk_id);
-    const auto krec = make_rows<D>(static_cast<TIn *>(a.st.buf_k), pg, a.Hk, h / r);
+    const auto krec = make_rows<D>(static_cast<TIn *>(a.st.buf_k), pg, a.Hk, hk);
     const auto urec = make_rows<D>(static_cast<TRec *>(a.st.buf_u), pg, a.Hv, h);
     const auto Grec = make_rows<1>(a.st.buf_G, pg, a.Hv, h);
-    const bool mu = ju < n && pu != ju, mk = h % r == 0 && jk < n && pk != jk, mG = tid < n && pj != tid;
+    const bool mu = ju < n && pu != ju, mk = h == hk * r && jk < n && pk != jk, mG = tid < n && pj != tid;
     const int eu = tid % PU * (16 / (int)sizeof(TRec)), ek = tid % PK * (16 / (int)sizeof(TIn));
     uint4 u = {0, 0, 0, 0}, k = {0, 0, 0, 0};
     float G = 0.0f;

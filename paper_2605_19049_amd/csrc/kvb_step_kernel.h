@@ -125,12 +125,12 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 
     const int tid = threadIdx.x;
     const int lb = logical_block(nblocks_arg);
-    const int b = lb / Hv_arg;
+    const int b = quotient(lb, Hv_arg);
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int h = lb % Hv_arg;
-    const int r = a.Hv / a.Hk;
-    const int hk = h / r;
+    const int h = lb - b * Hv_arg;
+    const int r = quotient(a.Hv, a.Hk);
+    const int hk = quotient(h, r);
     const int cap = a.cap;
     if (s < 0 || s >= a.st.n_slots)
         return;
@@ -415,7 +415,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     }
     if (tid == 0)
         *Grec.at(f, 0) = Gc;
-    if (h % r == 0 && tid < D / 8)   // the threads that loaded the new k row store it
+    if (h == hk * r && tid < D / 8)   // the threads that loaded the new k row store it
         store_raw8(krec.at(f, 8 * sub), k_raw);
     const int m = f + 1;
     if (overdue)
@@ -748,13 +748,13 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
 
     const int tid = threadIdx.x;
     const int lb = logical_block(nblocks_arg);
-    const int b = lb / nu_arg;
+    const int b = quotient(lb, nu_arg);
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int r = a.Hv / a.Hk;
+    const int r = quotient(a.Hv, a.Hk);
     const int per = (r + HB - 1) / HB;   // workgroups of a key head
-    const int hk = lb % nu_arg / per;
-    const int h0 = hk * r + lb % nu_arg % per * HB, hlast = hk * r + r - 1;
+    const int of_b = lb - b * nu_arg, hk = quotient(of_b, per);
+    const int h0 = hk * r + (of_b - hk * per) * HB, hlast = hk * r + r - 1;
     const int nh = min(HB, hlast - h0 + 1);
     const int cap = a.cap;
     if (s < 0 || s >= a.st.n_slots)
@@ -834,7 +834,7 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
         }
         __builtin_amdgcn_sched_barrier(0);
         if (l0 == 0 && a.advance)
-            advance_fill(&a.st.fill[s], lb % nu_arg == 0, nu_arg, 1);
+            advance_fill(&a.st.fill[s], of_b == 0, nu_arg, 1);
         if constexpr (MDOT) {
             if (l0 + 16 * wave < f) {   // uniform
                 // rows 4 lq + v of the product are k (v = 0) and q (v = 1) for every lq, its columns the records
