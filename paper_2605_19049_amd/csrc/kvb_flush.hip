@@ -448,7 +448,8 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 // commits them (Sec. 3.3, Eq. 8: the state is updated from the accepted tokens
 // only).  A few KB a unit: bound by the chain of loads, so every thread carries one 16-byte piece of one record of
 // each array, all moves are requested at once, and the stores come behind a barrier (a record may be the source of one
-// move and the destination of another).  7 requests of 32 heads, 8 nodes, fp16: move by move 4.2 us, at once 3.1 us.
+// move and the destination of another).  7 requests of 32 heads, 8 nodes, fp16, verified, compacted and committed: 22.1 us a
+// pass move by move, 21.1 at once.
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, bool PAGED>
 __global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg,
