@@ -127,6 +127,8 @@ int step_common(const kvb_shape *sh, const kvb_store *st, const int32_t *slot, i
                // chain: g stands in as a readable array of at least B*T words whose values are ignored
                parent ? parent : reinterpret_cast<const int32_t *>(g), parent ? 1 : 0};
     const int blocks = sh->B * sh->Hv;
+    if (advance && step_workgroups(a, sh->dk, blocks) > MAX_FILL_WG)
+        return KVB_EINVAL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     g_launch_status = hipSuccess;
     if (T > 1)   // several drafts: the matrix-core kernel (the head size was checked above)
@@ -220,6 +222,8 @@ int kvb_flush(const kvb_shape *shape, const kvb_store *store, const int32_t *slo
         return KVB_EINVAL;
     if (shape->B == 0)
         return KVB_OK;
+    if (shape->Hv > MAX_FILL_WG)
+        return KVB_EINVAL;
     FlushArgs a{dev_store(store), slot, accepted, shape->Hk, shape->Hv, shape->cap, threshold,
                 store->state && stream_state(shape, store, 192.0) ? 1 : 0};
     const int blocks = shape->B * shape->Hv;

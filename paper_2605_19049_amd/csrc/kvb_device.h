@@ -380,7 +380,8 @@ __device__ __forceinline__ void fma4(float4 &acc, float c, const float4 &x)
 // the word is positive throughout.  It is taken once the loads are in flight (take_ticket) and looked at at the end.
 // All of these hold the barrier, so every thread of the workgroup calls them (advance_fill_read, take_ticket: those
 // behind a barrier of the caller's are called by all, too).
-__host__ __device__ inline int fill_share(bool first, int nwg, int change)   // nwg <= 2^15 workgroups
+constexpr int MAX_FILL_WG = 1 << 15;   // workgroups of a request that bits 16.. can count, the sign apart
+__host__ __device__ inline int fill_share(bool first, int nwg, int change)   // nwg <= MAX_FILL_WG
 {
     return first ? change - (nwg - 1) * TICKET_ONE : TICKET_ONE;
 }
@@ -724,6 +725,18 @@ int dispatch(int dk, int in_dtype, int rec_dtype, F &&f)
         else
             f.template operator()<128, TIn, TRec>();
     });
+}
+
+// v-heads of a workgroup of kvb_buffer_step_kernel (the measurements stand there); blocks: B * Hv.
+inline int buffer_step_heads(int d, int Hk, int Hv, int blocks)
+{
+    return Hv > Hk && blocks >= (d == 128 ? 256 : 96) ? 2 : 1;
+}
+// Workgroups that add to a request's fill word when a token is appended.
+inline int step_workgroups(const StepArgs &a, int d, int blocks)
+{
+    const int hb = a.st.state ? 1 : buffer_step_heads(d, a.Hk, a.Hv, blocks);
+    return a.Hk * ((a.Hv / a.Hk + hb - 1) / hb);
 }
 
 // One launcher per translation unit.  They return KVB_EUNSUPPORTED for a head size or type pair

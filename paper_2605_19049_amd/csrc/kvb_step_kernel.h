@@ -702,7 +702,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 // lane ends up with both of its record for the head whose weights it makes.  128 contexts of up to 100 tokens, 32 heads,
 // fp16, 16 steps: 476 us with the dots on the vector ALU, sums by shuffles through LDS and 64-bit record addresses, 447
 // without the three.
-// Rule (launch_buffer_step): two heads a workgroup from as many units on as leave the CUs busy; below, the halves of
+// Rule (buffer_step_heads): two heads a workgroup from as many units on as leave the CUs busy; below, the halves of
 // the chip that would stay idle are worth more.  What two heads save besides keys are additions to the fill word, which
 // pass one at a time (about 10 ns each) where the slots of a batch share a 128-byte line, as the slots here do.
 // Passes beyond the fill load a valid record and compute nothing.
@@ -967,7 +967,7 @@ template <int D, typename TIn, typename TRec>
 void launch_buffer_step(const StepArgs &a, int blocks, hipStream_t stream)
 {
     const int B = blocks / a.Hv;
-    if (a.Hv > a.Hk && blocks >= (D == 128 ? 256 : 96))
+    if (buffer_step_heads(D, a.Hk, a.Hv, blocks) == 2)
         launch_buffer_step_h<D, TIn, TRec, 2>(a, B, stream);
     else
         launch_buffer_step_h<D, TIn, TRec, 1>(a, B, stream);

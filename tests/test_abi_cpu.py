@@ -114,6 +114,22 @@ def test_flush_verify_direct_argument_ranges():
     assert kvb.kvb_direct(sh, st, A, None, 8, A, A, A, A, A, A, stream=0, check=False) == kvb.EINVAL
 
 
+def test_more_heads_than_the_fill_word_counts():
+    """The workgroups of a request are counted in bits 16..30 of its fill word: one more than 2^15 would leave the word
+    wrong for good."""
+    st, none = _store(), _store(state=None)
+    big = kvb.shape(**{**GOOD, "B": 1, "Hk": 1, "Hv": 32769})
+    args = (A, A, A, A, A, A, A)
+    assert _decode(big, st) == kvb.EINVAL
+    assert kvb.kvb_decode_flush(big, st, *args, 4, stream=0, check=False) == kvb.EINVAL
+    assert kvb.kvb_flush(big, st, A, None, 1, stream=0, check=False) == kvb.EINVAL
+    assert kvb.kvb_flush(big, none, A, A, 1, stream=0, check=False) == kvb.EINVAL
+    # without a state two v-heads of a key head share a workgroup
+    for heads in (dict(Hk=32769, Hv=32769), dict(Hk=1, Hv=65537), dict(Hk=21846, Hv=65538), dict(Hk=16385, Hv=3 * 16385)):
+        assert _decode(kvb.shape(**{**GOOD, "B": 1, **heads}), none) == (kvb.EINVAL), heads
+    assert _decode(kvb.shape(**{**GOOD, "B": 0, "Hk": 1, "Hv": 65538}), none) == kvb.OK
+
+
 def test_paged_store_argument_ranges():
     sh = kvb.shape(**GOOD)   # cap = 16
     ok = dict(block_table=A, block_size=8, max_blocks=2, n_blocks=64)

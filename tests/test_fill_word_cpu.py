@@ -35,6 +35,18 @@ int main(int argc, char **argv)
 {
     const int nwg = atoi(argv[1]);
     long long bad = 0;
+    if (nwg > 4096) {   // the words at the ends of what bits 16.. can count: shares in, of the others, and of the first or not
+        for (int old = 0; old <= 128; old += 64)
+            for (int change = -old; change <= 8; ++change)
+                for (int others : {0, 1, nwg - 2, nwg - 1}) {
+                    const uint32_t w = (uint32_t)old + (uint32_t)others * (uint32_t)fill_share(false, nwg, change);
+                    const uint32_t all = w + (uint32_t)fill_share(true, nwg, change);
+                    bad += (int)w < 0 || ((int)w & FILL_MASK) != old;
+                    bad += others == nwg - 1 ? all != (uint32_t)(old + change) : (int)all >= 0 || ((int)all & FILL_MASK) != old + change;
+                }
+        printf("%lld\n", bad);
+        return 0;
+    }
     for (int old = 0; old <= 128; old += nwg > 1000 ? 127 : 1) {
         bad += states(nwg, old, 1, 16, false);          // a token was appended (whatever the threshold is)
         bad += states(nwg, old, -old, old, false);      // and the buffer folded, at threshold old + 1
@@ -57,7 +69,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("nwg", [1, 2, 3, 32, 255, 4096])
+@pytest.mark.parametrize("nwg", [1, 2, 3, 32, 255, 4096, 32768])
 def test_every_state_of_the_word(program, nwg):
     """A reading gives the old fill until the last share is in; then the word is the new fill."""
     assert int(subprocess.run([program, str(nwg)], check=True, stdout=subprocess.PIPE, text=True).stdout) == 0
