@@ -461,7 +461,7 @@ __device__ __forceinline__ int logical_block() { return logical_block(gridDim.x)
 // over all XCDs, one qk-head with its r v-heads (which share keys and queries through the XCD's L2) at a time; with
 // whole requests on one XCD, as the kernels with a ticket word need it, the XCD that drew the longest contexts set the
 // end of the launch (256 contexts of ~U(1,64): 118 -> 110 us; 96 of ~U(1,128): 130 -> 115 us).  The order of the requests is
-// another matter (longest_first in kvb_direct.hip).
+// another matter (longest_first).
 // Rounds of 8 qk-heads are dealt, one to an XCD; the units of the qk-heads that are left (fewer than 8) go one by one.
 // Where some are left, from 1024 units on (four workgroups a CU; below that all run at once, and what the v-heads of a
 // qk-head share is worth less than spreading contexts of one length over the CUs).  Against unit = workgroup id, d =
@@ -481,6 +481,52 @@ __host__ __device__ inline int dealt_unit(int x, int deal)
         return x;
     const int of = quotient(j, r);
     return (of * 8 + x % 8) * r + j - of * r;
+}
+
+// Whether kvb_direct takes the longest contexts first (how: ranked_request in kvb_direct.hip).  The sort costs every
+// workgroup 0.3 to 0.6 us and shortens the end of the launch, so it needs contexts whose work differs.
+// us a call in the order of the batch / sorted, 32 heads unless said:
+//   up to 128 tokens, d = 128: 96 contexts, bf16, 109 / 100; 128 of up to 100, fp16, 103 / 94; 400 of up to 112, fp16,
+//     473 / 451; 8 23.5 / 24.1; 4 29.0 / 29.6
+//   up to 64 tokens, d = 128, bf16: 256 contexts 105 / 106; 128 57 / 58; 96 46.6 / 47.6; 64 32.7 / 29.7; 24 16.7 / 16.4;
+//     16 16.5 / 15.2; 12 15.5 / 14.0; 8 12.8 / 13.4; fp16: 256 84 / 86; 96 37.9 / 37.8; 40 20.5 / 18.2; 8 11.7 / 12.2;
+//     heads of 8: 100 contexts 22.4 / 17.0, 45 13.6 / 13.1, 13 11.7 / 12.3
+//   up to 64 tokens, block rows: d = 64, heads of 16: 48 contexts 19.4 / 16.7, 100 32.0 / 27.7, 24 12.6 / 13.3, 8 9.4 / 10.2;
+//     500 of 32 heads and up to 40 139 / 153; fp32, d = 128: 40 48.2 / 43.8, 100 93 / 89; d = 32: 60 23.9 / 23.2
+// Below the lower lines all workgroups run at once; beyond the upper one the end is a small part of the launch, and
+// mixed lengths share the memory better (up to 128 tokens the work differs too much for that).
+// Short contexts (sorted / in the order of the batch, mean over 8 batches of ~U(1, Lmax); longest context in the columns):
+//                                  8..16       20     24     28     32     36     40     48     64
+//   d = 128, bf16,  768 units      1.07        0.93   0.93   0.96   0.97   0.96   0.94   0.88   0.95
+//                  1280                        1.13   1.14   1.03   1.02   1.04   1.05   1.00   0.99
+//                  2048            1.13..1.17  0.98   1.02   1.00   1.00   0.97   0.96   0.97   0.93
+//   d = 128, fp16, 1280                        0.97   0.97   0.93   0.95   0.92   0.93   0.87   0.89
+//                  1632                        1.10   1.12   1.07   1.04   1.04   0.99   0.96   0.97
+//   d = 128, fp32,  800                        1.04   0.98   0.94   0.91   0.92   0.89   0.93   0.87
+//                  1280            1.14        1.08   1.06   1.01   1.04   1.03   1.00   0.97   0.94
+//                  1632                        1.10   1.04   1.05   1.05   1.01   0.99   0.97   0.95
+//   d = 64,  bf16, 1280            1.09        0.95   0.93   0.90   0.91   0.94   0.90   0.91   0.91
+//                  2048            1.14        1.02   1.01   1.01   1.00   0.98   0.95   0.95   0.93
+//   d = 32,  fp16, 1632                        1.06   1.03   0.97   0.97   1.00   0.98   0.89   0.88
+// Up to 16 tokens all contexts are of one class and there is nothing to sort.  Launches of about one round of workgroups
+// gain from 20 tokens on, larger ones later.
+inline bool longest_first(int blocks, int Lmax, int d, int in_dtype)
+{
+    const bool fp32 = d == 128 && in_dtype == KVB_F32;
+    if (blocks < (d == 128 && !fp32 ? 320 : 512))
+        return false;
+    if (Lmax > 64)
+        return true;
+    const bool one_round = blocks <= (d <= 64 || in_dtype == KVB_F16 ? 1280 : 1024);
+    const int least = d <= 64 ? (one_round ? 20 : 28) : !one_round ? 40 : fp32 ? 36 : 20;
+    return blocks <= 2560 && Lmax >= least;
+}
+// The leading argument of kvb_direct's kernels: Hv, or with its sign bit set a batch of B (<= MAX_RANKED) requests to be
+// sorted in bits 16.., Hv in the rest.
+constexpr int MAX_RANKED = 2 * NT;
+__host__ __device__ inline int rank_lead(int B, int Hv, bool rank)
+{
+    return rank && B > 1 && B <= MAX_RANKED && Hv < 65536 ? (int)(0x80000000u | (uint32_t)B << 16 | (uint32_t)Hv) : Hv;
 }
 
 struct Store {

@@ -326,26 +326,8 @@ __device__ __forceinline__ f32x4_t mm16_pieces(const uint2 (&x)[NPX], const uint
 // batch, by counting, into classes of 16 tokens (the blocks that the kernels work in; the order of the batch inside a
 // class) and takes the p-th request of that order: one vector load of lengths in the place of the scalar one, a barrier
 // and a scan over 64 counts, 0.3 to 0.6 us.
-// lead: Hv, or with its sign bit set a batch of B (<= MAX_RANKED) requests to be sorted in bits 16.., Hv in the rest.
-// Rule (longest_first), us a call in the order of the batch / sorted, 32 heads unless said:
-//   up to 128 tokens, d = 128: 96 contexts, bf16, 109 / 100; 128 of up to 100, fp16, 103 / 94; 400 of up to 112, fp16,
-//     473 / 451; 8 23.5 / 24.1; 4 29.0 / 29.6
-//   up to 64 tokens, d = 128, bf16: 256 contexts 105 / 106; 128 57 / 58; 96 46.6 / 47.6; 64 32.7 / 29.7; 24 16.7 / 16.4;
-//     16 16.5 / 15.2; 12 15.5 / 14.0; 8 12.8 / 13.4; fp16: 256 84 / 86; 96 37.9 / 37.8; 40 20.5 / 18.2; 8 11.7 / 12.2;
-//     heads of 8: 100 contexts 22.4 / 17.0, 45 13.6 / 13.1, 13 11.7 / 12.3
-//   up to 64 tokens, block rows: d = 64, heads of 16: 48 contexts 19.4 / 16.7, 100 32.0 / 27.7, 24 12.6 / 13.3, 8 9.4 / 10.2;
-//     500 of 32 heads and up to 40 139 / 153; fp32, d = 128: 40 48.2 / 43.8, 100 93 / 89; d = 32: 60 23.9 / 23.2
-// Below the lower lines all workgroups run at once; beyond the upper one the end is a small part of the launch, and
-// mixed lengths share the memory better (up to 128 tokens the work differs too much for that).
-constexpr int MAX_RANKED = 2 * NT;
-inline bool longest_first(int blocks, int Lmax, bool mfma)
-{
-    return blocks >= (mfma ? 320 : 512) && (Lmax > 64 || blocks <= 2560);
-}
-__host__ __device__ inline int rank_lead(int B, int Hv, bool rank)
-{
-    return rank && B > 1 && B <= MAX_RANKED && Hv < 65536 ? (int)(0x80000000u | (uint32_t)B << 16 | (uint32_t)Hv) : Hv;
-}
+// (The rule, longest_first, and the leading kernel argument, rank_lead, are in kvb_device.h.)
+
 // inclusive sum over the wave
 __device__ __forceinline__ int wave_sum(int x)
 {
@@ -1502,8 +1484,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
 // ---------------------------------------------------------------------------
 int launch_direct(int dk, int in_dtype, int rec_dtype, const DirectArgs &a, int blocks, hipStream_t stream)
 {
-    const bool mfma = dk == 128 && in_dtype != KVB_F32, sorted = longest_first(blocks, a.Lmax, mfma);
-    const int32_t lead = rank_lead(blocks / a.Hv, a.Hv, sorted), deal = deal_of(blocks, a.Hv / a.Hk);
+    const bool mfma = dk == 128 && in_dtype != KVB_F32;
+    const int32_t lead = rank_lead(blocks / a.Hv, a.Hv, longest_first(blocks, a.Lmax, dk, in_dtype)), deal = deal_of(blocks, a.Hv / a.Hk);
     auto start = [&](auto paged, auto contiguous) {
         launch(a.st.block_table ? paged : contiguous, blocks, stream, a.len, lead, deal, a);
     };

@@ -1,4 +1,5 @@
-"""Which unit (request, v-head) a workgroup of kvb_direct takes, from the functions of csrc/kvb_device.h run on the host."""
+"""Which unit (request, v-head) a workgroup of kvb_direct takes, and in which launches the requests are sorted, from the
+functions of csrc/kvb_device.h run on the host."""
 import os
 import subprocess
 
@@ -13,6 +14,15 @@ SRC = r"""
 #include <cstdlib>
 int main(int argc, char **argv)
 {
+    if (argc == 1) {   // d, input type, units, longest context of every launch that sorts
+        for (int d : {32, 64, 128})
+            for (int type : {KVB_F32, KVB_BF16, KVB_F16})
+                for (int blocks = 1; blocks < 20000; blocks += blocks < 3000 ? 1 : 997)
+                    for (int Lmax = 1; Lmax <= 128; ++Lmax)
+                        if (kvb_impl::longest_first(blocks, Lmax, d, type))
+                            printf("%d %d %d %d\n", d, type, blocks, Lmax);
+        return 0;
+    }
     const int blocks = atoi(argv[1]), deal = kvb_impl::deal_of(blocks, atoi(argv[2]));
     for (int x = 0; x < blocks; ++x)
         printf("%d\n", kvb_impl::dealt_unit(x, deal));
@@ -21,7 +31,7 @@ int main(int argc, char **argv)
 
 
 @pytest.fixture(scope="module")
-def units(tmp_path_factory):
+def program(tmp_path_factory):
     d = tmp_path_factory.mktemp("dealing")
     src, exe = os.path.join(d, "deal.hip"), os.path.join(d, "deal")
     with open(src, "w") as f:
@@ -29,17 +39,17 @@ def units(tmp_path_factory):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     subprocess.run([hipcc] + build.HIPCC_FLAGS + ["-o", exe, src], check=True, stderr=subprocess.DEVNULL)
 
-    def run(blocks, r):
-        return np.array(subprocess.run([exe, str(blocks), str(r)], check=True, stdout=subprocess.PIPE, text=True).stdout.split(), int)
+    def run(*args):
+        return np.array(subprocess.run([exe] + [str(a) for a in args], check=True, stdout=subprocess.PIPE, text=True).stdout.split(), int)
     return run
 
 
 @pytest.mark.parametrize("B, Hk, Hv", [(64, 16, 32), (13, 4, 8), (5, 4, 16), (7, 2, 16), (3, 8, 24), (5, 3, 9), (1, 1, 1), (1, 8, 8), (500, 16, 32), (255, 4, 8), (101, 4, 16), (2, 1, 8), (300000, 1, 32)])
-def test_dealing(units, B, Hk, Hv):
+def test_dealing(program, B, Hk, Hv):
     """Every unit is taken once.  Where the qk-heads divide by 8, and from 1024 units on, the v-heads of a qk-head share an
     XCD (workgroup id modulo 8), all but those of fewer than 8 qk-heads, and every XCD has as many qk-heads."""
     blocks, r = B * Hv, Hv // Hk
-    u = units(blocks, r)
+    u = program(blocks, r)
     assert np.array_equal(np.sort(u), np.arange(blocks))
     xcd = np.empty(blocks, int)
     xcd[u] = np.arange(blocks) % 8
@@ -49,3 +59,13 @@ def test_dealing(units, B, Hk, Hv):
     assert split <= B * Hk % 8, split
     whole = xcd.reshape(B * Hk, r)[:B * Hk // 8 * 8, 0]
     assert np.ptp(np.bincount(whole, minlength=8)) == 0
+
+
+def test_no_sort_without_different_lengths(program):
+    """Contexts of up to 16 tokens are all of one class of the sort, which would cost each workgroup a barrier and a scan for
+    the order of the batch.  Longer ones: in launches of more than a round, and at most of a few."""
+    d, _, blocks, Lmax = program().reshape(-1, 4).T
+    assert Lmax.min() > 16
+    short = Lmax <= 64
+    assert blocks[short].min() >= 320 and blocks[short].max() <= 2560
+    assert (d[blocks == blocks.max()] == 128).any() and blocks[~short].max() > 10000   # above 64 tokens without an upper line
