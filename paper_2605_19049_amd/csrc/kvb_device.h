@@ -568,11 +568,14 @@ struct Pages {
             return s;
     }
     __device__ __forceinline__ int off(int l) const { return PAGED ? (l & (bs - 1)) : l; }
-    // row of record l of head `head` (H heads per block) in units of one record
-    __device__ __forceinline__ size_t row(int l, int H, int head) const
+    // row of the first record that the block of record l holds of head `head` (H heads per block), in units of one record
+    __device__ __forceinline__ size_t block_row(int l, int H, int head) const
     {
-        return ((size_t)blk(l) * H + head) * bs + off(l);
+        const size_t unit = (size_t)blk(l) * H + head;
+        return PAGED ? unit << lg : unit * bs;
     }
+    // row of record l
+    __device__ __forceinline__ size_t row(int l, int H, int head) const { return block_row(l, H, head) + off(l); }
 };
 // The records of one head as an array of rows of E elements (a scalar address and 32 bits of offset where the rows of a
 // slot are contiguous: with 64-bit arithmetic for each load a wave alone on its SIMD spends a microsecond on addresses).
@@ -591,10 +594,15 @@ struct Rows {
     }
     __device__ __forceinline__ T *at(int l, int e) const   // element e of record l
     {
+        // (through a byte pointer: through an integer the compiler loses the address space and emits flat accesses)
+        // Paged: the block in 64 bits, by a shift, and 32 bits inside it.  Row by row in 64 bits a load took three
+        // multiplications and more registers than kernels at the edge of their budget have: kvb_decode with fp32 inputs and
+        // a 64-record window spilled values of loads in flight, each a wait for all of them (150 requests of 32 heads, 48
+        // records, four steps 343 us, 263 so; 298 before records had this form at all).
         if constexpr (PAGED)
-            return p + pg.row(l, H, head) * E + e;
+            return reinterpret_cast<T *>(reinterpret_cast<Byte *>(p) + (pg.block_row(l, H, head) * (E * sizeof(T)) +
+                                                                        (uint32_t)((pg.off(l) * E + e) * (int)sizeof(T))));
         else
-            // (through a byte pointer: through an integer the compiler loses the address space and emits flat accesses)
             return reinterpret_cast<T *>(reinterpret_cast<Byte *>(p) + (uint32_t)((l * E + e) * (int)sizeof(T)));
     }
 };

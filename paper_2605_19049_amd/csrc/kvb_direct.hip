@@ -417,8 +417,8 @@ __device__ __forceinline__ int ranked_request(const int32_t *len, int B, int Lma
 // before it (8 block rows solved one after the other with fp32 matrix instructions); 128 of ~U(1,100),
 // fp16 throughout: 193 -> 127 us.  Two workgroups per CU without any spill were 5 % slower than three that spill.  Token rows
 // are a scalar address and the lane's own row, whose offsets the second panel works out again: 64-bit addresses lane by
-// lane, kept from the first panel, made three workgroups spill 15 to 24 words (now one with fp32 records, none with 16-bit
-// ones): 96 contexts 100 -> 95 us (both sorted by length);
+// lane, kept from the first panel, made three workgroups spill 15 to 24 words (now one with contiguous fp32 records, else
+// none): 96 contexts 100 -> 95 us (both sorted by length);
 // pieces of U_0 kept in registers instead of cut again: two fit.
 // ---------------------------------------------------------------------------
 // Workgroups per CU: the two fp16 pieces need 28 KB of LDS and 95 registers, which leaves room for

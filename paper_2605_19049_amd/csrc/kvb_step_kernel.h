@@ -208,7 +208,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
             atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
         return;
     }
-    const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[tid / 64], tid % 64, blk_id);
+    const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[__builtin_amdgcn_readfirstlane(tid / 64)], tid % 64, blk_id);
     const auto krec = make_rows<D>(static_cast<TIn *>(a.st.buf_k), pg, a.Hk, hk);
     const auto urec = make_rows<D>(static_cast<TRec *>(a.st.buf_u), pg, a.Hv, h);
     const auto Grec = make_rows<1>(a.st.buf_G, pg, a.Hv, h);
@@ -790,7 +790,7 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
             atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
         return;
     }
-    const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[tid / 64], tid % 64, blk_id);
+    const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[__builtin_amdgcn_readfirstlane(tid / 64)], tid % 64, blk_id);
     const auto krec = make_rows<D>(static_cast<TIn *>(a.st.buf_k), pg, a.Hk, hk);
     // (of head h0; the next heads' records follow a block of cap or block_size records further on)
     const auto urec = make_rows<D>(static_cast<TRec *>(a.st.buf_u), pg, a.Hv, h0);

@@ -12,6 +12,7 @@ import pytest
 from paper_2605_19049_amd import kvb
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 TARGET = re.compile(r"<[^>+]*\+0x([0-9a-f]+)>")
 REG = re.compile(r"\b([va])(?:(\d+)\b|\[(\d+):(\d+)\])")
 
@@ -151,11 +152,19 @@ def early_reads(ins, adr):
     return sorted(bad)
 
 
+def spills(path):
+    """Vector registers that each kernel spills, from the code object's metadata."""
+    notes = subprocess.run([READELF, "--notes", path], check=True, stdout=subprocess.PIPE, text=True).stdout
+    names, counts = [re.findall(r"^ {4}\.%s: +(\S+)$" % key, notes, re.M) for key in ("name", "vgpr_spill_count")]
+    assert len(names) == len(counts) and names
+    return dict(zip(names, map(int, counts)))
+
+
 def scan(path):
-    res = []
+    res, spilled = [], spills(path)
     for name, ins, adr in kernels(path):
         res.append((name, len(ins), any(x.startswith("global_atomic_add") for x in ins), unordered_tickets(ins, adr),
-                    early_reads(ins, adr)))
+                    early_reads(ins, adr), spilled[name]))
     return res
 
 
@@ -181,3 +190,19 @@ def test_matrix_results_are_waited_for(scanned):
     """No path reads the result of a matrix instruction before the wait states it needs."""
     bad = [(r[0], r[4][:3]) for r in scanned if r[4]]
     assert not bad, "%d kernels, e.g. %s" % (len(bad), bad[:2])
+
+
+# (pattern of the mangled name, registers): kernels held at three workgroups a CU that spill after all
+SPILLS = [("kvb_step_kernelILi128EffLi64ELb1", 8),            # kvb_decode_flush, fp32, 64-record window
+          ("kvb_verify_mfma_kernelILi128EffLi32ELb1", 3),     # kvb_verify, fp32, 32-record window
+          (r"kvb_direct_mfma_kernelIN\S+EfLb1ELb0", 1)]       # kvb_direct above 64 tokens, contiguous fp32 records
+
+
+def test_spills(scanned):
+    """A value of a load in flight that is spilled makes the wave wait there for every load it has issued."""
+    over = {}
+    for r in scanned:
+        allowed = max([n for pattern, n in SPILLS if re.search(pattern, r[0])], default=0)
+        if r[5] > allowed:
+            over[r[0]] = (r[5], allowed)
+    assert not over, over
