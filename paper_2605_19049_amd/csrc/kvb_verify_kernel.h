@@ -401,16 +401,27 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             acc[t] *= gam;
     }
 
+    // The lane's indices from here on.  Carried through the state pass they cost the fp32 kernels with a 32-record window three
+    // spilled registers (five with paged records), one of them the decay of the wave's keys, whose load is then waited for,
+    // and with it everything requested before it: there they are worked out again from an opaque thread index.  200 requests of 16
+    // heads, 6 drafts: 62.2 -> 57.0 us, paged 65.6 -> 58.8; 60 of 16 heads, 8 drafts: 23.6 -> 22.2, paged 24.8 -> 22.3.  (The
+    // others spill nothing: 200 requests of 32 heads of 64 went from 34.3 to 34.7 with it, 60 of 32, fp32, 64-record window, from
+    // 49.5 to 50.2.)
+    int tid2 = tid;
+    if constexpr (D == 128 && sizeof(TIn) == 4 && WREC == 32)
+        asm volatile("" : "+v"(tid2));
+    const int lm2 = tid2 % 16, lq2 = tid2 % 64 / 16, colf2 = WC * (wave % NWC) + tid2 % 64 % WC;
+
     // ---- 5. stage 1: decayed dot products with every buffered and new key -------
     // Gkey: cumulative log decay of key n of the tile (a buffered one from memory, a new one from above)
     auto key_tile = [&](int tile, const uint4(&kk)[NWA], float Gkey) {
         const f32x4_t c1 = dot_tile<TIn>(wa, kk);
-        // this lane: rows m = 4 lq + v of W against key n
-        const int n = 16 * tile + lm;
+        // this lane: rows m = 4 lq2 + v of W against key n
+        const int n = 16 * tile + lm2;
         float o[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int m = 4 * lq + v, i = m % 8;
+            const int m = 4 * lq2 + v, i = m % 8;
             const bool isq = m >= 8;
             // a buffered key is seen by every draft; a new one by its descendants (q rows: and by itself)
             const bool above = n >= f && ((ancRow[v] >> min(n - f, 31)) & 1);
@@ -423,7 +434,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
                 o[v] = (isq ? w : -w) * c1[v];
             }
         }
-        *reinterpret_cast<float4 *>(&cW[n][4 * lq]) = make_float4(o[0], o[1], o[2], o[3]);
+        *reinterpret_cast<float4 *>(&cW[n][4 * lq2]) = make_float4(o[0], o[1], o[2], o[3]);
     };
     auto key_G = [&](int n, float buffered) {   // (the read without a condition, then the select)
         const float fresh = sGc[wave][min(max(n - f, 0), TMX - 1)];
@@ -433,10 +444,10 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     for (int x = 0; x < NTW; ++x) {
         const int tile = wave + NW * x;
         if (tile < ntile)
-            key_tile(tile, kt[x], key_G(16 * tile + lm, Gn[x]));
+            key_tile(tile, kt[x], key_G(16 * tile + lm2, Gn[x]));
     }
     for (int tile = wave + NW * NTW; TAIL && tile < ntile; tile += NW) {   // keys beyond the register window
-        const int n = 16 * tile + lm;
+        const int n = 16 * tile + lm2;
         const TIn *kp = key_at(n);
         uint4 kk[NWA];
 #pragma unroll
@@ -451,8 +462,8 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
 #pragma unroll
     for (int sq = 0; sq < WQ; ++sq) {
         if (sq < nquad) {   // uniform
-            const bool ok = 4 * sq + lq < f;
-            float aw = cW[4 * sq + lq][lm];
+            const bool ok = 4 * sq + lq2 < f;
+            float aw = cW[4 * sq + lq2][lm2];
             if constexpr (CHAINS)   // (past the records the row holds a draft's weights: 0 * Inf is NaN)
                 aw = ok ? aw : 0.0f;
             const Cols<CT> uv = unpack_cols(uq[sq]);
@@ -468,7 +479,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         RawCols<TRec, CT> u4r[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int l = 4 * (s0 + j) + lq;
+            const int l = 4 * (s0 + j) + lq2;
             u4r[j] = load_raw_cols<CT>(static_cast<const TRec *>(urec.at(l < f ? l : 0, col2)));
         }
         Cols<CT> u4[4];
@@ -477,9 +488,9 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             u4[j] = unpack_cols(u4r[j]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int l = 4 * (s0 + j) + lq;   // < 4 * 35 + 4 = 144 rows of cW
+            const int l = 4 * (s0 + j) + lq2;   // < 4 * 35 + 4 = 144 rows of cW
             if (s0 + j < nquad) {   // uniform
-                float aw = cW[l][lm];
+                float aw = cW[l][lm2];
                 if constexpr (CHAINS)
                     aw = l < f ? aw : 0.0f;
 #pragma unroll
@@ -497,14 +508,14 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             settle<SETTLE_FP32>(part[0][t], part[NACC - 1][t]);
         add_chains();
     }
-    // acc[t][v] = row m = 4 lq + v, column col2 + t
+    // acc[t][v] = row m = 4 lq2 + v, column col2 + t
     if (wave < NWC)   // uniform
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             if constexpr (CT == 2)
-                *reinterpret_cast<float2 *>(&fin[4 * lq + v][col2]) = make_float2(acc[0][v], acc[CT - 1][v]);
+                *reinterpret_cast<float2 *>(&fin[4 * lq2 + v][col2]) = make_float2(acc[0][v], acc[CT - 1][v]);
             else
-                fin[4 * lq + v][col2] = acc[0][v];
+                fin[4 * lq2 + v][col2] = acc[0][v];
         }
     __syncthreads();
 
@@ -524,8 +535,8 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
 #pragma unroll
         for (int i = 0; i < TMX; ++i) {
             if (i < T) {   // uniform
-                fu[i] = fin[i][colf];
-                fo[i] = fin[8 + i][colf];
+                fu[i] = fin[i][colf2];
+                fo[i] = fin[8 + i][colf2];
 #pragma unroll
                 for (int j = 0; j <= i; ++j) {
                     ck[i][j] = cW[f + j][i];       // K rows are stored negated
@@ -562,8 +573,8 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
                 const float ui = rounded_to<TRec>(bet[i] * acc);
                 ao = fmaf(cq[i][i], ui, ao);
                 uprev[i] = ui;
-                fin[i][colf] = ui;                 // a lane overwrites only what it has read itself
-                fin[8 + i][colf] = a.scale * ao;
+                fin[i][colf2] = ui;                 // a lane overwrites only what it has read itself
+                fin[8 + i][colf2] = a.scale * ao;
             }
         }
     }
@@ -581,8 +592,8 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     }
     if (tid < T)
         *Grec.at(f + tid, 0) = GcMine;   // (lane = draft)
-    if (h % r == 0 && wave == 0 && lm < T) {   // lanes holding k rows store them
-        TIn *kw = krec.at(f + lm, EW * lq);
+    if (h % r == 0 && wave == 0 && lm2 < T) {   // lanes holding k rows store them
+        TIn *kw = krec.at(f + lm2, EW * lq2);
 #pragma unroll
         for (int st = 0; st < NWA; ++st)
             *reinterpret_cast<uint4 *>(kw + 4 * EW * st) = wa[st];

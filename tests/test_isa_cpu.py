@@ -194,7 +194,6 @@ def test_matrix_results_are_waited_for(scanned):
 
 # (pattern of the mangled name, registers): kernels held at three workgroups a CU that spill after all
 SPILLS = [("kvb_step_kernelILi128EffLi64ELb1", 8),            # kvb_decode_flush, fp32, 64-record window
-          ("kvb_verify_mfma_kernelILi128EffLi32ELb1", 3),     # kvb_verify, fp32, 32-record window
           (r"kvb_direct_mfma_kernelIN\S+EfLb1ELb0", 1)]       # kvb_direct above 64 tokens, contiguous fp32 records
 
 
