@@ -84,10 +84,11 @@ extern "C" {
 typedef struct kvb_shape {
     int32_t B;         /* requests in this call (0 = no-op)                                */
     int32_t Hk;        /* q/k heads                                                        */
-    int32_t Hv;        /* v heads, Hv % Hk == 0.  The calls that change `fill` take up to  */
-                       /* 32768; kvb_decode without a state, where two heads share a       */
-                       /* workgroup (Hv > Hk, and B * Hv >= 256), Hk * ceil(Hv / Hk / 2)   */
-                       /* up to 32768; kvb_verify, kvb_compact and kvb_direct have no limit */
+    int32_t Hv;        /* v heads, Hv % Hk == 0.  At most (KVB_EINVAL beyond): 32768 for   */
+                       /* calls that change `fill`, for kvb_decode without a state counted */
+                       /* as Hk * ceil(Hv / Hk / 2); less than 4 GiB of v a draft for      */
+                       /* several drafts of kvb_verify; Hv * dv * max(Lmax, 64) <= 2^32    */
+                       /* for kvb_direct                                                   */
     int32_t dk;        /* key/query head size;   compiled: dk == dv in {32, 64, 128}       */
     int32_t dv;        /* value head size                                                  */
     int32_t cap;       /* records one request's buffer can hold, 1..KVB_MAX_CAP            */

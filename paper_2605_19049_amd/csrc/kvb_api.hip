@@ -127,6 +127,9 @@ int step_common(const kvb_shape *sh, const kvb_store *st, const int32_t *slot, i
                // chain: g stands in as a readable array of at least B*T words whose values are ignored
                parent ? parent : reinterpret_cast<const int32_t *>(g), parent ? 1 : 0};
     const int blocks = sh->B * sh->Hv;
+    // (kvb_verify steps from draft to draft in 32 bits of bytes)
+    if (T > 1 && (long long)sh->Hv * sh->dv * (sh->in_dtype == KVB_F32 ? 4 : 2) > 0xFFFFFFFFLL)
+        return KVB_EINVAL;
     if (advance && step_workgroups(a, sh->dk, blocks) > MAX_FILL_WG)
         return KVB_EINVAL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
@@ -252,6 +255,9 @@ int kvb_direct(const kvb_shape *shape, const kvb_store *store, const int32_t *sl
         return KVB_EINVAL;
     if (shape->B == 0)
         return KVB_OK;
+    // offsets in 32 bits: of the elements of a context, and of the bytes of 16 rows in fp32
+    if ((long long)shape->Hv * shape->dv * (Lmax > 64 ? Lmax : 64) > 1LL << 32)
+        return KVB_EINVAL;
     DirectArgs a{dev_store(store), slot, len, q, k, v, g, beta, out, shape->out_dtype == KVB_F32, shape->Hk,
                  shape->Hv, shape->cap, Lmax, shape->scale};
     const int blocks = shape->B * shape->Hv;

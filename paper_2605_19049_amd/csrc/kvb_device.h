@@ -483,6 +483,14 @@ __host__ __device__ inline int dealt_unit(int x, int deal)
     return (of * 8 + x % 8) * r + j - of * r;
 }
 
+// The byte offset of one of 16 rows, cut off where `left` rows follow the first; own: the row times the stride.  (In 32 bits, so
+// the rows behind the sixteenth are no part of the product: 127 rows leave 32 bits from 132105 heads on.)
+__host__ __device__ inline uint32_t row_of_16(uint32_t own, int left, uint32_t stride)
+{
+    const uint32_t last = (uint32_t)(left < 15 ? left : 15) * stride;
+    return own < last ? own : last;
+}
+
 // Whether kvb_direct takes the longest contexts first (how: ranked_request in kvb_direct.hip).  The sort costs every
 // workgroup 0.3 to 0.6 us and shortens the end of the launch, so it needs contexts whose work differs.
 // us a call in the order of the batch / sorted, 32 heads unless said:

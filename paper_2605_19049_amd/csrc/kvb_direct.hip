@@ -527,8 +527,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     // 16 rows from i0 on as a scalar address; a lane adds its own row (times the stride), cut off at the last row
     auto row_at = [&](const TIn *base, uint32_t stride, int i0, uint32_t own, uint32_t in_row) {
         const int r0 = min(i0, L - 1);   // (scalars)
-        const uint32_t last = (uint32_t)(L - 1 - r0) * stride;
-        return reinterpret_cast<const char *>(base) + (size_t)r0 * stride + (min(own, last) + in_row);
+        return reinterpret_cast<const char *>(base) + (size_t)r0 * stride + (row_of_16(own, L - 1 - r0, stride) + in_row);
     };
     const uint32_t own_s = (uint32_t)srow * qk_stride, own_c = (uint32_t)c16 * qk_stride;
     uint32_t own_v[4];

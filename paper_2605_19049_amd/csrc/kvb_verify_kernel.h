@@ -216,10 +216,10 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     const auto urec = make_rows<D>(static_cast<TRec *>(a.st.buf_u), pg, a.Hv, h);
     const auto Grec = make_rows<1>(a.st.buf_G, pg, a.Hv, h);
     const TIn *knew = kin + ((size_t)b * T * a.Hk + hk) * D;
-    // 16-byte piece lq of key n of the chunk, a buffered one or a new one
+    // 16-byte piece lq of key n of the chunk, a buffered one or a new one (which is found in 32 bits of such pieces)
     auto key_at = [&](int n) {
         return n < f ? krec.at(min(n, cap - 1), EW * lq)
-                     : knew + (uint32_t)(min(max(n - f, 0), T - 1) * a.Hk * D + EW * lq);
+                     : knew + (size_t)((uint32_t)min(max(n - f, 0), T - 1) * ((uint32_t)a.Hk * (D / EW)) + lq) * EW;
     };
     const int ntile = (nrec + 15) / 16;
 
@@ -247,11 +247,19 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     }
     // v of this wave's columns (used by its first WC lanes in the last stage)
     const int colf = WC * (wave % NWC) + lane % WC;
-    const TIn *vrow = vin + ((size_t)b * T * a.Hv + h) * D;
+    // (the lane's address of draft 0, which the compiler is kept from taking apart, and a scalar 64-bit row: an offset of rows and
+    // columns in 32 bits of elements would wrap from 4.8 million heads on, and a scalar address for each row cost 200 requests
+    // of 32 heads of 64 35.0 us instead of 34.3 and 34.5.  A draft's step fits 32 bits: the host checks it)
+    const uint32_t v_step = (uint32_t)a.Hv * (uint32_t)(D * sizeof(TIn));
+    uint64_t v_at = reinterpret_cast<uint64_t>(vin + ((size_t)b * T * a.Hv + h) * D + colf);
+    asm volatile("" : "+v"(v_at));
+    using VBits = std::conditional_t<sizeof(TIn) == 4, float, uint16_t>;
     TIn v_raw[TMX];
 #pragma unroll
-    for (int i = 0; i < TMX; ++i)
-        v_raw[i] = vrow[(uint32_t)(min(i, T - 1) * a.Hv * D + colf)];
+    for (int i = 0; i < TMX; ++i) {
+        const uint64_t row = (uint64_t)(uint32_t)min(i, T - 1) * v_step;
+        v_raw[i] = __builtin_bit_cast(TIn, *reinterpret_cast<const VBits __attribute__((address_space(1))) *>(v_at + row));
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     // Drafts form a chain (kvb_verify) or a tree (kvb_verify_tree): the decay of a draft runs along its own root path,

@@ -130,6 +130,17 @@ def test_more_heads_than_the_fill_word_counts():
     assert _decode(kvb.shape(**{**GOOD, "B": 0, "Hk": 1, "Hv": 65538}), none) == kvb.OK
 
 
+def test_more_heads_than_32_bit_offsets_reach():
+    tok = (A, A, A, A, A, A)
+    for dt, heads in ((kvb.BF16, 1 << 24), (kvb.F32, 1 << 23)):   # a draft's v is 4 GiB
+        big = kvb.shape(**{**GOOD, "B": 1, "Hk": 1, "Hv": heads, "in_dtype": dt})
+        assert kvb.kvb_verify(big, _store(), A, 2, *tok, stream=0, check=False) == kvb.EINVAL
+        assert kvb.kvb_verify_tree(big, _store(), A, 2, A, *tok, stream=0, check=False) == kvb.EINVAL
+    for Lmax, heads in ((1, (1 << 19) + 1), (64, (1 << 19) + 1), (128, (1 << 18) + 1)):
+        big = kvb.shape(**{**GOOD, "B": 1, "Hk": 1, "Hv": heads, "cap": 128})
+        assert kvb.kvb_direct(big, _store(), A, A, Lmax, A, A, A, A, A, A, stream=0, check=False) == kvb.EINVAL
+
+
 def test_paged_store_argument_ranges():
     sh = kvb.shape(**GOOD)   # cap = 16
     ok = dict(block_table=A, block_size=8, max_blocks=2, n_blocks=64)

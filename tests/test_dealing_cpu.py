@@ -1,5 +1,5 @@
-"""Which unit (request, v-head) a workgroup of kvb_direct takes, and in which launches the requests are sorted, from the
-functions of csrc/kvb_device.h run on the host."""
+"""Which unit (request, v-head) a workgroup of kvb_direct takes, in which launches the requests are sorted, and which rows the
+lanes read, from the functions of csrc/kvb_device.h run on the host."""
 import os
 import subprocess
 
@@ -21,6 +21,15 @@ int main(int argc, char **argv)
                     for (int Lmax = 1; Lmax <= 128; ++Lmax)
                         if (kvb_impl::longest_first(blocks, Lmax, d, type))
                             printf("%d %d %d %d\n", d, type, blocks, Lmax);
+        return 0;
+    }
+    if (argc == 2) {   // wrong row offsets for a number of heads of 128 16-bit elements
+        const uint32_t stride = (uint32_t)atoi(argv[1]) * 256u;
+        int bad = 0;
+        for (int left = 0; left < 128; ++left)
+            for (int row = 0; row < 16; ++row)
+                bad += kvb_impl::row_of_16((uint32_t)row * stride, left, stride) != (uint32_t)(row < left ? row : left) * stride;
+        printf("%d\n", bad);
         return 0;
     }
     const int blocks = atoi(argv[1]), deal = kvb_impl::deal_of(blocks, atoi(argv[2]));
@@ -69,3 +78,9 @@ def test_no_sort_without_different_lengths(program):
     short = Lmax <= 64
     assert blocks[short].min() >= 320 and blocks[short].max() <= 2560
     assert (d[blocks == blocks.max()] == 128).any() and blocks[~short].max() > 10000   # above 64 tokens without an upper line
+
+
+@pytest.mark.parametrize("heads", [1, 32, 132104, 132105, 200000, 264207, 1000000])
+def test_row_offsets(program, heads):
+    """A row of 16, or the last one there is, also where the rows of a whole context leave 32 bits."""
+    assert program(heads)[0] == 0
