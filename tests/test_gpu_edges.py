@@ -217,3 +217,27 @@ def test_buffer_step_blocks(d, in_dtype, rec_dtype, Hk, Hv, block_size):
         errs += [H.rel_err(H.host(out[b]), o[0, -1], lay.out_unit), H.rel_err(lay.u_records(b, 0, fills[b] + 1).transpose(1, 0, 2), u[0])]
     say("buffer step, d=%d %s/%s %d/%d heads: rel err %.2e" % (d, in_dtype, rec_dtype, Hk, Hv, max(errs)))
     H.check(errs, in_dtype, rec_dtype, "buffer step")
+
+
+@pytest.mark.parametrize("in_dtype", ["bf16", "f16"])
+def test_buffer_step_dots_add_pairwise(in_dtype):
+    """kvb_decode without a state, delta values that pick one record each: its outputs are the dot products of the new query
+    with the buffered keys.  128 positive terms, summed as 32, 64 and 128 of them: each level rounds by 0.289 units of at most
+    2^-23 of its sums in the root mean square, and the sums of a level below count half as much and are twice as many."""
+    d, Hk, Hv, B = 128, 2, 4, 48
+    rng = np.random.default_rng(930)
+    lay = H.Layer(B, Hk, Hv, d, d, 128, in_dtype, with_state=False)
+    keys = np.abs(rng.standard_normal((B, Hk, 128, d)))
+    lay.ds.buf_k.copy_(H.dev(keys.astype(np.float32), in_dtype))
+    lay.ds.buf_u.copy_(torch.eye(128, device="cuda").expand(B, Hv, 128, d))
+    lay.ds.fill.fill_(127)
+    zeros = np.zeros((B, Hv), np.float32)
+    tok = H.upload_tokens({"q": np.abs(rng.standard_normal((B, Hk, d))).astype(np.float32), "k": np.zeros((B, Hk, d), np.float32),
+                           "v": np.zeros((B, Hv, d), np.float32), "g": zeros, "beta": zeros}, in_dtype)
+    out = lay.new_out(B, Hv, d)
+    lay.decode(tok, out)
+    q, k = H.host(tok["q"]).astype(np.float64), H.host(lay.ds.buf_k).astype(np.float64)
+    want = np.repeat(np.einsum("bhd,bhld->bhl", q, k), Hv // Hk, axis=1)[..., :127]
+    err = np.linalg.norm(H.host(out)[..., :127] - want) / np.linalg.norm(want)
+    say("dots of the buffer step, %s: rms error %.2e" % (in_dtype, err))
+    assert err < 0.289 * 2.0 ** -23 * (1 + 1 / 2 + 1 / 4) ** 0.5, err
