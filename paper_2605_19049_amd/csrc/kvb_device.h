@@ -102,16 +102,7 @@ __device__ __forceinline__ uint32_t pack_pair(float lo, float hi)
     return (uint32_t)from_f32<T>(lo).bits | ((uint32_t)from_f32<T>(hi).bits << 16);
 }
 
-// 8 consecutive elements starting at p (p is 16-byte aligned for the 16-bit types, 32 for fp32).
-__device__ __forceinline__ void load8(const float *p, float (&o)[8])
-{
-    const float4 a = *reinterpret_cast<const float4 *>(p);
-    const float4 b = *reinterpret_cast<const float4 *>(p + 4);
-    o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
-    o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
-}
-
-// The same 8 elements as untouched bits: issuing a load and converting its result are
+// 8 consecutive elements starting at p (p is 16-byte aligned) as untouched bits: issuing a load and converting its result are
 // kept apart so that no wait lands between two loads.
 template <typename T>
 struct Raw8 {
@@ -141,11 +132,6 @@ __device__ __forceinline__ void unpack8(const Raw8<T> &r, float (&o)[8])
     const float2 a = unpack_pair<T>(r.w.x), b = unpack_pair<T>(r.w.y), c = unpack_pair<T>(r.w.z), d = unpack_pair<T>(r.w.w);
     o[0] = a.x; o[1] = a.y; o[2] = b.x; o[3] = b.y;
     o[4] = c.x; o[5] = c.y; o[6] = d.x; o[7] = d.y;
-}
-template <typename T>
-__device__ __forceinline__ void load8(const T *p, float (&o)[8])
-{
-    unpack8(load_raw8(p), o);
 }
 
 // 4 and 2 consecutive elements of a record array (delta values), raw and converted.
@@ -234,17 +220,6 @@ struct Out {
                 store2(static_cast<float *>(p) + i, x, y);
             else
                 store2(static_cast<TIn *>(p) + i, x, y);
-        }
-    }
-    __device__ __forceinline__ void put2_nt(size_t i, float x, float y) const
-    {
-        if constexpr (sizeof(TIn) == 4) {
-            store2_nt(static_cast<float *>(p) + i, x, y);
-        } else {
-            if (wide)
-                store2_nt(static_cast<float *>(p) + i, x, y);
-            else
-                store2_nt(static_cast<TIn *>(p) + i, x, y);
         }
     }
     // element i0 + i, i0 a scalar (64-bit) and i the lane's (its byte offset in 32 bits)
@@ -455,7 +430,6 @@ __device__ __forceinline__ int logical_block(int n)
     const int x = blockIdx.x;
     return (n % 8 == 0) ? (x % 8) * (n / 8) + x / 8 : x;
 }
-__device__ __forceinline__ int logical_block() { return logical_block(gridDim.x); }
 
 // Which unit a workgroup of kvb_direct takes, whose work grows with the context: the heads of a request are dealt
 // over all XCDs, one qk-head with its r v-heads (which share keys and queries through the XCD's L2) at a time; with
