@@ -190,6 +190,58 @@ def test_direct_longest_first(d, Lmax, in_dtype, B, Hv):
     H.check(e, in_dtype, what="longest first")
 
 
+SORTED_FORMS = [(128, 128, "f16", "f16", 16), (128, 128, "bf16", "f32", 8), (128, 64, "bf16", "bf16", 8), (128, 64, "f32", "f32", None),
+                (128, 64, "f32", "f32", 16), (64, 64, "bf16", "f32", 8), (32, 64, "f16", "f16", None), (32, 64, "f32", "f32", 16)]
+
+
+@pytest.mark.parametrize("d, Lmax, in_dtype, rec_dtype, block_size", SORTED_FORMS)
+def test_direct_longest_first_forms(d, Lmax, in_dtype, rec_dtype, block_size):
+    """The sorted launch with paged and 16-bit records, and in the block-row kernel, whose tables share its tiles."""
+    B = 65
+    lens = np.random.default_rng(895 + d).integers(0, Lmax + 1, B).astype(np.int32)
+    e = _direct_case(B=B, Hk=4, Hv=8, d=d, Lmax=Lmax, cap=Lmax, in_dtype=in_dtype, seed=896 + d, lens=lens, then_decode=False,
+                     rec_dtype=rec_dtype, out_dtype=rec_dtype, block_size=block_size, scatter=True)
+    say("direct, longest first, d=%d %s/%s: rel err out/u/decode/state %.2e %.2e %.2e %.2e" % ((d, in_dtype, rec_dtype) + e))
+    H.check(e, in_dtype, rec_dtype, "longest first")
+
+
+@pytest.mark.parametrize("d, Lmax, in_dtype, rec_dtype, block_size", [SORTED_FORMS[i] for i in (1, 2, 3, 5, 6)])
+def test_direct_longest_first_what_is_flagged(d, Lmax, in_dtype, rec_dtype, block_size):
+    """Lengths outside 0..Lmax, sorted as the Lmax that they are clamped to and flagged, and slots outside the store, whose
+    requests are skipped: each at its own place of the sorted order, with every other request as it should be."""
+    B, Hk, Hv = 70, 4, 8
+    rng = np.random.default_rng(897 + d + Lmax)
+    lens = rng.integers(0, Lmax + 1, B).astype(np.int32)
+    lens[[0, 17, 68]] = [-1, Lmax + 1, -2 ** 31]
+    lens[[33, 64]] = [2 ** 31 - 1, 0]
+    clamped = np.where((lens < 0) | (lens > Lmax), Lmax, lens).astype(np.int32)
+    slots = rng.permutation(B).astype(np.int32)
+    skipped = [5, 17, 69]
+    slots[skipped] = [B, -1, 2 ** 31 - 1]
+    tok = synth.token_stream(rng, B, Lmax, Hk, Hv, d, d, in_dtype)
+    lay = H.Layer(B, Hk, Hv, d, d, Lmax, in_dtype, n_slots=B, slots=slots, with_state=False, rec_dtype=rec_dtype, out_dtype=rec_dtype,
+                  block_size=block_size)
+    lay.ds.fill.fill_(3)
+    out = lay.new_out(B, Lmax, Hv, d, fill=float("nan"))
+    lay.direct(H.dev(lens), Lmax, H.upload_tokens(tok, in_dtype), out)
+    torch.cuda.synchronize()
+    done = np.setdiff1d(np.arange(B), skipped)
+    fill, status = np.full(B, 3, np.int32), np.zeros(B, np.int32)
+    fill[slots[done]] = clamped[done]
+    status[slots[done]] = np.where(lens[done] != clamped[done], 1, 0)   # KVB_STATUS_OVERFLOW
+    assert np.array_equal(lay.ds.fill.cpu().numpy(), fill) and np.array_equal(lay.ds.status.cpu().numpy(), status)
+    assert lay.spare_clean()
+    ref, u_ref, _ = oracle.kvb_direct_expected(tok["q"], tok["k"], tok["v"], tok["g"], tok["beta"], clamped)
+    ref[skipped] = np.nan
+    got = H.host(out)
+    valid = ~np.isnan(ref)
+    assert np.array_equal(valid, ~np.isnan(got)), "what a request does not have was written, or what it has was not"
+    errs = [H.rel_err(got[valid], ref[valid], lay.out_unit)]
+    errs += [H.rel_err(lay.u_records(b, 0, clamped[b]).transpose(1, 0, 2), u_ref[b, :clamped[b]]) for b in done if clamped[b] > 0]
+    say("direct, longest first, flagged, d=%d %s/%s: rel err %.2e" % (d, in_dtype, rec_dtype, max(errs)))
+    H.check(errs, in_dtype, rec_dtype, "longest first, flagged")
+
+
 @pytest.mark.parametrize("d, in_dtype, rec_dtype", [(128, i, r) for i, r in TYPES + [("f32", "f32")]]
                          + [(64, "bf16", "f32"), (64, "f32", "f32"), (32, "f16", "f16")])
 @pytest.mark.parametrize("Hk, Hv, block_size", [(1, 2, None), (16, 48, None), (16, 32, 16)])

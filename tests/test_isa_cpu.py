@@ -116,6 +116,8 @@ def effect(x):
     ops = rest.split(", ")
     if op.startswith("v_mfma"):   # (the accumulator input is forwarded)
         return 1, regs(ops[1]) | regs(ops[2]), regs(ops[0]), mfma_wait(op)
+    if op.startswith(("v_fmac", "v_permlane", "v_swap")):   # (the destination is read as well)
+        return 1, regs(rest), 0, 0
     if op.startswith("v_") or any(x in op for x in ("_load_", "_read", "permute", "swizzle")):
         return 1, regs(", ".join(ops[1:])), 0, 0
     if op.startswith(("ds_", "global_", "buffer_", "scratch_", "flat_")):
