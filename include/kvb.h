@@ -108,9 +108,10 @@ typedef struct kvb_store {
     void    *buf_u;   /* device [n_slots, Hv, cap, dv] rec_dtype                            */
     float   *buf_G;   /* device [n_slots, Hv, cap]     fp32                                 */
     int32_t *fill;    /* device [n_slots]; 0..cap between calls.  While a call that changes
-                         fill runs, bits 16.. of the word count the workgroups that have
-                         read it; the last one brings it back to a plain count, which it is
-                         again when the call's kernel ends.                                 */
+                         fill runs, the word belongs to its workgroups: bits 16.. count
+                         them, it may be negative, and the low half may hold the new count
+                         before the records exist.  Neither count can be read from it until
+                         the call's kernel has ended, when it is a plain count again.        */
     int32_t *status;  /* device [n_slots] sticky KVB_STATUS_* bits, or NULL                 */
     int32_t  n_slots; /* slots in the arrays above; requests whose slot is outside
                          0..n_slots-1 are skipped                                           */

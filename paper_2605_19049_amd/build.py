@@ -21,8 +21,8 @@ HIPCC_FLAGS = [
     "-std=c++20", "-O3", "--offload-arch=gfx950",
     # hipcc must not emit packed-fp32 VALU instructions on this target
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # keep the single-lane ticket atomics as written: the wave-aggregating rewrite reads
-    # the result back at once, which would make the wave wait for its whole state tile
+    # keep the single-lane atomics on the fill word as written: where the result is wanted (the tickets
+    # of a fold) the wave-aggregating rewrite reads it back at once, which would make the wave wait for its whole state tile
     "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
     # leading scalar kernel arguments arrive in SGPRs at wave launch (kvb_step_kernel uses it)
     "-mllvm", "-amdgpu-kernarg-preload-count=4",

@@ -423,7 +423,7 @@ __host__ __device__ inline int quotient(int x, int d)
 
 // Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2).  Map them so
 // that XCD x works on one contiguous eighth of the (request, head) units: all heads of a
-// request then share an L2, which keeps the per-request ticket atomics and the keys that
+// request then share an L2, which keeps the additions to its fill word and the keys that
 // grouped heads share inside one XCD.
 __device__ __forceinline__ int logical_block(int n)
 {
@@ -433,7 +433,7 @@ __device__ __forceinline__ int logical_block(int n)
 
 // Which unit a workgroup of kvb_direct takes, whose work grows with the context: the heads of a request are dealt
 // over all XCDs, one qk-head with its r v-heads (which share keys and queries through the XCD's L2) at a time; with
-// whole requests on one XCD, as the kernels with a ticket word need it, the XCD that drew the longest contexts set the
+// whole requests on one XCD, as the kernels that add to a fill word need it, the XCD that drew the longest contexts set the
 // end of the launch (256 contexts of ~U(1,64): 118 -> 110 us; 96 of ~U(1,128): 130 -> 115 us).  The order of the requests is
 // another matter (longest_first).
 // Rounds of 8 qk-heads are dealt, one to an XCD; the units of the qk-heads that are left (fewer than 8) go one by one.

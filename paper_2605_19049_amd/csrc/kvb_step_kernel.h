@@ -723,7 +723,16 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 //   d = 128, fp32           4.9 / 5.7    5.6 / 5.9    5.3 / 6.1    5.6 / 6.3    6.4 / 6.3    7.0 / 6.3
 //   d = 64,  bf16 / fp32    4.6 / 4.8    5.4 / 5.0    5.1 / 5.0    5.4 / 5.1    6.2 / 5.4    6.9 / 5.7
 //   d = 32,  fp16 / fp16    4.6 / 4.8    5.4 / 5.0    5.1 / 4.9    5.4 / 5.0    6.2 / 5.4    6.8 / 5.7
-// The lines: 256 units at d = 128, 96 below.
+// The lines: 256 units at d = 128, 96 below.  Three v-heads to a key head, where the second workgroup of a key head has one of them:
+//   requests of 9 heads        11           16           22           30           45           60           120          240
+//   units                      99           144          198          270          405          540          1080         2160
+//   d = 128, bf16 / fp32       5.4 / 5.8    5.6 / 6.0    5.7 / 6.0    6.7 / 6.2    7.1 / 7.1    7.3 / 7.4    9.0 / 8.7    14.3 / 13.5
+//     0..119 records           6.5 / 7.5    6.5 / 7.3    6.6 / 7.5    8.2 / 7.5    8.4 / 9.5    9.1 / 9.5   12.0 / 13.0   19.7 / 20.6
+//   d = 128, fp16 / fp16       5.3 / 5.6    5.4 / 5.8    5.6 / 5.8    6.7 / 6.0    7.1 / 6.9    7.2 / 7.2    9.0 / 8.4    13.1 / 11.6
+//   d = 64,  bf16 / fp32       5.3 / 5.2    5.2 / 5.0    5.4 / 5.1    6.2 / 5.6    6.5 / 6.4    7.0 / 6.3    7.5 / 6.8    10.5 /  9.1
+//   d = 32,  fp16 / fp16       5.2 / 5.0    5.1 / 4.9    5.4 / 5.1    6.1 / 5.3    6.2 / 5.9    7.0 / 6.2    7.6 / 6.2     9.5 /  8.0
+// The lines are the same ones; long fp32 records of d = 128 are better off with one head (there the kernel with two was as fast
+// as, or faster than, the one with two heads from 512 units on only, which these lines replaced: 9.4, 10.9, 14.5 and 22.4).
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int HB, bool PAGED>
 __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot_arg, int32_t nu_arg, int32_t nblocks_arg,

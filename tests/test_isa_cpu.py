@@ -72,7 +72,7 @@ def blocks(ins, adr):
 
 
 def unordered_tickets(ins, adr):
-    """Ticket atomics that some path reaches without a workgroup barrier."""
+    """Additions to the fill word that some path reaches without a workgroup barrier."""
     bl = blocks(ins, adr)
     bad, seen, todo = [], {0}, [0]
     while todo:
@@ -180,8 +180,8 @@ def scanned(tmp_path_factory):
 
 
 def test_tickets_follow_a_barrier(scanned):
-    """Each wave reads fill[slot] for itself, and the workgroup with the last ticket replaces it: a ticket may only be
-    taken when every wave of the workgroup has read.  The barrier stands behind the branch on the value read."""
+    """Each wave reads fill[slot] for itself, and the last addition of the request's workgroups makes the new count of it: a
+    workgroup may only add when every wave of it has read.  The barrier stands behind the branch on the value read."""
     with_ticket = [r for r in scanned if r[2]]
     assert len(with_ticket) > 100, len(with_ticket)
     bad = [(r[0], r[3]) for r in with_ticket if r[3]]
