@@ -122,7 +122,7 @@ int step_common(const kvb_shape *sh, const kvb_store *st, const int32_t *slot, i
         return KVB_EINVAL;
     if (sh->B == 0)
         return KVB_OK;
-    StepArgs a{dev_store(st), slot, q, k, v, g, beta, out, sh->out_dtype == KVB_F32, sh->Hk, sh->Hv, sh->cap, T,
+    StepArgs a{dev_store(st), slot, q, k, v, g, beta, out, sh->out_dtype == KVB_F32, sh->Hk, sh->Hv, sh->Hv / sh->Hk, sh->cap, T,
                sh->scale, advance, threshold, stream_state(sh, st) ? 1 : 0,
                // chain: g stands in as a readable array of at least B*T words whose values are ignored
                parent ? parent : reinterpret_cast<const int32_t *>(g), parent ? 1 : 0};
@@ -200,7 +200,7 @@ int kvb_compact(const kvb_shape *shape, const kvb_store *store, const int32_t *s
         return KVB_EINVAL;
     if (shape->B == 0)
         return KVB_OK;
-    CompactArgs a{dev_store(store), slot, path, path_len, shape->Hk, shape->Hv, shape->cap, T};
+    CompactArgs a{dev_store(store), slot, path, path_len, shape->Hk, shape->Hv, shape->Hv / shape->Hk, shape->cap, T};
     const int blocks = shape->B * shape->Hv;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     g_launch_status = hipSuccess;
@@ -227,7 +227,7 @@ int kvb_flush(const kvb_shape *shape, const kvb_store *store, const int32_t *slo
         return KVB_OK;
     if (shape->Hv > MAX_FILL_WG)
         return KVB_EINVAL;
-    FlushArgs a{dev_store(store), slot, accepted, shape->Hk, shape->Hv, shape->cap, threshold,
+    FlushArgs a{dev_store(store), slot, accepted, shape->Hk, shape->Hv, shape->Hv / shape->Hk, shape->cap, threshold,
                 store->state && stream_state(shape, store, 192.0) ? 1 : 0};
     const int blocks = shape->B * shape->Hv;
     hipStream_t hs = static_cast<hipStream_t>(stream);
@@ -259,7 +259,7 @@ int kvb_direct(const kvb_shape *shape, const kvb_store *store, const int32_t *sl
     if ((long long)shape->Hv * shape->dv * (Lmax > 64 ? Lmax : 64) > 1LL << 32)
         return KVB_EINVAL;
     DirectArgs a{dev_store(store), slot, len, q, k, v, g, beta, out, shape->out_dtype == KVB_F32, shape->Hk,
-                 shape->Hv, shape->cap, Lmax, shape->scale};
+                 shape->Hv, shape->Hv / shape->Hk, shape->cap, Lmax, shape->scale};
     const int blocks = shape->B * shape->Hv;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     g_launch_status = hipSuccess;

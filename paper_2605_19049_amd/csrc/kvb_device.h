@@ -415,7 +415,9 @@ __device__ __forceinline__ void store_raw8(T *p, const Raw8<T> &r)
 // x / d for a scalar d > 0, x >= 0.  The division stands ahead of the load of slot[b], the head of every dependent chain;
 // in general it is some fifteen dependent instructions through the vector ALU, and head counts are powers of two mostly:
 // 16 steps of one request 62.7 -> 61.7 us, of 64 430 -> 427, kvb_direct of 2 contexts 8.8 -> 8.6.  (Not in kvb_verify, where
-// 24 requests, fp32, went from 20.3 to 20.6.)
+// 24 requests, fp32, went from 20.3 to 20.6.)  Other head counts pay for the test; Hv / Hk comes with the arguments, so that one
+// division is left behind the slot: 217 contexts of 9 heads of 32 12.1 us before the test, 12.3 with it and both, 12.0 so; 16
+// steps of one request of 32 heads 57.0 -> 55.9.
 __host__ __device__ inline int quotient(int x, int d)
 {
     return (d & (d - 1)) == 0 ? x >> __builtin_ctz(d) : x / d;
@@ -621,6 +623,7 @@ __device__ __forceinline__ Pages<PAGED> make_pages(const Store &st, int s, int c
     return pg;
 }
 
+// (r, in the arguments of every kernel: Hv / Hk, the v-heads of a qk-head)
 struct StepArgs {
     Store st;
     const int32_t *slot;
@@ -628,7 +631,7 @@ struct StepArgs {
     const float *g, *beta;
     void *out;
     int32_t out_wide;   // fp32 outputs (otherwise the 16-bit input type)
-    int32_t Hk, Hv, cap, T;
+    int32_t Hk, Hv, r, cap, T;
     float scale;
     int32_t advance;    // 1: decode (fill += T after the step); 0: verify (fill untouched)
     int32_t threshold;  // fused decode + flush only: fold the buffer into the state once it holds this many
@@ -644,7 +647,7 @@ struct FlushArgs {
     Store st;
     const int32_t *slot;
     const int32_t *accepted;
-    int32_t Hk, Hv, cap, threshold;
+    int32_t Hk, Hv, r, cap, threshold;
     int32_t stream;   // non-temporal state loads and stores
 };
 
@@ -656,7 +659,7 @@ struct DirectArgs {
     const float *g, *beta;
     void *out;
     int32_t out_wide;   // fp32 outputs (otherwise the 16-bit input type)
-    int32_t Hk, Hv, cap, Lmax;
+    int32_t Hk, Hv, r, cap, Lmax;
     float scale;
 };
 
@@ -665,7 +668,7 @@ struct CompactArgs {
     const int32_t *slot;
     const int32_t *path;
     const int32_t *path_len;
-    int32_t Hk, Hv, cap, T;
+    int32_t Hk, Hv, r, cap, T;
 };
 
 // ---------------------------------------------------------------------------
@@ -772,7 +775,7 @@ inline int buffer_step_heads(int d, int Hk, int Hv, int blocks)
 inline int step_workgroups(const StepArgs &a, int d, int blocks)
 {
     const int hb = a.st.state ? 1 : buffer_step_heads(d, a.Hk, a.Hv, blocks);
-    return a.Hk * ((a.Hv / a.Hk + hb - 1) / hb);
+    return a.Hk * ((a.r + hb - 1) / hb);
 }
 
 // One launcher per translation unit.  They return KVB_EUNSUPPORTED for a head size or type pair

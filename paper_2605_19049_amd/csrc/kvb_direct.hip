@@ -142,7 +142,7 @@ __device__ __forceinline__ void solve_by_token(const DirectArgs &a, int b, int h
     // (opaque: nothing computed for the kernel's own work stays in a register for this)
     asm volatile("" : "+v"(lane), "+v"(col0), "+s"(b), "+s"(h), "+s"(L));
     const int c16 = lane % 16, lq = lane / 16;
-    const int hk = h / (a.Hv / a.Hk);
+    const int hk = h / a.r;
     const TIn *kbase = static_cast<const TIn *>(a.k) + ((size_t)b * a.Lmax * a.Hk + hk) * D;
     const TIn *qbase = static_cast<const TIn *>(a.q) + ((size_t)b * a.Lmax * a.Hk + hk) * D;
     const TIn *vbase = static_cast<const TIn *>(a.v) + ((size_t)b * a.Lmax * a.Hv + h) * D + col0;
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     }
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
     const int h = lb - place * Hv;
-    const int r = quotient(a.Hv, a.Hk);
+    const int r = a.r;
     const int hk = quotient(h, r);
     const int Lmax = a.Lmax;
 
@@ -1253,7 +1253,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     }
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
     const int h = lb - place * Hv;
-    const int r = quotient(a.Hv, a.Hk);
+    const int r = a.r;
     const int hk = quotient(h, r);
     const int Lmax = a.Lmax;
 
@@ -1484,7 +1484,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
 int launch_direct(int dk, int in_dtype, int rec_dtype, const DirectArgs &a, int blocks, hipStream_t stream)
 {
     const bool mfma = dk == 128 && in_dtype != KVB_F32;
-    const int32_t lead = rank_lead(blocks / a.Hv, a.Hv, longest_first(blocks, a.Lmax, dk, in_dtype)), deal = deal_of(blocks, a.Hv / a.Hk);
+    const int32_t lead = rank_lead(blocks / a.Hv, a.Hv, longest_first(blocks, a.Lmax, dk, in_dtype)), deal = deal_of(blocks, a.r);
     auto start = [&](auto paged, auto contiguous) {
         launch(a.st.block_table ? paged : contiguous, blocks, stream, a.len, lead, deal, a);
     };

@@ -49,7 +49,7 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
     const int h = lb - b * Hv_arg;
-    const int hk = quotient(h, quotient(a.Hv, a.Hk));
+    const int hk = quotient(h, a.r);
     const int cap = a.cap;
 
     if (s < 0 || s >= a.st.n_slots)
@@ -232,7 +232,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
     const int h = lb - b * Hv_arg;
-    const int hk = quotient(h, quotient(a.Hv, a.Hk));
+    const int hk = quotient(h, a.r);
     const int cap = a.cap;
 
     if (s < 0 || s >= a.st.n_slots)
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
     const int h = (int)blockIdx.x - b * Hv_arg;
-    const int r = quotient(a.Hv, a.Hk), hk = quotient(h, r);
+    const int r = a.r, hk = quotient(h, r);
     if (s < 0 || s >= a.st.n_slots)
         return;
     const int blk_id = load_block_id<PAGED>(a.st, s, lane);

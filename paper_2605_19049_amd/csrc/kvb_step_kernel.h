@@ -129,7 +129,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
     const int h = lb - b * Hv_arg;
-    const int r = quotient(a.Hv, a.Hk);
+    const int r = a.r;
     const int hk = quotient(h, r);
     const int cap = a.cap;
     if (s < 0 || s >= a.st.n_slots)
@@ -760,7 +760,7 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
     const int b = quotient(lb, nu_arg);
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int r = quotient(a.Hv, a.Hk);
+    const int r = a.r;
     const int per = (r + HB - 1) / HB;   // workgroups of a key head
     const int of_b = lb - b * nu_arg, hk = quotient(of_b, per);
     const int h0 = hk * r + (of_b - hk * per) * HB, hlast = hk * r + r - 1;
@@ -980,7 +980,7 @@ void launch_step_s(const StepArgs &a, int blocks, hipStream_t stream)
 template <int D, typename TIn, typename TRec, int HB>
 void launch_buffer_step_h(const StepArgs &a, int B, hipStream_t stream)
 {
-    const int32_t nu = a.Hk * ((a.Hv / a.Hk + HB - 1) / HB);   // workgroups of a request
+    const int32_t nu = a.Hk * ((a.r + HB - 1) / HB);   // workgroups of a request
     if (a.st.block_table)
         launch(kvb_buffer_step_kernel<D, TIn, TRec, HB, true>, B * nu, stream, a.slot, nu, B * nu, a);
     else

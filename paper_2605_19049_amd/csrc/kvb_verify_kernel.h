@@ -147,7 +147,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     const int s = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
     const int h = lb % Hv_arg;
-    const int r = a.Hv / a.Hk;
+    const int r = a.r;
     const int hk = h / r;
     const int T = a.T;
     const int cap = a.cap;
