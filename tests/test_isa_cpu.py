@@ -162,11 +162,23 @@ def spills(path):
     return dict(zip(names, map(int, counts)))
 
 
+def waits_at_the_exit(ins, adr, window):
+    """Waits for every load and atomic ahead of the compare of the fill with `window` + 1: (compares, those behind a wait)."""
+    found, bad = 0, []
+    for first, end, _ in blocks(ins, adr):
+        compare = [i for i in range(first, end) if re.match(r"s_cmpk?_l[te]_[iu]32 s\d+, 0x%x$" % (window + 1), ins[i])]
+        if compare and ins[end - 1].startswith("s_cbranch_scc"):
+            found += 1
+            bad += [ins[i] for i in range(first, compare[-1]) if re.match(r"s_waitcnt .*vmcnt\(0\)", ins[i])]
+    return found, bad
+
+
 def scan(path):
     res, spilled = [], spills(path)
     for name, ins, adr in kernels(path):
         res.append((name, len(ins), any(x.startswith("global_atomic_add") for x in ins), unordered_tickets(ins, adr),
-                    early_reads(ins, adr), spilled[name]))
+                    early_reads(ins, adr), spilled[name],
+                    waits_at_the_exit(ins, adr, 64) if "kvb_buffer_step_kernelILi128E" in name else None))
     return res
 
 
@@ -207,3 +219,13 @@ def test_spills(scanned):
         if r[5] > allowed:
             over[r[0]] = (r[5], allowed)
     assert not over, over
+
+
+def test_short_windows_wait_for_no_atomic(scanned):
+    """kvb_decode without a state: a context of up to 64 records leaves the loop over 64 records at a time without a wait for
+    what the wave has in flight, the addition to the fill among it."""
+    checked = [r for r in scanned if r[6] and re.search(r"Li128ENS_\S+Li1ELb[01]E", r[0])]   # 16-bit inputs, one head
+    assert len(checked) == 8, [r[0] for r in checked]
+    assert all(r[6][0] for r in checked), [r[0] for r in checked if not r[6][0]]
+    bad = [(r[0], r[6][1]) for r in checked if r[6][1]]
+    assert not bad, bad
