@@ -709,28 +709,28 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 // One head a workgroup / two, 32 heads, us a call, each request at its own fill:
 //                           0..60 records                          0..10 records       0..119 records
 //   requests                16           32           128          32           128    128
-//   d = 128, bf16 / fp32    10.2 /  7.6  10.5 /  8.2  20.4 / 19.0  10.2 / 7.7  16.1 / 12.7  30.6 / 31.2
-//   d = 128, fp16 / fp16     9.8 /  7.1  10.4 /  7.9  19.0 / 15.7  10.1 / 7.2  15.9 / 11.9  25.7 / 23.2
-//   d = 64,  bf16 / fp32    10.0 /  7.3  10.7 /  7.7  15.8 / 12.7  10.5 / 7.4  14.4 / 10.2  17.7 / 17.7
-//   d = 64,  fp32           10.0 /  7.3  10.7 /  7.5  16.4 / 14.1  10.4 / 7.4  14.6 / 10.4  19.1 / 19.7
-//   d = 32,  fp16 / fp16     9.9 /  7.2  10.8 /  7.5  14.4 / 10.3  10.6 / 7.4  14.2 /  9.9  15.3 / 11.6
-//   d = 32,  fp32            9.9 /  7.2  10.3 /  7.5  14.6 / 10.6  10.4 / 7.4  14.4 / 10.3  16.0 / 14.8
+//   d = 128, bf16 / fp32     8.6 /  6.6  10.2 /  8.3  22.2 / 19.3   8.1 /  6.1  19.5 / 15.0  30.6 / 30.0
+//   d = 128, fp16 / fp16     8.5 /  6.8  10.2 /  8.0  21.4 / 17.4   8.1 /  6.0  19.2 / 14.4  27.1 / 22.5
+//   d = 64,  bf16 / fp32     9.1 /  6.8   9.5 /  7.2  18.4 / 14.1   9.1 /  6.8  16.7 / 11.9  21.5 / 18.6
+//   d = 64,  fp32            9.1 /  6.8   9.7 /  7.1  18.1 / 15.5   9.1 /  6.7  16.2 / 12.1  22.3 / 20.6
+//   d = 32,  fp16 / fp16     8.4 /  6.2   9.7 /  7.0  15.5 / 10.3   8.2 /  6.2  14.3 / 10.0  15.2 / 12.0
+//   d = 32,  fp32            8.4 /  6.3   9.5 /  7.0  14.7 / 10.8   8.2 /  6.2  14.4 / 10.5  16.9 / 14.4
 // Around the lines, 0..60 records (requests of 32 heads, or of 8 where marked):
 //   requests                2            4            13 of 8      30 of 8      6            8
 //   units                   64           128          104          240          192          256
-//   d = 128, bf16 / fp32    4.9 / 5.3    5.6 / 5.5    5.4 / 5.7    5.7 / 5.9    6.5 / 6.0    7.1 / 6.2
-//   d = 128, fp16 / fp16    4.8 / 5.3    5.2 / 5.4    5.2 / 5.6    5.8 / 5.8    6.1 / 5.8    6.8 / 6.0
-//   d = 128, fp32           4.9 / 5.7    5.6 / 5.9    5.3 / 6.1    5.6 / 6.3    6.4 / 6.3    7.0 / 6.3
-//   d = 64,  bf16 / fp32    4.6 / 4.8    5.4 / 5.0    5.1 / 5.0    5.4 / 5.1    6.2 / 5.4    6.9 / 5.7
-//   d = 32,  fp16 / fp16    4.6 / 4.8    5.4 / 5.0    5.1 / 4.9    5.4 / 5.0    6.2 / 5.4    6.8 / 5.7
+//   d = 128, bf16 / fp32    4.6 / 5.2    5.1 / 5.6    4.9 / 5.6    5.5 / 5.9    6.4 / 5.9    7.1 / 6.1
+//   d = 128, fp16 / fp16    4.6 / 5.1    5.0 / 5.5    4.9 / 5.5    5.3 / 5.7    6.2 / 5.7    6.9 / 6.0
+//   d = 128, fp32           4.8 / 5.5    5.5 / 5.8    5.2 / 5.9    5.5 / 6.2    6.3 / 6.2    7.1 / 6.3
+//   d = 64,  bf16 / fp32    4.6 / 4.6    5.2 / 4.8    5.0 / 4.8    5.4 / 5.0    6.1 / 5.3    6.8 / 5.7
+//   d = 32,  fp16 / fp16    4.5 / 4.4    5.2 / 4.7    4.9 / 4.6    5.2 / 4.8    5.9 / 5.1    6.7 / 5.5
 // The lines: 256 units at d = 128, 96 below.  Three v-heads to a key head, where the second workgroup of a key head has one of them:
 //   requests of 9 heads        11           16           22           30           45           60           120          240
 //   units                      99           144          198          270          405          540          1080         2160
-//   d = 128, bf16 / fp32       5.4 / 5.8    5.6 / 6.0    5.7 / 6.0    6.7 / 6.2    7.1 / 7.1    7.3 / 7.4    9.0 / 8.7    14.3 / 13.5
-//     0..119 records           6.5 / 7.5    6.5 / 7.3    6.6 / 7.5    8.2 / 7.5    8.4 / 9.5    9.1 / 9.5   12.0 / 13.0   19.7 / 20.6
-//   d = 128, fp16 / fp16       5.3 / 5.6    5.4 / 5.8    5.6 / 5.8    6.7 / 6.0    7.1 / 6.9    7.2 / 7.2    9.0 / 8.4    13.1 / 11.6
-//   d = 64,  bf16 / fp32       5.3 / 5.2    5.2 / 5.0    5.4 / 5.1    6.2 / 5.6    6.5 / 6.4    7.0 / 6.3    7.5 / 6.8    10.5 /  9.1
-//   d = 32,  fp16 / fp16       5.2 / 5.0    5.1 / 4.9    5.4 / 5.1    6.1 / 5.3    6.2 / 5.9    7.0 / 6.2    7.6 / 6.2     9.5 /  8.0
+//   d = 128, bf16 / fp32       5.3 / 5.7    5.5 / 5.9    5.6 / 5.9    6.6 / 6.1    7.1 / 7.3    7.1 / 7.3    8.9 / 8.6    14.3 / 13.6
+//     0..119 records           6.5 / 7.4    6.4 / 7.4    6.6 / 7.5    8.2 / 7.5    8.3 / 9.4    8.7 / 9.3   11.8 / 12.8   19.8 / 20.7
+//   d = 128, fp16 / fp16       5.2 / 5.5    5.2 / 5.7    5.5 / 5.8    6.6 / 6.0    7.0 / 7.1    7.1 / 7.1    8.9 / 8.2    12.8 / 11.9
+//   d = 64,  bf16 / fp32       5.1 / 5.0    5.1 / 5.0    5.2 / 5.0    6.2 / 5.5    6.5 / 6.3    7.0 / 6.3    7.2 / 6.8    10.2 /  9.1
+//   d = 32,  fp16 / fp16       5.1 / 4.8    5.0 / 4.8    5.2 / 4.9    5.9 / 5.2    6.2 / 5.9    6.9 / 6.2    7.1 / 6.1     9.1 /  7.9
 // The lines are the same ones; long fp32 records of d = 128 are better off with one head (there the kernel with two was as fast
 // as, or faster than, the one with two heads from 512 units on only, which these lines replaced: 9.4, 10.9, 14.5 and 22.4).
 // ---------------------------------------------------------------------------
