@@ -87,7 +87,7 @@ Store dev_store(const kvb_store *st)
 {
     return Store{st->state, st->buf_k, st->buf_u, st->buf_G, st->fill, st->status, st->n_slots,
                  st->block_table, st->block_table ? st->block_size : 0, st->block_table ? st->max_blocks : 1,
-                 st->block_table ? st->n_blocks : 0};
+                 st->block_table ? st->n_blocks : 0, st->flags & KVB_STORE_FILL_APART ? 5 : 0};
 }
 
 // The status of the launch this thread has just made (what the launch call itself returned:

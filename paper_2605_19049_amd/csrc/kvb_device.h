@@ -350,6 +350,12 @@ __device__ __forceinline__ void fma4(float4 &acc, float c, const float4 &x)
 // workgroup holding it, which is what this replaced, 64 requests of 32 heads took 469 us for 16 steps of
 // kvb_decode_flush and take 460, a single request 74.6 and 71.2, 13 of 8 heads 97.3 and 94.7.
 //
+// Additions to one 128-byte line pass one at a time, about 10 ns each, whatever the word or the XCD, and reads of the line
+// queue behind them.  With the fills of 32 slots to a line that is what bounded launches of a few hundred workgroups on
+// (KVB_STORE_FILL_APART gives each slot a line).  Packed / apart, us: kvb_decode_flush, 8 steps of 8 requests of 32 heads 61.2 / 49.7,
+// 16 requests 86.6 / 73.0, 24 114 / 104, d = 64 8 requests 56.9 / 39.8, 60 requests 127 / 98; kvb_verify and commit of 24
+// requests 28.7 / 26.4; kvb_direct and 16 steps of kvb_decode without a state, 24 contexts, 121.7 / 106.2; one request 60.5 / 60.9.
+//
 // publish_fill: a ticket that comes back; whoever holds the last one stores the new plain count.  For changes from
 // which the old count does not follow (a fold that was due earlier, or by kvb_flush; a commit cut off at cap), where
 // the word is positive throughout.  It is taken once the loads are in flight (take_ticket) and looked at at the end.
@@ -527,6 +533,9 @@ struct Store {
     int32_t block_size;           // records per block, a power of two (cap when not paged)
     int32_t max_blocks;           // row length of block_table (1 when not paged)
     int32_t n_blocks;             // blocks in the pools; ids are clamped into 0..n_blocks-1
+    int32_t fill_lg;              // the fill of slot s is word s << fill_lg (0, or 5 with KVB_STORE_FILL_APART)
+    // (of one workgroup's slot: a word that the request's other workgroups may be adding to)
+    __device__ __forceinline__ int32_t *fill_of(int s) const { return fill + ((size_t)s << fill_lg); }
 };
 
 // Where record l of the request lives.  The record arrays are [blocks, heads, block_size, ...]:

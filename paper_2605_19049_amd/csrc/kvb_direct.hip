@@ -508,7 +508,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     }
     if (L == 0) {
         if (h == 0 && tid == 0)
-            a.st.fill[s] = 0;
+            *a.st.fill_of(s) = 0;
         return;
     }
     // ---- every input of the workgroup is requested at once ------------------------
@@ -1184,7 +1184,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     if (__builtin_expect(!all_finite(big), 0))
         solve_by_token<D, 2, TIn, TRec>(a, b, h, L, col2, sG, sB, ru, lane);
     if (h == 0 && tid == 0)
-        a.st.fill[s] = L;
+        *a.st.fill_of(s) = L;
 }
 
 // ---------------------------------------------------------------------------
@@ -1267,7 +1267,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     }
     if (L == 0) {
         if (h == 0 && tid == 0)
-            a.st.fill[s] = 0;
+            *a.st.fill_of(s) = 0;
         return;
     }
     // ---- every input is requested at once (no branch around a load; a row past the context re-reads its last row)
@@ -1475,7 +1475,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
             solve_by_token<D, NC, TIn, TRec>(a, b, h, L, col0, sG, sB, ru, lane);
     }
     if (h == 0 && tid == 0)
-        a.st.fill[s] = L;
+        *a.st.fill_of(s) = L;
 }
 
 // ---------------------------------------------------------------------------

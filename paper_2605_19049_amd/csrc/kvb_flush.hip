@@ -55,7 +55,7 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     if (s < 0 || s >= a.st.n_slots)
         return;
     const int blk_id = load_block_id<PAGED>(a.st, s, lane);
-    const int word = a.st.fill[s];
+    const int word = *a.st.fill_of(s);
     int nacc = a.accepted ? a.accepted[b] : 0;
     if (nacc < 0)
         nacc = 0;
@@ -71,9 +71,9 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     if (!do_flush) {
         // (fill only moves when something was accepted)
         if (m != f + nacc)
-            publish_fill(&a.st.fill[s], a.Hv, m);
+            publish_fill(a.st.fill_of(s), a.Hv, m);
         else if (nacc > 0)
-            advance_fill(&a.st.fill[s], h == 0, a.Hv, nacc);
+            advance_fill(a.st.fill_of(s), h == 0, a.Hv, nacc);
         return;
     }
     const size_t unit = (size_t)s * a.Hv + h;
@@ -115,7 +115,7 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
         for (int v = 0; v < 4; ++v)
             copy_row<CT>(sreg[rt][v], state_at(RT * v + rt));
     __builtin_amdgcn_sched_barrier(0);
-    const int ticket = take_ticket(&a.st.fill[s]);
+    const int ticket = take_ticket(a.st.fill_of(s));
 
     // the sums, apart from the state, so that nothing waits for it before the end
     f32x4_t acc[RT][CT];
@@ -169,7 +169,7 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
             copy_row<CT>(state_at(RT * v + rt), o);
         }
     if (tid == 0)
-        publish_if_last(&a.st.fill[s], ticket, a.Hv, 0);
+        publish_if_last(a.st.fill_of(s), ticket, a.Hv, 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -237,7 +237,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 
     if (s < 0 || s >= a.st.n_slots)
         return;
-    const int word = a.st.fill[s];
+    const int word = *a.st.fill_of(s);
     int nacc = a.accepted ? a.accepted[b] : 0;
     if (nacc < 0)
         nacc = 0;
@@ -251,9 +251,9 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     const bool do_flush = a.st.state != nullptr && m >= a.threshold && m > 0;
     if (!do_flush) {
         if (m != f + nacc)
-            publish_fill(&a.st.fill[s], a.Hv, m);
+            publish_fill(a.st.fill_of(s), a.Hv, m);
         else if (nacc > 0)
-            advance_fill(&a.st.fill[s], h == 0, a.Hv, nacc);
+            advance_fill(a.st.fill_of(s), h == 0, a.Hv, nacc);
         return;
     }
     const size_t unit = (size_t)s * a.Hv + h;
@@ -300,7 +300,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 #pragma unroll
     for (int rt = 0; rt < WIN; ++rt)
         issue_state(rt);
-    const int ticket = take_ticket(&a.st.fill[s]);
+    const int ticket = take_ticket(a.st.fill_of(s));
 
     // B operands of a chunk: piece p of Gamma_l u_l[col2 + t], 8 records to a lane.  down, up: the power of two that
     // column t is cut at and its inverse, the same in the four lanes that hold the column
@@ -438,7 +438,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
             finish(rt, acc[rt][0], acc[rt][1]);
     }
     if (tid == 0)
-        publish_if_last(&a.st.fill[s], ticket, a.Hv, 0);
+        publish_if_last(a.st.fill_of(s), ticket, a.Hv, 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -472,7 +472,7 @@ __global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg
     const int ju = tid / PU, jk = tid / PK;
     const int pj = path[min(lane, a.T - 1)], pu = path[min(ju, a.T - 1)], pk = path[min(jk, a.T - 1)];
     const int n = a.path_len[b];
-    const int f = a.st.fill[s] & FILL_MASK;
+    const int f = *a.st.fill_of(s) & FILL_MASK;
     const int before = __shfl_up(pj, 1);
     const bool wrong = lane < n && lane < a.T && (pj <= (lane > 0 ? before : -1) || pj >= a.T);
     if (n < 0 || n > a.T || f + a.T > a.cap || __any(wrong)) {   // uniform

@@ -154,7 +154,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     const Raw8<TIn> k_raw = load_raw8(kin + nr_o);
     const TIn v_raw = vin[((size_t)b * a.Hv + h) * D + tid % D];
 
-    const int word = a.st.fill[s];
+    const int word = *a.st.fill_of(s);
     // ---- 2. the state tile goes in flight ------------------------------------
     // Decoding one token (EARLY): the state's address needs the slot only, so its loads go out
     // before the fill count is known.  Each dependent scalar load costs microseconds while the
@@ -240,7 +240,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     const bool fold = FUSE && f + 1 >= a.threshold, overdue = FUSE && f + 1 > a.threshold;
     // youngest memory operation of the wave (EARLY: behind the barrier that it needs anyway, below)
     if (!EARLY && a.advance && !overdue)
-        advance_fill(&a.st.fill[s], h == 0, a.Hv, fold ? -f : 1);
+        advance_fill(a.st.fill_of(s), h == 0, a.Hv, fold ? -f : 1);
 
     // ---- 3. decayed dot products of the new rows with every earlier key ----
     float4 accU = make_float4(0.f, 0.f, 0.f, 0.f), accO = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -256,7 +256,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
             // (younger loads) are not touched before the last state row has been used
             __syncthreads();
             if (a.advance && !overdue)
-                advance_fill_read(&a.st.fill[s], h == 0, a.Hv, fold ? -f : 1);
+                advance_fill_read(a.st.fill_of(s), h == 0, a.Hv, fold ? -f : 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int p = 0; p < NPASS; ++p) {
@@ -419,7 +419,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
         store_raw8(krec.at(f, 8 * sub), k_raw);
     const int m = f + 1;
     if (overdue)
-        publish_fill(&a.st.fill[s], a.Hv, 0);
+        publish_fill(a.st.fill_of(s), a.Hv, 0);
     if constexpr (FUSE) {
         if (fold) {
             const float gam = expf(Gc);
@@ -793,7 +793,7 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
     const TIn v_raw = static_cast<const TIn *>(a.v)[((size_t)b * a.Hv + h0 + jc) * D + tid % D];
     const float bet = a.beta[(size_t)b * a.Hv + h0 + jc];
     const float g_w = a.g[(size_t)b * a.Hv + h0 + jw];
-    const int f = fill_before(a.st.fill[s], 0);
+    const int f = fill_before(*a.st.fill_of(s), 0);
     if (f + 1 > cap) {
         if (tid == 0 && a.st.status)
             atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
@@ -843,7 +843,7 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
         }
         __builtin_amdgcn_sched_barrier(0);
         if (l0 == 0 && a.advance)
-            advance_fill(&a.st.fill[s], of_b == 0, nu_arg, 1);
+            advance_fill(a.st.fill_of(s), of_b == 0, nu_arg, 1);
         if constexpr (MDOT) {
             if (l0 + 16 * wave < f) {   // uniform
                 // rows 4 lq + v of the product are k (v = 0) and q (v = 1) for every lq, its columns the records

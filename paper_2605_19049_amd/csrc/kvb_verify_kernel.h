@@ -204,7 +204,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     if constexpr (EARLY)
         issue_state();
 
-    const int f = a.st.fill[s] & FILL_MASK;
+    const int f = *a.st.fill_of(s) & FILL_MASK;
     if (f + T > cap) {
         if (tid == 0 && a.st.status)
             atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);

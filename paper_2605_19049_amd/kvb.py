@@ -16,7 +16,8 @@ F32, BF16, F16 = 0, 1, 2
 MAX_CAP, MAX_DRAFTS, MAX_DIRECT_LEN = 128, 8, 128
 STATUS_OVERFLOW = 1
 STATUS_BADPATH = 2
-STORE_STREAM, STORE_RESIDENT = 1, 2
+STORE_STREAM, STORE_RESIDENT, STORE_FILL_APART = 1, 2, 4
+FILL_APART = 32   # words from one slot's fill to the next with STORE_FILL_APART
 
 EXPORTS = ("kvb_decode", "kvb_decode_flush", "kvb_flush", "kvb_verify", "kvb_verify_tree", "kvb_compact", "kvb_direct",
            "kvb_timer_create", "kvb_timer_arm", "kvb_timer_read", "kvb_timer_destroy",
@@ -110,6 +111,10 @@ def torch_dtype(code):
 
 def store(state, buf_k, buf_u, buf_G, fill, status, n_slots, flags=0, block_table=None, block_size=0,
           max_blocks=0, n_blocks=0):
+    """fill: a contiguous int32 tensor [n_slots], or one with a line to each slot (stride FILL_APART, as DeviceStore's);
+    an address needs STORE_FILL_APART in flags where it is of the second kind."""
+    if hasattr(fill, "stride") and fill.dim() == 1 and fill.stride(0) == FILL_APART:
+        flags |= STORE_FILL_APART
     return KvbStore(_ptr(state), _ptr(buf_k), _ptr(buf_u), _ptr(buf_G), _ptr(fill), _ptr(status), n_slots, flags,
                     _ptr(block_table), block_size, max_blocks, n_blocks)
 
@@ -245,7 +250,8 @@ class DeviceStore:
         self.buf_k = torch.zeros((nb, Hk, per, dk), dtype=kd, device=device)
         self.buf_u = torch.zeros((nb, Hv, per, dv), dtype=torch_dtype(rec_dtype), device=device)
         self.buf_G = torch.zeros((nb, Hv, per), dtype=torch.float32, device=device)
-        self.fill = torch.zeros((n_slots,), dtype=torch.int32, device=device)
+        # a 128-byte line to each slot's word
+        self.fill = torch.zeros((n_slots, FILL_APART), dtype=torch.int32, device=device)[:, 0]
         self.status = torch.zeros((n_slots,), dtype=torch.int32, device=device)
 
     def c(self, with_state=True, flags=0):
