@@ -508,7 +508,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     }
     if (L == 0) {
         if (h == 0 && tid == 0)
-            *a.st.fill_of(s) = 0;
+            put<false>(a.st.fill_of(s), 0);
         return;
     }
     // ---- every input of the workgroup is requested at once ------------------------
@@ -620,7 +620,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
         sG[row] = gv;
         sB[row] = bv;
         if (row < L)
-            *Grec.at(row, 0) = gv;
+            put<false>(Grec.at(row, 0), gv);
     }
     // stage K; the thread that loaded a piece of K also appends it to the buffer
 #pragma unroll
@@ -628,7 +628,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
         if (p < nb) {   // uniform
             *reinterpret_cast<u32x4_t *>(sK + (16 * p + srow) * GS + 8 * sc8) = kst[p];
             if (h == hk * r && 16 * p + srow < L)
-                *reinterpret_cast<u32x4_t *>(krec.at(16 * p, srow, 8 * sc8)) = kst[p];
+                put<false>(reinterpret_cast<u32x4_t *>(krec.at(16 * p, srow, 8 * sc8)), kst[p]);
         }
     }
     __syncthreads();
@@ -930,7 +930,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
                 *reinterpret_cast<u32x4_t *>(sK + (16 * p + srow) * GS + 8 * sc8) = ks[p];
                 *reinterpret_cast<u32x4_t *>(sK1 + (16 * p + srow) * GS + 8 * sc8) = ks[NB + p];
                 if (h == hk * r && LM + 16 * p + srow < L)
-                    *reinterpret_cast<u32x4_t *>(krec.at(LM + 16 * p, srow, 8 * sc8)) = ks[NB + p];
+                    put<false>(reinterpret_cast<u32x4_t *>(krec.at(LM + 16 * p, srow, 8 * sc8)), ks[NB + p]);
             }
             __syncthreads();
 
@@ -1184,7 +1184,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     if (__builtin_expect(!all_finite(big), 0))
         solve_by_token<D, 2, TIn, TRec>(a, b, h, L, col2, sG, sB, ru, lane);
     if (h == 0 && tid == 0)
-        *a.st.fill_of(s) = L;
+        put<false>(a.st.fill_of(s), L);
 }
 
 // ---------------------------------------------------------------------------
@@ -1267,7 +1267,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
     }
     if (L == 0) {
         if (h == 0 && tid == 0)
-            *a.st.fill_of(s) = 0;
+            put<false>(a.st.fill_of(s), 0);
         return;
     }
     // ---- every input is requested at once (no branch around a load; a row past the context re-reads its last row)
@@ -1323,7 +1323,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
         const int row = NT / CPR * p + srow;
         *reinterpret_cast<u32x4_t *>(sK + row * GS + EPC * sch) = kst[p];
         if (h == hk * r && row < L)
-            *reinterpret_cast<u32x4_t *>(kb + rk(row) * D + EPC * sch) = kst[p];
+            put<false>(reinterpret_cast<u32x4_t *>(kb + rk(row) * D + EPC * sch), kst[p]);
     }
     // Cumulative log decay and beta.  Token by token: only differences G_i - G_l are used, nearby ones above all,
     // and the roundings of a running sum cancel in them (a scan over the wave was 1.4 times further off in the
@@ -1341,7 +1341,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
         sG[lane] = run;
         sB[lane] = lane < L ? beta_raw : 0.0f;
         if (lane < L)
-            a.st.buf_G[ru(lane)] = run;
+            put<false>(a.st.buf_G + ru(lane), run);
     }
     __syncthreads();
 
@@ -1475,7 +1475,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
             solve_by_token<D, NC, TIn, TRec>(a, b, h, L, col0, sG, sB, ru, lane);
     }
     if (h == 0 && tid == 0)
-        *a.st.fill_of(s) = L;
+        put<false>(a.st.fill_of(s), L);
 }
 
 // ---------------------------------------------------------------------------

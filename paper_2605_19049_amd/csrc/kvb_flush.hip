@@ -166,7 +166,10 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 #pragma unroll
             for (int t = 0; t < CT; ++t)
                 o[t] = fmaf(gam, sreg[rt][v][t], acc[rt][t][v]);
-            copy_row<CT>(state_at(RT * v + rt), o);
+            if constexpr (CT == 2)
+                store2(state_at(RT * v + rt), o[0], o[CT - 1]);
+            else
+                store1(state_at(RT * v + rt), o[0]);
         }
     if (tid == 0)
         publish_if_last(a.st.fill_of(s), ticket, a.Hv, 0);
@@ -405,10 +408,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
             float2 o;
             o.x = fmaf(gam, sreg[rt % WIN][v].x, c0[v] * up[0]);
             o.y = fmaf(gam, sreg[rt % WIN][v].y, c1[v] * up[1]);
-            if constexpr (STREAM)
-                store2_nt(state_at(8 * v + rt), o.x, o.y);
-            else
-                *reinterpret_cast<float2 *>(state_at(8 * v + rt)) = o;
+            store2<STREAM>(state_at(8 * v + rt), o.x, o.y);
         }
         if (rt + WIN < 8) {
             __builtin_amdgcn_sched_barrier(0);
@@ -498,11 +498,11 @@ __global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg
     asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(u.z), "+v"(u.w), "+v"(k.x), "+v"(k.y), "+v"(k.z), "+v"(k.w), "+v"(G));
     __syncthreads();
     if (mu)
-        *reinterpret_cast<uint4 *>(urec.at(f + ju, eu)) = u;
+        put<false>(reinterpret_cast<uint4 *>(urec.at(f + ju, eu)), u);
     if (mk)
-        *reinterpret_cast<uint4 *>(krec.at(f + jk, ek)) = k;
+        put<false>(reinterpret_cast<uint4 *>(krec.at(f + jk, ek)), k);
     if (mG)
-        *Grec.at(f + tid, 0) = G;
+        put<false>(Grec.at(f + tid, 0), G);
 }
 
 // ---------------------------------------------------------------------------

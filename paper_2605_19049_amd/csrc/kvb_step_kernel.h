@@ -410,13 +410,13 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
         const TRec ur_new = from_f32<TRec>(bet * (to_f32(v_raw) + au));
         u_new = to_f32(ur_new);
         ao = fmaf(cQ[f], u_new, ao);
-        out.put1(((size_t)b * a.Hv + h) * D + tid, a.scale * ao);
-        *urec.at(f, tid) = ur_new;
+        out.template put1<STREAM>(((size_t)b * a.Hv + h) * D + tid, a.scale * ao);
+        put<STREAM>(urec.at(f, tid), ur_new);
     }
     if (tid == 0)
-        *Grec.at(f, 0) = Gc;
+        put<STREAM>(Grec.at(f, 0), Gc);
     if (h == hk * r && tid < D / 8)   // the threads that loaded the new k row store it
-        store_raw8(krec.at(f, 8 * sub), k_raw);
+        store_raw8<STREAM>(krec.at(f, 8 * sub), k_raw);
     const int m = f + 1;
     if (overdue)
         publish_fill(a.st.fill_of(s), a.Hv, 0);
@@ -679,15 +679,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
             }
             float4 *sw = reinterpret_cast<float4 *>(a.st.state + unit * D * D);
 #pragma unroll
-            for (int p = 0; p < NPASS; ++p) {
-                if constexpr (STREAM) {   // a state that is streamed in is streamed out again (+1 % on 1 GiB of state)
-                    typedef float v4f __attribute__((ext_vector_type(4)));
-                    __builtin_nontemporal_store(v4f{sreg[p].x, sreg[p].y, sreg[p].z, sreg[p].w},
-                                                reinterpret_cast<v4f *>(sw + (size_t)(rg + RPP * p) * LPR + c4));
-                } else {
-                    sw[(size_t)(rg + RPP * p) * LPR + c4] = sreg[p];
-                }
-            }
+            for (int p = 0; p < NPASS; ++p)   // (a state that is streamed in is streamed out again: +1 % on 1 GiB of state)
+                put<STREAM>(sw + (size_t)(rg + RPP * p) * LPR + c4, sreg[p]);
         }
     }
 }
@@ -946,10 +939,10 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
         const TRec ur_new = from_f32<TRec>(bet * (to_f32(v_raw) + au));
         ao = fmaf(sQK, to_f32(ur_new), ao);
         out.put1(((size_t)b * a.Hv + h0 + jc) * D + col, a.scale * ao);
-        *urec.at(f, jc * pg.bs * D + col) = ur_new;
+        put<false>(urec.at(f, jc * pg.bs * D + col), ur_new);
     }
     if (own < nh && (MDOT ? tid < 64 && lm == 0 : grp == 0))
-        *Grec.at(f, jw * pg.bs) = Gc;
+        put<false>(Grec.at(f, jw * pg.bs), Gc);
     if (h0 == hk * r && tid < D / 8)   // the threads that loaded the new k row store it
         store_raw8(krec.at(f, 8 * sub), k_raw);
 }

@@ -594,17 +594,17 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         const int i = is_u ? rr : rr - T;
         const float4 val = *reinterpret_cast<const float4 *>(&fin[is_u ? i : 8 + i][4 * c4]);
         if (is_u)   // (already rounded to the record type: the conversion is exact)
-            store4(urec.at(f + i, 4 * c4), val);
+            store4<STREAM>(urec.at(f + i, 4 * c4), val);
         else
-            out.put4((((size_t)b * T + i) * a.Hv + h) * D + 4 * c4, val);
+            out.template put4<STREAM>((((size_t)b * T + i) * a.Hv + h) * D + 4 * c4, val);
     }
     if (tid < T)
-        *Grec.at(f + tid, 0) = GcMine;   // (lane = draft)
+        put<STREAM>(Grec.at(f + tid, 0), GcMine);   // (lane = draft)
     if (h % r == 0 && wave == 0 && lm2 < T) {   // lanes holding k rows store them
         TIn *kw = krec.at(f + lm2, EW * lq2);
 #pragma unroll
         for (int st = 0; st < NWA; ++st)
-            *reinterpret_cast<uint4 *>(kw + 4 * EW * st) = wa[st];
+            put<STREAM>(reinterpret_cast<uint4 *>(kw + 4 * EW * st), wa[st]);
     }
 }
 
