@@ -110,6 +110,12 @@ __device__ __forceinline__ f32x4_t dot_tile(const uint4 (&a)[N], const uint4 (&b
 // With a workgroup to a CU, every phase is as long as its instructions: the drafts' decays are worked out a draft to a
 // lane (draft after draft in scalar registers took 1.0 us, now 0.23) and record addresses are 32-bit offsets: 7 requests
 // of 32 heads, 8 tree drafts, fp16, with compaction and commit, 24.5 -> 23.9 us (every workgroup 8.8 -> 7.8).
+// What concerns the drafts alone (their decays, their weights among themselves) is worked out while the state is in flight
+// and stays in registers, from where the substitution takes it as scalars; only the weights of the buffered records cross
+// waves behind the state.  Against one set of key tiles for records and drafts behind the state, a table of the weights in LDS and
+// results by whole rows (112 registers now at d = 128 with 16 records and 134 with 64, were 118 and 161): 200 requests of 32
+// heads of 32 34.5 -> 28.9 us, of 64 46.7 -> 45.0; 60 of 64, 64 records, 23.3 -> 22.2; 100 of 32 heads of 128, 96 records, 7
+// drafts 85.4 -> 83.5; 24, 16 records, 24.7 -> 24.2; 300 182 -> 182 (memory).
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int WREC, bool HAS_STATE, bool STREAM, bool PAGED>
 // (register budgets: 4 waves per SIMD with a record window of 16 or 32, 3 with the 64-record window or with
@@ -126,20 +132,23 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     constexpr int EW = 16 / (int)sizeof(TIn);                 // elements of a 16-byte piece of a key row
     constexpr int NWA = D / (4 * EW);                         // pieces of a row that a lane holds (lq 0..3 side by side)
     constexpr int TMX = KVB_MAX_DRAFTS;                       // 8
-    constexpr int NTILE = (KVB_MAX_CAP + TMX + 15) / 16;      // key tiles of 16 (9)
-    // tiles per wave held in registers
-    constexpr int NTW = D * sizeof(TIn) > 256 ? 1 : ((WREC + TMX + 15) / 16 + NW - 1) / NW;
+    constexpr int NTILE = KVB_MAX_CAP / 16;                   // tiles of 16 buffered keys
+    static_assert((WREC + 15) / 16 <= NW, "a wave holds one tile of the window's keys");
     constexpr int WQ = WREC / 4;                              // record quads held in registers
     constexpr bool TAIL = WREC >= 64;
     constexpr bool EARLY = HAS_STATE;   // state loads issued before the fill is known
     static_assert(TMX == 8, "row m of W is draft m % 8");
 
     __shared__ __attribute__((aligned(16))) float sW[D][16];
-    __shared__ __attribute__((aligned(16))) float cW[NTILE * 16][16];
+    __shared__ __attribute__((aligned(16))) float cW[NTILE * 16][16];   // weights of the buffered records
     __shared__ __attribute__((aligned(16))) float fin[16][D];
     __shared__ int sBlk[NW][MAX_BLOCKS];
-    __shared__ __attribute__((aligned(16))) float sGc[NW][TMX], sGam[NW][TMX];   // by draft: G and exp(G), each wave's own copy
-    __shared__ __attribute__((aligned(16))) int sAnc[NW][TMX];                   // ancestors
+    // fp32 inputs, whose products are 16 times as long: the weights of the drafts are one wave's work, beside the key tiles
+    constexpr bool ONE_WAVE = sizeof(TIn) == 4;
+    __shared__ float4 sPair[ONE_WAVE ? 64 : 1];
+    // by draft, each wave's own copy: the log decay from the committed context to the draft, its exponential, the ancestors
+    __shared__ __attribute__((aligned(16))) float sRel[NW][TMX], sDec[NW][TMX];
+    __shared__ __attribute__((aligned(16))) int sAnc[NW][TMX];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;   // (a scalar)
     const int lb = logical_block(nblocks_arg);
@@ -210,32 +219,23 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             atomicOr(&a.st.status[s], KVB_STATUS_OVERFLOW);
         return;
     }
-    const int nrec = f + T;
     const Pages<PAGED> pg = make_pages<PAGED>(a.st, s, cap, sBlk[wave], lane, blk_id);
     const auto krec = make_rows<D>(static_cast<TIn *>(a.st.buf_k), pg, a.Hk, hk);
     const auto urec = make_rows<D>(static_cast<TRec *>(a.st.buf_u), pg, a.Hv, h);
     const auto Grec = make_rows<1>(a.st.buf_G, pg, a.Hv, h);
-    const TIn *knew = kin + ((size_t)b * T * a.Hk + hk) * D;
-    // 16-byte piece lq of key n of the chunk, a buffered one or a new one (which is found in 32 bits of such pieces)
-    auto key_at = [&](int n) {
-        return n < f ? krec.at(min(n, cap - 1), EW * lq)
-                     : knew + (size_t)((uint32_t)min(max(n - f, 0), T - 1) * ((uint32_t)a.Hk * (D / EW)) + lq) * EW;
-    };
-    const int ntile = (nrec + 15) / 16;
 
     // ---- 3. loads that need the fill ------------------------------------------
     float G_prev = f > 0 ? *Grec.at(f - 1, 0) : 0.0f;
-    // keys of this wave's tiles (buffered first, then the new ones)
-    uint4 kt[NTW][NWA];
-    float Gn[NTW];
-#pragma unroll
-    for (int x = 0; x < NTW; ++x) {
-        const int n = 16 * (wave + NW * x) + lm;
-        const TIn *kp = key_at(n);
-        Gn[x] = *Grec.at(n < f ? n : 0, 0);
+    // this wave's tile of buffered keys: key 16 wave + lm, 16-byte pieces lq
+    uint4 kt[NWA];
+    float Gn;
+    {
+        const int n = 16 * wave + lm, nc = n < f ? n : 0;
+        const TIn *kp = krec.at(nc, EW * lq);
+        Gn = *Grec.at(nc, 0);
 #pragma unroll
         for (int st = 0; st < NWA; ++st)
-            kt[x][st] = *reinterpret_cast<const uint4 *>(kp + 4 * EW * st);
+            kt[st] = *reinterpret_cast<const uint4 *>(kp + 4 * EW * st);
     }
     // buffered delta values: quad sq = records 4 sq .. 4 sq + 3, this lane: record 4 sq + lq,
     // columns col2 (d = 128: and the next)
@@ -244,21 +244,6 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     for (int sq = 0; sq < WQ; ++sq) {
         const int l = 4 * sq + lq;
         uq[sq] = load_raw_cols<CT>(static_cast<const TRec *>(urec.at(l < f ? l : 0, col2)));
-    }
-    // v of this wave's columns (used by its first WC lanes in the last stage)
-    const int colf = WC * (wave % NWC) + lane % WC;
-    // (the lane's address of draft 0, which the compiler is kept from taking apart, and a scalar 64-bit row: an offset of rows and
-    // columns in 32 bits of elements would wrap from 4.8 million heads on, and a scalar address for each row cost 200 requests
-    // of 32 heads of 64 35.0 us instead of 34.3 and 34.5.  A draft's step fits 32 bits: the host checks it)
-    const uint32_t v_step = (uint32_t)a.Hv * (uint32_t)(D * sizeof(TIn));
-    uint64_t v_at = reinterpret_cast<uint64_t>(vin + ((size_t)b * T * a.Hv + h) * D + colf);
-    asm volatile("" : "+v"(v_at));
-    using VBits = std::conditional_t<sizeof(TIn) == 4, float, uint16_t>;
-    TIn v_raw[TMX];
-#pragma unroll
-    for (int i = 0; i < TMX; ++i) {
-        const uint64_t row = (uint64_t)(uint32_t)min(i, T - 1) * v_step;
-        v_raw[i] = __builtin_bit_cast(TIn, *reinterpret_cast<const VBits __attribute__((address_space(1))) *>(v_at + row));
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -285,35 +270,51 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         if (__any(bad && di < T) && tid == 0 && a.st.status)
             atomicOr(&a.st.status[s], KVB_STATUS_BADPATH);
     }
-    // Whatever a lane needs of other drafts it reads from the wave's table in LDS (an array indexed at run time would
-    // live in scratch memory, whose loads share the counter of the state loads).
-    float bet[TMX];      // betas, wave-uniform
-    float GcMine;        // of draft lane % 8, the row of W that this lane loaded
-    float GcRow[4];      // of the draft of accumulator row 4 lq + v: draft v (lq even) or 4 + v (lq odd)
-    int ancRow[4];       // its ancestors
-    auto finish_Gc = [&]() {
+    // Decays are taken from the committed context on (the record before the drafts), whose own decay comes with the records,
+    // behind the state: exp(G_i) = exp(G_prev) exp(rel_i), and of record l exp(G_i - G_l) = exp(G_prev - G_l) exp(rel_i), so that
+    // all that concerns the drafts alone is ready before the state is.  Whatever a lane needs of other drafts it reads from the
+    // wave's table in LDS (an array indexed at run time would live in scratch memory, whose loads share the counter of the
+    // state loads).
+    float rel = 0.0f;    // of draft lane % 8, the row of W that this lane loaded
+    float decRow[4];     // exp(rel) of the draft of accumulator row 4 lq + v: draft v (lq even) or 4 + v (lq odd); 0 past the drafts
+    auto draft_decays = [&]() {
         const int path = anc | 1 << di;
-        float run = G_prev;
 #pragma unroll
         for (int j = 0; j < TMX; ++j) {
             const float gj = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, g_raw), j));
-            bet[j] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, beta_mine), j));
-            run += path >> j & 1 ? gj : 0.0f;
+            rel += path >> j & 1 ? gj : 0.0f;
         }
-        GcMine = run;
         if (lane < TMX) {
-            sGc[wave][lane] = run;
-            sGam[wave][lane] = lane < T ? expf(run) : 0.0f;
+            sRel[wave][lane] = rel;
+            sDec[wave][lane] = lane < T ? expf(rel) : 0.0f;
             sAnc[wave][lane] = anc;
         }
         __builtin_amdgcn_wave_barrier();   // (the same wave reads them)
-        const float4 G4 = *reinterpret_cast<const float4 *>(&sGc[wave][4 * (lq % 2)]);
-        const int4 A4 = *reinterpret_cast<const int4 *>(&sAnc[wave][4 * (lq % 2)]);
-        GcRow[0] = G4.x; GcRow[1] = G4.y; GcRow[2] = G4.z; GcRow[3] = G4.w;
-        ancRow[0] = A4.x; ancRow[1] = A4.y; ancRow[2] = A4.z; ancRow[3] = A4.w;
+        const float4 d4 = *reinterpret_cast<const float4 *>(&sDec[wave][4 * (lq % 2)]);
+        decRow[0] = d4.x; decRow[1] = d4.y; decRow[2] = d4.z; decRow[3] = d4.w;
     };
-    if constexpr (!EARLY)
-        finish_Gc();
+    // Weights of the drafts among themselves, in every wave's registers: row m = 4 lq + v of W against key lm of it, seen by the
+    // draft's descendants (q rows: and by itself).  Where they are used they are scalars.
+    float pair_w[4];
+    auto draft_tile = [&]() {
+        const f32x4_t c1 = dot_tile<TIn>(wa, wa);
+        const float4 r4 = *reinterpret_cast<const float4 *>(&sRel[wave][4 * (lq % 2)]);
+        const int4 a4 = *reinterpret_cast<const int4 *>(&sAnc[wave][4 * (lq % 2)]);
+        const float relRow[4] = {r4.x, r4.y, r4.z, r4.w};
+        const int ancRow[4] = {a4.x, a4.y, a4.z, a4.w};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int m = 4 * lq + v, i = m % 8;
+            const bool isq = m >= 8;
+            const bool ok = i < T && lm < T && ((ancRow[v] >> lm & 1) || (isq && lm == i));
+            const float w = expf(relRow[v] - rel);   // (lane lm < 8: draft lm)
+            pair_w[v] = ok ? (isq ? w : -w) * c1[v] : 0.0f;
+            asm volatile("" : "+v"(pair_w[v]));
+        }
+    };
+    auto scalar_of = [](float x, int from) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), from));
+    };
 
     // ---- 4. weights of the state rows ------------------------------------------
     // The sums.  One chain of multiply-adds holds a rounding of the whole sum for each of its terms, which for fp32
@@ -345,12 +346,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     };
     const bool live = lm % 8 < T;
     {
-        float gam;
-        if constexpr (EARLY)
-            gam = live ? 1.0f : 0.0f;
-        else
-            gam = live ? expf(GcMine) : 0.0f;
-        const float sg = lm < 8 ? -gam : gam;
+        const float sg = !live ? 0.0f : lm < 8 ? -1.0f : 1.0f;
         // piece st of the rows belongs to wave st % 4 and covers state rows 4 EW st + EW lq ..
 #pragma unroll
         for (int g = 0; g < NWA; g += NW) {
@@ -391,89 +387,88 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             }
         }
     };
-    if constexpr (EARLY) {
-        __syncthreads();   // sW complete
-        __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();   // sW complete
+    __builtin_amdgcn_sched_barrier(0);
+    draft_decays();
+    if constexpr (!ONE_WAVE)
+        draft_tile();
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (HAS_STATE)
         state_rows();
-        // pins the sums, and whatever derives from the loads younger than the state, to this
-        // point: pure arithmetic is otherwise free to drift across the fences
-        if constexpr (CT == 2)
-            asm volatile("" : "+v"(acc[CT - 1]));
-        asm volatile("" : "+v"(acc[0]), "+v"(G_prev), "+v"(g_raw), "+v"(beta_mine));
-        __builtin_amdgcn_sched_barrier(0);
-        finish_Gc();
-        // acc*[v] is row m = 4 lq + v = draft m % 8: apply its gamma
-        const f32x4_t gam = *reinterpret_cast<const f32x4_t *>(&sGam[wave][4 * (lq % 2)]);
+    // pins the sums, and whatever derives from the loads younger than the state, to this
+    // point: pure arithmetic is otherwise free to drift across the fences
+    if constexpr (CT == 2)
+        asm volatile("" : "+v"(acc[CT - 1]));
+    asm volatile("" : "+v"(acc[0]), "+v"(G_prev));
+    __builtin_amdgcn_sched_barrier(0);
+    // v of this wave's columns (used by its first WC lanes in the last stage)
+    const int colf = WC * (wave % NWC) + lane % WC;
+    // (the lane's address of draft 0, which the compiler is kept from taking apart, and a scalar 64-bit row: an offset of rows and
+    // columns in 32 bits of elements would wrap from 4.8 million heads on, and a scalar address for each row cost 200 requests
+    // of 32 heads of 64 35.0 us instead of 34.3 and 34.5.  A draft's step fits 32 bits: the host checks it)
+    const uint32_t v_step = (uint32_t)a.Hv * (uint32_t)(D * sizeof(TIn));
+    uint64_t v_at = reinterpret_cast<uint64_t>(vin + ((size_t)b * T * a.Hv + h) * D + colf);
+    asm volatile("" : "+v"(v_at));
+    using VBits = std::conditional_t<sizeof(TIn) == 4, float, uint16_t>;
+    TIn v_raw[TMX];
 #pragma unroll
-        for (int t = 0; t < CT; ++t)
-            acc[t] *= gam;
+    for (int i = 0; i < TMX; ++i) {
+        const uint64_t row = (uint64_t)(uint32_t)min(i, T - 1) * v_step;
+        v_raw[i] = __builtin_bit_cast(TIn, *reinterpret_cast<const VBits __attribute__((address_space(1))) *>(v_at + row));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (HAS_STATE) {
+        // acc*[v] is row m = 4 lq + v = draft m % 8: apply its gamma
+        const float base = expf(G_prev);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+                acc[t][v] *= base * decRow[v];
     }
 
-    // The lane's indices from here on.  Carried through the state pass they cost the fp32 kernels with a 32-record window three
-    // spilled registers (five with paged records), one of them the decay of the wave's keys, whose load is then waited for,
-    // and with it everything requested before it: there they are worked out again from an opaque thread index.  200 requests of 16
-    // heads, 6 drafts: 62.2 -> 57.0 us, paged 65.6 -> 58.8; 60 of 16 heads, 8 drafts: 23.6 -> 22.2, paged 24.8 -> 22.3.  (The
-    // others spill nothing: 200 requests of 32 heads of 64 went from 34.3 to 34.7 with it, 60 of 32, fp32, 64-record window, from
-    // 49.5 to 50.2.)
-    int tid2 = tid;
-    if constexpr (D == 128 && sizeof(TIn) == 4 && WREC == 32)
-        asm volatile("" : "+v"(tid2));
-    const int lm2 = tid2 % 16, lq2 = tid2 % 64 / 16, colf2 = WC * (wave % NWC) + tid2 % 64 % WC;
-
-    // ---- 5. stage 1: decayed dot products with every buffered and new key -------
-    // Gkey: cumulative log decay of key n of the tile (a buffered one from memory, a new one from above)
+    // ---- 5. stage 1: decayed dot products with every buffered key -------
     auto key_tile = [&](int tile, const uint4(&kk)[NWA], float Gkey) {
         const f32x4_t c1 = dot_tile<TIn>(wa, kk);
-        // this lane: rows m = 4 lq2 + v of W against key n
-        const int n = 16 * tile + lm2;
+        // this lane: rows m = 4 lq + v of W against key n
+        const int n = 16 * tile + lm;
+        const float w = lq < 2 ? -expf(G_prev - Gkey) : expf(G_prev - Gkey);   // (k rows are negated)
         float o[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int m = 4 * lq2 + v, i = m % 8;
-            const bool isq = m >= 8;
-            // a buffered key is seen by every draft; a new one by its descendants (q rows: and by itself)
-            const bool above = n >= f && ((ancRow[v] >> min(n - f, 31)) & 1);
-            const bool ok = i < T && n < nrec && (n < f || above || (isq && n - f == i));
-            if constexpr (CHAINS) {   // (what is masked stays out whatever its product is, as on the vector ALU)
-                const float w = expf(GcRow[v] - Gkey);
-                o[v] = ok ? (isq ? w : -w) * c1[v] : 0.0f;
-            } else {
-                const float w = ok ? expf(GcRow[v] - Gkey) : 0.0f;
-                o[v] = (isq ? w : -w) * c1[v];
-            }
-        }
-        *reinterpret_cast<float4 *>(&cW[n][4 * lq2]) = make_float4(o[0], o[1], o[2], o[3]);
+        for (int v = 0; v < 4; ++v)
+            o[v] = n < f ? w * decRow[v] * c1[v] : 0.0f;
+        *reinterpret_cast<float4 *>(&cW[n][4 * lq]) = make_float4(o[0], o[1], o[2], o[3]);
     };
-    auto key_G = [&](int n, float buffered) {   // (the read without a condition, then the select)
-        const float fresh = sGc[wave][min(max(n - f, 0), TMX - 1)];
-        return n < f ? buffered : fresh;
-    };
-#pragma unroll
-    for (int x = 0; x < NTW; ++x) {
-        const int tile = wave + NW * x;
-        if (tile < ntile)
-            key_tile(tile, kt[x], key_G(16 * tile + lm2, Gn[x]));
-    }
-    for (int tile = wave + NW * NTW; TAIL && tile < ntile; tile += NW) {   // keys beyond the register window
-        const int n = 16 * tile + lm2;
-        const TIn *kp = key_at(n);
+    if (16 * wave < f && 16 * wave < WREC)   // uniform
+        key_tile(wave, kt, Gn);
+    for (int tile = NW + wave; TAIL && 16 * tile < f; tile += NW) {   // keys beyond the register window
+        const int n = 16 * tile + lm, nc = n < f ? n : 0;
+        const TIn *kp = krec.at(nc, EW * lq);
         uint4 kk[NWA];
 #pragma unroll
         for (int st = 0; st < NWA; ++st)
             kk[st] = *reinterpret_cast<const uint4 *>(kp + 4 * EW * st);
-        key_tile(tile, kk, key_G(n, *Grec.at(n < f ? n : 0, 0)));
+        key_tile(tile, kk, *Grec.at(nc, 0));
+    }
+    if constexpr (ONE_WAVE) {
+        if (wave == NW - 1) {   // (whose key tile is the last to fill)
+            draft_tile();
+            sPair[lane] = make_float4(pair_w[0], pair_w[1], pair_w[2], pair_w[3]);
+        }
     }
     __syncthreads();
+    if constexpr (ONE_WAVE) {
+        const float4 w4 = sPair[lane];
+        pair_w[0] = w4.x; pair_w[1] = w4.y; pair_w[2] = w4.z; pair_w[3] = w4.w;
+    }
 
     // ---- 6. stage 2 on the fp32 matrix cores: records (and, if not yet done, state rows)
     const int nquad = (f + 3) / 4;
 #pragma unroll
     for (int sq = 0; sq < WQ; ++sq) {
         if (sq < nquad) {   // uniform
-            const bool ok = 4 * sq + lq2 < f;
-            float aw = cW[4 * sq + lq2][lm2];
-            if constexpr (CHAINS)   // (past the records the row holds a draft's weights: 0 * Inf is NaN)
-                aw = ok ? aw : 0.0f;
+            const bool ok = 4 * sq + lq < f;
+            const float aw = cW[4 * sq + lq][lm];   // (zero past the records)
             const Cols<CT> uv = unpack_cols(uq[sq]);
 #pragma unroll
             for (int t = 0; t < CT; ++t)
@@ -487,7 +482,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         RawCols<TRec, CT> u4r[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int l = 4 * (s0 + j) + lq2;
+            const int l = 4 * (s0 + j) + lq;
             u4r[j] = load_raw_cols<CT>(static_cast<const TRec *>(urec.at(l < f ? l : 0, col2)));
         }
         Cols<CT> u4[4];
@@ -496,11 +491,9 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             u4[j] = unpack_cols(u4r[j]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int l = 4 * (s0 + j) + lq2;   // < 4 * 35 + 4 = 144 rows of cW
+            const int l = 4 * (s0 + j) + lq;
             if (s0 + j < nquad) {   // uniform
-                float aw = cW[l][lm2];
-                if constexpr (CHAINS)
-                    aw = l < f ? aw : 0.0f;
+                const float aw = cW[l][lm];
 #pragma unroll
                 for (int t = 0; t < CT; ++t)
                     add(j, t, aw, l < f ? u4[j].x[t] : 0.0f);
@@ -516,16 +509,16 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
             settle<SETTLE_FP32>(part[0][t], part[NACC - 1][t]);
         add_chains();
     }
-    // acc[t][v] = row m = 4 lq2 + v, column col2 + t
+    // acc[t][v] = row m = 4 lq + v, column col2 + t
     if (wave < NWC)   // uniform
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             if constexpr (CT == 2)
-                *reinterpret_cast<float2 *>(&fin[4 * lq2 + v][col2]) = make_float2(acc[0][v], acc[CT - 1][v]);
+                *reinterpret_cast<float2 *>(&fin[4 * lq + v][col2]) = make_float2(acc[0][v], acc[CT - 1][v]);
             else
-                fin[4 * lq2 + v][col2] = acc[0][v];
+                fin[4 * lq + v][col2] = acc[0][v];
         }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();   // (a wave finishes its own columns)
 
     // ---- 5. the T new rows among themselves; results ---------------------------
     // (all loads are consumed before the first store: the memory counter also counts stores,
@@ -537,71 +530,58 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
         asm volatile("" : "+v"(vf[i]));
     }
     if (lane < WC && wave < NWC) {
-        // every LDS value of the substitution is fetched up front (independent reads, one
-        // round trip for all) rather than one by one along the serial chain
-        float fu[TMX], fo[TMX], ck[TMX][TMX], cq[TMX][TMX];
+        // (every LDS value of the substitution is fetched up front: one round trip for all)
+        float fu[TMX], fo[TMX];
 #pragma unroll
         for (int i = 0; i < TMX; ++i) {
-            if (i < T) {   // uniform
-                fu[i] = fin[i][colf2];
-                fo[i] = fin[8 + i][colf2];
-#pragma unroll
-                for (int j = 0; j <= i; ++j) {
-                    ck[i][j] = cW[f + j][i];       // K rows are stored negated
-                    cq[i][j] = cW[f + j][8 + i];
-                }
-            } else {
-                fu[i] = fo[i] = 0.0f;
-#pragma unroll
-                for (int j = 0; j <= i; ++j)
-                    ck[i][j] = cq[i][j] = 0.0f;
-            }
+            fu[i] = fin[i][colf];
+            fo[i] = fin[8 + i][colf];
         }
 #pragma unroll
-        for (int i = 0; i < TMX; ++i) {
+        for (int i = 0; i < TMX; ++i)
             asm volatile("" : "+v"(fu[i]), "+v"(fo[i]));
-#pragma unroll
-            for (int j = 0; j <= i; ++j)
-                asm volatile("" : "+v"(ck[i][j]), "+v"(cq[i][j]));
-        }
         float uprev[TMX];
 #pragma unroll
         for (int i = 0; i < TMX; ++i) {
-            if (i < T) {
-                float acc = vf[i] + fu[i];
+            if (i < T) {   // uniform
+                float acc = vf[i] + fu[i];   // (the weights of k rows are negated)
                 float ao = fo[i];
 #pragma unroll
-                for (int j = 0; j < TMX; ++j) {
-                    if (j < i) {
-                        acc = fmaf(ck[i][j], uprev[j], acc);
-                        ao = fmaf(cq[i][j], uprev[j], ao);
-                    }
+                for (int j = 0; j < i; ++j) {
+                    acc = fmaf(scalar_of(pair_w[i % 4], 16 * (i / 4) + j), uprev[j], acc);
+                    ao = fmaf(scalar_of(pair_w[i % 4], 16 * (2 + i / 4) + j), uprev[j], ao);
                 }
                 // the record as it will be stored is what every later use reads
-                const float ui = rounded_to<TRec>(bet[i] * acc);
-                ao = fmaf(cq[i][i], ui, ao);
+                const float ui = rounded_to<TRec>(scalar_of(beta_mine, i) * acc);
+                ao = fmaf(scalar_of(pair_w[i % 4], 16 * (2 + i / 4) + i), ui, ao);
                 uprev[i] = ui;
-                fin[i][colf2] = ui;                 // a lane overwrites only what it has read itself
-                fin[8 + i][colf2] = a.scale * ao;
+                fin[i][colf] = ui;                 // a lane overwrites only what it has read itself
+                fin[8 + i][colf] = a.scale * ao;
             }
         }
     }
-    __syncthreads();
-    // results leave as whole rows, 16 bytes per lane: T rows of u, then T rows of out
-    for (int idx = tid; idx < 2 * T * (D / 4); idx += NT) {
-        const int rr = idx / (D / 4), c4 = idx % (D / 4);
+    // results leave by rows, 16 bytes per lane, T rows of u, then T rows of out: the wave's own columns where its part of a
+    // record is a 128-byte line, else whole rows
+    constexpr bool WHOLE = sizeof(TRec) == 2 || D < 128;
+    constexpr int PR = WHOLE ? D / 4 : WC / 4;   // pieces of a row
+    if constexpr (WHOLE)
+        __syncthreads();
+    else
+        __builtin_amdgcn_wave_barrier();
+    for (int idx = WHOLE ? tid : lane; idx < 2 * T * PR; idx += WHOLE ? NT : 64) {
+        const int rr = idx / PR, col = 4 * (idx % PR) + (WHOLE ? 0 : WC * wave);
         const bool is_u = rr < T;
         const int i = is_u ? rr : rr - T;
-        const float4 val = *reinterpret_cast<const float4 *>(&fin[is_u ? i : 8 + i][4 * c4]);
+        const float4 val = *reinterpret_cast<const float4 *>(&fin[is_u ? i : 8 + i][col]);
         if (is_u)   // (already rounded to the record type: the conversion is exact)
-            store4<STREAM>(urec.at(f + i, 4 * c4), val);
+            store4<STREAM>(urec.at(f + i, col), val);
         else
-            out.template put4<STREAM>((((size_t)b * T + i) * a.Hv + h) * D + 4 * c4, val);
+            out.template put4<STREAM>((((size_t)b * T + i) * a.Hv + h) * D + col, val);
     }
     if (tid < T)
-        put<STREAM>(Grec.at(f + tid, 0), GcMine);   // (lane = draft)
-    if (h % r == 0 && wave == 0 && lm2 < T) {   // lanes holding k rows store them
-        TIn *kw = krec.at(f + lm2, EW * lq2);
+        put<STREAM>(Grec.at(f + tid, 0), G_prev + rel);   // (lane = draft)
+    if (h % r == 0 && wave == 0 && lm < T) {   // lanes holding k rows store them
+        TIn *kw = krec.at(f + lm, EW * lq);
 #pragma unroll
         for (int st = 0; st < NWA; ++st)
             put<STREAM>(reinterpret_cast<uint4 *>(kw + 4 * EW * st), wa[st]);
