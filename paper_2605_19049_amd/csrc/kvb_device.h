@@ -441,13 +441,31 @@ __device__ __forceinline__ void store_raw8(T *p, const Raw8<T> &r)
 
 // x / d for a scalar d > 0, x >= 0.  The division stands ahead of the load of slot[b], the head of every dependent chain;
 // in general it is some fifteen dependent instructions through the vector ALU, and head counts are powers of two mostly:
-// 16 steps of one request 62.7 -> 61.7 us, of 64 430 -> 427, kvb_direct of 2 contexts 8.8 -> 8.6.  (Not in kvb_verify, where
-// 24 requests, fp32, went from 20.3 to 20.6.)  Other head counts pay for the test; Hv / Hk comes with the arguments, so that one
+// 16 steps of one request 62.7 -> 61.7 us, of 64 430 -> 427, kvb_direct of 2 contexts 8.8 -> 8.6.  Other head counts pay for the test; Hv / Hk comes with the arguments, so that one
 // division is left behind the slot: 217 contexts of 9 heads of 32 12.1 us before the test, 12.3 with it and both, 12.0 so; 16
 // steps of one request of 32 heads 57.0 -> 55.9.
 __host__ __device__ inline int quotient(int x, int d)
 {
     return (d & (d - 1)) == 0 ? x >> __builtin_ctz(d) : x / d;
+}
+
+// s, behind the loads of all that is listed: from here on they are in scalar registers, requested ahead and waited for together
+// with s.  Left alone the compiler requested the argument block in four pieces and waited for each in turn, for the first (the head
+// counts of a division) even ahead of the load of s: that chain is the start of every workgroup.  us without and with: 16 steps of
+// kvb_decode_flush of one request 61.2 / 59.7, 8 steps of 8 requests 47.0 / 45.2, 16 steps of 64 441 / 436; kvb_verify and commit of 24
+// requests 24.3 / 23.6, of 7 trees 19.8 / 19.0; 16 steps of kvb_decode without a state, 24 contexts, 104.5 / 100.4.  (Not a volatile statement: behind one the compiler takes memory as changed and loads scalars, the fill among them,
+// through the vector memory path, where each waits for every load before it.)
+template <typename A, typename B, typename C, typename D, typename E, typename F, typename G>
+__device__ __forceinline__ int with_registers(int s, A a, B b, C c, D d, E e, F f, G g)
+{
+    asm("" : "+s"(s) : "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g));
+    return s;
+}
+template <typename A, typename B, typename C, typename D, typename E, typename F, typename G, typename... T>
+__device__ __forceinline__ int with_registers(int s, A a, B b, C c, D d, E e, F f, G g, T... t)
+{
+    asm("" : "+s"(s) : "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g));
+    return with_registers(s, t...);
 }
 
 // Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2).  Map them so

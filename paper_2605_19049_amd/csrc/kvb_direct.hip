@@ -493,6 +493,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
         L = len_arg[b];
     }
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
+    L = with_registers(L, a.slot, a.q, a.k, a.v, a.g, a.beta, a.st.fill, a.st.buf_k, a.st.buf_u, a.st.buf_G, a.st.n_slots, a.Lmax, a.Hk, a.Hv);
     const int h = lb - place * Hv;
     const int r = a.r;
     const int hk = quotient(h, r);
@@ -1252,6 +1253,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
         L = len_arg[b];
     }
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
+    L = with_registers(L, a.slot, a.q, a.k, a.v, a.g, a.beta, a.st.fill, a.st.buf_k, a.st.buf_u, a.st.buf_G, a.st.n_slots, a.Lmax, a.Hk, a.Hv);
     const int h = lb - place * Hv;
     const int r = a.r;
     const int hk = quotient(h, r);

@@ -46,8 +46,10 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     const int lm = lane % 16, lq = lane / 16;
     const int lb = logical_block(nblocks_arg);
     const int b = quotient(lb, Hv_arg);
-    const int s = slot_arg[b];
+    const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
+    const int s = with_registers(slot, a.accepted, a.st.fill, a.st.state, a.st.buf_k, a.st.buf_u, a.st.buf_G, a.st.n_slots, a.st.fill_lg, a.Hk, a.Hv, a.r, a.cap,
+                                 a.threshold, a.st.status);
     const int h = lb - b * Hv_arg;
     const int hk = quotient(h, a.r);
     const int cap = a.cap;
@@ -232,8 +234,10 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
     const int lm = lane % 16, lq = lane / 16;
     const int lb = logical_block(nblocks_arg);
     const int b = quotient(lb, Hv_arg);
-    const int s = slot_arg[b];
+    const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
+    const int s = with_registers(slot, a.accepted, a.st.fill, a.st.state, a.st.buf_k, a.st.buf_u, a.st.buf_G, a.st.n_slots, a.st.fill_lg, a.Hk, a.Hv, a.r, a.cap,
+                                 a.threshold, a.st.status);
     const int h = lb - b * Hv_arg;
     const int hk = quotient(h, a.r);
     const int cap = a.cap;
@@ -460,8 +464,10 @@ __global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg
     __shared__ int sBlk[NW][MAX_BLOCKS];
     const int tid = threadIdx.x, lane = tid % 64;
     const int b = quotient(blockIdx.x, Hv_arg);
-    const int s = slot_arg[b];
+    const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
+    const int s = with_registers(slot, a.path, a.path_len, a.st.fill, a.st.buf_k, a.st.buf_u, a.st.buf_G, a.st.n_slots, a.st.fill_lg, a.Hk, a.Hv, a.r, a.cap, a.T,
+                                 a.st.status);
     const int h = (int)blockIdx.x - b * Hv_arg;
     const int r = a.r, hk = quotient(h, r);
     if (s < 0 || s >= a.st.n_slots)

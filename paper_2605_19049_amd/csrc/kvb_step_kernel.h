@@ -126,8 +126,9 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     const int tid = threadIdx.x;
     const int lb = logical_block(nblocks_arg);
     const int b = quotient(lb, Hv_arg);
-    const int s = slot_arg[b];
+    const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
+    const int s = with_registers(slot, a.q, a.k, a.v, a.st.state, a.st.fill, a.st.buf_k, a.st.buf_u, a.st.buf_G, a.g, a.beta, a.st.n_slots, a.st.fill_lg, a.r, a.cap);
     const int h = lb - b * Hv_arg;
     const int r = a.r;
     const int hk = quotient(h, r);
@@ -751,8 +752,9 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
     const int tid = threadIdx.x;
     const int lb = logical_block(nblocks_arg);
     const int b = quotient(lb, nu_arg);
-    const int s = slot_arg[b];
+    const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
+    const int s = with_registers(slot, a.q, a.k, a.v, a.Hv, a.st.fill, a.st.buf_k, a.st.buf_u, a.st.buf_G, a.g, a.beta, a.st.n_slots, a.st.fill_lg, a.r, a.cap);
     const int r = a.r;
     const int per = (r + HB - 1) / HB;   // workgroups of a key head
     const int of_b = lb - b * nu_arg, hk = quotient(of_b, per);

@@ -152,12 +152,14 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;   // (a scalar)
     const int lb = logical_block(nblocks_arg);
-    const int b = lb / Hv_arg;
-    const int s = slot_arg[b];
+    const int b = quotient(lb, Hv_arg);
+    const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
-    const int h = lb % Hv_arg;
+    const int s = with_registers(slot, a.q, a.k, a.v, a.g, a.beta, a.parent, a.st.state, a.st.fill, a.st.buf_k, a.st.buf_u, a.st.buf_G, a.st.n_slots, a.st.fill_lg,
+                                 a.T);
+    const int h = lb - b * Hv_arg;
     const int r = a.r;
-    const int hk = h / r;
+    const int hk = quotient(h, r);
     const int T = a.T;
     const int cap = a.cap;
 
