@@ -468,16 +468,6 @@ __device__ __forceinline__ int with_registers(int s, A a, B b, C c, D d, E e, F 
     return with_registers(s, t...);
 }
 
-// Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2).  Map them so
-// that XCD x works on one contiguous eighth of the (request, head) units: all heads of a
-// request then share an L2, which keeps the additions to its fill word and the keys that
-// grouped heads share inside one XCD.
-__device__ __forceinline__ int logical_block(int n)
-{
-    const int x = blockIdx.x;
-    return (n % 8 == 0) ? (x % 8) * (n / 8) + x / 8 : x;
-}
-
 // Which unit a workgroup of kvb_direct takes, whose work grows with the context: the heads of a request are dealt
 // over all XCDs, one qk-head with its r v-heads (which share keys and queries through the XCD's L2) at a time; with
 // whole requests on one XCD, as the kernels that add to a fill word need it, the XCD that drew the longest contexts set the
@@ -502,6 +492,32 @@ __host__ __device__ inline int dealt_unit(int x, int deal)
         return x;
     const int of = quotient(j, r);
     return (of * 8 + x % 8) * r + j - of * r;
+}
+
+// The same for the kernels whose workgroups share a request's fill word, over n workgroups of which each qk-head has r: dealt in
+// rounds of 8 qk-heads, or XCD x works on one contiguous eighth, so that what the heads of a request read in common is in one L2,
+// or unit = workgroup id.  In one word, steps and a power of two, without a branch ahead of the load of the slot: workgroup
+// x = 8 j + c takes c * (the upper 27 bits) + 8 (j & -run) + (j & run - 1), run = 1 << the lower 5 bits.
+// Dealt, the requests that fold (and write their states back) are no XCD's alone.  (With the fill words of 32 slots to a line it
+// was slower, since a line's additions then came from all XCDs.)  Eighths / dealt, us: kvb_decode_flush, 16 steps of 64 requests of
+// 32 heads 436 / 397, 4 of 500 935 / 917, 8 of 24 96.4 / 92.4, of 16 67.1 / 62.7, of 32 of 16 69.8 / 67.4; below 512 units it
+// depends on where the states lie, 8 steps of 12 of 32 heads 52.0 / 50.0, of 20 of 16 53.2 / 52.9 or 63.2, of 60 of 8 60.9 / 64.4.
+// kvb_decode without a state, 128 requests 424 / 417, 24 99.7 / 103, 60 of 16 heads 48.2 / 49.0.  kvb_verify and commit, both alike
+// (one dealt and the other not is 1 to 6 % slower than either): 128 requests 88.6 / 83.6, 300 182 / 173, 60 of 16 heads 32.7 / 31.7,
+// 24 of 32 23.8 / 23.3, 24 of 16 18.5 / 18.5, 40 of 8 19.7 / 20.2.  The fold after kvb_direct, which deals at any size, of 10 contexts
+// 28.9 / 27.9, of 100 126 / 124.
+constexpr int DEAL_STEP = 512, DEAL_BUFFER_STEP = 1024, DEAL_SPEC = 512;   // the least units (workgroups) to deal
+inline int unit_deal(int n, int r, int least)
+{
+    const bool small = n < 1 << 29;
+    if (small && n >= least && (r & (r - 1)) == 0 && r < 1 << 26 && n % 8 == 0 && n / 8 % r == 0)
+        return (int)((uint32_t)r << 5 | (uint32_t)__builtin_ctz(r));
+    return small && n % 8 == 0 ? (int)((uint32_t)(n / 8) << 5 | 31u) : 1 << 5;
+}
+__host__ __device__ inline int unit_of(uint32_t x, uint32_t deal)
+{
+    const uint32_t j = x >> 3, rest = j & ((1u << (deal & 31u)) - 1u);
+    return (int)((x & 7u) * (deal >> 5) + 8u * (j - rest) + rest);
 }
 
 // The byte offset of one of 16 rows, cut off where `left` rows follow the first; own: the row times the stride.  (In 32 bits, so
@@ -752,12 +768,12 @@ void launch(void (*kernel)(Params...), int blocks, hipStream_t stream, const Arg
 // (slot, Hv, grid size) as three plain leading arguments ahead of the argument struct: the build preloads the first
 // kernel-argument words into scalar registers at wave launch, so the load of slot[b] -- the head of every dependent
 // chain -- goes out at once.
-#define LAUNCH_LEAD(blocks, stream, a, ...)                                            \
-    do {                                                                               \
-        if ((a).st.block_table)                                                        \
-            launch(__VA_ARGS__, true>, blocks, stream, (a).slot, (a).Hv, blocks, a);   \
-        else                                                                           \
-            launch(__VA_ARGS__, false>, blocks, stream, (a).slot, (a).Hv, blocks, a);  \
+#define LAUNCH_LEAD(blocks, deal, stream, a, ...)                                    \
+    do {                                                                             \
+        if ((a).st.block_table)                                                      \
+            launch(__VA_ARGS__, true>, blocks, stream, (a).slot, (a).Hv, deal, a);   \
+        else                                                                         \
+            launch(__VA_ARGS__, false>, blocks, stream, (a).slot, (a).Hv, deal, a);  \
     } while (0)
 
 // The compiled (input type, record type) pairs: fp32 records with any input type, 16-bit records

@@ -35,7 +35,7 @@ __device__ __forceinline__ void copy_row(T *dst, const T *src)
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, bool PAGED>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : D == 64 ? 3 : 4)))
-void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg, const FlushArgs a)
+void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg, const FlushArgs a)
 {
     constexpr int RT = D == 128 ? 8 : D == 64 ? 2 : 1;   // 16-row tiles of a wave
     constexpr int CT = D == 32 ? 1 : 2;                  // 16-column tiles of a wave
@@ -44,7 +44,7 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
     const int lm = lane % 16, lq = lane / 16;
-    const int lb = logical_block(nblocks_arg);
+    const int lb = unit_of(blockIdx.x, deal_arg);
     const int b = quotient(lb, Hv_arg);
     const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
@@ -218,7 +218,7 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 template <typename TIn, typename TRec, bool MULTI, bool STREAM, bool PAGED>
 // (register budgets: 3 workgroups per CU, 2 where the sums persist)
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MULTI ? 2 : 3)))
-void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg, const FlushArgs a)
+void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg, const FlushArgs a)
 {
     // (the three leading arguments repeat a.slot, a.Hv and the grid size: preloaded into scalar registers
     // at wave launch, so that the load of slot[b] does not wait for the fetch of the argument block)
@@ -232,7 +232,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;   // (a scalar)
     const int lm = lane % 16, lq = lane / 16;
-    const int lb = logical_block(nblocks_arg);
+    const int lb = unit_of(blockIdx.x, deal_arg);
     const int b = quotient(lb, Hv_arg);
     const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
@@ -456,7 +456,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblo
 // pass move by move, 21.1 at once.
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, bool PAGED>
-__global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg,
+__global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
                                                          const CompactArgs a)
 {
     constexpr int PU = D * sizeof(TRec) / 16, PK = D * sizeof(TIn) / 16;   // pieces of a record
@@ -516,30 +516,31 @@ __global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg
 // ---------------------------------------------------------------------------
 int launch_flush(int dk, int in_dtype, int rec_dtype, const FlushArgs &a, int blocks, hipStream_t stream)
 {
+    const int deal = unit_deal(blocks, a.r, a.accepted ? DEAL_SPEC : 0);
     if (dk == 128 && in_dtype != KVB_F32)   // the matrix-core kernel
         return dispatch_types16(in_dtype, rec_dtype, [&]<typename TIn, typename TRec>() {
             if (a.cap <= 32) {
                 if (a.stream)
-                    LAUNCH_LEAD(blocks, stream, a, kvb_flush_mfma_kernel<TIn, TRec, false, true);
+                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, false, true);
                 else
-                    LAUNCH_LEAD(blocks, stream, a, kvb_flush_mfma_kernel<TIn, TRec, false, false);
+                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, false, false);
             } else {
                 if (a.stream)
-                    LAUNCH_LEAD(blocks, stream, a, kvb_flush_mfma_kernel<TIn, TRec, true, true);
+                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, true, true);
                 else
-                    LAUNCH_LEAD(blocks, stream, a, kvb_flush_mfma_kernel<TIn, TRec, true, false);
+                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, true, false);
             }
         });
     return dispatch(dk, in_dtype, rec_dtype, [&]<int D, typename TIn, typename TRec>() {
         if constexpr (!(D == 128 && sizeof(TIn) == 2))
-            LAUNCH_LEAD(blocks, stream, a, kvb_flush_rows_kernel<D, TIn, TRec);
+            LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_rows_kernel<D, TIn, TRec);
     });
 }
 
 int launch_compact(int dk, int in_dtype, int rec_dtype, const CompactArgs &a, int blocks, hipStream_t stream)
 {
     return dispatch(dk, in_dtype, rec_dtype,
-                    [&]<int D, typename TIn, typename TRec>() { LAUNCH_LEAD(blocks, stream, a, kvb_compact_kernel<D, TIn, TRec); });
+                    [&]<int D, typename TIn, typename TRec>() { LAUNCH_LEAD(blocks, 0, stream, a, kvb_compact_kernel<D, TIn, TRec); });
 }
 
 }  // namespace kvb_impl

@@ -83,7 +83,7 @@ template <int D, typename TIn, typename TRec, int WREC, bool FUSE, bool STREAM, 
 // (register budget: the 64-record decode variants sit at the edge of three workgroups per CU; hold them there,
 // and those with the matrix-core update, which would spread the state over accumulation registers)
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WREC == 64 || (FUSE && D == 128 && sizeof(TIn) == 2) ? 3 : 1)))
-void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg,
+void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
                                                       const StepArgs a)
 {
     // The three leading arguments repeat a.slot, a.Hv and the grid size: as plain leading kernel
@@ -124,7 +124,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
     __shared__ __attribute__((aligned(16))) uint16_t uT[MFOLD ? UPC : 1][MFOLD ? D : 1][FS];  // of Gamma_fl u_l, by column
 
     const int tid = threadIdx.x;
-    const int lb = logical_block(nblocks_arg);
+    const int lb = unit_of(blockIdx.x, deal_arg);
     const int b = quotient(lb, Hv_arg);
     const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
@@ -729,7 +729,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_ar
 // as, or faster than, the one with two heads from 512 units on only, which these lines replaced: 9.4, 10.9, 14.5 and 22.4).
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int HB, bool PAGED>
-__global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot_arg, int32_t nu_arg, int32_t nblocks_arg,
+__global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot_arg, int32_t nu_arg, int32_t deal_arg,
                                                              const StepArgs a)
 {
     // (leading arguments: as in kvb_step_kernel, with the workgroups of a request in the place of its heads)
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot
     __shared__ int sBlk[NW][MAX_BLOCKS];
 
     const int tid = threadIdx.x;
-    const int lb = logical_block(nblocks_arg);
+    const int lb = unit_of(blockIdx.x, deal_arg);
     const int b = quotient(lb, nu_arg);
     const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
@@ -957,34 +957,36 @@ void launch_step_s(const StepArgs &a, int blocks, hipStream_t stream)
 {
     // (a branch inside the kernel around the state loads would make the compiler's wait
     // counters conservative at the join, so these are compile-time variants)
+    const int deal = unit_deal(blocks, a.r, DEAL_STEP);
     const bool st = a.stream_state != 0 && D == 128;   // the small head sizes are not tuned: no streaming variant
     if (a.threshold > 0) {
         if constexpr (D == 128) {
             if (st) {
-                LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, true);
+                LAUNCH_LEAD(blocks, deal, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, true);
                 return;
             }
         }
-        LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, false);
+        LAUNCH_LEAD(blocks, deal, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, true, false);
         return;
     }
     if constexpr (D == 128) {
         if (st) {
-            LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, false, true);
+            LAUNCH_LEAD(blocks, deal, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, false, true);
             return;
         }
     }
-    LAUNCH_LEAD(blocks, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, false, false);
+    LAUNCH_LEAD(blocks, deal, stream, a, kvb_step_kernel<D, TIn, TRec, WREC, false, false);
 }
 
 template <int D, typename TIn, typename TRec, int HB>
 void launch_buffer_step_h(const StepArgs &a, int B, hipStream_t stream)
 {
-    const int32_t nu = a.Hk * ((a.r + HB - 1) / HB);   // workgroups of a request
+    const int32_t per = (a.r + HB - 1) / HB, nu = a.Hk * per;   // workgroups of a key head and of a request
+    const int deal = unit_deal(B * nu, per, DEAL_BUFFER_STEP);
     if (a.st.block_table)
-        launch(kvb_buffer_step_kernel<D, TIn, TRec, HB, true>, B * nu, stream, a.slot, nu, B * nu, a);
+        launch(kvb_buffer_step_kernel<D, TIn, TRec, HB, true>, B * nu, stream, a.slot, nu, deal, a);
     else
-        launch(kvb_buffer_step_kernel<D, TIn, TRec, HB, false>, B * nu, stream, a.slot, nu, B * nu, a);
+        launch(kvb_buffer_step_kernel<D, TIn, TRec, HB, false>, B * nu, stream, a.slot, nu, deal, a);
 }
 
 template <int D, typename TIn, typename TRec>

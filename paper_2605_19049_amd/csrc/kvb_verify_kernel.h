@@ -122,7 +122,7 @@ template <int D, typename TIn, typename TRec, int WREC, bool HAS_STATE, bool STR
 // fp32 keys of 128, whose operands take twice the registers; without a state 2, which keeps the sums out of the
 // accumulation registers, where settle() could not hold them)
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(!HAS_STATE ? 2 : (WREC <= 32 ? 4 : 3) - (D * sizeof(TIn) > 256))))
-void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nblocks_arg, const StepArgs a)
+void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg, const StepArgs a)
 {
     // (the three leading arguments repeat a.slot, a.Hv and the grid size: preloaded into scalar registers
     // at wave launch, so that the load of slot[b] does not wait for the fetch of the argument block)
@@ -151,7 +151,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
     __shared__ __attribute__((aligned(16))) int sAnc[NW][TMX];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;   // (a scalar)
-    const int lb = logical_block(nblocks_arg);
+    const int lb = unit_of(blockIdx.x, deal_arg);
     const int b = quotient(lb, Hv_arg);
     const int32_t slot = slot_arg[b];
     __builtin_amdgcn_sched_barrier(0);   // nothing that needs the argument block goes above this load
@@ -596,17 +596,18 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t nbl
 template <int D, typename TIn, typename TRec, int WREC>
 void launch_verify_w(const StepArgs &a, int blocks, hipStream_t stream)
 {
+    const int deal = unit_deal(blocks, a.r, DEAL_SPEC);
     if (!a.st.state) {
-        LAUNCH_LEAD(blocks, stream, a, kvb_verify_mfma_kernel<D, TIn, TRec, WREC, false, false);
+        LAUNCH_LEAD(blocks, deal, stream, a, kvb_verify_mfma_kernel<D, TIn, TRec, WREC, false, false);
         return;
     }
     if constexpr (D == 128) {   // (the small head sizes are not tuned: no streaming variant)
         if (a.stream_state) {
-            LAUNCH_LEAD(blocks, stream, a, kvb_verify_mfma_kernel<D, TIn, TRec, WREC, true, true);
+            LAUNCH_LEAD(blocks, deal, stream, a, kvb_verify_mfma_kernel<D, TIn, TRec, WREC, true, true);
             return;
         }
     }
-    LAUNCH_LEAD(blocks, stream, a, kvb_verify_mfma_kernel<D, TIn, TRec, WREC, true, false);
+    LAUNCH_LEAD(blocks, deal, stream, a, kvb_verify_mfma_kernel<D, TIn, TRec, WREC, true, false);
 }
 
 template <int D, typename TIn, typename TRec>

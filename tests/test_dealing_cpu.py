@@ -32,6 +32,13 @@ int main(int argc, char **argv)
         printf("%d\n", bad);
         return 0;
     }
+    if (argc == 4) {   // units of the kernels that share fill words, dealt from argv[3] units on
+        const int n = atoi(argv[1]);
+        const uint32_t word = (uint32_t)kvb_impl::unit_deal(n, atoi(argv[2]), atoi(argv[3]));
+        for (int x = 0; x < n; ++x)
+            printf("%d\n", kvb_impl::unit_of((uint32_t)x, word));
+        return 0;
+    }
     const int blocks = atoi(argv[1]), deal = kvb_impl::deal_of(blocks, atoi(argv[2]));
     for (int x = 0; x < blocks; ++x)
         printf("%d\n", kvb_impl::dealt_unit(x, deal));
@@ -84,3 +91,21 @@ def test_no_sort_without_different_lengths(program):
 def test_row_offsets(program, heads):
     """A row of 16, or the last one there is, also where the rows of a whole context leave 32 bits."""
     assert program(heads)[0] == 0
+
+
+@pytest.mark.parametrize("B, Hk, r", [(64, 16, 2), (13, 4, 2), (1, 16, 2), (7, 2, 4), (5, 3, 3), (24, 3, 3), (16, 3, 3), (1, 1, 1), (1, 8, 1), (23, 16, 1), (500, 16, 2), (255, 4, 2), (3, 1, 16), (2, 8, 8)])
+@pytest.mark.parametrize("least", [0, 512])
+def test_units_of_shared_fill_words(program, B, Hk, r, least):
+    """Every unit is taken once.  Dealt, where the qk-heads divide by 8, r is a power of two and the units are enough: the v-heads of
+    a qk-head on one XCD (workgroup id modulo 8), consecutive qk-heads on consecutive ones; else whole eighths, or as they come."""
+    n = B * Hk * r
+    u = program(n, r, least)
+    assert np.array_equal(np.sort(u), np.arange(n))
+    xcd = np.empty(n, int)
+    xcd[u] = np.arange(n) % 8
+    if n >= least and r & (r - 1) == 0 and B * Hk % 8 == 0:
+        assert np.array_equal(xcd, np.arange(n) // r % 8)
+    elif n % 8 == 0:
+        assert np.array_equal(xcd, np.arange(n) // (n // 8))
+    else:
+        assert np.array_equal(u, np.arange(n))
