@@ -130,7 +130,7 @@ int step_common(const kvb_shape *sh, const kvb_store *st, const int32_t *slot, i
     // (kvb_verify steps from draft to draft in 32 bits of bytes)
     if (T > 1 && (long long)sh->Hv * sh->dv * (sh->in_dtype == KVB_F32 ? 4 : 2) > 0xFFFFFFFFLL)
         return KVB_EINVAL;
-    if (advance && step_workgroups(a, sh->dk, blocks) > MAX_FILL_WG)
+    if (advance && step_workgroups(a, sh->dk, sh->in_dtype == KVB_F32, blocks) > MAX_FILL_WG)
         return KVB_EINVAL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     g_launch_status = hipSuccess;

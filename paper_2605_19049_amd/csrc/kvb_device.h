@@ -830,15 +830,16 @@ int dispatch(int dk, int in_dtype, int rec_dtype, F &&f)
     });
 }
 
-// v-heads of a workgroup of kvb_buffer_step_kernel (the measurements stand there); blocks: B * Hv.
-inline int buffer_step_heads(int d, int Hk, int Hv, int blocks)
+// v-heads of a workgroup of kvb_buffer_step_kernel (the measurements stand there); blocks: B * Hv, wide: fp32 inputs.
+inline int buffer_step_heads(int d, bool wide, int Hk, int Hv, int cap, int blocks)
 {
-    return Hv > Hk && blocks >= (d == 128 ? 256 : 96) ? 2 : 1;
+    const bool one = d == 128 && wide && cap > 64 && Hv <= MAX_FILL_WG;
+    return Hv > Hk && blocks >= 320 && !one ? 2 : 1;
 }
 // Workgroups that add to a request's fill word when a token is appended.
-inline int step_workgroups(const StepArgs &a, int d, int blocks)
+inline int step_workgroups(const StepArgs &a, int d, bool wide, int blocks)
 {
-    const int hb = a.st.state ? 1 : buffer_step_heads(d, a.Hk, a.Hv, blocks);
+    const int hb = a.st.state ? 1 : buffer_step_heads(d, wide, a.Hk, a.Hv, a.cap, blocks);
     return a.Hk * ((a.r + hb - 1) / hb);
 }
 

@@ -717,36 +717,29 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
 // fp16, 16 steps: 476 us with the dots on the vector ALU, sums by shuffles through LDS and 64-bit record addresses, 447
 // without the three.
 // Rule (buffer_step_heads): two heads a workgroup from as many units on as leave the CUs busy; below, the halves of
-// the chip that would stay idle are worth more.  What two heads save besides keys are additions to the fill word, which
-// pass one at a time (about 10 ns each) where the slots of a batch share a 128-byte line, as the slots here do.
+// the chip that would stay idle are worth more.  What two heads save are the keys and half of the workgroups.
 // Passes beyond the fill load a valid record and compute nothing.
-// One head a workgroup / two, 32 heads, us a call, each request at its own fill:
-//                           0..60 records                          0..10 records       0..119 records
-//   requests                16           32           128          32           128    128
-//   d = 128, bf16 / fp32     8.6 /  6.6  10.2 /  8.3  22.2 / 19.3   8.1 /  6.1  19.5 / 15.0  30.6 / 30.0
-//   d = 128, fp16 / fp16     8.5 /  6.8  10.2 /  8.0  21.4 / 17.4   8.1 /  6.0  19.2 / 14.4  27.1 / 22.5
-//   d = 64,  bf16 / fp32     9.1 /  6.8   9.5 /  7.2  18.4 / 14.1   9.1 /  6.8  16.7 / 11.9  21.5 / 18.6
-//   d = 64,  fp32            9.1 /  6.8   9.7 /  7.1  18.1 / 15.5   9.1 /  6.7  16.2 / 12.1  22.3 / 20.6
-//   d = 32,  fp16 / fp16     8.4 /  6.2   9.7 /  7.0  15.5 / 10.3   8.2 /  6.2  14.3 / 10.0  15.2 / 12.0
-//   d = 32,  fp32            8.4 /  6.3   9.5 /  7.0  14.7 / 10.8   8.2 /  6.2  14.4 / 10.5  16.9 / 14.4
-// Around the lines, 0..60 records (requests of 32 heads, or of 8 where marked):
-//   requests                2            4            13 of 8      30 of 8      6            8
-//   units                   64           128          104          240          192          256
-//   d = 128, bf16 / fp32    4.6 / 5.2    5.1 / 5.6    4.9 / 5.6    5.5 / 5.9    6.4 / 5.9    7.1 / 6.1
-//   d = 128, fp16 / fp16    4.6 / 5.1    5.0 / 5.5    4.9 / 5.5    5.3 / 5.7    6.2 / 5.7    6.9 / 6.0
-//   d = 128, fp32           4.8 / 5.5    5.5 / 5.8    5.2 / 5.9    5.5 / 6.2    6.3 / 6.2    7.1 / 6.3
-//   d = 64,  bf16 / fp32    4.6 / 4.6    5.2 / 4.8    5.0 / 4.8    5.4 / 5.0    6.1 / 5.3    6.8 / 5.7
-//   d = 32,  fp16 / fp16    4.5 / 4.4    5.2 / 4.7    4.9 / 4.6    5.2 / 4.8    5.9 / 5.1    6.7 / 5.5
-// The lines: 256 units at d = 128, 96 below.  Three v-heads to a key head, where the second workgroup of a key head has one of them:
-//   requests of 9 heads        11           16           22           30           45           60           120          240
-//   units                      99           144          198          270          405          540          1080         2160
-//   d = 128, bf16 / fp32       5.3 / 5.7    5.5 / 5.9    5.6 / 5.9    6.6 / 6.1    7.1 / 7.3    7.1 / 7.3    8.9 / 8.6    14.3 / 13.6
-//     0..119 records           6.5 / 7.4    6.4 / 7.4    6.6 / 7.5    8.2 / 7.5    8.3 / 9.4    8.7 / 9.3   11.8 / 12.8   19.8 / 20.7
-//   d = 128, fp16 / fp16       5.2 / 5.5    5.2 / 5.7    5.5 / 5.8    6.6 / 6.0    7.0 / 7.1    7.1 / 7.1    8.9 / 8.2    12.8 / 11.9
-//   d = 64,  bf16 / fp32       5.1 / 5.0    5.1 / 5.0    5.2 / 5.0    6.2 / 5.5    6.5 / 6.3    7.0 / 6.3    7.2 / 6.8    10.2 /  9.1
-//   d = 32,  fp16 / fp16       5.1 / 4.8    5.0 / 4.8    5.2 / 4.9    5.9 / 5.2    6.2 / 5.9    6.9 / 6.2    7.1 / 6.1     9.1 /  7.9
-// The lines are the same ones; long fp32 records of d = 128 are better off with one head (there the kernel with two was as fast
-// as, or faster than, the one with two heads from 512 units on only, which these lines replaced: 9.4, 10.9, 14.5 and 22.4).
+// One head a workgroup / two, a line to each fill word, us a call, each request at its own fill, 0..60 records unless said:
+//   requests of 32 heads       2            4            8            16           32           64            128           16, 0..10    128, 0..10    32, 0..119    128, 0..119
+//   units                      64           128          256          512          1024         2048          4096          512          4096          1024          4096
+//   d = 128, bf16 / fp32       4.6 / 5.2    4.9 / 5.6    5.1 / 5.8    5.9 / 5.9    7.9 / 7.1    11.9 / 11.6   19.3 / 18.4   5.0 / 4.8    15.1 / 12.1   10.1 / 10.8   27.6 / 28.6
+//   d = 128, fp16 / fp16       4.5 / 5.0    4.9 / 5.4    5.0 / 5.6    5.8 / 5.7    7.8 / 6.7    11.5 /  8.9   18.5 / 14.7   5.0 / 4.7    15.0 / 11.2    9.5 /  8.3   24.2 / 20.7
+//   d = 128, fp32              4.7 / 5.3    5.0 / 5.7    5.3 / 6.1    6.0 / 6.2    7.8 / 8.4    12.7 / 13.3   20.7 / 21.4   4.9 / 4.8    14.5 / 12.3   10.8 / 12.1   32.2 / 34.2
+//   d = 64,  bf16 / fp32       4.2 / 4.6    4.2 / 4.6    4.4 / 4.8    5.0 / 4.8    6.0 / 5.5     8.1 /  7.0   12.3 / 11.8   4.6 / 4.3    10.5 /  9.0    7.3 /  6.5   17.5 / 17.8
+//   d = 64,  fp32              4.1 / 4.6    4.2 / 4.6    4.3 / 4.8    4.9 / 4.8    5.9 / 5.7     8.0 /  7.4   13.1 / 13.1   4.6 / 4.3    10.6 /  9.1    7.4 /  8.2   19.4 / 20.2
+//   d = 32,  fp16 / fp16       4.2 / 4.4    4.1 / 4.4    4.2 / 4.5    4.7 / 4.6    5.4 / 5.0     6.6 /  6.1    9.2 /  7.8   4.5 / 4.3     8.8 /  7.3    5.9 /  5.6   10.9 /  9.7
+//   d = 32,  fp32              4.1 / 4.3    4.1 / 4.3    4.1 / 4.3    4.7 / 4.5    5.4 / 5.1     6.8 /  6.4    9.5 /  8.5   4.4 / 4.2     8.9 /  7.8    6.0 /  5.6   12.8 / 12.8
+// Three v-heads to a key head, where the second workgroup of a key head has one of them, and heads of 8:
+//   requests                   16 of 9      45 of 9      120 of 9     240 of 9      13 of 8      30 of 8      100 of 8
+//   units                      144          405          1080         2160          104          240          800
+//   d = 128, bf16 / fp32       5.2 / 5.8    6.3 / 6.6    8.7 / 8.3    12.4 / 12.8   4.8 / 5.5    5.1 / 5.8    7.4 / 7.0
+//   d = 128, fp16 / fp16       5.1 / 5.6    6.2 / 6.2    8.5 / 8.0    12.0 / 11.5   4.8 / 5.3    5.1 / 5.6    7.4 / 6.7
+//   d = 128, fp32              5.3 / 6.0    6.2 / 6.6    8.1 / 8.5    12.4 / 13.6   4.9 / 5.7    5.3 / 6.1    7.1 / 7.4
+//   d = 64,  bf16 / fp32       4.4 / 4.7    5.3 / 5.4    6.4 / 6.3     8.4 /  8.8   4.4 / 4.8    4.6 / 5.0    5.7 / 5.5
+//   d = 32,  fp16 / fp16       4.2 / 4.5    4.9 / 5.0    5.5 / 5.6     7.1 /  7.0   4.1 / 4.5    4.2 / 4.5    5.1 / 5.1
+// The line: 320 units (12 contexts of 32 heads, d = 128, bf16, up to 48 tokens and 16 steps, 384 units, 90.1 / 86.7 a pass; 8
+// contexts, fp16, 72.6 / 79.3).  fp32 inputs at d = 128 keep one head unless the buffers are short (cap <= 64: 100 contexts of up to
+// 40 tokens, 8 steps, 187.6 / 184.7), or one head has more workgroups a request than a fill word counts.
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int HB, bool PAGED>
 __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot_arg, int32_t nu_arg, int32_t deal_arg,
@@ -1013,7 +1006,7 @@ template <int D, typename TIn, typename TRec>
 void launch_buffer_step(const StepArgs &a, int blocks, hipStream_t stream)
 {
     const int B = blocks / a.Hv;
-    if (buffer_step_heads(D, a.Hk, a.Hv, blocks) == 2)
+    if (buffer_step_heads(D, sizeof(TIn) == 4, a.Hk, a.Hv, a.cap, blocks) == 2)
         launch_buffer_step_h<D, TIn, TRec, 2>(a, B, stream);
     else
         launch_buffer_step_h<D, TIn, TRec, 1>(a, B, stream);

@@ -271,6 +271,38 @@ def test_buffer_step_blocks(d, in_dtype, rec_dtype, Hk, Hv, block_size):
     H.check(errs, in_dtype, rec_dtype, "buffer step")
 
 
+@pytest.mark.parametrize("d, in_dtype, rec_dtype, cap", [(128, i, r, 128) for i, r in TYPES] + [(128, "f32", "f32", 32), (64, "bf16", "f32", 128), (64, "f32", "f32", 48),
+                                                         (32, "f16", "f16", 128)])
+@pytest.mark.parametrize("block_size", [None, 16])
+def test_buffer_step_two_heads(d, in_dtype, rec_dtype, cap, block_size):
+    """kvb_decode without a state in launches that take two v-heads a workgroup (540 units, five v-heads to a key head, so that one
+    is left over): around the tiles and blocks that cap holds, the token that joins fills[b] records, and the record it leaves."""
+    rng = np.random.default_rng(950 + d)
+    Hk, Hv, B = 2, 10, 54
+    edges = [f for f in (0, 1, 15, 16, 17, 31, 47, 63, 64, 65, 127) if f < cap]
+    fills = np.array([edges[b % len(edges)] for b in range(B)], np.int32)
+    n = cap
+    tok = synth.token_stream(rng, B, n, Hk, Hv, d, d, in_dtype)
+    dtok = H.upload_tokens(tok, in_dtype)
+    lay = H.Layer(B, Hk, Hv, d, d, cap, in_dtype, with_state=False, rec_dtype=rec_dtype, out_dtype=rec_dtype, block_size=block_size)
+    for t in range(n - 1):   # request b joins so that all end at token n - 1
+        who = torch.from_numpy(np.flatnonzero(fills >= n - 1 - t)).cuda()
+        if len(who):
+            view = {x: y[who, t].contiguous() for x, y in dtok.items()}
+            lay.decode(view, lay.new_out(len(who), Hv, d), slot=lay.slot[who].contiguous(), B=len(who))
+    out = lay.new_out(B, Hv, d, fill=float("nan"))
+    lay.decode(H.step_view(dtok, n - 1), out)
+    torch.cuda.synchronize()
+    assert np.array_equal(lay.fill(), fills + 1) and lay.spare_clean()
+    errs = []
+    for b in range(len(edges)):
+        own = {x: y[b:b + 1, n - 1 - fills[b]:] for x, y in tok.items()}
+        o, u, _, _ = oracle.gdn_sequence(np.zeros((1, Hv, d, d)), own["q"], own["k"], own["v"], own["g"], own["beta"])
+        errs += [H.rel_err(H.host(out[b]), o[0, -1], lay.out_unit), H.rel_err(lay.u_records(b, 0, fills[b] + 1).transpose(1, 0, 2), u[0])]
+    say("buffer step, two heads, d=%d %s/%s: rel err %.2e" % (d, in_dtype, rec_dtype, max(errs)))
+    H.check(errs, in_dtype, rec_dtype, "buffer step, two heads")
+
+
 @pytest.mark.parametrize("in_dtype", ["bf16", "f16"])
 def test_buffer_step_dots_add_pairwise(in_dtype):
     """kvb_decode without a state, delta values that pick one record each: its outputs are the dot products of the new query
