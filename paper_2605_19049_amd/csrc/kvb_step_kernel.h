@@ -698,10 +698,11 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
                     }
                 }
             }
-            float4 *sw = reinterpret_cast<float4 *>(a.st.state + unit * D * D);
+            float *sw = a.st.state + unit * D * D;
+            const uint32_t lane_at = (uint32_t)(rg * LPR + c4) * 16;
 #pragma unroll
             for (int p = 0; p < NPASS; ++p)   // (a state that is streamed in is streamed out again: +1 % on 1 GiB of state)
-                put<STREAM>(sw + (size_t)(rg + RPP * p) * LPR + c4, sreg[p]);
+                put_at<STREAM>(sw + RPP * p * D, lane_at, sreg[p]);
         }
     }
 }
