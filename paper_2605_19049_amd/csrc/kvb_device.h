@@ -482,7 +482,7 @@ __device__ __forceinline__ int with_registers(int s, A a, B b, C c, D d, E e, F 
 
 // Which unit a workgroup of kvb_direct takes, whose work grows with the context: the heads of a request are dealt
 // over all XCDs, one qk-head with its r v-heads (which share keys and queries through the XCD's L2) at a time; with
-// whole requests on one XCD, as the kernels that add to a fill word need it, the XCD that drew the longest contexts set the
+// whole requests on one XCD, the XCD that drew the longest contexts set the
 // end of the launch (256 contexts of ~U(1,64): 118 -> 110 us; 96 of ~U(1,128): 130 -> 115 us).  The order of the requests is
 // another matter (longest_first).
 // Rounds of 8 qk-heads are dealt, one to an XCD; the units of the qk-heads that are left (fewer than 8) go one by one.
@@ -777,7 +777,7 @@ void launch(void (*kernel)(Params...), int blocks, hipStream_t stream, const Arg
 
 // Picks the paged or the contiguous instance of a kernel template whose last parameter is PAGED;
 // the arguments after `a` are the kernel's name and its leading template arguments.  They take
-// (slot, Hv, grid size) as three plain leading arguments ahead of the argument struct: the build preloads the first
+// (slot, Hv, dealing of the units) as three plain leading arguments ahead of the argument struct: the build preloads the first
 // kernel-argument words into scalar registers at wave launch, so the load of slot[b] -- the head of every dependent
 // chain -- goes out at once.
 #define LAUNCH_LEAD(blocks, deal, stream, a, ...)                                    \

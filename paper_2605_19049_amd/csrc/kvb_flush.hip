@@ -220,7 +220,7 @@ template <typename TIn, typename TRec, bool MULTI, bool STREAM, bool PAGED>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MULTI ? 2 : 3)))
 void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg, const FlushArgs a)
 {
-    // (the three leading arguments repeat a.slot, a.Hv and the grid size: preloaded into scalar registers
+    // (the three leading arguments are a.slot, a.Hv and the dealing of the units: preloaded into scalar registers
     // at wave launch, so that the load of slot[b] does not wait for the fetch of the argument block)
     constexpr int D = 128;
     constexpr int CH = 32;   // records per chunk

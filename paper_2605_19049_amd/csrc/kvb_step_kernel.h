@@ -86,7 +86,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WREC == 64 |
 void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
                                                       const StepArgs a)
 {
-    // The three leading arguments repeat a.slot, a.Hv and the grid size: as plain leading kernel
+    // The three leading arguments are a.slot, a.Hv and the dealing of the units (unit_deal): as plain leading kernel
     // arguments they are preloaded into scalar registers at wave launch (the build asks for it), so
     // the load of slot[b] -- the head of the dependent chain to the first state byte -- goes out at
     // once instead of after the round trip that fetches the argument block.

@@ -118,13 +118,13 @@ __device__ __forceinline__ f32x4_t dot_tile(const uint4 (&a)[N], const uint4 (&b
 // drafts 85.4 -> 83.5; 24, 16 records, 24.7 -> 24.2; 300 182 -> 182 (memory).
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int WREC, bool HAS_STATE, bool STREAM, bool PAGED>
-// (register budgets: 4 waves per SIMD with a record window of 16 or 32, 3 with the 64-record window or with
+// (register budgets: at least 4 waves per SIMD with a record window of 16 or 32, 3 with the 64-record window or with
 // fp32 keys of 128, whose operands take twice the registers; without a state 2, which keeps the sums out of the
 // accumulation registers, where settle() could not hold them)
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(!HAS_STATE ? 2 : (WREC <= 32 ? 4 : 3) - (D * sizeof(TIn) > 256))))
 void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg, const StepArgs a)
 {
-    // (the three leading arguments repeat a.slot, a.Hv and the grid size: preloaded into scalar registers
+    // (the three leading arguments are a.slot, a.Hv and the dealing of the units: preloaded into scalar registers
     // at wave launch, so that the load of slot[b] does not wait for the fetch of the argument block)
     constexpr int CT = D == 128 ? 2 : 1;                      // adjacent columns of a lane
     constexpr int WC = 16 * CT;                               // columns of a wave
