@@ -172,8 +172,8 @@ __device__ __forceinline__ float2 unpack2r(const Raw2<T> &r) { return unpack_pai
 // next one waits for that.  These go through to memory as they are made (device scope, nobody is ordered by them) or, NT,
 // past the caches, for what a state that is streamed too leaves behind.  With plain stores / through, us: kvb_decode_flush, 8
 // steps of 8 requests of 32 heads 49.5 / 46.1, of 24 103.3 / 96.6, 16 steps of 64 437 / 433; kvb_verify and commit of 24
-// requests of 16 heads, fp32, 20.2 / 19.0.
-template <bool NT, typename T>
+// requests of 16 heads, fp32, 20.2 / 19.0.  PLAIN: a plain store all the same, for what the next launch reads back (kvb_decode_flush).
+template <bool NT, bool PLAIN = false, typename T>
 __device__ __forceinline__ void put(T *p, const T &x)
 {
     static_assert(sizeof(T) == 2 || sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16);
@@ -182,6 +182,8 @@ __device__ __forceinline__ void put(T *p, const T &x)
     using Bits = std::conditional_t<sizeof(T) == 2, uint16_t, std::conditional_t<sizeof(T) == 4, uint32_t, std::conditional_t<sizeof(T) == 8, v2, v4>>>;
     if constexpr (NT)
         __builtin_nontemporal_store(__builtin_bit_cast(Bits, x), reinterpret_cast<Bits *>(p));
+    else if constexpr (PLAIN)
+        *reinterpret_cast<Bits *>(p) = __builtin_bit_cast(Bits, x);
     else if constexpr (sizeof(T) == 16)   // (the widest that there is an atomic store of is 8 bytes)
         asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(__builtin_bit_cast(v4, x)) : "memory");
     else if constexpr (sizeof(T) == 8)
@@ -191,13 +193,15 @@ __device__ __forceinline__ void put(T *p, const T &x)
 }
 // 16 bytes at a scalar address and the lane's offset (a register to a store's address, not two: with two the fold of fp32 inputs and
 // 64-record windows spilled 4, and 8 steps of 8 requests took 45.3 us instead of 45.0).
-template <bool NT>
+template <bool NT, bool PLAIN = false>
 __device__ __forceinline__ void put_at(float *base, uint32_t lane_at, const float4 &x)
 {
     typedef float v4f __attribute__((ext_vector_type(4)));
     const v4f v = {x.x, x.y, x.z, x.w};
     if constexpr (NT)
         __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(reinterpret_cast<char *>(base) + lane_at));
+    else if constexpr (PLAIN)
+        *reinterpret_cast<v4f *>(reinterpret_cast<char *>(base) + lane_at) = v;
     else
         asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 0" ::"v"(lane_at), "v"(v), "s"(base) : "memory");
 }
@@ -218,15 +222,15 @@ __device__ __forceinline__ void store2_nt(T *p, float x, float y)
     static_assert(sizeof(T) == 2, "a 16-bit storage type");
     __builtin_nontemporal_store(pack_pair<T>(x, y), reinterpret_cast<uint32_t *>(p));
 }
-template <bool NT = false>
-__device__ __forceinline__ void store4(float *p, const float4 &v) { put<NT>(reinterpret_cast<float4 *>(p), v); }
+template <bool NT = false, bool PLAIN = false>
+__device__ __forceinline__ void store4(float *p, const float4 &v) { put<NT, PLAIN>(reinterpret_cast<float4 *>(p), v); }
 template <bool NT = false, typename T>
 __device__ __forceinline__ void store4(T *p, const float4 &v)
 {
     put<NT>(reinterpret_cast<uint2 *>(p), make_uint2(pack_pair<T>(v.x, v.y), pack_pair<T>(v.z, v.w)));
 }
-template <bool NT = false, typename T>
-__device__ __forceinline__ void store1(T *p, float x) { put<NT>(p, from_f32<T>(x)); }
+template <bool NT = false, bool PLAIN = false, typename T>
+__device__ __forceinline__ void store1(T *p, float x) { put<NT, PLAIN>(p, from_f32<T>(x)); }
 
 // The output array has a run-time element type (KVB_F32 or the 16-bit input type TIn): the
 // stores sit at the end of every kernel, where a uniform branch costs nothing.
@@ -234,13 +238,13 @@ template <typename TIn>
 struct Out {
     void *p;
     bool wide;   // fp32 elements
-    template <bool NT = false>
+    template <bool NT = false, bool PLAIN = false>
     __device__ __forceinline__ void put1(size_t i, float x) const
     {
         if (sizeof(TIn) == 4 || wide)
-            store1<NT>(static_cast<float *>(p) + i, x);
+            store1<NT, PLAIN>(static_cast<float *>(p) + i, x);
         else
-            store1<NT>(static_cast<TIn *>(p) + i, x);
+            store1<NT, PLAIN>(static_cast<TIn *>(p) + i, x);
     }
     __device__ __forceinline__ void put2(size_t i, float x, float y) const
     {
@@ -439,16 +443,16 @@ __device__ __forceinline__ void publish_fill(int32_t *word, int nwg, int new_fil
         publish_if_last(word, ticket, nwg, new_fill);
 }
 
-template <bool NT = false>
+template <bool NT = false, bool PLAIN = false>
 __device__ __forceinline__ void store_raw8(float *p, const Raw8<float> &r)
 {
-    store4<NT>(p, r.a);
-    store4<NT>(p + 4, r.b);
+    store4<NT, PLAIN>(p, r.a);
+    store4<NT, PLAIN>(p + 4, r.b);
 }
-template <bool NT = false, typename T>
+template <bool NT = false, bool PLAIN = false, typename T>
 __device__ __forceinline__ void store_raw8(T *p, const Raw8<T> &r)
 {
-    put<NT>(reinterpret_cast<uint4 *>(p), r.w);
+    put<NT, PLAIN>(reinterpret_cast<uint4 *>(p), r.w);
 }
 
 // x / d for a scalar d > 0, x >= 0.  The division stands ahead of the load of slot[b], the head of every dependent chain;

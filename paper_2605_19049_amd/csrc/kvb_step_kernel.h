@@ -401,24 +401,40 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
 
     // ---- 6. finish the new row, write results --------------------------------
     float u_new = 0.0f;
-    if (tid < D) {
-        float au = 0.0f, ao = 0.0f;
+    auto write_row = [&](auto plain) __attribute__((always_inline)) {
+        constexpr bool PLAIN = decltype(plain)::value;
+        if (tid < D) {
+            float au = 0.0f, ao = 0.0f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            au += red[w][0][tid];
-            ao += red[w][1][tid];
+            for (int w = 0; w < NW; ++w) {
+                au += red[w][0][tid];
+                ao += red[w][1][tid];
+            }
+            // the record as it is stored is what every later use reads, this token's output included
+            const TRec ur_new = from_f32<TRec>(bet * (to_f32(v_raw) + au));
+            u_new = to_f32(ur_new);
+            ao = fmaf(cQ[f], u_new, ao);
+            out.template put1<STREAM, PLAIN>(((size_t)b * a.Hv + h) * D + tid, a.scale * ao);
+            put<STREAM, PLAIN>(urec.at(f, tid), ur_new);
         }
-        // the record as it is stored is what every later use reads, this token's output included
-        const TRec ur_new = from_f32<TRec>(bet * (to_f32(v_raw) + au));
-        u_new = to_f32(ur_new);
-        ao = fmaf(cQ[f], u_new, ao);
-        out.template put1<STREAM>(((size_t)b * a.Hv + h) * D + tid, a.scale * ao);
-        put<STREAM>(urec.at(f, tid), ur_new);
+        if (tid == 0)
+            put<STREAM, PLAIN>(Grec.at(f, 0), Gc);
+        if (h == hk * r && tid < D / 8)   // the threads that loaded the new k row store it
+            store_raw8<STREAM, PLAIN>(krec.at(f, 8 * sub), k_raw);
+    };
+    // Where at least every fourth step folds (threshold up to 4; 1 is recurrent decoding), what a step leaves is read back by the
+    // next few, mostly on the same XCD, and stays in its L2; with fewer folds it goes through to memory.  us a step, plain /
+    // through, with a plain state: threshold 1, 128 requests of 32 heads 81.9 / 86.6, one 5.14 / 5.35; threshold 2, 128
+    // requests 59.8 / 60.9.  By the workgroup's own fold instead of the threshold: 83.0 at threshold 1, and 16 steps of 13
+    // requests of 8 heads with 32 fp16 records 78.8 instead of 78.0.
+    if constexpr (FUSE && !STREAM) {
+        if (a.threshold <= 4)
+            write_row(std::true_type{});
+        else
+            write_row(std::false_type{});
+    } else {
+        write_row(std::false_type{});
     }
-    if (tid == 0)
-        put<STREAM>(Grec.at(f, 0), Gc);
-    if (h == hk * r && tid < D / 8)   // the threads that loaded the new k row store it
-        store_raw8<STREAM>(krec.at(f, 8 * sub), k_raw);
     const int m = f + 1;
     if (overdue)
         publish_fill(a.st.fill_of(s), a.Hv, 0);
@@ -701,8 +717,10 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
             float *sw = a.st.state + unit * D * D;
             const uint32_t lane_at = (uint32_t)(rg * LPR + c4) * 16;
 #pragma unroll
-            for (int p = 0; p < NPASS; ++p)   // (a state that is streamed in is streamed out again: +1 % on 1 GiB of state)
-                put_at<STREAM>(sw + RPP * p * D, lane_at, sreg[p]);
+            for (int p = 0; p < NPASS; ++p)   // (a state that is streamed in is streamed out again: +1 % on 1 GiB of state;
+                                              // otherwise it stays in the L2: threshold 1, through / plain, us a step: 16
+                                              // requests 11.8 / 10.1, one 5.73 / 5.29; 64, with the rest through, 40.7 / 41.4)
+                put_at<STREAM, true>(sw + RPP * p * D, lane_at, sreg[p]);
         }
     }
 }
