@@ -184,8 +184,10 @@ __device__ __forceinline__ void put(T *p, const T &x)
         __builtin_nontemporal_store(__builtin_bit_cast(Bits, x), reinterpret_cast<Bits *>(p));
     else if constexpr (PLAIN)
         *reinterpret_cast<Bits *>(p) = __builtin_bit_cast(Bits, x);
-    else if constexpr (sizeof(T) == 16)   // (the widest that there is an atomic store of is 8 bytes)
-        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(__builtin_bit_cast(v4, x)) : "memory");
+    else if constexpr (sizeof(T) == 16)
+        // (the widest that there is an atomic store of is 8 bytes.  The compiler does not look inside: for two wait states no
+        // vector instruction may overwrite the data of a store of more than 8 bytes, and it places them behind its own stores only)
+        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(__builtin_bit_cast(v4, x)) : "memory");
     else if constexpr (sizeof(T) == 8)
         __hip_atomic_store(reinterpret_cast<uint64_t *>(p), __builtin_bit_cast(uint64_t, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else
@@ -203,7 +205,7 @@ __device__ __forceinline__ void put_at(float *base, uint32_t lane_at, const floa
     else if constexpr (PLAIN)
         *reinterpret_cast<v4f *>(reinterpret_cast<char *>(base) + lane_at) = v;
     else
-        asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 0" ::"v"(lane_at), "v"(v), "s"(base) : "memory");
+        asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 1" ::"v"(lane_at), "v"(v), "s"(base) : "memory");
 }
 // The same of already-rounded or to-be-rounded values into an array of type T.
 template <bool NT = false>

@@ -154,6 +154,54 @@ def early_reads(ins, adr):
     return sorted(bad)
 
 
+@functools.lru_cache(None)
+def store_data(x):
+    """Mask of the data registers of a store of more than 8 bytes, or 0."""
+    op, _, rest = x.partition(" ")
+    if not re.match(r"(global|flat|scratch|buffer)_store_\w*x[34]$", op):
+        return 0
+    ops = rest.split(", ")
+    return regs(ops[0] if op.startswith("buffer") else ops[1])
+
+
+@functools.lru_cache(None)
+def written(x):
+    """Mask of the vector registers that a vector instruction writes (a load's come from elsewhere)."""
+    op, _, rest = x.partition(" ")
+    if not op.startswith("v_"):
+        return 0
+    ops = rest.split(", ")
+    return regs(", ".join(ops[:2]) if "swap" in op else ops[0])
+
+
+STORE_WAIT = 2   # wait states for which the data registers of a store of more than 8 bytes stay as they are
+
+
+def early_overwrites(ins, adr):
+    """Vector instructions that some path lets overwrite the data of a store of more than 8 bytes before it has been read."""
+    bl = blocks(ins, adr)
+    state, bad, todo = {0: frozenset()}, set(), [0]
+    while todo:
+        n = todo.pop()
+        first, end, succ = bl[n]
+        pending = dict(state[n])   # data mask -> wait states still needed
+        for i in range(first, end):
+            if any(written(ins[i]) & m for m in pending):
+                bad.add((i, ins[i]))
+            slots = int(ins[i].split()[1], 0) + 1 if ins[i].startswith("s_nop") else 1
+            pending = {m: w - slots for m, w in pending.items() if w > slots}
+            if store_data(ins[i]):
+                pending[store_data(ins[i])] = STORE_WAIT
+        for s in succ:
+            new = dict(state.get(s, ()))
+            for m, w in pending.items():
+                new[m] = max(w, new.get(m, 0))
+            if s not in state or new != dict(state[s]):
+                state[s] = frozenset(new.items())
+                todo.append(s)
+    return sorted(bad)
+
+
 def spills(path):
     """Vector registers that each kernel spills, from the code object's metadata."""
     notes = subprocess.run([READELF, "--notes", path], check=True, stdout=subprocess.PIPE, text=True).stdout
@@ -178,7 +226,8 @@ def scan(path):
     for name, ins, adr in kernels(path):
         res.append((name, len(ins), any(x.startswith("global_atomic_add") for x in ins), unordered_tickets(ins, adr),
                     early_reads(ins, adr), spilled[name],
-                    waits_at_the_exit(ins, adr, 64) if "kvb_buffer_step_kernelILi128E" in name else None))
+                    waits_at_the_exit(ins, adr, 64) if "kvb_buffer_step_kernelILi128E" in name else None,
+                    early_overwrites(ins, adr), sum(1 for x in ins if store_data(x))))
     return res
 
 
@@ -204,6 +253,27 @@ def test_matrix_results_are_waited_for(scanned):
     """No path reads the result of a matrix instruction before the wait states it needs."""
     bad = [(r[0], r[4][:3]) for r in scanned if r[4]]
     assert not bad, "%d kernels, e.g. %s" % (len(bad), bad[:2])
+
+
+def test_store_data_stays(scanned):
+    """No path overwrites the data of a store of more than 8 bytes before the wait states it needs, stores written by hand
+    (behind which the compiler places none) among them."""
+    assert sum(r[8] for r in scanned) > 1000
+    bad = [(r[0], r[7][:3]) for r in scanned if r[7]]
+    assert not bad, "%d kernels, e.g. %s" % (len(bad), bad[:2])
+
+
+@pytest.mark.parametrize("ins, found", [
+    (["global_store_dwordx4 v[18:19], v[14:17], off sc1", "s_nop 0", "v_lshl_add_u64 v[14:15], v[0:1], 0, v[2:3]"], 1),
+    (["global_store_dwordx4 v[18:19], v[14:17], off sc1", "s_nop 1", "v_lshl_add_u64 v[14:15], v[0:1], 0, v[2:3]"], 0),
+    (["global_store_dwordx3 v18, v[14:16], s[0:1]", "v_mov_b32_e32 v16, 0"], 1),
+    (["global_store_dwordx2 v[18:19], v[14:15], off sc1", "v_mov_b32_e32 v14, 0"], 0),
+    (["global_store_dwordx4 v[18:19], v[14:17], off", "v_mov_b32_e32 v18, 0", "v_mov_b32_e32 v1, v14"], 0),   # addresses, reads
+    (["buffer_store_dwordx4 v[4:7], v1, s[0:3], 0 offen", "s_nop 0", "v_swap_b32 v9, v7"], 1),
+    (["global_store_dwordx4 v[18:19], v[14:17], off", "s_branch -> 12", "s_nop 0", "v_mov_b32_e32 v17, 0"], 1)])   # over a jump
+def test_store_data_check(ins, found):
+    adr = [4 * i for i in range(len(ins))]
+    assert len(early_overwrites(ins + ["s_endpgm"], adr + [4 * len(ins)])) == found
 
 
 # (pattern of the mangled name, registers): kernels held at three workgroups a CU that spill after all
