@@ -104,9 +104,8 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
     constexpr int EPT = LT * D / NT;
     // the fused state update runs on the matrix cores (see fold_tile)
     constexpr bool MFOLD = FUSE && D == 128 && sizeof(TIn) == 2;
-    constexpr bool F16 = __is_same(TRec, f16_t);                  // fp16 pieces (a fp16 record is in range however it is weighted), else bf16
-    constexpr int KPC = __is_same(TIn, f16_t) && !F16 ? 2 : 1;   // pieces of a key
-    constexpr int UPC = F16 ? 2 : 3;                             // of a weighted delta value
+    constexpr int KPC = __is_same(TIn, f16_t) ? 2 : 1;   // bf16 pieces of a key
+    constexpr int UPC = 3;                               // bf16 pieces of a weighted delta value
     constexpr int FS = 24;                               // halves per staged row: 16 records + padding (16-byte reads)
     // state loads issued before the fill is known (the 64-record window keeps the records first:
     // holding it across the state pass costs a workgroup per CU)
@@ -453,11 +452,9 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
                 // in which some request folds.  13 requests of 8 heads, C = 32, fp16, 16 steps: 120 -> 99 us;
                 // 64 of 32 heads, C = 16, bf16: 483 -> 475 us; 1 of 32: 76.1 -> 74.9 us.  (500 of 32 at C = 64:
                 // the same 1072 us, its launches wait for memory.)
-                // fp16 records are in the range of fp16 however they are weighted, so there (as in kvb_flush) Gamma u is two fp16
-                // pieces, 22 bits, a rest below 6e-8 dropped, and a fp16 key is its own: two products a tile instead of six.  The
-                // states' errors against 64 bits are the same to five digits at buffers of 8 to 128 records (1.7e-4 to 2.0e-4, the
-                // records' own).  13 requests of 8 heads, 16 steps, C = 32 85.6 -> 78.6 us, C = 16 80.3 -> 76.1; 20 of 32, 8 steps,
-                // C = 32 83.3 -> 79.6.
+                // (With fp16 records two fp16 pieces of Gamma u and a key as it is, two products instead of six, took 78.6 us for the
+                // first of these instead of 85.6, but what lies below 6e-8 is lost: of values of 1e-4 half the bits.  Scaling the
+                // columns first takes the maximum over all waves and 64 products a lane, as much as it saves.)
                 // Pieces of an infinity are NaN: a wave whose result is not finite folds again on the vector ALU.
                 // The records of a tile go to contraction slots 2 (r % 8) + r / 8, so that the two a thread
                 // stages share a word.
@@ -484,10 +481,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
                             const float x = l < f ? kf[e] : l == f ? k8[e] : 0.0f;
                             const int row = 32 * (e / 2) + 8 * (sub / 4) + 4 * (e % 2) + sub % 4;
                             const uint32_t top = __float_as_uint(x) & 0xFFFF0000u;
-                            if constexpr (F16)
-                                kT[0][row][at] = from_f32<f16_t>(x).bits;   // (exact)
-                            else
-                                kT[0][row][at] = (uint16_t)(top >> 16);
+                            kT[0][row][at] = (uint16_t)(top >> 16);
                             if constexpr (KPC == 2)
                                 kT[KPC - 1][row][at] = (uint16_t)(__float_as_uint(x - __uint_as_float(top)) >> 16);
                         }
@@ -501,14 +495,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
                             float ra = la < f ? wa * xa[e] : la == f ? nw : 0.0f;
                             float rb = lb8 < f ? wb * xb[e] : lb8 == f ? nw : 0.0f;
 #pragma unroll
-                            for (int q = 0; q < UPC; ++q) {   // the leading 8 bits of what is left (fp16: 11, rounded); the rest is exact
-                                if constexpr (F16) {
-                                    const f16_t ha = from_f32<f16_t>(ra), hb = from_f32<f16_t>(rb);
-                                    *reinterpret_cast<uint32_t *>(&uT[q][32 * e + c4][2 * rg]) = (uint32_t)ha.bits | (uint32_t)hb.bits << 16;
-                                    ra -= to_f32(ha);
-                                    rb -= to_f32(hb);
-                                    continue;
-                                }
+                            for (int q = 0; q < UPC; ++q) {   // the leading 8 bits of what is left; the rest is exact
                                 const uint32_t ta = __float_as_uint(ra) & 0xFFFF0000u, tb = __float_as_uint(rb) & 0xFFFF0000u;
                                 *reinterpret_cast<uint32_t *>(&uT[q][32 * e + c4][2 * rg]) = (ta >> 16) | tb;
                                 ra -= __uint_as_float(ta);
@@ -517,22 +504,18 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
                         }
                     }
                     __syncthreads();
-                    uint4 ka[KPC];
+                    bf16x8_t ka[KPC];
 #pragma unroll
                     for (int x = 0; x < KPC; ++x)
-                        ka[x] = *reinterpret_cast<const uint4 *>(&kT[x][32 * wv + lane % 32][8 * (lane / 32)]);
+                        ka[x] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(&kT[x][32 * wv + lane % 32][8 * (lane / 32)]));
 #pragma unroll
                     for (int q = UPC - 1; q >= 0; --q)   // smallest pieces first
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const uint4 ub8 = *reinterpret_cast<const uint4 *>(&uT[q][32 * e + lane % 32][8 * (lane / 32)]);
+                            const bf16x8_t ub8 = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(&uT[q][32 * e + lane % 32][8 * (lane / 32)]));
 #pragma unroll
-                            for (int x = KPC - 1; x >= 0; --x) {
-                                if constexpr (F16)
-                                    acc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, ka[x]), __builtin_bit_cast(f16x8_t, ub8), acc[e], 0, 0, 0);
-                                else
-                                    acc[e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka[x]), __builtin_bit_cast(bf16x8_t, ub8), acc[e], 0, 0, 0);
-                            }
+                            for (int x = KPC - 1; x >= 0; --x)
+                                acc[e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[x], ub8, acc[e], 0, 0, 0);
                         }
                 };
                 if constexpr (WREC <= 32) {   // the whole buffer is in registers: a key pass is one tile, two passes of u fill it

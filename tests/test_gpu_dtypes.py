@@ -96,6 +96,36 @@ def test_fp16_flush_split_is_exact_to_fp32_rounding():
         assert excess.max() <= 0.0
 
 
+@pytest.mark.parametrize("in_dtype, rec_dtype", [("f16", "f16"), ("bf16", "bf16"), ("f16", "f32"), ("bf16", "f32")])
+@pytest.mark.parametrize("C, last_g", [(16, -0.25), (17, -12.0), (32, -12.0), (64, -0.25)])
+def test_fused_fold_keeps_24_bits_of_small_values(in_dtype, rec_dtype, C, last_g):
+    """The fold inside kvb_decode_flush at value scales of 1 to 1e-6, one to a request, and behind a last token that writes nothing
+    (beta = 0) and decays what the buffer holds: every element against the sum, in 64 bits, over the records as they are stored."""
+    rng = np.random.default_rng(372 + C)
+    scales = np.array([1.0, 1e-2, 1e-3, 1e-4, 1e-6])
+    B, Hk, Hv, d = len(scales), 1, 2, 128
+    tok = synth.token_stream(rng, B, C, Hk, Hv, d, d, in_dtype)
+    tok["v"] = H.host(H.dev((tok["v"] * scales[:, None, None, None]).astype(np.float32), in_dtype))
+    tok["g"][:, :-1] *= 0.25
+    tok["g"][:, -1], tok["beta"][:, -1] = last_g, 0.0
+    lay = H.Layer(B, Hk, Hv, d, d, cap=C, in_dtype=in_dtype, rec_dtype=rec_dtype)
+    _, _, S, fills = H.run_decode(lay, np.zeros((B, Hv, d, d), np.float32), tok, C, final_flush=False, fused=True)
+    assert fills[-1] == 0
+    worst = []
+    for b in range(B):
+        k, u, G = (H.host(x).astype(np.float64) for x in lay.ds.records(b, 0, C))
+        x = G[:, -1:] - G
+        uw = np.exp(x)[..., None] * u
+        ref, size = np.einsum("lk,hlv->hkv", k[0], uw), np.einsum("lk,hlv->hkv", np.abs(k[0]), np.abs(uw))
+        # In units of 2^-24 of the sum of magnitudes: the difference of the decays (|x| / 2 of the weight), its exponential (2),
+        # the product (1/2), C + 1 terms added, a term and a sum rounded or cut each time (2 (C + 1)).  Two pieces instead of
+        # three leave up to 2^-16 of a term, 256 such units; two fp16 pieces 2^-25, which of values of 1e-4 is 5000.
+        bound = (0.5 * np.abs(x).max() + 2.5 + 2 * (C + 1)) * 2.0 ** -24
+        worst.append((np.abs(S[b] - ref) / np.maximum(size, 1e-300)).max() / bound)
+    say("fused fold, %s/%s C=%d g=%g: error over bound by scale %s" % (in_dtype, rec_dtype, C, last_g, " ".join("%.3f" % w for w in worst)))
+    assert max(worst) < 1.0, worst
+
+
 # --------------------------------------------------------------------------- 16-bit records
 @pytest.mark.parametrize("in_dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("d, B, Hk, Hv, C, steps, fused", [

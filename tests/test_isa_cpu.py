@@ -104,7 +104,7 @@ def mfma_wait(op):
     """Wait states between a matrix instruction and a read of its result: its passes of 4 cycles and 2 (fp32), or 4
     (16-bit types)."""
     return {"v_mfma_f32_16x16x4_f32": 8 + 2, "v_mfma_f32_16x16x32_bf16": 4 + 4, "v_mfma_f32_16x16x32_f16": 4 + 4,
-            "v_mfma_f32_32x32x16_bf16": 8 + 4, "v_mfma_f32_32x32x16_f16": 8 + 4}[op]
+            "v_mfma_f32_32x32x16_bf16": 8 + 4}[op]
 
 
 @functools.lru_cache(None)
