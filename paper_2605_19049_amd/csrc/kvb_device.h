@@ -516,15 +516,38 @@ __host__ __device__ inline int dealt_unit(int x, int deal)
 // rounds of 8 qk-heads, or XCD x works on one contiguous eighth, so that what the heads of a request read in common is in one L2,
 // or unit = workgroup id.  In one word, steps and a power of two, without a branch ahead of the load of the slot: workgroup
 // x = 8 j + c takes c * (the upper 27 bits) + 8 (j & -run) + (j & run - 1), run = 1 << the lower 5 bits.
-// Dealt, the requests that fold (and write their states back) are no XCD's alone.  (With the fill words of 32 slots to a line it
-// was slower, since a line's additions then came from all XCDs.)  Eighths / dealt, us: kvb_decode_flush, 16 steps of 64 requests of
+// Dealt, the requests that fold (and write their states back) are no XCD's alone.  Eighths / dealt, with a
+// line to each fill word, us: kvb_decode_flush, 16 steps of 64 requests of
 // 32 heads 436 / 397, 4 of 500 935 / 917, 8 of 24 96.4 / 92.4, of 16 67.1 / 62.7, of 32 of 16 69.8 / 67.4; below 512 units it
 // depends on where the states lie, 8 steps of 12 of 32 heads 52.0 / 50.0, of 20 of 16 53.2 / 52.9 or 63.2, of 60 of 8 60.9 / 64.4.
 // kvb_decode without a state, 128 requests 424 / 417, 24 99.7 / 103, 60 of 16 heads 48.2 / 49.0.  kvb_verify and commit, both alike
 // (one dealt and the other not is 1 to 6 % slower than either): 128 requests 88.6 / 83.6, 300 182 / 173, 60 of 16 heads 32.7 / 31.7,
 // 24 of 32 23.8 / 23.3, 24 of 16 18.5 / 18.5, 40 of 8 19.7 / 20.2.  The fold after kvb_direct, which deals at any size, of 10 contexts
 // 28.9 / 27.9, of 100 126 / 124.
+// Packed fill words (32 slots to a line): dealt, the additions to a line come from all XCDs, and at d = 128 that is the better way below
+// 1536 units all the same (PACKED_END), and above them in kvb_decode_flush.  Before units were dealt and results sent through / eighths / dealt, us,
+// means of three or four placements: kvb_decode_flush, 8 steps of 16 requests of 32 heads 93 / 90 / 82, 24 116 / 120 / 105, 32 134 / 142 /
+// 137, 128 414 / 415 / 407, 256 827 / 831 / 826, 16 of 64 446 / 456 / 446; kvb_decode, 8 steps of 24 109 / 121 / 105, 64 221 / 217 / 236, 128
+// 401 / 400 / 411; kvb_direct and fold of 24 53 / 52 / 48.5, 128 174 / 172 / 174; threshold 1, 24 277 / 300 / 264, 64 634 / 640 / 676.
+// Not dealt at d = 64 (kvb_decode_flush, 60 requests 124 / 121 / 131, 200 210 / 211 / 254), for kvb_verify and commit (24 requests 32.5 / 31.2 / 31.6,
+// 48 46.9 / 43.8 / 46.1, 128 87.3 / 86.3 / 87.9, 300 188 / 189 / 184) and kvb_decode without a state (128 requests 21.3 / 21.0 / 22.4).
 constexpr int DEAL_STEP = 512, DEAL_BUFFER_STEP = 1024, DEAL_SPEC = 512;   // the least units (workgroups) to deal
+constexpr int PACKED_END = 1536, NO_DEALING = 0x7FFFFFFF;
+// From how many units on kvb_step_kernel deals, with n of them (threshold: 0 where it does not fold; apart: a line to each fill word)
+inline int step_deals_from(int d, int n, int threshold, bool apart)
+{
+    if (!apart)
+        return d == 128 && (n < PACKED_END || threshold > 0) ? DEAL_STEP : NO_DEALING;
+    return DEAL_STEP;
+}
+// the same for kvb_flush (commits: of accepted drafts), and for the others
+inline int fold_deals_from(int d, int n, bool commits, bool apart)
+{
+    if (!apart)
+        return d == 128 && n < PACKED_END && !commits ? DEAL_STEP : NO_DEALING;
+    return commits ? DEAL_SPEC : 0;
+}
+inline int deals_from(int least, bool apart) { return apart ? least : NO_DEALING; }
 inline int unit_deal(int n, int r, int least)
 {
     const bool small = n < 1 << 29;
@@ -607,6 +630,7 @@ struct Store {
     int32_t max_blocks;           // row length of block_table (1 when not paged)
     int32_t n_blocks;             // blocks in the pools; ids are clamped into 0..n_blocks-1
     int32_t fill_lg;              // the fill of slot s is word s << fill_lg (0, or 5 with KVB_STORE_FILL_APART)
+    bool apart() const { return fill_lg != 0; }   // (on the host)
     // (of one workgroup's slot: a word that the request's other workgroups may be adding to)
     __device__ __forceinline__ int32_t *fill_of(int s) const { return fill + ((size_t)s << fill_lg); }
 };
@@ -848,16 +872,19 @@ int dispatch(int dk, int in_dtype, int rec_dtype, F &&f)
     });
 }
 
-// v-heads of a workgroup of kvb_buffer_step_kernel (the measurements stand there); blocks: B * Hv, wide: fp32 inputs.
-inline int buffer_step_heads(int d, bool wide, int Hk, int Hv, int cap, int blocks)
+// v-heads of a workgroup of kvb_buffer_step_kernel (the measurements stand there); blocks: B * Hv, wide: fp32 inputs,
+// apart: a line to each fill word.
+inline int buffer_step_heads(int d, bool wide, int Hk, int Hv, int cap, int blocks, bool apart)
 {
+    if (!apart)
+        return Hv > Hk && blocks >= (d == 128 ? 256 : 96) ? 2 : 1;
     const bool one = d == 128 && wide && cap > 64 && Hv <= MAX_FILL_WG;
     return Hv > Hk && blocks >= 320 && !one ? 2 : 1;
 }
 // Workgroups that add to a request's fill word when a token is appended.
 inline int step_workgroups(const StepArgs &a, int d, bool wide, int blocks)
 {
-    const int hb = a.st.state ? 1 : buffer_step_heads(d, wide, a.Hk, a.Hv, a.cap, blocks);
+    const int hb = a.st.state ? 1 : buffer_step_heads(d, wide, a.Hk, a.Hv, a.cap, blocks, a.st.apart());
     return a.Hk * ((a.r + hb - 1) / hb);
 }
 

@@ -742,6 +742,9 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
 // The line: 320 units (12 contexts of 32 heads, d = 128, bf16, up to 48 tokens and 16 steps, 384 units, 90.1 / 86.7 a pass; 8
 // contexts, fp16, 72.6 / 79.3).  fp32 inputs at d = 128 keep one head unless the buffers are short (cap <= 64: 100 contexts of up to
 // 40 tokens, 8 steps, 187.6 / 184.7), or one head has more workgroups a request than a fill word counts.
+// Packed fill words (32 slots to a line): two heads also halve the additions that queue for a line, and win earlier, from 256
+// units on at d = 128 and 96 below, with fp32 inputs too.  One / two: 8 requests of 32 heads, up to 48 records, d = 128, bf16 6.2 / 5.3,
+// fp32, cap 128, 6.8 / 5.8; 6 of d = 64 5.9 / 5.1; 128 of up to 108 records, fp32 33.5 / 30.5; 13 of 8 heads, d = 128, 4.9 / 5.6.
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, int HB, bool PAGED>
 __global__ __launch_bounds__(NT) void kvb_buffer_step_kernel(const int32_t *slot_arg, int32_t nu_arg, int32_t deal_arg,
@@ -972,7 +975,7 @@ void launch_step_s(const StepArgs &a, int blocks, hipStream_t stream)
 {
     // (a branch inside the kernel around the state loads would make the compiler's wait
     // counters conservative at the join, so these are compile-time variants)
-    const int deal = unit_deal(blocks, a.r, DEAL_STEP);
+    const int deal = unit_deal(blocks, a.r, step_deals_from(D, blocks, a.threshold, a.st.apart()));
     const bool st = a.stream_state != 0 && D == 128;   // the small head sizes are not tuned: no streaming variant
     if (a.threshold > 0) {
         if constexpr (D == 128) {
@@ -997,7 +1000,7 @@ template <int D, typename TIn, typename TRec, int HB>
 void launch_buffer_step_h(const StepArgs &a, int B, hipStream_t stream)
 {
     const int32_t per = (a.r + HB - 1) / HB, nu = a.Hk * per;   // workgroups of a key head and of a request
-    const int deal = unit_deal(B * nu, per, DEAL_BUFFER_STEP);
+    const int deal = unit_deal(B * nu, per, deals_from(DEAL_BUFFER_STEP, a.st.apart()));
     if (a.st.block_table)
         launch(kvb_buffer_step_kernel<D, TIn, TRec, HB, true>, B * nu, stream, a.slot, nu, deal, a);
     else
@@ -1008,7 +1011,7 @@ template <int D, typename TIn, typename TRec>
 void launch_buffer_step(const StepArgs &a, int blocks, hipStream_t stream)
 {
     const int B = blocks / a.Hv;
-    if (buffer_step_heads(D, sizeof(TIn) == 4, a.Hk, a.Hv, a.cap, blocks) == 2)
+    if (buffer_step_heads(D, sizeof(TIn) == 4, a.Hk, a.Hv, a.cap, blocks, a.st.apart()) == 2)
         launch_buffer_step_h<D, TIn, TRec, 2>(a, B, stream);
     else
         launch_buffer_step_h<D, TIn, TRec, 1>(a, B, stream);

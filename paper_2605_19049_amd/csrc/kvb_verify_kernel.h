@@ -596,7 +596,7 @@ void kvb_verify_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t dea
 template <int D, typename TIn, typename TRec, int WREC>
 void launch_verify_w(const StepArgs &a, int blocks, hipStream_t stream)
 {
-    const int deal = unit_deal(blocks, a.r, DEAL_SPEC);
+    const int deal = unit_deal(blocks, a.r, deals_from(DEAL_SPEC, a.st.apart()));
     if (!a.st.state) {
         LAUNCH_LEAD(blocks, deal, stream, a, kvb_verify_mfma_kernel<D, TIn, TRec, WREC, false, false);
         return;

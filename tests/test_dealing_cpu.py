@@ -12,6 +12,7 @@ SRC = r"""
 #include "kvb_device.h"
 #include <cstdio>
 #include <cstdlib>
+#include <utility>
 int main(int argc, char **argv)
 {
     if (argc == 1) {   // d, input type, units, longest context of every launch that sorts
@@ -37,6 +38,27 @@ int main(int argc, char **argv)
         const uint32_t word = (uint32_t)kvb_impl::unit_deal(n, atoi(argv[2]), atoi(argv[3]));
         for (int x = 0; x < n; ++x)
             printf("%d\n", kvb_impl::unit_of((uint32_t)x, word));
+        return 0;
+    }
+    if (argc == 3 && atoi(argv[1]) == 0) {   // the rules that look at where the fill words lie
+        if (atoi(argv[2]) == 0) {   // units to deal from: d, units, threshold, apart, of kvb_step_kernel, a fold, a commit, others at 512
+            for (int d : {32, 64, 128})
+                for (int n : {1, 511, 512, 1535, 1536, 100000})
+                    for (int threshold : {0, 1, 2, 3, 16})
+                        for (int apart = 0; apart < 2; ++apart)
+                            printf("%d %d %d %d %d %d %d %d\n", d, n, threshold, apart, kvb_impl::step_deals_from(d, n, threshold, apart),
+                                   kvb_impl::fold_deals_from(d, n, false, apart), kvb_impl::fold_deals_from(d, n, true, apart), kvb_impl::deals_from(512, apart));
+            return 0;
+        }
+        // v-heads of a workgroup of kvb_decode without a state: d, fp32 inputs, heads, cap, requests, apart, answer
+        for (int d : {32, 64, 128})
+            for (int wide = 0; wide < 2; ++wide)
+                for (auto [Hk, Hv] : {std::pair(1, 1), {1, 2}, {4, 4}, {3, 9}, {16, 32}, {1, 32768}, {1, 32769}, {16384, 65536}})
+                    for (int cap : {16, 64, 65, 128})
+                        for (int B : {1, 2, 3, 7, 8, 10, 11, 13, 36, 60, 96, 256, 320, 500})
+                            for (int apart = 0; apart < 2; ++apart)
+                                printf("%d %d %d %d %d %d %d %d\n", d, wide, Hk, Hv, cap, B, apart,
+                                       kvb_impl::buffer_step_heads(d, wide, Hk, Hv, cap, B * Hv, apart));
         return 0;
     }
     const int blocks = atoi(argv[1]), deal = kvb_impl::deal_of(blocks, atoi(argv[2]));
@@ -109,3 +131,32 @@ def test_units_of_shared_fill_words(program, B, Hk, r, least):
         assert np.array_equal(xcd, np.arange(n) // (n // 8))
     else:
         assert np.array_equal(u, np.arange(n))
+
+
+def test_packed_fill_words_deal_where_it_pays(program):
+    """With 32 fill words to a line kvb_verify, commits, kvb_decode without a state and small heads stay in eighths, decoding with
+    a state and folding at d = 128 deal from 512 units on, without a fold in the kernel or behind it up to 1535."""
+    rows = program(0, 0).reshape(-1, 8)
+    assert len(rows) == 3 * 6 * 5 * 2
+    never = 2 ** 31 - 1
+    for d, n, threshold, apart, step, fold, commit, other in rows:
+        if apart:
+            assert (step, fold, commit, other) == (512, 0, 512, 512)
+        else:
+            assert step == (512 if d == 128 and (threshold > 0 or n < 1536) else never)
+            assert fold == (512 if d == 128 and n < 1536 else never) and commit == other == never
+    assert np.array_equal(program(2048, 2, never), np.arange(2048) % 8 * 256 + np.arange(2048) // 8)   # (eighths)
+
+
+def test_heads_of_a_buffer_step(program):
+    """Two v-heads a workgroup by the lines of each layout of the fill words; where one head has more workgroups a request than a
+    word counts (2^15) and two do not, two are taken."""
+    rows = program(0, 1).reshape(-1, 8)
+    assert len(rows) == 3 * 2 * 8 * 4 * 14 * 2
+    for d, wide, Hk, Hv, cap, B, apart, heads in rows:
+        n, grouped = B * Hv, Hv > Hk
+        if not apart:
+            assert heads == (2 if grouped and n >= (256 if d == 128 else 96) else 1)
+        else:
+            assert heads == (2 if grouped and n >= 320 and not (d == 128 and wide and cap > 64 and Hv <= 2 ** 15) else 1)
+        assert Hv <= 2 ** 15 or heads == (2 if grouped else 1)

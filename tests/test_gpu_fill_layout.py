@@ -5,7 +5,9 @@ import pytest
 import torch
 
 import harness as H
+from harness import oracle
 from paper_2605_19049_amd import kvb, synth
+from test_gpu_parity import say
 
 pytestmark = pytest.mark.gpu
 
@@ -74,6 +76,37 @@ def test_fill_words_apart(in_dtype, rec_dtype, d, block_size):
         apart = run(True, in_dtype, rec_dtype, d, block_size, by_address)
         for (name, a), (_, b) in zip(packed, apart):
             assert all(torch.equal(x, y) for x, y in zip(a, b)), name
+
+
+@pytest.mark.parametrize("d, in_dtype, rec_dtype, B", [(64, "bf16", "f32", 18), (32, "f32", "f32", 17), (128, "f32", "f32", 44), (128, "bf16", "f32", 44), (128, "f16", "f16", 90),
+                                                        (64, "bf16", "f32", 90), (64, "f32", "f32", 90)])
+@pytest.mark.parametrize("apart", [False, True])
+def test_launches_that_the_layout_decides(d, in_dtype, rec_dtype, B, apart):
+    """Sizes at which the layouts differ in the v-heads a workgroup takes (kvb_decode without a state, 102 to 264 units) or in how
+    units are dealt (540): a context decoded from the buffer alone, folded, and decoded on with folds, against the recurrence."""
+    rng = np.random.default_rng(61 + B)
+    Hk, Hv, n, C = 2, 6, 6, 4
+    lay = H.Layer(B, Hk, Hv, d, d, 128, in_dtype, scale=d ** -0.5, n_slots=B + 9, slots=rng.permutation(B + 9)[:B], rec_dtype=rec_dtype, out_dtype=rec_dtype)
+    if not apart:
+        lay.ds.fill = torch.zeros(B + 9, dtype=torch.int32, device="cuda")
+    tok = synth.token_stream(rng, B, 2 * n, Hk, Hv, d, d, in_dtype)
+    dtok = H.upload_tokens(tok, in_dtype)
+    out = lay.new_out(B, 2 * n, Hv, d, fill=float("nan"))
+    for t in range(2 * n):
+        o = lay.new_out(B, Hv, d, fill=float("nan"))
+        if t < n:
+            lay.decode(H.step_view(dtok, t), o, use_state=False)
+        else:
+            lay.decode_flush(H.step_view(dtok, t), o, C)
+        if t == n - 1:
+            lay.flush(1)
+        out[:, t] = o
+    torch.cuda.synchronize()
+    assert bool((lay.fill() == n % C).all()) and not lay.status().any() and int(lay.ds.fill.sum()) == B * (n % C)
+    ref, _, _ = oracle.kvb_decode_expected(np.zeros((B, Hv, d, d)), tok["q"], tok["k"], tok["v"], tok["g"], tok["beta"], scale=d ** -0.5)
+    e = H.rel_err(H.host(out), ref, lay.out_unit)
+    say("%s fill words, d=%d %s/%s B=%d: rel err %.2e" % ("apart" if apart else "packed", d, in_dtype, rec_dtype, B, e))
+    H.check([e], in_dtype, rec_dtype, "fill layout")
 
 
 def test_device_store_keeps_a_line_to_each_slot():
