@@ -533,12 +533,18 @@ __host__ __device__ inline int dealt_unit(int x, int deal)
 // 48 46.9 / 43.8 / 46.1, 128 87.3 / 86.3 / 87.9, 300 188 / 189 / 184) and kvb_decode without a state (128 requests 21.3 / 21.0 / 22.4).
 constexpr int DEAL_STEP = 512, DEAL_BUFFER_STEP = 1024, DEAL_SPEC = 512;   // the least units (workgroups) to deal
 constexpr int PACKED_END = 1536, NO_DEALING = 0x7FFFFFFF;
+// Where every step folds, no XCD has less to do, and whole eighths keep what the heads of a request share, and the state from one step to the
+// next, in one L2: at threshold 1, and at 2 of a streamed state, nothing is dealt.  Eighths / dealt, 16 steps of threshold 1: 16 requests of
+// 32 heads 177 / 180 us, 24 269 / 266, 64 629 / 657 (fp16 637 / 657), 128 1300 / 1315; 8 steps of 256 1510 / 1572; 4 of 400 1175 / 1223.
+// Threshold 2: 64 requests 583 / 515, 128 (8 steps) 537 / 509, streamed, 256 1120 / 1140, 400 (4 steps) 873 / 892; threshold 3, streamed, 256
+// 1022 / 1005.  With packed words only from PACKED_END on: 24 requests 300 / 264, 64 640 / 676, 256 1512 / 1580.
 // From how many units on kvb_step_kernel deals, with n of them (threshold: 0 where it does not fold; apart: a line to each fill word)
-inline int step_deals_from(int d, int n, int threshold, bool apart)
+inline int step_deals_from(int d, int n, int threshold, bool stream, bool apart)
 {
+    const bool level = threshold > 0 && threshold <= (stream ? 2 : 1);
     if (!apart)
-        return d == 128 && (n < PACKED_END || threshold > 0) ? DEAL_STEP : NO_DEALING;
-    return DEAL_STEP;
+        return d == 128 && (n < PACKED_END || (threshold > 0 && !level)) ? DEAL_STEP : NO_DEALING;
+    return level ? NO_DEALING : DEAL_STEP;
 }
 // the same for kvb_flush (commits: of accepted drafts), and for the others
 inline int fold_deals_from(int d, int n, bool commits, bool apart)
