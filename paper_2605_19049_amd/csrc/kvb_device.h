@@ -538,13 +538,20 @@ constexpr int PACKED_END = 1536, NO_DEALING = 0x7FFFFFFF;
 // 32 heads 177 / 180 us, 24 269 / 266, 64 629 / 657 (fp16 637 / 657), 128 1300 / 1315; 8 steps of 256 1510 / 1572; 4 of 400 1175 / 1223.
 // Threshold 2: 64 requests 583 / 515, 128 (8 steps) 537 / 509, streamed, 256 1120 / 1140, 400 (4 steps) 873 / 892; threshold 3, streamed, 256
 // 1022 / 1005.  With packed words only from PACKED_END on: 24 requests 300 / 264, 64 640 / 676, 256 1512 / 1580.
-// From how many units on kvb_step_kernel deals, with n of them (threshold: 0 where it does not fold; apart: a line to each fill word)
-inline int step_deals_from(int d, int n, int threshold, bool stream, bool apart)
+// kvb_flush without accepted drafts comes behind kvb_direct, which deals at any size, or behind kvb_decode.  The two are alike, or a fold
+// has its state and records in other L2s than its decode: so kvb_decode deals at any size as well.  kvb_decode in eighths and the fold dealt /
+// both in eighths / both dealt, 16 steps of kvb_decode and kvb_flush: C = 16, 4 requests of 32 heads 102.9 / 98.6 / 99.4, 8 124 / 117 / 114, 15
+// 159 / 151 / 156; C = 1, 4 requests 169 / 137 / 144, 8 233 / 164 / 181, 15 393 / 242 / 265 (before all this 175, 240, 315); kvb_direct and the
+// fold, 10 contexts dealt / the fold in eighths 31.8 / 36.1, 15 36.3 / 40.3.  kvb_decode alone, 8 steps of 4 requests, eighths / dealt 39.7 /
+// 38.8, 8 39.2 / 39.6 to 44.8 with where the states lie, 15 61.6 / 58.2.
+// From how many units on kvb_step_kernel deals, with n of them (threshold: 0 where it does not fold; appends: not for kvb_verify of one
+// draft, which goes with its commit; apart: a line to each fill word)
+inline int step_deals_from(int d, int n, int threshold, bool stream, bool appends, bool apart)
 {
     const bool level = threshold > 0 && threshold <= (stream ? 2 : 1);
     if (!apart)
         return d == 128 && (n < PACKED_END || (threshold > 0 && !level)) ? DEAL_STEP : NO_DEALING;
-    return level ? NO_DEALING : DEAL_STEP;
+    return level ? NO_DEALING : threshold == 0 && appends ? 0 : DEAL_STEP;
 }
 // the same for kvb_flush (commits: of accepted drafts), and for the others
 inline int fold_deals_from(int d, int n, bool commits, bool apart)

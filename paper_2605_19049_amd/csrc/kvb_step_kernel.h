@@ -976,7 +976,7 @@ void launch_step_s(const StepArgs &a, int blocks, hipStream_t stream)
     // (a branch inside the kernel around the state loads would make the compiler's wait
     // counters conservative at the join, so these are compile-time variants)
     const bool st = a.stream_state != 0 && D == 128;   // the small head sizes are not tuned: no streaming variant
-    const int deal = unit_deal(blocks, a.r, step_deals_from(D, blocks, a.threshold, st, a.st.apart()));
+    const int deal = unit_deal(blocks, a.r, step_deals_from(D, blocks, a.threshold, st, a.advance != 0, a.st.apart()));
     if (a.threshold > 0) {
         if constexpr (D == 128) {
             if (st) {
