@@ -109,12 +109,33 @@ def torch_dtype(code):
     return {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16}[code]
 
 
+def _fill_layout(fill, n_slots, flags):
+    """STORE_FILL_APART or 0 for a tensor of fills; ValueError where the kernels would find a slot in another word or outside."""
+    def wrong(why):
+        return ValueError("fill of shape %s and stride %s for %d slots: %s" % (tuple(fill.shape), tuple(fill.stride()), n_slots, why))
+    if fill.element_size() != 4 or fill.is_floating_point():
+        raise wrong("%s, not int32" % fill.dtype)
+    count = fill.numel()
+    if fill.stride() == (FILL_APART,) and count > 1:
+        if count < n_slots:
+            raise wrong("too short")
+        return STORE_FILL_APART
+    if not fill.is_contiguous():
+        raise wrong("neither contiguous nor one word in %d" % FILL_APART)
+    if count < (FILL_APART * (n_slots - 1) + 1 if flags & STORE_FILL_APART else n_slots):
+        raise wrong("too short")
+    if not flags & STORE_FILL_APART and n_slots > 1 and tuple(fill.shape) == (n_slots, FILL_APART):
+        raise wrong("pass its first column, or STORE_FILL_APART")
+    return 0
+
+
 def store(state, buf_k, buf_u, buf_G, fill, status, n_slots, flags=0, block_table=None, block_size=0,
           max_blocks=0, n_blocks=0):
-    """fill: a contiguous int32 tensor [n_slots], or one with a line to each slot (stride FILL_APART, as DeviceStore's);
-    an address needs STORE_FILL_APART in flags where it is of the second kind."""
-    if hasattr(fill, "stride") and fill.dim() == 1 and fill.stride(0) == FILL_APART:
-        flags |= STORE_FILL_APART
+    """fill: an int32 tensor, contiguous (packed: slot s is element s) or [n_slots] of stride FILL_APART (a line to each slot, as
+    DeviceStore's); with STORE_FILL_APART in flags also a contiguous [n_slots, FILL_APART].  An address is taken as the flag says:
+    DeviceStore(...).fill.data_ptr() needs it."""
+    if hasattr(fill, "stride"):
+        flags |= _fill_layout(fill, n_slots, flags)
     return KvbStore(_ptr(state), _ptr(buf_k), _ptr(buf_u), _ptr(buf_G), _ptr(fill), _ptr(status), n_slots, flags,
                     _ptr(block_table), block_size, max_blocks, n_blocks)
 
@@ -221,7 +242,8 @@ def bind(fn_name, *args):
 
 class DeviceStore:
     """Caller-side holder of the device arrays of include/kvb.h's kvb_store, allocated
-    with PyTorch (memory plumbing only)."""
+    with PyTorch (memory plumbing only).  fill is [n_slots] with 128 bytes from one slot's word to the next: a kvb_store
+    built from its address needs STORE_FILL_APART in flags (c() sets it)."""
 
     def __init__(self, n_slots, Hk, Hv, dk, dv, cap, in_dtype, device="cuda", with_state=True,
                  block_size=None, n_blocks=None, block_table=None, rec_dtype=F32):

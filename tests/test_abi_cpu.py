@@ -184,6 +184,25 @@ def test_check_flag_raises():
     assert e.value.code == kvb.EINVAL
 
 
+def test_fill_tensors_say_where_their_words_are():
+    """kvb.store takes a fill tensor by its layout, and refuses one whose slots the kernels would look for elsewhere."""
+    import torch
+    n, apart = 5, kvb.STORE_FILL_APART
+    rows = torch.zeros((n, kvb.FILL_APART), dtype=torch.int32)
+    packed = torch.zeros(n, dtype=torch.int32)
+    for fill, flags, want in [(packed, 0, 0), (torch.zeros(n + 3, dtype=torch.int32), 0, 0), (packed.view(n, 1), 0, 0), (rows[:, 0], 0, apart),
+                              (rows[:, 0], apart, apart), (rows[:, 3], kvb.STORE_STREAM, apart | kvb.STORE_STREAM), (rows, apart, apart),
+                              (rows.view(-1), apart, apart), (rows[:, 0].clone(), 0, 0), (A, 0, 0), (A, apart, apart)]:
+        st = _store(fill=fill, flags=flags, n_slots=n)
+        assert st.flags == want and st.fill == (fill if isinstance(fill, int) else fill.data_ptr())
+    # one slot: its word is the first one in either layout
+    assert _store(fill=rows[:1, 0], n_slots=1).fill == rows.data_ptr() and _store(fill=packed[:1], flags=apart, n_slots=1).flags == apart
+    for fill, flags in [(rows, 0), (packed, apart), (rows.view(-1)[:-kvb.FILL_APART], apart), (rows[:, ::2][:, 0][:3], 0), (rows[:, 0][:4], 0),
+                        (rows.view(-1)[::2][:n], 0), (rows[:, :2], 0), (packed[:4], 0), (packed.long(), 0), (packed.float(), 0), (packed.expand(3, n), 0)]:
+        with pytest.raises(ValueError):
+            _store(fill=fill, flags=flags, n_slots=n)
+
+
 C_PROBE = r"""
 #include <stdio.h>
 #include <stddef.h>
