@@ -193,19 +193,18 @@ __device__ __forceinline__ void put(T *p, const T &x)
     else
         __hip_atomic_store(reinterpret_cast<Bits *>(p), __builtin_bit_cast(Bits, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// 16 bytes at a scalar address and the lane's offset (a register to a store's address, not two: with two the fold of fp32 inputs and
-// 64-record windows spilled 4, and 8 steps of 8 requests took 45.3 us instead of 45.0).
-template <bool NT, bool PLAIN = false>
+// A plain or non-temporal store of 16 bytes at a scalar address and the lane's offset (a register to a store's address, not two: with
+// two the fold of fp32 inputs and 64-record windows spilled 4, and 8 steps of 8 requests took 45.3 us instead of 45.0).
+template <bool NT>
 __device__ __forceinline__ void put_at(float *base, uint32_t lane_at, const float4 &x)
 {
     typedef float v4f __attribute__((ext_vector_type(4)));
+    v4f *p = reinterpret_cast<v4f *>(reinterpret_cast<char *>(base) + lane_at);
     const v4f v = {x.x, x.y, x.z, x.w};
     if constexpr (NT)
-        __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(reinterpret_cast<char *>(base) + lane_at));
-    else if constexpr (PLAIN)
-        *reinterpret_cast<v4f *>(reinterpret_cast<char *>(base) + lane_at) = v;
+        __builtin_nontemporal_store(v, p);
     else
-        asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 1" ::"v"(lane_at), "v"(v), "s"(base) : "memory");
+        *p = v;
 }
 // The same of already-rounded or to-be-rounded values into an array of type T.
 template <bool NT = false>

@@ -456,8 +456,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal
 // pass move by move, 21.1 at once.
 // ---------------------------------------------------------------------------
 template <int D, typename TIn, typename TRec, bool PAGED>
-__global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
-                                                         const CompactArgs a)
+__global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg, int32_t Hv_arg, const CompactArgs a)
 {
     constexpr int PU = D * sizeof(TRec) / 16, PK = D * sizeof(TIn) / 16;   // pieces of a record
     static_assert(KVB_MAX_DRAFTS * PU <= NT && KVB_MAX_DRAFTS * PK <= NT, "a thread to each piece");
@@ -539,8 +538,12 @@ int launch_flush(int dk, int in_dtype, int rec_dtype, const FlushArgs &a, int bl
 
 int launch_compact(int dk, int in_dtype, int rec_dtype, const CompactArgs &a, int blocks, hipStream_t stream)
 {
-    return dispatch(dk, in_dtype, rec_dtype,
-                    [&]<int D, typename TIn, typename TRec>() { LAUNCH_LEAD(blocks, 0, stream, a, kvb_compact_kernel<D, TIn, TRec); });
+    return dispatch(dk, in_dtype, rec_dtype, [&]<int D, typename TIn, typename TRec>() {
+        if (a.st.block_table)
+            launch(kvb_compact_kernel<D, TIn, TRec, true>, blocks, stream, a.slot, a.Hv, a);
+        else
+            launch(kvb_compact_kernel<D, TIn, TRec, false>, blocks, stream, a.slot, a.Hv, a);
+    });
 }
 
 }  // namespace kvb_impl

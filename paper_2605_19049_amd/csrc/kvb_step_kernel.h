@@ -703,7 +703,7 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
             for (int p = 0; p < NPASS; ++p)   // (a state that is streamed in is streamed out again: +1 % on 1 GiB of state;
                                               // otherwise it stays in the L2: threshold 1, through / plain, us a step: 16
                                               // requests 11.8 / 10.1, one 5.73 / 5.29; 64, with the rest through, 40.7 / 41.4)
-                put_at<STREAM, true>(sw + RPP * p * D, lane_at, sreg[p]);
+                put_at<STREAM>(sw + RPP * p * D, lane_at, sreg[p]);
         }
     }
 }
