@@ -552,11 +552,30 @@ inline int step_deals_from(int d, int n, int threshold, bool stream, bool append
         return d == 128 && (n < PACKED_END || (threshold > 0 && !level)) ? DEAL_STEP : NO_DEALING;
     return level ? NO_DEALING : threshold == 0 && appends ? 0 : DEAL_STEP;
 }
+// kvb_flush where (nearly) every request folds, d = 128: behind a dealt kvb_verify or kvb_decode the fold is faster in eighths all the same, from
+// 768 units on and while it has not much more state than the last-level cache holds (3584 units; 4096 are 256 MiB).  Dealt before and dealt / dealt
+// before and eighths / both in eighths, which kvb_verify and kvb_decode cannot know to take (before all this), us: commits of 4 drafts at threshold 1,
+// 16 requests of 32 heads (2 drafts) 19.1 / 24.6 / 16.4 (22.1), 24 29.9 / 28.5 / 24.1 (30.6), 40 (2) 46.8 / 42.2 / 38.2 (44.3), 64 70.3 / 63.7 /
+// 61.4 (67.2), 96 99.6 / 91.6 / 89.0 (94.6), 112 (2) 120.7 / 115.8 / 116.0 (116.8), 128 140 / 150 / 138 (140), fp32, 64 73.0 / 69.7 / 68.9 (71.6),
+// 200 of 8 heads 57.8 / 53.5 / 49.8 (54.9); at threshold 2, 40 44.1 / 41.2 / 38.0 (43.9), 2 drafts 37.0 / 39.7 / 36.3 (42.1), 96 90.8 / 86.5 / 85.0
+// (89.5), 2 drafts 77.6 / 76.9 / 76.2 (80.2), 200 of 8 heads 53.7 / 50.2 / 46.9 (51.9); at threshold 3, 64 57.2 / 57.1 / 55.3 (60.0), at 4 49.2 / 53.8 / 52.7 (58.0).  16 steps of kvb_decode
+// and kvb_flush at threshold 1, 24 443 / 426 / 359 (481), 64 1070 / 965 / 907 (1003), 96 1520 / 1398 / 1348 (1454), 128 (8 steps) 1034 / 1062 / 988
+// (994); at threshold 2, 64 718 / 773 / 737 (789).  Up to two drafts, all folded in their round, stay slower than before from 4096 units on: one,
+// 128 requests 129 / 135 / 124 (125), 200 206 / 207 / 202 (201); two, 128 137 (136), fp16 135 (132).
+// The fold behind kvb_direct, dealt / eighths (before): up to 64 tokens, 24 contexts 38.0 / 39.3 (40.3), 64 83.6 / 86.7 (88.2), fp32, 48 87 / 97 (100); up
+// to 16, 24 27.5 / 28.1 (29.9), 48 48.3 / 48.5 (49.6), fp16 45.5 / 43.8 (45.8), 96 90.9 / 89.9 (91.6), fp32, 48 53.6 / 51.4 (55.2).  So without accepted
+// drafts, eighths are for buffers of up to 16 records.  (Streamed, 4096 units and more, dealt / eighths: 128 contexts of up to 64 154.8 / 159.5
+// (158.9); the kernel by itself over the same 64 records a request again and again, though, 115 / 105 (104).)
+// d = 64, dealt as behind / in eighths: commits at threshold 1, 60 requests of 16 heads 13.2 / 17.4 (17.7), 200 31.5 / 35.0 (37.6).
+constexpr int LEVEL_FOLD = 768, LEVEL_FOLD_2 = 1536, LEVEL_FOLD_END = 3840;   // units: at threshold 1, at 2, and below
 // the same for kvb_flush (commits: of accepted drafts), and for the others
-inline int fold_deals_from(int d, int n, bool commits, bool apart)
+inline int fold_deals_from(int d, int n, bool commits, int threshold, int cap, bool apart)
 {
     if (!apart)
         return d == 128 && n < PACKED_END && !commits ? DEAL_STEP : NO_DEALING;
+    const bool level = commits ? threshold == 1 || (threshold == 2 && n >= LEVEL_FOLD_2) : threshold == 1 && cap <= 16;
+    if (d == 128 && level && n >= LEVEL_FOLD && n < LEVEL_FOLD_END)
+        return NO_DEALING;
     return commits ? DEAL_SPEC : 0;
 }
 inline int deals_from(int least, bool apart) { return apart ? least : NO_DEALING; }

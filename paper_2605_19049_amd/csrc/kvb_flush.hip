@@ -515,7 +515,7 @@ __global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg
 // ---------------------------------------------------------------------------
 int launch_flush(int dk, int in_dtype, int rec_dtype, const FlushArgs &a, int blocks, hipStream_t stream)
 {
-    const int deal = unit_deal(blocks, a.r, fold_deals_from(dk, blocks, a.accepted != nullptr, a.st.apart()));
+    const int deal = unit_deal(blocks, a.r, fold_deals_from(dk, blocks, a.accepted != nullptr, a.threshold, a.cap, a.st.apart()));
     if (dk == 128 && in_dtype != KVB_F32)   // the matrix-core kernel
         return dispatch_types16(in_dtype, rec_dtype, [&]<typename TIn, typename TRec>() {
             if (a.cap <= 32) {

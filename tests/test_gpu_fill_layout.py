@@ -109,6 +109,36 @@ def test_launches_that_the_layout_decides(d, in_dtype, rec_dtype, B, apart):
     H.check([e], in_dtype, rec_dtype, "fill layout")
 
 
+@pytest.mark.parametrize("in_dtype, rec_dtype", [("bf16", "f32"), ("f16", "f16"), ("f32", "f32")])
+@pytest.mark.parametrize("B, threshold, commit", [(96, 1, False), (96, 1, True), (192, 2, True), (480, 1, True)])
+def test_folds_of_whole_batches(in_dtype, rec_dtype, B, threshold, commit):
+    """kvb_flush where all requests fold, or nearly, at the sizes where units are no longer dealt for it and where they are again: a
+    request is folded to the same bits as in launches of 64 and of 32 requests."""
+    rng = np.random.default_rng(B + threshold)
+    Hk, Hv, d, cap = 4, 8, 128, 16
+    lay = H.Layer(B, Hk, Hv, d, d, cap, in_dtype, n_slots=B + 5, slots=rng.permutation(B + 5)[:B], rec_dtype=rec_dtype)
+    ds = lay.ds
+    ds.state.normal_(0, 0.5)
+    ds.buf_u.copy_(torch.randn(ds.buf_u.shape, device="cuda"))
+    ds.buf_k.copy_(torch.nn.functional.normalize(torch.randn(ds.buf_k.shape, device="cuda"), dim=-1))
+    ds.buf_G.copy_(-0.25 * torch.arange(1, cap + 1, device="cuda").float().expand_as(ds.buf_G))
+    fills = torch.from_numpy(rng.integers(0, cap - 3, B).astype(np.int32)).cuda()
+    acc = torch.from_numpy(rng.integers(0, 4, B).astype(np.int32)).cuda() if commit else None
+    state = ds.state.clone()
+    seen = []
+    for parts in ([(0, B)], [(b, min(b + 64, B)) for b in range(0, B, 64)]):
+        ds.state.copy_(state)
+        ds.fill.fill_(7)
+        ds.fill[lay.slot.long()] = fills
+        for lo, hi in parts:
+            kvb.kvb_flush(lay.shape(hi - lo), ds.c(), lay.slot[lo:hi].contiguous(), None if acc is None else acc[lo:hi].contiguous(), threshold)
+        torch.cuda.synchronize()
+        seen.append((ds.state.clone(), ds.fill.clone()))
+    due = (fills if acc is None else fills + acc) >= threshold
+    assert bool((seen[0][1][lay.slot.long()] == torch.where(due, 0, fills if acc is None else fills + acc)).all()) and not ds.status.any()
+    assert all(torch.equal(x, y) for x, y in zip(*seen)) and not torch.equal(seen[0][0], state)
+
+
 def test_device_store_keeps_a_line_to_each_slot():
     ds = kvb.DeviceStore(3, 1, 2, 32, 32, 8, kvb.F32)
     assert ds.fill.shape == (3,) and ds.fill.stride() == (kvb.FILL_APART,) and ds.fill.data_ptr() % 128 == 0
