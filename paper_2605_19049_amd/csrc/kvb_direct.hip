@@ -509,7 +509,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     }
     if (L == 0) {
         if (h == 0 && tid == 0)
-            put<false>(a.st.fill_of(s), 0);
+            put<false, true>(a.st.fill_of(s), 0);
         return;
     }
     // ---- every input of the workgroup is requested at once ------------------------
@@ -620,8 +620,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
         }
         sG[row] = gv;
         sB[row] = bv;
+        // Decays and the fill, parts of a line, are plain stores: through the L2 each waits for memory, which short contexts do not
+        // hide.  Through / plain, paged bf16 contexts of up to 15 tokens: 37 of 8 heads 6.57 / 6.34 us, 121 9.12 / 8.87; of up to 34,
+        // 13 of 32 heads 9.88 / 9.75; kvb_direct and fold, 70 to 500 us, the same.  Keys, whole lines, go through (plain: 48 of 16
+        // heads up to 57 tokens 12.9 / 13.3, 8 paged blocks 12.7 / 13.0).
         if (row < L)
-            put<false>(Grec.at(row, 0), gv);
+            put<false, true>(Grec.at(row, 0), gv);
     }
     // stage K; the thread that loaded a piece of K also appends it to the buffer
 #pragma unroll
@@ -1185,7 +1189,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(DIRECT_WG_PE
     if (__builtin_expect(!all_finite(big), 0))
         solve_by_token<D, 2, TIn, TRec>(a, b, h, L, col2, sG, sB, ru, lane);
     if (h == 0 && tid == 0)
-        put<false>(a.st.fill_of(s), L);
+        put<false, true>(a.st.fill_of(s), L);
 }
 
 // ---------------------------------------------------------------------------
