@@ -426,8 +426,11 @@ void kvb_step_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg,
     // through, with a plain state: threshold 1, 128 requests of 32 heads 81.9 / 86.6, one 5.14 / 5.35; threshold 2, 128
     // requests 59.8 / 60.9.  By the workgroup's own fold instead of the threshold: 83.0 at threshold 1, and 16 steps of 13
     // requests of 8 heads with 32 fp16 records 78.8 instead of 78.0.
+    // Also where buffers grow past the 64 records that are loaded ahead: the rest is read late, from the L2 sooner.  Threshold 128, through / plain:
+    // 4 requests of 8 heads, 8 steps 53.8 / 52.2, 11 of 16 heads of 32 39.4 / 37.1, 4 of 9 heads of 64, 16 steps 82.9 / 81.0; 64 of 32
+    // 575 / 576, 333 of 9 894 / 892.
     if constexpr (FUSE && !STREAM) {
-        if (a.threshold <= 4)
+        if (a.threshold <= 4 || a.threshold > 64)
             write_row(std::true_type{});
         else
             write_row(std::false_type{});

@@ -71,15 +71,15 @@ def test_fused_update_tiles(in_dtype, rec_dtype, C):
     H.check(e, in_dtype, rec_dtype, "fused update")
 
 
-@pytest.mark.parametrize("C", [4, 5])
+@pytest.mark.parametrize("C", [4, 5, 64, 65])
 @pytest.mark.parametrize("d, in_dtype, rec_dtype", [(128, "bf16", "f32"), (128, "f16", "f16"), (64, "f32", "f32"), (32, "bf16", "f32")])
 def test_fused_results_kept_or_sent_through(d, in_dtype, rec_dtype, C):
-    """kvb_decode_flush at the highest threshold whose results stay in the cache and at the next one: each step reads the
+    """kvb_decode_flush on both sides of the thresholds from and up to which results stay in the cache: each step reads the
     records and, after two folds, the state that the steps before it left, in a buffer longer than the threshold."""
     rng = np.random.default_rng(970 + C)
     S0 = H.prefix_state(rng, 20, 2, 6, d, d, in_dtype, 16)
     tok = synth.token_stream(rng, 20, 2 * C + 2, 2, 6, d, d, in_dtype)
-    lay = H.Layer(20, 2, 6, d, d, cap=16, in_dtype=in_dtype, scale=d ** -0.5, rec_dtype=rec_dtype)
+    lay = H.Layer(20, 2, 6, d, d, cap=max(16, C + 7), in_dtype=in_dtype, scale=d ** -0.5, rec_dtype=rec_dtype)
     o, u, S, _ = H.run_decode(lay, S0, tok, C, final_flush=False, fused=True)
     o_ref, u_ref, _ = oracle.kvb_decode_expected(S0, tok["q"], tok["k"], tok["v"], tok["g"], tok["beta"], scale=d ** -0.5)
     _, _, S_ref = oracle.kvb_decode_expected(S0, *(tok[x][:, :2 * C] for x in ("q", "k", "v", "g", "beta")), scale=d ** -0.5)
