@@ -531,12 +531,14 @@ __host__ __device__ inline int dealt_unit(int x, int deal)
 // Not dealt at d = 64 (kvb_decode_flush, 60 requests 124 / 121 / 131, 200 210 / 211 / 254), for kvb_verify and commit (24 requests 32.5 / 31.2 / 31.6,
 // 48 46.9 / 43.8 / 46.1, 128 87.3 / 86.3 / 87.9, 300 188 / 189 / 184) and kvb_decode without a state (128 requests 21.3 / 21.0 / 22.4).
 constexpr int DEAL_STEP = 512, DEAL_BUFFER_STEP = 1024, DEAL_SPEC = 512;   // the least units (workgroups) to deal
-constexpr int PACKED_END = 1536, NO_DEALING = 0x7FFFFFFF;
+constexpr int PACKED_END = 1536, LEVEL_STEP = 1024, NO_DEALING = 0x7FFFFFFF;
 // Where every step folds, no XCD has less to do, and whole eighths keep what the heads of a request share, and the state from one step to the
-// next, in one L2: at threshold 1, and at 2 of a streamed state, nothing is dealt.  Eighths / dealt, 16 steps of threshold 1: 16 requests of
-// 32 heads 177 / 180 us, 24 269 / 266, 64 629 / 657 (fp16 637 / 657), 128 1300 / 1315; 8 steps of 256 1510 / 1572; 4 of 400 1175 / 1223.
-// Threshold 2: 64 requests 583 / 515, 128 (8 steps) 537 / 509, streamed, 256 1120 / 1140, 400 (4 steps) 873 / 892; threshold 3, streamed, 256
-// 1022 / 1005.  With packed words only from PACKED_END on: 24 requests 300 / 264, 64 640 / 676, 256 1512 / 1580.
+// next, in one L2: at threshold 1 (d = 128: from 1024 units on), and at 2 of a streamed state, nothing is dealt.  Eighths / dealt, us a step of
+// threshold 1: 16 requests of 32 heads 10.5 / 10.0, 24 16.3 / 14.5, 28 19.0 / 17.4 to 19.5, 32 20.6 / 20.7, 48 29.8 / 30.4, 64 39.1 / 40.6 (fp16 39.6 /
+// 41.0), 96 57.8 / 59.9, 128 82.0 / 81.1, 256 184 / 186; fp32, 24 15.8 / 14.6; 96 of 8 heads 16.3 / 14.6, 128 20.6 / 20.8, 400 60.7 / 62.7; d = 64, 32 of 16
+// heads 5.65 / 5.80, 200 19.2 / 19.6; 4 steps of 400 of 32 1175 / 1223.  Threshold 2, 16 steps: 64 requests 583 / 515, 128 (8) 537 / 509, streamed,
+// 256 1120 / 1140, 400 (4 steps) 873 / 892; threshold 3, streamed, 256 1022 / 1005.  With packed words only from PACKED_END on: 24 requests 300 / 264, 64
+// 640 / 676, 256 1512 / 1580.
 // kvb_flush without accepted drafts comes behind kvb_direct, which deals at any size, or behind kvb_decode.  The two are alike, or a fold
 // has its state and records in other L2s than its decode: so kvb_decode deals at any size as well.  kvb_decode in eighths and the fold dealt /
 // both in eighths / both dealt, 16 steps of kvb_decode and kvb_flush: C = 16, 4 requests of 32 heads 102.9 / 98.6 / 99.4, 8 124 / 117 / 114, 15
@@ -547,7 +549,7 @@ constexpr int PACKED_END = 1536, NO_DEALING = 0x7FFFFFFF;
 // draft, which goes with its commit; apart: a line to each fill word)
 inline int step_deals_from(int d, int n, int threshold, bool stream, bool appends, bool apart)
 {
-    const bool level = threshold > 0 && threshold <= (stream ? 2 : 1);
+    const bool level = threshold > 0 && threshold <= (stream ? 2 : 1) && (d < 128 || n >= LEVEL_STEP);
     if (!apart)
         return d == 128 && (n < PACKED_END || (threshold > 0 && !level)) ? DEAL_STEP : NO_DEALING;
     return level ? NO_DEALING : threshold == 0 && appends ? 0 : DEAL_STEP;
