@@ -523,22 +523,24 @@ __host__ __device__ inline int dealt_unit(int x, int deal)
 // (one dealt and the other not is 1 to 6 % slower than either): 128 requests 88.6 / 83.6, 300 182 / 173, 60 of 16 heads 32.7 / 31.7,
 // 24 of 32 23.8 / 23.3, 24 of 16 18.5 / 18.5, 40 of 8 19.7 / 20.2.  The fold after kvb_direct, which deals at any size, of 10 contexts
 // 28.9 / 27.9, of 100 126 / 124.
-// Packed fill words (32 slots to a line): dealt, the additions to a line come from all XCDs, and at d = 128 that is the better way below
-// 1536 units all the same (PACKED_END), and above them in kvb_decode_flush.  Before units were dealt and results sent through / eighths / dealt, us,
-// means of three or four placements: kvb_decode_flush, 8 steps of 16 requests of 32 heads 93 / 90 / 82, 24 116 / 120 / 105, 32 134 / 142 /
-// 137, 128 414 / 415 / 407, 256 827 / 831 / 826, 16 of 64 446 / 456 / 446; kvb_decode, 8 steps of 24 109 / 121 / 105, 64 221 / 217 / 236, 128
-// 401 / 400 / 411; kvb_direct and fold of 24 53 / 52 / 48.5, 128 174 / 172 / 174; threshold 1, 24 277 / 300 / 264, 64 634 / 640 / 676.
-// Not dealt at d = 64 (kvb_decode_flush, 60 requests 124 / 121 / 131, 200 210 / 211 / 254), for kvb_verify and commit (24 requests 32.5 / 31.2 / 31.6,
-// 48 46.9 / 43.8 / 46.1, 128 87.3 / 86.3 / 87.9, 300 188 / 189 / 184) and kvb_decode without a state (128 requests 21.3 / 21.0 / 22.4).
+// Packed fill words (32 slots to a line): dealt, the additions to a line come from all XCDs, which is dearest where the slots of a batch are
+// neighbours.  Only kvb_decode_flush at d = 128 below 832 units is faster so in any order of slots; all else stays in eighths.  Before units were dealt
+// and results sent through / eighths / dealt, slots in order and (at random), us: kvb_decode_flush, 16 steps at C = 8, 16 requests of 32 heads 190 /
+// 188 / 162 (162 / 155 / 152), 20 223 / 214 / 202 (201 / 198 / 160), 24 226 / 218 / 213 (214 / 212 / 206), 28 234 / 239 / 249 (234 / 231 / 228), 31 242 /
+// 247 / 274 (254 / 267 / 253), 48 360 / 360 / 388 (362 / 361 / 352), 64 451 / 459 / 553 (458 / 469 / 450), 48 of 16 206 / 211 / 200 (205 / 209 / 200), 60 of 16 232 /
+// 235 / 266 (233 / 255 / 246); threshold 1, 24 277 / 263 / 272 (266 / 269 / 268), 31 316 / 317 / 360 (314 / 337 / 335).  kvb_decode and kvb_flush, 16 steps
+// at C = 16, 24 280 / 257 / 263 (276 / 250 / 276), 64 532 / 501 / 641 (615 / 578 / 557); kvb_decode, 8 steps, 24 100 / 97 / 104 (94 / 94 / 93), 32 114 /
+// 111 / 134 (111 / 108 / 118), 64 185 / 180 / 247 (200 / 198 / 198); kvb_direct of up to 16 tokens and fold, 24 29.7 / 28.2 / 30.4 (29.6 / 27.4 / 27.9).  Slots at
+// random: d = 64, kvb_decode_flush, 60 requests 124 / 121 / 131, 200 210 / 211 / 254; kvb_verify and commit, 24 requests 32.5 / 31.2 / 31.6, 48 46.9 / 43.8 /
+// 46.1, 128 87.3 / 86.3 / 87.9, 300 188 / 189 / 184; kvb_decode without a state, 128 requests 21.3 / 21.0 / 22.4.
 constexpr int DEAL_STEP = 512, DEAL_BUFFER_STEP = 1024, DEAL_SPEC = 512;   // the least units (workgroups) to deal
-constexpr int PACKED_END = 1536, LEVEL_STEP = 1024, NO_DEALING = 0x7FFFFFFF;
+constexpr int PACKED_END = 832, LEVEL_STEP = 1024, NO_DEALING = 0x7FFFFFFF;
 // Where every step folds, no XCD has less to do, and whole eighths keep what the heads of a request share, and the state from one step to the
 // next, in one L2: at threshold 1 (d = 128: from 1024 units on), and at 2 of a streamed state, nothing is dealt.  Eighths / dealt, us a step of
 // threshold 1: 16 requests of 32 heads 10.5 / 10.0, 24 16.3 / 14.5, 28 19.0 / 17.4 to 19.5, 32 20.6 / 20.7, 48 29.8 / 30.4, 64 39.1 / 40.6 (fp16 39.6 /
 // 41.0), 96 57.8 / 59.9, 128 82.0 / 81.1, 256 184 / 186; fp32, 24 15.8 / 14.6; 96 of 8 heads 16.3 / 14.6, 128 20.6 / 20.8, 400 60.7 / 62.7; d = 64, 32 of 16
 // heads 5.65 / 5.80, 200 19.2 / 19.6; 4 steps of 400 of 32 1175 / 1223.  Threshold 2, 16 steps: 64 requests 583 / 515, 128 (8) 537 / 509, streamed,
-// 256 1120 / 1140, 400 (4 steps) 873 / 892; threshold 3, streamed, 256 1022 / 1005.  With packed words only from PACKED_END on: 24 requests 300 / 264, 64
-// 640 / 676, 256 1512 / 1580.
+// 256 1120 / 1140, 400 (4 steps) 873 / 892; threshold 3, streamed, 256 1022 / 1005.
 // kvb_flush without accepted drafts comes behind kvb_direct, which deals at any size, or behind kvb_decode.  The two are alike, or a fold
 // has its state and records in other L2s than its decode: so kvb_decode deals at any size as well.  kvb_decode in eighths and the fold dealt /
 // both in eighths / both dealt, 16 steps of kvb_decode and kvb_flush: C = 16, 4 requests of 32 heads 102.9 / 98.6 / 99.4, 8 124 / 117 / 114, 15
@@ -551,7 +553,7 @@ inline int step_deals_from(int d, int n, int threshold, bool stream, bool append
 {
     const bool level = threshold > 0 && threshold <= (stream ? 2 : 1) && (d < 128 || n >= LEVEL_STEP);
     if (!apart)
-        return d == 128 && (n < PACKED_END || (threshold > 0 && !level)) ? DEAL_STEP : NO_DEALING;
+        return d == 128 && threshold > 0 && n < PACKED_END ? DEAL_STEP : NO_DEALING;
     return level ? NO_DEALING : threshold == 0 && appends ? 0 : DEAL_STEP;
 }
 // kvb_flush where (nearly) every request folds, d = 128: behind a dealt kvb_verify or kvb_decode the fold is faster in eighths all the same, from
@@ -573,10 +575,8 @@ constexpr int LEVEL_FOLD = 768, LEVEL_FOLD_2 = 1536, LEVEL_FOLD_END = 3840;   //
 // the same for kvb_flush (commits: of accepted drafts), and for the others
 inline int fold_deals_from(int d, int n, bool commits, int threshold, int cap, bool apart)
 {
-    if (!apart)
-        return d == 128 && n < PACKED_END && !commits ? DEAL_STEP : NO_DEALING;
     const bool level = commits ? threshold == 1 || (threshold == 2 && n >= LEVEL_FOLD_2) : threshold == 1 && cap <= 16;
-    if (d == 128 && level && n >= LEVEL_FOLD && n < LEVEL_FOLD_END)
+    if (!apart || (d == 128 && level && n >= LEVEL_FOLD && n < LEVEL_FOLD_END))
         return NO_DEALING;
     return commits ? DEAL_SPEC : 0;
 }

@@ -43,7 +43,7 @@ int main(int argc, char **argv)
     if (argc == 3 && atoi(argv[1]) == 0) {   // the rules that look at where the fill words lie
         if (atoi(argv[2]) == 0) {   // units to deal from: d, units, threshold, apart, of kvb_step_kernel (plain, streamed, kvb_verify), folds of 16 and of 17 records, a commit, others at 512
             for (int d : {32, 64, 128})
-                for (int n : {1, 511, 512, 767, 768, 1023, 1024, 1535, 1536, 3839, 3840, 100000})
+                for (int n : {1, 511, 512, 767, 768, 831, 832, 1023, 1024, 1535, 1536, 3839, 3840, 100000})
                     for (int threshold : {0, 1, 2, 3, 16})
                         for (int apart = 0; apart < 2; ++apart)
                             printf("%d %d %d %d %d %d %d %d %d %d %d\n", d, n, threshold, apart, kvb_impl::step_deals_from(d, n, threshold, false, true, apart),
@@ -138,10 +138,9 @@ def test_units_of_shared_fill_words(program, B, Hk, r, least):
 def test_which_launches_deal(program):
     """Where every step folds (or, streamed, every second) no unit is dealt, at d = 128 from 1024 units on; kvb_decode and the fold behind it are alike at any
     size, kvb_verify and the commit behind it too, but where every request folds, or nearly, at d = 128 and the state is no larger
-    than the last-level cache.  With 32 fill words to a line kvb_verify, commits, kvb_decode without a state and small heads stay in
-    eighths, decoding with a state and folding at d = 128 deal from 512 units on, up to 1535 without a fold in the kernel."""
+    than the last-level cache.  With 32 fill words to a line only kvb_decode_flush at d = 128 and from 512 to 831 units deals."""
     rows = program(0, 0).reshape(-1, 11)
-    assert len(rows) == 3 * 12 * 5 * 2
+    assert len(rows) == 3 * 14 * 5 * 2
     never = 2 ** 31 - 1
     for d, n, threshold, apart, step, streamed, verify, fold, fold_long, commit, other in rows:
         large = d < 128 or n >= 1024
@@ -149,15 +148,14 @@ def test_which_launches_deal(program):
             if apart:
                 assert got == (never if level else 512 if threshold else 0)
             else:
-                assert got == (512 if d == 128 and (n < 1536 or (threshold > 0 and not level)) else never)
+                assert got == (512 if d == 128 and threshold and n < 832 else never)
         if apart:
             cached = d == 128 and 768 <= n < 3840
             assert fold == (never if cached and threshold == 1 else 0) and fold_long == 0
             assert commit == (never if cached and (threshold == 1 or (threshold == 2 and n >= 1536)) else 512)
             assert other == 512 and (threshold or verify == 512)
         else:
-            assert fold == fold_long == (512 if d == 128 and n < 1536 else never) and commit == other == never
-            assert threshold or step == fold
+            assert fold == fold_long == commit == other == never
     assert np.array_equal(program(2048, 2, never), np.arange(2048) % 8 * 256 + np.arange(2048) // 8)   # (eighths)
 
 
