@@ -214,8 +214,9 @@ void kvb_flush_rows_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal
 // together pay: measured at 256 MiB of state and 64 records, 138 us with either or neither,
 // 107 us with both (a state that passes through the cache in one direction still turns it
 // over); at 128 MiB, which the cache keeps, they cost 10 %.
+// PLAIN: a state that is not streamed is stored plainly and stays in the L2 (launch_flush: when), else through it.
 // ---------------------------------------------------------------------------
-template <typename TIn, typename TRec, bool MULTI, bool STREAM, bool PAGED>
+template <typename TIn, typename TRec, bool MULTI, bool STREAM, bool PLAIN, bool PAGED>
 // (register budgets: 3 workgroups per CU, 2 where the sums persist)
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MULTI ? 2 : 3)))
 void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal_arg, const FlushArgs a)
@@ -412,7 +413,7 @@ void kvb_flush_mfma_kernel(const int32_t *slot_arg, int32_t Hv_arg, int32_t deal
             float2 o;
             o.x = fmaf(gam, sreg[rt % WIN][v].x, c0[v] * up[0]);
             o.y = fmaf(gam, sreg[rt % WIN][v].y, c1[v] * up[1]);
-            store2<STREAM>(state_at(8 * v + rt), o.x, o.y);
+            put<STREAM, PLAIN>(reinterpret_cast<float2 *>(state_at(8 * v + rt)), o);
         }
         if (rt + WIN < 8) {
             __builtin_amdgcn_sched_barrier(0);
@@ -516,18 +517,25 @@ __global__ __launch_bounds__(NT) void kvb_compact_kernel(const int32_t *slot_arg
 int launch_flush(int dk, int in_dtype, int rec_dtype, const FlushArgs &a, int blocks, hipStream_t stream)
 {
     const int deal = unit_deal(blocks, a.r, fold_deals_from(dk, blocks, a.accepted != nullptr, a.threshold, a.cap, a.st.apart()));
+    // Folds of up to 32 records without accepted drafts, of 257 to 512 units: their states (16 to 32 MiB) stay in the L2s for whoever comes next.
+    // kvb_direct and fold again and again, through / plain (plain before), us: 25 of 16 heads up to 19 tokens 21.6 / 18.8 (20.5), 9 of 32 up to 12 17.3 / 15.6
+    // (17.9), 48 of 9 up to 22 22.3 / 19.8 (20.8).  With more records, more units or accepted drafts through is faster: 23 of 16 up to 39 21.9 / 22.8, 17
+    // up to 103 36.3 / 37.3, 109 up to 17 47.7 / 52.9; commits 1 to 5 %.  (A branch in the kernel instead of an instance: 90 of 32 up to 31 92.8 / 96.5.)
+    const bool plain = !a.accepted && blocks > 256 && blocks <= 512;
     if (dk == 128 && in_dtype != KVB_F32)   // the matrix-core kernel
         return dispatch_types16(in_dtype, rec_dtype, [&]<typename TIn, typename TRec>() {
             if (a.cap <= 32) {
                 if (a.stream)
-                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, false, true);
+                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, false, true, false);
+                else if (plain)
+                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, false, false, true);
                 else
-                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, false, false);
+                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, false, false, false);
             } else {
                 if (a.stream)
-                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, true, true);
+                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, true, true, false);
                 else
-                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, true, false);
+                    LAUNCH_LEAD(blocks, deal, stream, a, kvb_flush_mfma_kernel<TIn, TRec, true, false, false);
             }
         });
     return dispatch(dk, in_dtype, rec_dtype, [&]<int D, typename TIn, typename TRec>() {

@@ -110,10 +110,10 @@ def test_launches_that_the_layout_decides(d, in_dtype, rec_dtype, B, apart):
 
 
 @pytest.mark.parametrize("in_dtype, rec_dtype", [("bf16", "f32"), ("f16", "f16"), ("f32", "f32")])
-@pytest.mark.parametrize("B, threshold, commit", [(96, 1, False), (96, 1, True), (192, 2, True), (480, 1, True)])
+@pytest.mark.parametrize("B, threshold, commit", [(33, 1, False), (64, 1, False), (96, 1, False), (96, 1, True), (192, 2, True), (480, 1, True)])
 def test_folds_of_whole_batches(in_dtype, rec_dtype, B, threshold, commit):
-    """kvb_flush where all requests fold, or nearly, at the sizes where units are no longer dealt for it and where they are again: a
-    request is folded to the same bits as in launches of 64 and of 32 requests."""
+    """kvb_flush where all requests fold, or nearly, at the sizes where states are stored plainly (264 to 512 units), where units are
+    no longer dealt for it and where they are again: a request is folded to the same bits as in smaller launches."""
     rng = np.random.default_rng(B + threshold)
     Hk, Hv, d, cap = 4, 8, 128, 16
     lay = H.Layer(B, Hk, Hv, d, d, cap, in_dtype, n_slots=B + 5, slots=rng.permutation(B + 5)[:B], rec_dtype=rec_dtype)
@@ -126,7 +126,8 @@ def test_folds_of_whole_batches(in_dtype, rec_dtype, B, threshold, commit):
     acc = torch.from_numpy(rng.integers(0, 4, B).astype(np.int32)).cuda() if commit else None
     state = ds.state.clone()
     seen = []
-    for parts in ([(0, B)], [(b, min(b + 64, B)) for b in range(0, B, 64)]):
+    few = 32 if B <= 64 else 64
+    for parts in ([(0, B)], [(b, min(b + few, B)) for b in range(0, B, few)]):
         ds.state.copy_(state)
         ds.fill.fill_(7)
         ds.fill[lay.slot.long()] = fills
