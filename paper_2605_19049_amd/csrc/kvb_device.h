@@ -172,7 +172,8 @@ __device__ __forceinline__ float2 unpack2r(const Raw2<T> &r) { return unpack_pai
 // next one waits for that.  These go through to memory as they are made (device scope, nobody is ordered by them) or, NT,
 // past the caches, for what a state that is streamed too leaves behind.  With plain stores / through, us: kvb_decode_flush, 8
 // steps of 8 requests of 32 heads 49.5 / 46.1, of 24 103.3 / 96.6, 16 steps of 64 437 / 433; kvb_verify and commit of 24
-// requests of 16 heads, fp32, 20.2 / 19.0.  PLAIN: a plain store all the same, for what the next launch reads back (kvb_decode_flush).
+// requests of 16 heads, fp32, 20.2 / 19.0.  PLAIN: a plain store all the same, for what is read back soon (kvb_decode_flush,
+// small folds by kvb_flush) and for the parts of a line that end a short launch (kvb_direct); the lines are measured there.
 template <bool NT, bool PLAIN = false, typename T>
 __device__ __forceinline__ void put(T *p, const T &x)
 {
